@@ -31,6 +31,7 @@
 #include <cstddef>
 #include <cstring>
 #include <map>
+#include <new>
 #include <vector>
 
 namespace cuesim {
@@ -46,6 +47,10 @@ constexpr int kLoadBatch = 10;              // tile rows a wavefront has in flig
 constexpr int kConeSlots = 1;               // cones per thread held in registers
 constexpr int kPartCones = kConeSlots * kThreads;   // cones one work item steps
 constexpr size_t kStaticLds = kMaxTileTargets * 16 + 3 * 9 * 4 + 16;   // static LDS per tile
+constexpr int kSmallest = 192;              // and when a tile's cones are split furthest
+constexpr int kHeadItems = 64;              // sources and targets of a tile kept at a fixed
+                                            // stride, found from the tile number alone
+constexpr int kSpecCones = 128;             // cone slots read before the tile's count is known
 constexpr int kGuardRows = 4;               // one above and three below each species plane
 constexpr int kXcds = 8;                    // dies (XCDs); workgroup b of a launch runs on die
                                             // b % kXcds
@@ -60,16 +65,17 @@ struct TiledArgs2D {
     int nx, ny;
     int tiles_x, n_tiles;
     int tx_core, ty_core, halo, height;   // TX, TY, H, loaded height HL
-    const int32_t* src_start;
+    const int4* head;          // per tile: first target, targets, first source, sources
     const int2* src_entry;     // (LDS index within the species plane, species)
     const float* src_amount;
-    const int32_t* tgt_start;  // per tile: targets within reach of its cones this launch
-    const float4* tgt_pts;
-    float4* bucket[2];         // per tile: cone slots (x, y, theta, id bits); the input
-                               // bucket's slots of a tile are owned by its workgroup and
-                               // updated in place
-    int32_t* count[2];         // the input counts are zeroed by each workgroup for reuse as
-                               // the next launch's output
+    const float4* tgt_pts;     // targets within reach of the tile's cones this launch
+    const int2* head_src;      // per tile, kHeadItems each: the first sources, (LDS index |
+                               // species << 24, amount bits), and the first targets
+    const float4* head_tgt;
+    float4* bucket[2];         // per tile: cone slots (x, y, theta, id); the launch reads one
+                               // half and fills the other
+    int32_t* count[3];         // cones per tile: this launch's input, its output, and last
+                               // launch's input, zeroed for the next launch's output
     int capacity;
     int cone_rows;             // stencil rows a wavefront gives up per cone slot it steps
     ConeArrays cones;
@@ -117,6 +123,7 @@ __device__ __forceinline__ GlobalPtr<T> gbl(T* p) {
 // clang vectors.
 using f4v = float __attribute__((ext_vector_type(4)));
 using i2v = int __attribute__((ext_vector_type(2)));
+using i4v = int __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ float4 gload(GlobalPtr<const float4> p) {
     const f4v v = *(GlobalPtr<const f4v>)p;
     return make_float4(v.x, v.y, v.z, v.w);
@@ -155,10 +162,11 @@ __device__ __forceinline__ RowVec<CPL> load_row(GlobalPtr<const float> f, int nx
 // row and parks the copy in guard row HL, which is never meaningful.  Cells outside the grid
 // read as zero; cells inside never use them (they take their own value for out-of-grid
 // neighbours).
-template <int CPL, bool ALIGNED>
+// issued() runs once the first batch's loads are on their way (before the wait for them).
+template <int CPL, bool ALIGNED, class Issued>
 __device__ __forceinline__ void load_tile(float* dst, GlobalPtr<const float> f, int nx, int ny,
                                           int y0, int HL, int gx0, int cx, int wave,
-                                          const bool (&col_in)[CPL]) {
+                                          const bool (&col_in)[CPL], const Issued& issued) {
     using V = typename Row<CPL>::T;
     constexpr int W = 64 * CPL;
     for (int ly0 = wave; ly0 < HL; ly0 += kLoadBatch * kWaves) {
@@ -166,6 +174,7 @@ __device__ __forceinline__ void load_tile(float* dst, GlobalPtr<const float> f, 
 #pragma unroll
         for (int r = 0; r < kLoadBatch; ++r)
             v[r] = load_row<CPL, ALIGNED>(f, nx, ny, y0 + min(ly0 + r * kWaves, HL - 1), gx0);
+        if (ly0 == wave) issued();
 #pragma unroll
         for (int r = 0; r < kLoadBatch; ++r) {
             const int ly = min(ly0 + r * kWaves, HL);
@@ -193,14 +202,17 @@ struct LdsField2D {
 // Value held by the lane below (lane_from_left) or above (lane_from_right) in the
 // wavefront: a whole-wave DPP shift by one lane, which moves data between lanes inside the
 // VALU instead of through the LDS crossbar.  Lane 0 (resp. 63) receives 0; it holds the
-// tile's outermost column, which is never valid after the first sub-step.
+// tile's outermost column, which is never valid after the first sub-step.  That 0 comes from
+// the shift's own bound control and not from a zeroed destination, so the compiler folds the
+// shift into the addition that takes its result: 12 instead of 16 VALU instructions per row
+// of two cells, and the stencil is bound by them.
 __device__ __forceinline__ float lane_from_left(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138 /* wave_shr:1 */,
-                                                      0xF, 0xF, false));
+                                                      0xF, 0xF, true));
 }
 __device__ __forceinline__ float lane_from_right(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130 /* wave_shl:1 */,
-                                                      0xF, 0xF, false));
+                                                      0xF, 0xF, true));
 }
 
 // How a tile meets the grid's first and last column (the zero-flux rule: a missing
@@ -519,20 +531,91 @@ __device__ __forceinline__ void store_core(float* const dst[], const TiledArgs2D
     }
 }
 
-// Parts of a tile holding c cones when a part takes at most p of them (at least one part
-// per tile).  The tile's cones are shared evenly among its parts (build_items).
+// Candidate part sizes of a crowded tile, largest first: the parts that a launch steps it in
+// take at most this many cones each.  A persistent launch, whose queue balances itself, uses
+// the first only.
+static_assert(kPartCones == 512, "candidate part sizes assume 512-cone parts");
 __device__ __forceinline__ int tile_parts(int c, int p) { return max(1, (c + p - 1) / p); }
+// Parts of a tile of c cones under candidate j (constant divisors: no integer division).
+__device__ __forceinline__ int candidate_parts(int c, int j) {
+    switch (j) {
+        case 1: return tile_parts(c, 384);
+        case 2: return tile_parts(c, 320);
+        case 3: return tile_parts(c, 256);
+        case 4: return tile_parts(c, 192);
+        default: return tile_parts(c, kPartCones);
+    }
+}
+static_assert(kSmallest == 192, "the smallest candidate");
+
+// Where the cones put into the next launch's buckets list the further parts of the tiles
+// they crowd.
+struct PartLists {
+    LaunchState* ls;
+    int4* list;   // the next launch's lists, one per candidate size, `cap` entries each
+    int cap;
+    int phase;    // of the next launch
+    int sizes;    // candidates in use
+    int sim;
+};
+
+// A tile's count has gone from `before` to `now` cones by one atomic addition: every part
+// that these cones opened goes to the candidates' lists.  Additions to one count follow one
+// another, so each part is listed once, whatever their order; a part's cones are decided
+// from the final count by the launch that steps them.  A list longer than `cap` is not used
+// (kPartSizes: the full-part list always fits).
+__device__ __forceinline__ void list_parts(const PartLists& to, int tile, int before, int now) {
+    if (now <= kSmallest) return;
+    for (int j = 0; j < to.sizes; ++j) {
+        const int a = candidate_parts(before, j), b = candidate_parts(now, j);
+        if (b <= a) continue;
+        const int at = atomicAdd(&to.ls->extra_n[to.phase][j], b - a);
+        for (int q = a; q < b; ++q)
+            if (at + q - a < to.cap)
+                to.list[j * to.cap + at + q - a] = make_int4(to.sim, tile, q, 0);
+    }
+}
+
+// A workgroup's place in the launch: which tile and part it steps, and the launch's state as
+// every workgroup read it.
+struct TileWork {
+    int tile, part, chosen;   // chosen: candidate part size in use
+    int steps;
+    uint32_t first_step;
+    int par, phase;
+};
+
+// Advance the launch state for the next launch: by the last workgroup to have read it.
+__device__ __forceinline__ void advance_launch(LaunchState* ls, uint32_t next_step, int par,
+                                               int phase) {
+    ls->step = next_step;
+    ls->parity = par ^ 1;
+    ls->phase = phase == 2 ? 0 : phase + 1;
+}
+
+// Count this workgroup (one thread of it) as having read the launch state: its place in the
+// order.  The counter wraps to zero at the last one.  (The compiler turns an addition into a
+// wavefront-wide one and waits for its answer on the spot, 1.5 us where every workgroup
+// starts at once; it leaves the wrapping increment alone.)
+__device__ __forceinline__ int arrive(LaunchState* ls) {
+    return (int)__builtin_amdgcn_atomic_inc32((uint32_t*)&ls->arrived, gridDim.x - 1,
+                                              __ATOMIC_RELAXED, "agent");
+}
 
 // One work item: one part of one tile of one simulation for `steps` sub-steps.  Every part
-// of a tile computes the tile's field; each part steps its share of the tile's cones,
-// [first_cone, first_cone + n_cones) with n_cones <= kPartCones, and only the part holding
-// the first cone writes the field back, so a tile crowded with cones is spread over several
-// workgroups.  par selects the input half of
-// every ping-pong pair (fields and cone buckets); the other half is written.
-template <int NS, int CPL, bool RECORD>
-__device__ __forceinline__ void tile_body(const TiledArgs2D& a, int tile, int first_cone,
-                                          int n_cones, int steps, uint32_t first_step,
-                                          int par) {
+// of a tile computes the tile's field; each part steps its even share of the tile's cones
+// (at most kPartCones), and only part 0 writes the field back, so a tile crowded with cones
+// is spread over several workgroups.  par selects the input half of every ping-pong pair
+// (fields and cone buckets; the other half is written), phase the input third of the counts.
+//
+// What a workgroup reads before its first sub-step is found from the tile number and the
+// launch state alone (count, header, the first sources and targets at a fixed stride, the
+// first cone slots), so that it all travels together with the tile's rows; before, headers,
+// targets and sources were read one after the other's answer (about 3 us of a launch).
+// (with LISTED the item comes from a persistent launch's queue)
+template <int NS, int CPL, bool RECORD, bool LISTED>
+__device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& w,
+                                          const PartLists& lists) {
     using V = typename Row<CPL>::T;
     constexpr int W = 64 * CPL;
     extern __shared__ __align__(16) float lds[];
@@ -540,11 +623,14 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, int tile, int fi
     __shared__ int dest_base[9];
     __shared__ int dest_fill[9];
     __shared__ float4 tile_targets[kMaxTileTargets];
+    const int tile = w.tile, steps = w.steps, par = w.par;
+    const uint32_t first_step = w.first_step;
     const float* in[SIM_MAX_SPECIES] = {a.field[0][par], a.field[NS > 1 ? 1 : 0][par]};
     float* out[SIM_MAX_SPECIES] = {a.field[0][par ^ 1], a.field[NS > 1 ? 1 : 0][par ^ 1]};
-    float4* const bucket_in = a.bucket[par];
     float4* const bucket_out = a.bucket[par ^ 1];
-    int32_t* const count_out = a.count[par ^ 1];
+    int32_t* const count_in = a.count[w.phase];
+    int32_t* const count_out = a.count[lists.phase];
+    int32_t* const count_next = a.count[3 - w.phase - lists.phase];
 
     const int tx = tile % a.tiles_x, ty = tile / a.tiles_x;
     const int tiles_y = a.n_tiles / a.tiles_x;
@@ -559,24 +645,44 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, int tile, int fi
     const int cx = CPL * lane;
     const int gx0 = x0 + cx;
 
-    // 0. this part's cones and the tile's targets, fetched first so that their latency
-    //    overlaps the tile load.  Every cone of the part stays in registers for the whole
-    //    launch: cone i sits in thread i % kThreads, slot i / kThreads (a part holds at
-    //    most kPartCones = kConeSlots * kThreads cones).
-    const bool first_part = first_cone == 0;
-    const GlobalPtr<const float4> live = gbl(bucket_in) + (size_t)tile * a.capacity + first_cone;
-    const int t_lo = gbl(a.tgt_start)[tile], n_tt = gbl(a.tgt_start)[tile + 1] - t_lo;
-    const TileContact contact{tile_targets, n_tt, n_tt <= kMaxTileTargets, &a.rules.targets};
-    if (contact.staged)
-        for (int k = threadIdx.x; k < n_tt; k += kThreads)
-            tile_targets[k] = gload(gbl(a.tgt_pts) + t_lo + k);
+    // 0. the tile's count and header, its first sources (every wavefront keeps them, one per
+    //    lane) and targets, and the first cone slots, requested together with the tile's
+    //    rows.  Every cone of the part stays in registers for the whole launch: cone i sits
+    //    in thread i % kThreads, slot i / kThreads (a part holds at most kPartCones =
+    //    kConeSlots * kThreads cones).
+    const bool first_part = w.part == 0;
+    const GlobalPtr<const float4> live = gbl((const float4*)a.bucket[par]) +
+                                         (size_t)tile * a.capacity;
+    const bool spec = first_part && (int)threadIdx.x < min(kSpecCones, a.capacity);
     float4 mine[kConeSlots];
 #pragma unroll
-    for (int k = 0; k < kConeSlots; ++k) {
-        const int i = threadIdx.x + k * kThreads;
-        mine[k] = make_float4(0.0f, 0.0f, 0.0f, __int_as_float(-1));
-        if (i < n_cones) mine[k] = gload(live + i);
-    }
+    for (int k = 0; k < kConeSlots; ++k) mine[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (spec) mine[0] = gload(live + threadIdx.x);
+    const int2 hs = gload(gbl(a.head_src) + (size_t)tile * kHeadItems + lane);
+    float4 ht = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (wave == kWaves - 1) ht = gload(gbl(a.head_tgt) + (size_t)tile * kHeadItems + lane);
+    const int n_all = *gbl(count_in + tile);
+    const i4v head = *(GlobalPtr<const i4v>)gbl(a.head + tile);
+    const int t_lo = head.x, n_tt = head.y, src_lo = head.z, n_src = head.w;
+    const TileContact contact{tile_targets, n_tt, n_tt <= kMaxTileTargets, &a.rules.targets};
+    int n_cones = 0;
+    // the part's share of the tile's cones (the first n_all % parts parts take one more), and
+    // its remaining cones, once the count is there
+    auto rest = [&]() {
+        const int parts = candidate_parts(n_all, w.chosen);
+        const int each = parts == 1 ? n_all : n_all / parts, more = n_all - each * parts;
+        n_cones = each + (w.part < more ? 1 : 0);
+        const int first = w.part * each + min(w.part, more);
+#pragma unroll
+        for (int k = 0; k < kConeSlots; ++k) {
+            const int i = threadIdx.x + k * kThreads;
+            if (i < n_cones) {
+                if (k > 0 || !spec) mine[k] = gload(live + first + i);
+            } else {
+                mine[k].w = __int_as_float(-1);
+            }
+        }
+    };
 
     // 1. load the tile, kLoadBatch rows in flight per wavefront; cells outside the grid
     //    read as zero and are never used by cells inside it, which take their own value
@@ -591,9 +697,16 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, int tile, int fi
         const GlobalPtr<const float> f = gbl((const float*)in[s]);
         float* const dst = lds + s * plane + W;
         if (aligned)
-            load_tile<CPL, true>(dst, f, a.nx, a.ny, y0, HL, gx0, cx, wave, col_in);
+            load_tile<CPL, true>(dst, f, a.nx, a.ny, y0, HL, gx0, cx, wave, col_in,
+                                 [&] { if (s == 0) rest(); });
         else
-            load_tile<CPL, false>(dst, f, a.nx, a.ny, y0, HL, gx0, cx, wave, col_in);
+            load_tile<CPL, false>(dst, f, a.nx, a.ny, y0, HL, gx0, cx, wave, col_in,
+                                  [&] { if (s == 0) rest(); });
+    }
+    if (contact.staged) {
+        if (wave == kWaves - 1 && lane < n_tt) tile_targets[lane] = ht;
+        for (int k = kHeadItems + threadIdx.x; k < n_tt; k += kThreads)
+            tile_targets[k] = gload(gbl(a.tgt_pts) + t_lo + k);
     }
     // sin and cos of every heading, carried alongside the cone from sub-step to sub-step, and
     // the second half of the current Philox block
@@ -610,6 +723,12 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, int tile, int fi
         dest_fill[threadIdx.x] = 0;
     }
     __syncthreads();
+    // every wavefront of this workgroup has the launch state by now; the answer is looked at
+    // only after the sub-steps
+    int order = -1;
+    if (!LISTED && threadIdx.x == 0) order = arrive(lists.ls);
+    // last launch's input count becomes the next launch's output
+    if (first_part && threadIdx.x == 0) count_next[tile] = 0;
 
     // Strips of the tile's rows inside the grid, [r0, r1), per wavefront, balanced against
     // the cone work: a wavefront stepping cones in k register slots gives up
@@ -640,17 +759,9 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, int tile, int fi
         }
         if (wave == 0) ybeg = r0;
     }
-    const int src_lo = gbl(a.src_start)[tile], src_hi = gbl(a.src_start)[tile + 1];
-    // the tile's first 64 source entries, one per lane, kept in registers for every sub-step
-    const int n_src = src_hi - src_lo;
-    int src_cell = -1, src_plane = 0;
-    float src_q = 0.0f;
-    if (lane < n_src) {
-        const int2 ent = gload(gbl(a.src_entry) + src_lo + lane);
-        src_cell = ent.x;
-        src_plane = ent.y * plane;
-        src_q = gbl(a.src_amount)[src_lo + lane];
-    }
+    const int src_at = W + (hs.x >> 24) * plane + (hs.x & 0xffffff);   // LDS word
+    const int src_row = lane < n_src ? (hs.x & 0xffffff) / W : -1;
+    const float src_q = __int_as_float(hs.y);
     const ConeRules& rules = a.rules;
     const int cols = x0 > 0 && x0 + W < a.nx ? kNoWall : aligned ? kWallAligned : kWallAny;
     const LdsField2D f0{lds + W, x0, y0, W, HL};
@@ -689,9 +800,8 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, int tile, int fi
         //    after its own edge rows: a wavefront's LDS operations take effect in order, and
         //    the barrier below publishes them with the rest of the sub-step
         if (n_src > 0 && lo < hi) {
-            if (src_cell >= 0 && src_cell / W >= lo && src_cell / W < hi)
-                lds[src_plane + W + src_cell] += src_q;
-            for (int e = src_lo + 64 + lane; e < src_hi; e += 64) {
+            if (src_row >= lo && src_row < hi) lds[src_at] += src_q;
+            for (int e = src_lo + kHeadItems + lane; e < src_lo + n_src; e += 64) {
                 const int2 ent = gload(gbl(a.src_entry) + e);
                 const int row = ent.x / W;
                 if (row >= lo && row < hi) lds[ent.y * plane + W + ent.x] += gbl(a.src_amount)[e];
@@ -743,8 +853,10 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, int tile, int fi
     __syncthreads();
     if (threadIdx.x < 9 && dest_count[threadIdx.x] > 0) {
         const int dtx = tx + threadIdx.x % 3 - 1, dty = ty + threadIdx.x / 3 - 1;
-        dest_base[threadIdx.x] = atomicAdd(&count_out[dty * a.tiles_x + dtx],
-                                           dest_count[threadIdx.x]);
+        const int to = dty * a.tiles_x + dtx, n = dest_count[threadIdx.x];
+        const int before = atomicAdd(&count_out[to], n);
+        dest_base[threadIdx.x] = before;
+        list_parts(lists, to, before, before + n);
     }
     __syncthreads();
 #pragma unroll
@@ -755,241 +867,135 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, int tile, int fi
         const int slot = dest_base[d] + atomicAdd(&dest_fill[d], 1);
         gstore(gbl(bucket_out) + (size_t)(nty * a.tiles_x + ntx) * a.capacity + slot, mine[k]);
     }
+    if (!LISTED && order == (int)gridDim.x - 1)
+        advance_launch(lists.ls, first_step + (uint32_t)steps, par, w.phase);
 }
 
-// Candidate part sizes of a list laid out by die, largest first.  Only tiles of more than
-// the smallest candidate's cones can need more than one part under any of them.
-constexpr int kCand = 5;
-__device__ __forceinline__ int candidate_size(int j) {
-    return j == 0 ? kPartCones : j == 1 ? 384 : j == 2 ? 320 : j == 3 ? 256 : 192;
-}
-static_assert(kPartCones == 512, "candidate part sizes assume 512-cone parts");
-
-// Parts of a tile of c cones under candidate j (constant divisors: no integer division).
-__device__ __forceinline__ int candidate_parts(int c, int j) {
-    switch (j) {
-        case 1: return tile_parts(c, 384);
-        case 2: return tile_parts(c, 320);
-        case 3: return tile_parts(c, 256);
-        case 4: return tile_parts(c, 192);
-        default: return tile_parts(c, kPartCones);
-    }
-}
-
-// Expand the base items (simulation, tile) into work items (simulation, tile, first cone,
-// cones), one per part of a tile, from the tile counts of input half par_in; optionally zero
-// the counts of half par_zero for reuse as the next output.  Run by one whole workgroup.
-//
-// BY_DIE (a launch of one workgroup per item): the part size is the smallest candidate whose
-// list still fits ls->slots (the workgroups resident at once), so that the spare slots carry
-// the crowded tiles' cones in more, smaller parts and every item still starts at once.  The
-// extra parts of each candidate are counted in `extra` (kCand ints of LDS that the caller
-// has zeroed before a barrier) by the few threads whose tile is crowded.  The list is laid
-// out so that each die gets a contiguous run of the n items, in tile order -- neighbouring
-// tiles, whose overlapping halo rows and columns the die's L2 then fetches once: item q goes
-// to slot (q % per) * kXcds + q / per with per = ceil(n / kXcds), so that workgroup b (on die
-// b % kXcds) takes item (b % kXcds) * per + b / kXcds; slots without an item hold
-// simulation -1, and ls->n_items is the number of slots, kXcds * per.  Such a list serves one
-// simulation whose base items are (0, k), so the count arrays are read from table[0] once
-// rather than through base[] and the table for every tile.  Otherwise (a persistent launch,
-// whose queue balances itself) parts take up to kPartCones cones.
-template <bool BY_DIE>
-__device__ void build_items(const TiledArgs2D* __restrict__ table, const int2* __restrict__ base,
-                            int n_base, int par_in, int par_zero, bool zero, int4* items,
-                            int item_cap, LaunchState* ls, int* extra) {
-    __shared__ int wave_total[kWaves];
-    const int slots = BY_DIE ? ls->slots : 0;   // issued early, beside the count loads
-    const int per = (n_base + kThreads - 1) / kThreads;
-    const int lo = min((int)threadIdx.x * per, n_base), hi = min(lo + per, n_base);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int32_t* const counts_in = BY_DIE ? table[0].count[par_in] : nullptr;
-    int32_t* const counts_zero = BY_DIE ? table[0].count[par_zero] : nullptr;
-    auto count_of = [&](int k) {
-        int32_t* const c = BY_DIE ? counts_in + k : &table[base[k].x].count[par_in][base[k].y];
-        return __hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    };
-    const int c_lo = lo < hi ? count_of(lo) : 0;   // the first count is kept in a register
-    auto count_at = [&](int k) { return k == lo ? c_lo : count_of(k); };
-
-    int chosen = 0;   // candidate part size in use
-    if (BY_DIE) {
-        for (int k = lo; k < hi; ++k) {
-            const int c = count_at(k);
-            if (c > candidate_size(kCand - 1)) {
-#pragma unroll
-                for (int j = 1; j < kCand; ++j) {
-                    const int e = candidate_parts(c, j) - 1;
-                    if (e > 0) atomicAdd(&extra[j], e);
-                }
-            }
-        }
-        __syncthreads();
-        const int room = slots - n_base;
-#pragma unroll
-        for (int j = 1; j < kCand; ++j)   // the counts grow with j: keep the last that fits
-            if (extra[j] <= room) chosen = j;
-    }
-    int mine = 0;
-    for (int k = lo; k < hi; ++k) mine += candidate_parts(count_at(k), chosen);
-    // exclusive scan of `mine` over the workgroup: within each wavefront by lane shuffles,
-    // then across the wavefronts' totals
-    int incl = mine;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int v = __shfl_up(incl, off, 64);
-        if (lane >= off) incl += v;
-    }
-    if (lane == 63) wave_total[wave] = incl;
-    __syncthreads();
-    int at = incl - mine, total = 0;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-        const int t = wave_total[w];
-        at += w < wave ? t : 0;
-        total += t;
-    }
-    // (item_cap includes kXcds slots that a list laid out by die may leave empty; a list of
-    // parts of up to kPartCones cones always fits, and a smaller size is only chosen when its
-    // list fits ls->slots, which the host keeps within the same bound)
-    const int n = min(total, BY_DIE ? item_cap - kXcds : item_cap);
-    const int per_die = (n + kXcds - 1) / kXcds;
-    // item `at` goes to slot r * kXcds + d with (d, r) = (at / per_die, at % per_die) when laid
-    // out by die, stepped along without dividing again
-    int d = BY_DIE ? at / max(per_die, 1) : 0, r = BY_DIE ? at - d * per_die : 0;
-    for (int k = lo; k < hi; ++k) {
-        const int c = count_at(k);
-        const int parts = candidate_parts(c, chosen);
-        // the tile's cones shared evenly: the first c % parts parts take one more
-        const int each = parts == 1 ? c : c / parts, more = c - each * parts;
-        int first = 0;
-        const int2 bk = BY_DIE ? make_int2(0, k) : base[k];
-        for (int q = 0; q < parts; ++q, ++at) {
-            const int m = each + (q < more ? 1 : 0);
-            if (at < n) items[BY_DIE ? r * kXcds + d : at] = make_int4(bk.x, bk.y, first, m);
-            first += m;
-            if (BY_DIE && ++r == per_die) {
-                r = 0;
-                ++d;
-            }
-        }
-        if (zero) {
-            if (BY_DIE)
-                counts_zero[k] = 0;
-            else
-                table[bk.x].count[par_zero][bk.y] = 0;
-        }
-    }
-    if (BY_DIE)   // the slots that hold no item (at most kXcds - 1, below kXcds * per)
-        for (int b = threadIdx.x; b < kXcds * per_die; b += kThreads)
-            if ((b % kXcds) * per_die + b / kXcds >= n) items[b] = make_int4(-1, 0, 0, 0);
-    if (threadIdx.x == 0) ls->n_items = BY_DIE ? kXcds * per_die : n;
-}
-
-// The step kernel.  Work items (simulation, tile, first cone, cones) come from the list the
-// previous launch (or k_build_items) wrote: one workgroup per slot of a list laid out by
-// die, or, in persistent mode, a fixed grid pulling items from an atomic queue until it
-// runs dry.  The launch state (step counter, ping-pong parity) is read by
-// every workgroup at its start and advanced by the last workgroup to finish, so launches
+// The step kernel: one workgroup per tile (part 0) and one per listed further part of a
+// crowded tile.  The launch state (step counter, ping-pong parity, count phase) is read by
+// every workgroup at its start and advanced by the last one to have read it, so launches
 // need no host-side bookkeeping and can be captured in a graph and replayed.
+//
+// Tiles are dealt to the dies in contiguous stretches: the hardware deals workgroup b to die
+// b % kXcds, which takes tile (b % kXcds) * per + b / kXcds, per = ceil(n_tiles / kXcds), so
+// that the overlapping halo rows and columns of neighbouring tiles are fetched once into that
+// die's L2.  The further parts follow: of the candidate sizes the smallest whose list still
+// fits beside the tiles (`room`: workgroups resident at once), so that the spare places carry
+// the crowded tiles' cones in more, smaller parts and every workgroup still starts at once.
+// The lists were filled when the cones were put into their buckets (list_parts).  Earlier the
+// last workgroup to finish scanned every tile's count and laid out a list of work items: a
+// serial tail of 3-4 us on every launch, and an item to be read before anything else.
+//
+// What the launch reads that other workgroups change while it runs is the launch state's
+// first group alone, which is written after all have read it; counts, lists and buckets are
+// read by the next launch, after the kernel boundary.
 template <int NS, int CPL, bool RECORD>
-__global__ __launch_bounds__(kThreads) void k_tiled2d(const TiledArgs2D* __restrict__ table,
-                                                      int4* items, const int2* __restrict__ base,
-                                                      int n_base, int item_cap, int steps,
-                                                      LaunchState* ls, int persistent) {
-    __shared__ int item_idx;
-    __shared__ int last_out;
-    __shared__ int extra_parts[kCand];
-    const uint32_t first_step = ls->step;
-    const int par = ls->parity;
-    const int n_items = ls->n_items;
-    if (!persistent) {
-        // the item list has one slot per workgroup of the grid, laid out by die
-        // (build_items): fetch it alongside the launch state (a slot past n_items, or one
-        // holding simulation -1, is not used)
-        const int4 it = items[blockIdx.x];
-        if ((int)blockIdx.x < n_items && it.x >= 0)
-            tile_body<NS, CPL, RECORD>(table[it.x], it.y, it.z, it.w, steps, first_step, par);
-    } else {
-        // the next item is taken from the queue while the current one runs, so the queue's
-        // round trip is hidden behind the item's work
-        if (threadIdx.x == 0) item_idx = atomicAdd(&ls->next, 1);
-        __syncthreads();
-        int i = item_idx;
-        while (i < n_items) {
-            int next = 0;
-            if (threadIdx.x == 0) next = atomicAdd(&ls->next, 1);
-            const int4 it = items[i];
-            tile_body<NS, CPL, RECORD>(table[it.x], it.y, it.z, it.w, steps, first_step, par);
-            // every thread read item_idx before tile_body's first barrier
-            if (threadIdx.x == 0) item_idx = next;
-            __syncthreads();   // the item is done with LDS; item_idx holds the next index
-            i = item_idx;
+__global__ __launch_bounds__(kThreads) void k_tiled2d(TiledArgs2D a, int tile_wgs, int steps,
+                                                      LaunchState* ls, int4* extra,
+                                                      int extra_cap, int room) {
+    const int4 head = *(const int4*)ls;   // step, parity, phase
+    const int par = head.y, phase = head.z;
+    const int next_phase = phase == 2 ? 0 : phase + 1;
+    const PartLists lists{ls, extra + (size_t)(par ^ 1) * kPartSizes * extra_cap, extra_cap,
+                          next_phase, kPartSizes, 0};
+    int chosen = 0, chosen_n = min(ls->extra_n[phase][0], extra_cap);
+#pragma unroll
+    for (int j = 1; j < kPartSizes; ++j) {   // the counts grow with j: keep the last that fits
+        const int n = ls->extra_n[phase][j];
+        if (n <= room) {
+            chosen = j;
+            chosen_n = n;
         }
     }
-    // The last workgroup to finish lists the next launch's work items from the final tile
-    // counts, zeroes this launch's input counts and advances the launch state.  The only
-    // data it reads that other workgroups wrote during the launch are those counts, which
-    // are changed by read-modify-write atomics only (performed at the device's coherence
-    // point, all of a workgroup's complete before it counts itself out: their results were
-    // used before the barrier) and read back with agent-scope atomic loads.  So no fence is
-    // needed -- an agent-scope fence would write back and invalidate the whole L2 of the
-    // chiplet once per workgroup.  Everything else it writes is read by the next launch,
-    // after the kernel boundary.
-    if (threadIdx.x < kCand) extra_parts[threadIdx.x] = 0;   // for build_items
-    __syncthreads();
-    if (threadIdx.x == 0)
-        last_out = __hip_atomic_fetch_add(&ls->exited, 1, __ATOMIC_RELAXED,
-                                          __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
-    __syncthreads();
-    if (last_out) {
-        if (persistent)
-            build_items<false>(table, base, n_base, par ^ 1, par, true, items, item_cap, ls,
-                               extra_parts);
-        else
-            build_items<true>(table, base, n_base, par ^ 1, par, true, items, item_cap, ls,
-                              extra_parts);
-        if (threadIdx.x == 0) {
-            ls->exited = 0;
-            ls->next = 0;
-            ls->step = first_step + (uint32_t)steps;
-            ls->parity = par ^ 1;
-        }
+    TileWork w{-1, 0, chosen, steps, (uint32_t)head.x, par, phase};
+    const int b = blockIdx.x;
+    if (b < tile_wgs) {
+        const int t = (b % kXcds) * (tile_wgs / kXcds) + b / kXcds;
+        if (t < a.n_tiles) w.tile = t;
+    } else if (b - tile_wgs < chosen_n) {
+        const int4 it = extra[((size_t)par * kPartSizes + chosen) * extra_cap + b - tile_wgs];
+        w.tile = it.y;
+        w.part = it.z;
+    }
+    // the third of the list lengths that last launch read is the next launch's output
+    if (b == 0 && threadIdx.x < kPartSizes) ls->extra_n[3 - phase - next_phase][threadIdx.x] = 0;
+    if (w.tile >= 0) {
+        tile_body<NS, CPL, RECORD, false>(a, w, lists);
+    } else {
+        __syncthreads();   // every wavefront has read the launch state
+        if (threadIdx.x == 0 && arrive(ls) == (int)gridDim.x - 1)
+            advance_launch(ls, w.first_step + (uint32_t)steps, par, phase);
     }
 }
 
-// Work items for the current cone counts (after cones were put into the buckets).
-__global__ __launch_bounds__(kThreads) void k_build_items(const TiledArgs2D* __restrict__ table,
-                                                          int4* items,
-                                                          const int2* __restrict__ base,
-                                                          int n_base, int item_cap,
-                                                          LaunchState* ls, int by_die) {
-    __shared__ int extra_parts[kCand];
-    if (threadIdx.x < kCand) extra_parts[threadIdx.x] = 0;
+// The persistent form for a batch: a fixed grid pulls items (a tile of a simulation, then
+// the further parts of crowded ones) from an atomic queue until it runs dry.
+template <int NS, int CPL>
+__global__ __launch_bounds__(kThreads) void k_tiled2d_batch(
+    const TiledArgs2D* __restrict__ table, const int2* __restrict__ base, int n_base, int steps,
+    LaunchState* ls, int4* extra, int extra_cap) {
+    __shared__ int item_idx;
+    const int4 head = *(const int4*)ls;   // step, parity, phase
+    const int par = head.y, phase = head.z;
+    const int next_phase = phase == 2 ? 0 : phase + 1;
+    const int n_items = n_base + min(ls->extra_n[phase][0], extra_cap);
+    const int4* const listed = extra + (size_t)par * extra_cap;
+    if (blockIdx.x == 0 && threadIdx.x == 0) ls->extra_n[3 - phase - next_phase][0] = 0;
+    // the next item is taken from the queue while the current one runs, so the queue's
+    // round trip is hidden behind the item's work
+    if (threadIdx.x == 0) item_idx = atomicAdd(&ls->next, 1);
     __syncthreads();
-    if (by_die)
-        build_items<true>(table, base, n_base, ls->parity, 0, false, items, item_cap, ls,
-                          extra_parts);
-    else
-        build_items<false>(table, base, n_base, ls->parity, 0, false, items, item_cap, ls,
-                           extra_parts);
+    int i = item_idx;
+    while (i < n_items) {
+        int next = 0;
+        if (threadIdx.x == 0) next = atomicAdd(&ls->next, 1);
+        int sim, tile, part = 0;
+        if (i < n_base) {
+            const int2 it = base[i];
+            sim = it.x;
+            tile = it.y;
+        } else {
+            const int4 it = listed[i - n_base];
+            sim = it.x;
+            tile = it.y;
+            part = it.z;
+        }
+        const PartLists lists{ls, extra + (size_t)(par ^ 1) * extra_cap, extra_cap, next_phase,
+                              kBatchPartLists, sim};
+        const TileWork w{tile, part, 0, steps, (uint32_t)head.x, par, phase};
+        tile_body<NS, CPL, false, true>(table[sim], w, lists);
+        // every thread read item_idx before tile_body's first barrier
+        if (threadIdx.x == 0) item_idx = next;
+        __syncthreads();   // the item is done with LDS; item_idx holds the next index
+        i = item_idx;
+    }
+    // the last workgroup to run out of items has the queue and the launch state to itself
+    if (threadIdx.x == 0 && arrive(ls) == (int)gridDim.x - 1) {
+        ls->next = 0;
+        advance_launch(ls, (uint32_t)head.x + (uint32_t)steps, par, phase);
+    }
 }
 
 // Initial bucketing from the caller-order arrays (active cones only).
 __global__ void k_bucket2d(ConeArrays c, int nx, int ny, int tx_core, int ty_core, int tiles_x,
-                           float inv_dx, float4* bucket, int32_t* count, int capacity) {
+                           float inv_dx, float4* bucket, int32_t* count, int capacity,
+                           PartLists lists) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= c.n || c.status[i] != kActive) return;
     const float x = c.pos[2 * i], y = c.pos[2 * i + 1];
     const int t = cell_of(y, inv_dx, ny) / ty_core * tiles_x + cell_of(x, inv_dx, nx) / tx_core;
     const int slot = atomicAdd(&count[t], 1);
+    list_parts(lists, t, slot, slot + 1);
     bucket[(size_t)t * capacity + slot] = make_float4(x, y, c.dir[i], __int_as_float(i));
 }
 
-// Active cones from the buckets back into the caller-order arrays.
-__global__ void k_unbucket2d(ConeArrays c, const float4* bucket, const int32_t* count,
-                             int capacity) {
+// Active cones from the buckets back into the caller-order arrays; with `drop` the tile's
+// counts (and the lists of further parts) start over at none.
+__global__ void k_sync_cones2d(ConeArrays c, const float4* bucket, int32_t* count0,
+                               int32_t* count1, int32_t* count2, int phase, int capacity,
+                               bool drop, LaunchState* ls) {
     const int t = blockIdx.x;
-    const int n = count[t];
+    const int n = (phase == 0 ? count0 : phase == 1 ? count1 : count2)[t];
     for (int k = threadIdx.x; k < n; k += blockDim.x) {
         const float4 st = bucket[(size_t)t * capacity + k];
         const int id = __float_as_int(st.w);
@@ -998,6 +1004,10 @@ __global__ void k_unbucket2d(ConeArrays c, const float4* bucket, const int32_t* 
         c.pos[2 * id + 1] = st.y;
         c.dir[id] = st.z;
     }
+    if (!drop) return;
+    __syncthreads();   // every thread has the count
+    if (threadIdx.x == 0) count0[t] = count1[t] = count2[t] = 0;
+    if (t == 0 && threadIdx.x < 3 * 8) (&ls->extra_n[0][0])[threadIdx.x] = 0;
 }
 
 int ceil_div(int a, int b) { return (a + b - 1) / b; }
@@ -1013,6 +1023,12 @@ const void* kernel_for(int n_species, int cpl, bool record = false) {
     if (n_species == 1)
         return cpl == 4 ? (const void*)k_tiled2d<1, 4, false> : (const void*)k_tiled2d<1, 2, false>;
     return cpl == 4 ? (const void*)k_tiled2d<2, 4, false> : (const void*)k_tiled2d<2, 2, false>;
+}
+
+const void* batch_kernel_for(int n_species, int cpl) {
+    if (n_species == 1)
+        return cpl == 4 ? (const void*)k_tiled2d_batch<1, 4> : (const void*)k_tiled2d_batch<1, 2>;
+    return cpl == 4 ? (const void*)k_tiled2d_batch<2, 4> : (const void*)k_tiled2d_batch<2, 2>;
 }
 
 }  // namespace
@@ -1109,13 +1125,10 @@ hipError_t tiled_allocate(const TiledPlan& plan, TiledState& st, int n_cones,
     const int W = 64 * plan.cpl;
     st.capacity = std::max(1, n_cones);
     const size_t slots = (size_t)plan.n_tiles * st.capacity;
-    for (int b = 0; b < 2; ++b) {
-        if ((e = hipMalloc(&st.bucket[b], slots * sizeof(float4))) != hipSuccess) return e;
-        if ((e = hipMalloc(&st.count[b], plan.n_tiles * sizeof(int32_t))) != hipSuccess) return e;
-        if ((e = hipMemsetAsync(st.count[b], 0, plan.n_tiles * sizeof(int32_t), stream)) != hipSuccess)
-            return e;
-    }
+    if ((e = hipMalloc(&st.bucket[0], 2 * slots * sizeof(float4))) != hipSuccess) return e;
+    st.bucket[1] = st.bucket[0] + slots;
     st.cur = 0;
+    st.phase = 0;
     // per-tile source entries: every unique source cell inside a tile's loaded region
     std::vector<std::vector<std::pair<int2, float>>> per_tile(plan.n_tiles);
     const double vol = std::pow(p->dx, p->dim);
@@ -1137,34 +1150,27 @@ hipError_t tiled_allocate(const TiledPlan& plan, TiledState& st, int n_cones,
             }
         }
     }
-    std::vector<int32_t> start(plan.n_tiles + 1, 0);
+    std::vector<int4> head(plan.n_tiles, make_int4(0, 0, 0, 0));
+    std::vector<int2> head_src((size_t)plan.n_tiles * kHeadItems, make_int2(0, 0));
+    std::vector<float4> head_tgt((size_t)plan.n_tiles * kHeadItems);
     std::vector<int2> entry;
     std::vector<float> amount;
     for (int t = 0; t < plan.n_tiles; ++t) {
-        for (auto& en : per_tile[t]) {
+        head[t].z = (int)entry.size();
+        head[t].w = (int)per_tile[t].size();
+        for (size_t k = 0; k < per_tile[t].size(); ++k) {
+            const auto& en = per_tile[t][k];
             entry.push_back(en.first);
             amount.push_back(en.second);
+            if (k >= kHeadItems) continue;
+            int2& h = head_src[(size_t)t * kHeadItems + k];
+            h.x = en.first.x | en.first.y << 24;   // a tile holds fewer than 2^24 cells
+            std::memcpy(&h.y, &en.second, sizeof h.y);
         }
-        start[t + 1] = (int32_t)entry.size();
-    }
-    if ((e = hipMalloc(&st.src_start, start.size() * sizeof(int32_t))) != hipSuccess) return e;
-    if ((e = hipMalloc(&st.src_entry, std::max<size_t>(1, entry.size()) * sizeof(int2))) != hipSuccess)
-        return e;
-    if ((e = hipMalloc(&st.src_amount, std::max<size_t>(1, amount.size()) * sizeof(float))) != hipSuccess)
-        return e;
-    if ((e = hipMemcpy(st.src_start, start.data(), start.size() * sizeof(int32_t),
-                       hipMemcpyHostToDevice)) != hipSuccess)
-        return e;
-    if (!entry.empty()) {
-        if ((e = hipMemcpy(st.src_entry, entry.data(), entry.size() * sizeof(int2),
-                           hipMemcpyHostToDevice)) != hipSuccess)
-            return e;
-        if ((e = hipMemcpy(st.src_amount, amount.data(), amount.size() * sizeof(float),
-                           hipMemcpyHostToDevice)) != hipSuccess)
-            return e;
     }
     // per-tile target lists: every target within reach of a tip that starts the launch in
     // the tile core (core grown by the launch's travel, plus the contact radius)
+    std::vector<float4> tpts;
     {
         const double reach = (plan.move + 1) * p->dx + p->contact_radius;
         std::vector<std::vector<float4>> lists(plan.n_tiles);
@@ -1185,24 +1191,54 @@ hipError_t tiled_allocate(const TiledPlan& plan, TiledState& st, int n_cones,
                 }
             }
         }
-        std::vector<int32_t> tstart(plan.n_tiles + 1, 0);
-        std::vector<float4> tpts;
         for (int t = 0; t < plan.n_tiles; ++t) {
+            head[t].x = (int)tpts.size();
+            head[t].y = (int)lists[t].size();
             tpts.insert(tpts.end(), lists[t].begin(), lists[t].end());
-            tstart[t + 1] = (int32_t)tpts.size();
+            std::copy_n(lists[t].begin(), std::min<size_t>(lists[t].size(), kHeadItems),
+                        head_tgt.begin() + (size_t)t * kHeadItems);
         }
-        if (tpts.empty()) tpts.push_back(make_float4(0.0f, 0.0f, 0.0f, 0.0f));
-        if ((e = hipMalloc(&st.tgt_start, tstart.size() * sizeof(int32_t))) != hipSuccess) return e;
-        if ((e = hipMalloc(&st.tgt_pts, tpts.size() * sizeof(float4))) != hipSuccess) return e;
-        if ((e = hipMemcpy(st.tgt_start, tstart.data(), tstart.size() * sizeof(int32_t),
-                           hipMemcpyHostToDevice)) != hipSuccess)
-            return e;
-        if ((e = hipMemcpy(st.tgt_pts, tpts.data(), tpts.size() * sizeof(float4),
-                           hipMemcpyHostToDevice)) != hipSuccess)
-            return e;
     }
-    // argument table and launch state
-    TiledArgs2D a = {};
+    // further parts of crowded tiles: full parts always fit their list; smaller ones are used
+    // only when they fit beside the tiles
+    st.room = std::max(0, tiled_persistent_grid(plan.lds_bytes) - plan.n_tiles);
+    st.extra_cap = std::max(tiled_extra_capacity(n_cones),
+                            std::min(st.room, ceil_div(n_cones, kSmallest)));
+    st.room = std::min(st.room, st.extra_cap);
+    // one allocation: the launch state, counts and lists (zeroed), then the tables (one copy)
+    size_t bytes = 0;
+    auto place = [&](size_t n) {
+        const size_t at = bytes;
+        bytes += (n + 255) / 256 * 256;
+        return at;
+    };
+    const size_t n_t = (size_t)plan.n_tiles;
+    const size_t at_launch = place(sizeof(LaunchState));
+    size_t at_count[3];
+    for (size_t& c : at_count) c = place(n_t * sizeof(int32_t));
+    const size_t at_extra = place((size_t)2 * kPartSizes * st.extra_cap * sizeof(int4));
+    const size_t zeroed = bytes;
+    std::vector<char> tables;
+    auto table = [&](const auto& v) {
+        const size_t n = v.size() * sizeof(v[0]), at = place(n);
+        tables.resize(bytes - zeroed);
+        if (n) std::memcpy(tables.data() + (at - zeroed), v.data(), n);
+        return at;
+    };
+    const size_t at_head = table(head), at_entry = table(entry), at_amount = table(amount),
+                 at_tgt = table(tpts), at_hsrc = table(head_src), at_htgt = table(head_tgt);
+    if ((e = hipMalloc(&st.memory, bytes)) != hipSuccess ||
+        (e = hipMemsetAsync(st.memory, 0, zeroed, stream)) != hipSuccess ||
+        (e = hipMemcpy(st.memory + zeroed, tables.data(), tables.size(),
+                       hipMemcpyHostToDevice)) != hipSuccess)
+        return e;
+    st.launch = (LaunchState*)(st.memory + at_launch);
+    for (int b = 0; b < 3; ++b) st.count[b] = (int32_t*)(st.memory + at_count[b]);
+    st.extra = (int4*)(st.memory + at_extra);
+    // the kernel's arguments and the launch state
+    st.args = new (std::nothrow) TiledArgs2D();
+    if (!st.args) return hipErrorOutOfMemory;
+    TiledArgs2D& a = *st.args;
     for (int s = 0; s < plan.n_species; ++s) {
         a.field[s][0] = fields[s][0];
         a.field[s][1] = fields[s][1];
@@ -1216,36 +1252,21 @@ hipError_t tiled_allocate(const TiledPlan& plan, TiledState& st, int n_cones,
     a.ty_core = plan.core_y;
     a.halo = plan.halo;
     a.height = plan.height;
-    a.src_start = st.src_start;
-    a.src_entry = st.src_entry;
-    a.src_amount = st.src_amount;
-    a.tgt_start = st.tgt_start;
-    a.tgt_pts = st.tgt_pts;
+    a.head = (const int4*)(st.memory + at_head);
+    a.src_entry = (const int2*)(st.memory + at_entry);
+    a.src_amount = (const float*)(st.memory + at_amount);
+    a.tgt_pts = (const float4*)(st.memory + at_tgt);
+    a.head_src = (const int2*)(st.memory + at_hsrc);
+    a.head_tgt = (const float4*)(st.memory + at_htgt);
     a.bucket[0] = st.bucket[0];
     a.bucket[1] = st.bucket[1];
     a.count[0] = st.count[0];
     a.count[1] = st.count[1];
+    a.count[2] = st.count[2];
     a.capacity = st.capacity;
     a.cone_rows = plan.cone_rows;
     a.cones = cones;
     a.rules = rules;
-    if ((e = hipMalloc(&st.table, sizeof(TiledArgs2D))) != hipSuccess) return e;
-    if ((e = hipMemcpy(st.table, &a, sizeof a, hipMemcpyHostToDevice)) != hipSuccess) return e;
-    // work items: one per tile plus one per kPartCones further cones in a crowded tile (a
-    // list of smaller parts is used only when it fits the resident workgroups)
-    st.item_cap = tiled_item_capacity(plan.n_tiles, n_cones);
-    std::vector<int2> base(plan.n_tiles);
-    for (int t = 0; t < plan.n_tiles; ++t) base[t] = make_int2(0, t);
-    if ((e = hipMalloc(&st.base, base.size() * sizeof(int2))) != hipSuccess) return e;
-    if ((e = hipMemcpy(st.base, base.data(), base.size() * sizeof(int2),
-                       hipMemcpyHostToDevice)) != hipSuccess)
-        return e;
-    if ((e = hipMalloc(&st.items, (size_t)st.item_cap * sizeof(int4))) != hipSuccess) return e;
-    if ((e = hipMalloc(&st.launch, sizeof(LaunchState))) != hipSuccess) return e;
-    const LaunchState ls0 = tiled_launch_state(
-        std::min(tiled_persistent_grid(plan.lds_bytes), st.item_cap - kXcds));
-    if ((e = hipMemcpy(st.launch, &ls0, sizeof ls0, hipMemcpyHostToDevice)) != hipSuccess) return e;
-    st.cur = 0;
     for (bool record : {false, true})
         if ((e = hipFuncSetAttribute(kernel_for(plan.n_species, plan.cpl, record),
                                      hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1254,19 +1275,9 @@ hipError_t tiled_allocate(const TiledPlan& plan, TiledState& st, int n_cones,
     return hipSuccess;
 }
 
-hipError_t tiled_set_record(TiledState& st, float* tape, uint32_t n0, hipStream_t stream) {
-    struct {
-        float* record;
-        uint32_t record_n0;
-    } rec = {tape, n0};
-    st.recording = tape != nullptr;
-    static_assert(offsetof(TiledArgs2D, record_n0) == offsetof(TiledArgs2D, record) + sizeof(float*),
-                  "record and record_n0 are adjacent");
-    hipError_t e = hipMemcpyAsync((char*)st.table + offsetof(TiledArgs2D, record), &rec,
-                                  sizeof(float*) + sizeof(uint32_t), hipMemcpyHostToDevice,
-                                  stream);
-    if (e != hipSuccess) return e;
-    return hipStreamSynchronize(stream);
+void tiled_set_record(TiledState& st, float* tape, uint32_t n0) {
+    st.args->record = tape;
+    st.args->record_n0 = n0;
 }
 
 hipError_t tiled_set_launch_state(TiledState& st, uint32_t step, int parity, hipStream_t stream) {
@@ -1277,102 +1288,59 @@ hipError_t tiled_set_launch_state(TiledState& st, uint32_t step, int parity, hip
     return hipStreamSynchronize(stream);
 }
 
-LaunchState tiled_launch_state(int slots) {
-    LaunchState ls = {};
-    ls.slots = slots;
-    return ls;
-}
-
-int tiled_item_capacity(int n_tiles, int n_cones) {
-    // the items, plus the slots a list laid out by die may leave empty
-    return n_tiles + (n_cones + kPartCones - 1) / kPartCones + 1 + kXcds;
-}
-
-hipError_t tiled_build_items(const TiledArgs2D* table, int4* items, const int2* base,
-                             int n_base, int item_cap, LaunchState* launch, hipStream_t stream,
-                             bool by_die) {
-    hipLaunchKernelGGL(k_build_items, dim3(1), dim3(kThreads), 0, stream,
-                       table, items, base, n_base, item_cap, launch, by_die ? 1 : 0);
-    return hipGetLastError();
+int tiled_extra_capacity(int64_t n_cones) {
+    // a tile of c cones has ceil(c / kPartCones) - 1 < c / kPartCones further full parts
+    return (int)(n_cones / kPartCones) + 1;
 }
 
 void tiled_release(TiledState& st) {
-    for (int b = 0; b < 2; ++b) {
-        (void)hipFree(st.bucket[b]);
-        (void)hipFree(st.count[b]);
-        st.bucket[b] = nullptr;
-        st.count[b] = nullptr;
-    }
-    (void)hipFree(st.src_start);
-    (void)hipFree(st.src_entry);
-    (void)hipFree(st.src_amount);
-    (void)hipFree(st.tgt_start);
-    (void)hipFree(st.tgt_pts);
-    (void)hipFree(st.table);
-    (void)hipFree(st.launch);
-    (void)hipFree(st.items);
-    (void)hipFree(st.base);
-    st.table = nullptr;
-    st.launch = nullptr;
-    st.items = nullptr;
-    st.base = nullptr;
-    st.tgt_start = nullptr;
-    st.tgt_pts = nullptr;
-    st.src_start = nullptr;
-    st.src_entry = nullptr;
-    st.src_amount = nullptr;
+    (void)hipFree(st.bucket[0]);
+    (void)hipFree(st.memory);
+    delete st.args;
+    st = TiledState();
+}
+
+hipError_t tiled_bucket_batch(const TiledPlan& plan, TiledState& st, ConeArrays cones, int sim,
+                              LaunchState* launch, int4* extra, int extra_cap,
+                              hipStream_t stream) {
+    if (cones.n == 0) return hipSuccess;
+    const int sizes = launch == st.launch ? kPartSizes : kBatchPartLists;
+    const PartLists lists{launch, extra + (size_t)st.cur * sizes * extra_cap, extra_cap,
+                          st.phase, sizes, sim};
+    hipLaunchKernelGGL(k_bucket2d, dim3(ceil_div(cones.n, 256)), dim3(256), 0, stream, cones,
+                       plan.nx, plan.ny, plan.core_x, plan.core_y, plan.tiles_x, plan.inv_dx,
+                       st.bucket[st.cur], st.count[st.phase], st.capacity, lists);
+    return hipGetLastError();
 }
 
 hipError_t tiled_bucket(const TiledPlan& plan, TiledState& st, ConeArrays cones,
                         hipStream_t stream) {
-    hipError_t e;
-    for (int b = 0; b < 2; ++b)
-        if ((e = hipMemsetAsync(st.count[b], 0, plan.n_tiles * sizeof(int32_t), stream)) != hipSuccess)
-            return e;
-    if (cones.n > 0) {
-        hipLaunchKernelGGL(k_bucket2d, dim3(ceil_div(cones.n, 256)), dim3(256), 0, stream,
-                           cones, plan.nx, plan.ny, plan.core_x, plan.core_y, plan.tiles_x,
-                           plan.inv_dx, st.bucket[st.cur], st.count[st.cur], st.capacity);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    return tiled_build_items(st.table, st.items, st.base, plan.n_tiles, st.item_cap, st.launch,
-                             stream, true);
+    return tiled_bucket_batch(plan, st, cones, 0, st.launch, st.extra, st.extra_cap, stream);
 }
 
-hipError_t tiled_unbucket(const TiledPlan& plan, TiledState& st, ConeArrays cones,
-                          hipStream_t stream) {
-    hipLaunchKernelGGL(k_unbucket2d, dim3(plan.n_tiles), dim3(256), 0, stream, cones,
-                       st.bucket[st.cur], st.count[st.cur], st.capacity);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    for (int b = 0; b < 2; ++b)
-        if ((e = hipMemsetAsync(st.count[b], 0, plan.n_tiles * sizeof(int32_t), stream)) != hipSuccess)
-            return e;
-    return hipSuccess;
-}
-
-hipError_t tiled_sync_cones(const TiledPlan& plan, const TiledState& st, ConeArrays cones,
-                            hipStream_t stream) {
-    hipLaunchKernelGGL(k_unbucket2d, dim3(plan.n_tiles), dim3(256), 0, stream, cones,
-                       st.bucket[st.cur], st.count[st.cur], st.capacity);
+hipError_t tiled_sync_cones(const TiledPlan& plan, TiledState& st, ConeArrays cones,
+                            hipStream_t stream, bool drop) {
+    hipLaunchKernelGGL(k_sync_cones2d, dim3(plan.n_tiles), dim3(256), 0, stream, cones,
+                       st.bucket[st.cur], st.count[0], st.count[1], st.count[2], st.phase,
+                       st.capacity, drop, st.launch);
     return hipGetLastError();
 }
 
 hipError_t tiled_launch(const TiledPlan& plan, TiledState& st, int steps, hipStream_t stream,
                         hipEvent_t start, hipEvent_t stop) {
-    const TiledArgs2D* table = st.table;
-    int4* items = st.items;
-    const int2* base = st.base;
-    int n_base = plan.n_tiles;
-    int item_cap = st.item_cap;
-    LaunchState* ls = st.launch;
-    int persistent = 0;
-    void* args[] = {&table, &items, &base, &n_base, &item_cap, &steps, &ls, &persistent};
-    const hipError_t e = hipExtLaunchKernel(kernel_for(plan.n_species, plan.cpl, st.recording),
-                                            dim3(item_cap), dim3(kThreads), args,
-                                            plan.lds_bytes, stream, start, stop, 0);
-    if (e == hipSuccess) st.cur ^= 1;
+    int tile_wgs = ceil_div(plan.n_tiles, kXcds) * kXcds;
+    void* args[] = {st.args, &tile_wgs, &steps, &st.launch, &st.extra, &st.extra_cap, &st.room};
+    const hipError_t e = hipExtLaunchKernel(
+        kernel_for(plan.n_species, plan.cpl, st.args->record != nullptr),
+        dim3(tile_wgs + st.extra_cap), dim3(kThreads), args, plan.lds_bytes, stream, start, stop,
+        0);
+    if (e == hipSuccess) tiled_advanced(st, 1);
     return e;
+}
+
+void tiled_advanced(TiledState& st, int launches) {
+    st.cur ^= launches & 1;
+    st.phase = (st.phase + launches) % 3;
 }
 
 size_t tiled_table_entry_bytes() { return sizeof(TiledArgs2D); }
@@ -1383,18 +1351,18 @@ int tiled_persistent_grid(size_t lds_bytes) {
     return 256 * resident;
 }
 
-hipError_t tiled_launch_batch(const TiledArgs2D* table, int4* items, const int2* base,
-                              int n_base, int item_cap, int n_species, int cpl,
+hipError_t tiled_launch_batch(const TiledArgs2D* table, int4* extra, const int2* base,
+                              int n_base, int extra_cap, int n_species, int cpl,
                               size_t lds_bytes, int steps, LaunchState* launch,
                               hipStream_t stream) {
-    int persistent = 1;
-    void* args[] = {&table, &items, &base, &n_base, &item_cap, &steps, &launch, &persistent};
-    return hipLaunchKernel(kernel_for(n_species, cpl), dim3(tiled_persistent_grid(lds_bytes)),
-                           dim3(kThreads), args, lds_bytes, stream);
+    void* args[] = {&table, &base, &n_base, &steps, &launch, &extra, &extra_cap};
+    return hipLaunchKernel(batch_kernel_for(n_species, cpl),
+                           dim3(tiled_persistent_grid(lds_bytes)), dim3(kThreads), args,
+                           lds_bytes, stream);
 }
 
 hipError_t tiled_prepare_batch(int n_species, int cpl, size_t lds_bytes) {
-    return hipFuncSetAttribute(kernel_for(n_species, cpl),
+    return hipFuncSetAttribute(batch_kernel_for(n_species, cpl),
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
 }
 

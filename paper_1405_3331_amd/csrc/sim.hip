@@ -115,6 +115,7 @@ struct sim_handle {
     TiledPlan plan = {};
     TiledState tiled = {};
     bool cones_bucketed = false;   // active cones live in the tile buckets
+    bool cones_synced = true;      // the caller-order arrays hold the active cones' state
 
     // 3D: field step with its per-box source lists; active cones in spatial order,
     // refreshed every kOrderRefresh steps
@@ -394,15 +395,28 @@ sim_status item_size(sim_handle* h, sim_item what, int32_t index, size_t* bytes)
     return SIM_OK;
 }
 
-// Bring active cones from the tile buckets back into the caller-order arrays.
+// Bring the caller-order arrays up to date with the active cones' working copies (the tile
+// buckets, or the 3D spatial order), which stay valid: stepping goes on from them.
+sim_status sync_cones(sim_handle* h) {
+    if (h->cones_synced) return SIM_OK;
+    if (h->cones_ordered) HIP_TRY(h, order3d_end(h->order3d, h->cones, h->stream));
+    if (h->cones_bucketed)
+        HIP_TRY(h, tiled_sync_cones(h->plan, h->tiled, h->cones, h->stream, false));
+    h->cones_synced = true;
+    return SIM_OK;
+}
+
+// The same, and the working copies are given up: the caller-order arrays are about to change.
 sim_status unbucket(sim_handle* h) {
-    if (h->cones_ordered) {
-        HIP_TRY(h, order3d_end(h->order3d, h->cones, h->stream));
-        h->cones_ordered = false;
+    if (h->cones_bucketed) {
+        HIP_TRY(h, tiled_sync_cones(h->plan, h->tiled, h->cones, h->stream, true));
+        h->cones_bucketed = false;
+    } else {
+        sim_status st = sync_cones(h);
+        if (st != SIM_OK) return st;
     }
-    if (!h->cones_bucketed) return SIM_OK;
-    HIP_TRY(h, tiled_unbucket(h->plan, h->tiled, h->cones, h->stream));
-    h->cones_bucketed = false;
+    h->cones_ordered = false;
+    h->cones_synced = true;
     return SIM_OK;
 }
 
@@ -471,6 +485,7 @@ sim_status plain_step(sim_handle* h) {
         h->since_refresh += 1;
     }
     h->step += 1;
+    h->cones_synced = h->dim == 2;   // a 2D step works on the caller-order arrays
     return SIM_OK;
 }
 
@@ -485,6 +500,7 @@ sim_status tiled_steps(sim_handle* h, int64_t n) {
         sim_status st = timing_events(h, &t0, &t1);
         if (st != SIM_OK) return st;
         HIP_TRY(h, tiled_launch(h->plan, h->tiled, b, h->stream, t0, t1));
+        h->cones_synced = false;
         for (int s = 0; s < h->n_species; ++s) h->cur[s] ^= 1;
         h->step += b;
         n -= b;
@@ -644,8 +660,8 @@ struct sim_batch {
     void* table = nullptr;            // concatenated device argument tables
     int2* base = nullptr;             // every (simulation, tile), largest simulations first
     int n_base = 0;
-    int4* items = nullptr;            // (simulation, tile, part) work items of the next launch
-    int item_cap = 0;
+    int4* extra = nullptr;            // further parts of crowded tiles, [parity][extra_cap]
+    int extra_cap = 0;
     LaunchState* launch = nullptr;
     int n_species = 1, cpl = 2, block_steps = 1;
     size_t lds_bytes = 0;
@@ -688,11 +704,11 @@ void batch_release(sim_batch* b) {
     }
     b->sims.clear();
     if (b->table) (void)hipFree(b->table);
-    if (b->items) (void)hipFree(b->items);
+    if (b->extra) (void)hipFree(b->extra);
     if (b->base) (void)hipFree(b->base);
     if (b->launch) (void)hipFree(b->launch);
     b->table = nullptr;
-    b->items = nullptr;
+    b->extra = nullptr;
     b->base = nullptr;
     b->launch = nullptr;
     if (b->own_stream && b->stream) (void)hipStreamDestroy(b->stream);
@@ -701,8 +717,8 @@ void batch_release(sim_batch* b) {
 
 // One launch of `steps` steps for every simulation of the batch.
 sim_status batch_launch(sim_batch* b, int steps) {
-    BATCH_TRY(b, tiled_launch_batch((const TiledArgs2D*)b->table, b->items, b->base,
-                                    b->n_base, b->item_cap, b->n_species, b->cpl,
+    BATCH_TRY(b, tiled_launch_batch((const TiledArgs2D*)b->table, b->extra, b->base,
+                                    b->n_base, b->extra_cap, b->n_species, b->cpl,
                                     b->lds_bytes, steps, b->launch, b->stream));
     return SIM_OK;
 }
@@ -710,10 +726,9 @@ sim_status batch_launch(sim_batch* b, int steps) {
 // Mirror a completed launch of `steps` steps in every simulation's host-side state.
 void batch_advance(sim_batch* b, int steps, int launches) {
     for (sim_handle* h : b->sims) {
-        for (int l = 0; l < launches; ++l) {
-            for (int s = 0; s < h->n_species; ++s) h->cur[s] ^= 1;
-            h->tiled.cur ^= 1;
-        }
+        for (int s = 0; s < h->n_species; ++s) h->cur[s] ^= launches & 1;
+        tiled_advanced(h->tiled, launches);
+        h->cones_synced = false;
         h->step += (int64_t)steps * launches;
     }
     b->step += (int64_t)steps * launches;
@@ -844,7 +859,7 @@ sim_status sim_read_state(sim_handle* h, sim_item what, int32_t index, void* dst
     if (st != SIM_OK) return st;
     const size_t M = (size_t)h->n_cones;
     if (what == SIM_EVENTS || what == SIM_COUNTS) {
-        st = unbucket(h);
+        st = sync_cones(h);
         if (st != SIM_OK) return st;
         HIP_TRY(h, hipStreamSynchronize(h->stream));
         std::vector<int32_t> status(M), target(M), ev(M);
@@ -895,7 +910,7 @@ sim_status sim_read_state(sim_handle* h, sim_item what, int32_t index, void* dst
         case SIM_CONE_STATUS:
         case SIM_CONE_TARGET:
         case SIM_CONE_EVENT_STEP: {
-            st = unbucket(h);
+            st = sync_cones(h);
             if (st != SIM_OK) return st;
             HIP_TRY(h, hipStreamSynchronize(h->stream));
             const void* src = what == SIM_CONE_POS      ? (const void*)h->cones.pos
@@ -1058,7 +1073,7 @@ static int64_t cone_blocks(const sim_handle* h) { return adjoint_cone_blocks(std
 // Loss seed from the current (final) cone state: a_p = 2 w (p - t), a_theta = 0; the
 // per-workgroup loss partials are left in adj->loss_partial.
 static sim_status adjoint_seed(sim_handle* h) {
-    sim_status st = unbucket(h);
+    sim_status st = sync_cones(h);
     if (st != SIM_OK) return st;
     AdjointRun* a = h->adj;
     HIP_TRY(h, launch_adjoint_seed2d(h->cones.pos, a->tip_target, a->weight, a->acone,
@@ -1089,7 +1104,7 @@ struct RecordGuard {
     ~RecordGuard() {
         if (!h) return;
         h->record = nullptr;
-        if (h->block_steps > 1) (void)tiled_set_record(h->tiled, nullptr, 0, h->stream);
+        if (h->block_steps > 1) tiled_set_record(h->tiled, nullptr, 0);
     }
 };
 
@@ -1162,19 +1177,12 @@ sim_status sim_adjoint_run(sim_handle* h, int64_t n_steps, int32_t checkpoint_ev
             recording.h = h;
             h->record = a->tape;
             h->record_n0 = h->step;
-            if (h->block_steps > 1)
-                HIP_TRY(h, tiled_set_record(h->tiled, a->tape, (uint32_t)h->step, h->stream));
+            if (h->block_steps > 1) tiled_set_record(h->tiled, a->tape, (uint32_t)h->step);
         }
     }
     for (int j = 0; j < a->n_ckpt; ++j) {
-        // the cones' state into the caller-order arrays; tile buckets stay valid, so the run
-        // goes on without bucketing the cones again
-        if (h->cones_bucketed && !h->cones_ordered) {
-            HIP_TRY(h, tiled_sync_cones(h->plan, h->tiled, h->cones, h->stream));
-        } else {
-            sim_status st = unbucket(h);
-            if (st != SIM_OK) return st;
-        }
+        sim_status st = sync_cones(h);
+        if (st != SIM_OK) return st;
         // the checkpoint: fields and cone arrays in one copy launch
         CopySpans cp = {};
         size_t words = 0;
@@ -1196,7 +1204,7 @@ sim_status sim_adjoint_run(sim_handle* h, int64_t n_steps, int32_t checkpoint_ev
         }
         HIP_TRY(h, launch_copy_spans(cp, h->stream));
         const int64_t len = std::min<int64_t>(checkpoint_every, n_steps - (int64_t)j * checkpoint_every);
-        const sim_status st = sim_step(h, len);
+        st = sim_step(h, len);
         if (st != SIM_OK) return st;
     }
     sim_status st = adjoint_seed(h);
@@ -1555,8 +1563,8 @@ sim_status sim_batch_create(const sim_params* const* params, int32_t n, void* hi
     b->block_steps = b->sims[0]->plan.block_steps;
     if (total_cones > INT32_MAX / 2)
         return bail(batch_fail(b, SIM_EINVAL, "too many cones in the batch"));
-    b->item_cap = tiled_item_capacity(b->n_base, (int)total_cones);
-    // concatenated argument tables, work items, shared launch state
+    b->extra_cap = tiled_extra_capacity(total_cones);
+    // concatenated argument tables, tiles, shared launch state
     const size_t entry = tiled_table_entry_bytes();
     std::vector<int2> items;
     items.reserve(b->n_base);
@@ -1569,37 +1577,37 @@ sim_status sim_batch_create(const sim_params* const* params, int32_t n, void* hi
     });
     if ((e = hipMalloc(&b->table, entry * n)) != hipSuccess ||
         (e = hipMalloc(&b->base, sizeof(int2) * items.size())) != hipSuccess ||
-        (e = hipMalloc(&b->items, sizeof(int4) * b->item_cap)) != hipSuccess ||
+        (e = hipMalloc(&b->extra, sizeof(int4) * 2 * kBatchPartLists * b->extra_cap)) !=
+            hipSuccess ||
         (e = hipMalloc(&b->launch, sizeof(LaunchState))) != hipSuccess)
         return bail(batch_fail(b, SIM_ENOMEM, "batch allocation failed"));
     for (int i = 0; i < n; ++i)
-        if ((e = hipMemcpy((char*)b->table + entry * i, b->sims[i]->tiled.table, entry,
-                           hipMemcpyDeviceToDevice)) != hipSuccess)
-            return bail(batch_fail(b, SIM_EDEVICE, "table copy failed"));
+        if ((e = hipMemcpy((char*)b->table + entry * i, b->sims[i]->tiled.args, entry,
+                           hipMemcpyHostToDevice)) != hipSuccess)
+            return bail(batch_fail(b, SIM_EDEVICE, "table upload failed"));
     if ((e = hipMemcpy(b->base, items.data(), sizeof(int2) * items.size(),
                        hipMemcpyHostToDevice)) != hipSuccess)
         return bail(batch_fail(b, SIM_EDEVICE, "item upload failed"));
-    const LaunchState ls = tiled_launch_state(0);   // a persistent launch lists no slots
+    const LaunchState ls = {};
     if ((e = hipMemcpy(b->launch, &ls, sizeof ls, hipMemcpyHostToDevice)) != hipSuccess)
         return bail(batch_fail(b, SIM_EDEVICE, "launch state upload failed"));
     if ((e = tiled_prepare_batch(b->n_species, b->cpl, b->lds_bytes)) != hipSuccess)
         return bail(batch_fail(b, SIM_EDEVICE, "kernel attribute failed"));
     // initial bucketing of every simulation's cones
-    for (sim_handle* h : b->sims) {
-        if ((e = tiled_bucket(h->plan, h->tiled, h->cones, b->stream)) != hipSuccess)
+    for (int i = 0; i < n; ++i) {
+        sim_handle* h = b->sims[i];
+        if ((e = tiled_bucket_batch(h->plan, h->tiled, h->cones, i, b->launch, b->extra,
+                                    b->extra_cap, b->stream)) != hipSuccess)
             return bail(batch_fail(b, SIM_EDEVICE, "bucketing failed"));
         h->cones_bucketed = true;
     }
-    if ((e = tiled_build_items((const TiledArgs2D*)b->table, b->items, b->base, b->n_base,
-                               b->item_cap, b->launch, b->stream, false)) != hipSuccess)
-        return bail(batch_fail(b, SIM_EDEVICE, "work item listing failed"));
     // optional graph of `graph_launches` full-depth launches, replayed by sim_batch_step
     if (graph_launches > 0) {
         if ((e = hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal)) != hipSuccess)
             return bail(batch_fail(b, SIM_EDEVICE, "graph capture failed to start"));
         for (int l = 0; l < graph_launches; ++l) {
-            e = tiled_launch_batch((const TiledArgs2D*)b->table, b->items, b->base,
-                                   b->n_base, b->item_cap, b->n_species, b->cpl,
+            e = tiled_launch_batch((const TiledArgs2D*)b->table, b->extra, b->base,
+                                   b->n_base, b->extra_cap, b->n_species, b->cpl,
                                    b->lds_bytes, b->block_steps, b->launch, b->stream);
             if (e != hipSuccess) break;
         }
@@ -1623,18 +1631,8 @@ sim_status sim_batch_step(sim_batch* b, int64_t n_steps) {
     if (n_steps < 0) return batch_fail(b, SIM_EINVAL, "n_steps < 0");
     if (b->step + n_steps > 2147483647LL)
         return batch_fail(b, SIM_EINVAL, "step count would exceed 2^31-1");
-    bool rebucketed = false;
-    for (sim_handle* h : b->sims) {
+    for (sim_handle* h : b->sims)
         if (h->poisoned) return batch_fail(b, SIM_ESTATE, "a simulation hit a device error");
-        if (!h->cones_bucketed) {   // after a read of cones: put them back in the buckets
-            BATCH_TRY(b, tiled_bucket(h->plan, h->tiled, h->cones, b->stream));
-            h->cones_bucketed = true;
-            rebucketed = true;
-        }
-    }
-    if (rebucketed)
-        BATCH_TRY(b, tiled_build_items((const TiledArgs2D*)b->table, b->items, b->base,
-                                       b->n_base, b->item_cap, b->launch, b->stream, false));
     const int64_t per_graph = (int64_t)b->graph_launches * b->block_steps;
     while (per_graph > 0 && n_steps >= per_graph) {
         BATCH_TRY(b, hipGraphLaunch(b->graph_exec, b->stream));

@@ -30,42 +30,39 @@ struct TiledPlan {
     size_t lds_bytes = 0;
 };
 
-// Launch-to-launch state of the tiled kernel, in device memory: completed steps, which half
-// of every ping-pong pair is the input, and the work-queue counters (reset by the last
-// workgroup of each launch).
-struct LaunchState {
-    uint32_t step;
-    int32_t parity;
-    int32_t next;
-    int32_t exited;
-    int32_t n_items;   // work items of the next launch (listed by the last workgroup)
-    int32_t slots;     // work items a list laid out by die may hold (set by the host)
-};
+// Candidate part sizes of a crowded tile (kernels_tiled.hip).
+constexpr int kPartSizes = 5;
 
-// Initial launch state; `slots` bounds the work items of a list laid out by die (the
-// workgroups resident at once, and no more than its item capacity allows).
-LaunchState tiled_launch_state(int slots);
+// Launch-to-launch state of the tiled kernel, in device memory: completed steps, which half
+// of every ping-pong pair is the input (parity) and which third of the cone counts (phase),
+// the counters a launch resets by itself, and the crowded tiles' further parts, counted per
+// candidate size while the cones were put into their buckets ([phase], listed in
+// TiledState::extra).  The first group is read by every workgroup and so kept off the lines
+// that the atomics change.
+struct alignas(128) LaunchState {
+    uint32_t step;
+    int32_t parity, phase, unused;
+    alignas(128) int32_t next;   // the persistent queue
+    int32_t arrived;             // workgroups that have read the group above
+    alignas(128) int32_t extra_n[3][8];
+};
 
 struct TiledArgs2D;
 
 // Device buffers owned by the tiled path.
 struct TiledState {
     float4* bucket[2] = {nullptr, nullptr};    // per tile: cone slots (x, y, theta, id)
-    int32_t* count[2] = {nullptr, nullptr};    // cones per tile
+    char* memory = nullptr;                    // launch state, counts, lists and per-tile tables
+    int32_t* count[3] = {nullptr, nullptr, nullptr};   // cones per tile
     int cur = 0;                               // bucket buffer holding the live cones
+    int phase = 0;                             // and their counts (the device state's copies)
     int capacity = 0;                          // slots per tile
-    int32_t* src_start = nullptr;              // per tile: range into src_entry
-    int2* src_entry = nullptr;                 // (tile-local cell index, species)
-    float* src_amount = nullptr;
-    int32_t* tgt_start = nullptr;              // per tile: range into tgt_pts
-    float4* tgt_pts = nullptr;                 // targets a tile's cones can reach
-    TiledArgs2D* table = nullptr;              // device copy of this simulation's arguments
+    TiledArgs2D* args = nullptr;               // this simulation's arguments (host memory)
     LaunchState* launch = nullptr;             // device launch state
-    int2* base = nullptr;                      // (simulation, tile) per tile
-    int4* items = nullptr;                     // (simulation, tile, part) of the next launch
-    int item_cap = 0;
-    bool recording = false;                    // launches also write every sub-step's state
-                                               // to the run tape (tiled_set_record)
+    int4* extra = nullptr;                     // further parts of crowded tiles, (simulation,
+                                               // tile, part, 0): [parity][size][extra_cap]
+    int extra_cap = 0;
+    int room = 0;                              // workgroups resident beside one per tile
 };
 
 // Choose B and the tile shape; block_steps = 1 in the result means no tiling fits.
@@ -82,41 +79,41 @@ hipError_t tiled_allocate(const TiledPlan& plan, TiledState& st, int n_cones,
 hipError_t tiled_set_launch_state(TiledState& st, uint32_t step, int parity, hipStream_t stream);
 // Record mode: while tape is non-null every launch also writes the state after each of its
 // sub-steps to tape + ((step - n0) * n_species + s) * cells (null: off).
-hipError_t tiled_set_record(TiledState& st, float* tape, uint32_t n0, hipStream_t stream);
+void tiled_set_record(TiledState& st, float* tape, uint32_t n0);
 void tiled_release(TiledState& st);
-// Move active cones from the caller-order arrays into the tile buckets.
+// Move active cones from the caller-order arrays into the tile buckets (which hold none:
+// new, or dropped).  In a batch `launch` and `extra` are the batch's and sim its index.
 hipError_t tiled_bucket(const TiledPlan& plan, TiledState& st, ConeArrays cones,
                         hipStream_t stream);
-// Move active cones from the tile buckets back into the caller-order arrays.
-hipError_t tiled_unbucket(const TiledPlan& plan, TiledState& st, ConeArrays cones,
-                          hipStream_t stream);
-// The same copy of the active cones into the caller-order arrays, leaving the buckets and
-// counts in place, so that stepping continues without bucketing again.
-hipError_t tiled_sync_cones(const TiledPlan& plan, const TiledState& st, ConeArrays cones,
-                            hipStream_t stream);
+hipError_t tiled_bucket_batch(const TiledPlan& plan, TiledState& st, ConeArrays cones,
+                              int sim, LaunchState* launch, int4* extra, int extra_cap,
+                              hipStream_t stream);
+// Copy the active cones from the tile buckets into the caller-order arrays; the buckets stay
+// valid, so stepping goes on without bucketing again, unless `drop` empties them.
+hipError_t tiled_sync_cones(const TiledPlan& plan, TiledState& st, ConeArrays cones,
+                            hipStream_t stream, bool drop);
 // Advance `steps` (<= plan.block_steps) steps in one launch; flips st.cur like the device
 // parity.
 // start/stop (may be null): events the launch records around the kernel (timing).
 hipError_t tiled_launch(const TiledPlan& plan, TiledState& st, int steps, hipStream_t stream,
                         hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
 
+// Mirror launches that ran without tiled_launch (a batch's) in the host-side state.
+void tiled_advanced(TiledState& st, int launches);
+
 // Size in bytes of one argument-table entry (for batching several simulations).
 size_t tiled_table_entry_bytes();
 // One persistent launch over the work items of a batch whose argument tables are
 // concatenated in `table`; all simulations share n_species, cpl and `launch`.  base lists
-// every (simulation, tile); items receives the expanded (simulation, tile, part) list.
-hipError_t tiled_launch_batch(const TiledArgs2D* table, int4* items, const int2* base,
-                              int n_base, int item_cap, int n_species, int cpl,
+// every (simulation, tile); extra the further parts of crowded tiles.
+hipError_t tiled_launch_batch(const TiledArgs2D* table, int4* extra, const int2* base,
+                              int n_base, int extra_cap, int n_species, int cpl,
                               size_t lds_bytes, int steps, LaunchState* launch,
                               hipStream_t stream);
-// Upper bound on the work items of n_tiles tiles holding n_cones cones in total.
-int tiled_item_capacity(int n_tiles, int n_cones);
-// List the work items for the current cone counts (after cones were bucketed); by_die lays
-// the list out for a launch of one workgroup per slot (a contiguous run of tiles per die),
-// else in tile order for the persistent batch launch.
-hipError_t tiled_build_items(const TiledArgs2D* table, int4* items, const int2* base,
-                             int n_base, int item_cap, LaunchState* launch, hipStream_t stream,
-                             bool by_die);
+// Bound on the further parts of tiles holding n_cones cones in total, in full parts.
+int tiled_extra_capacity(int64_t n_cones);
+constexpr int kBatchPartLists = 1;   // a batch lists full parts only: extra is
+                                     // [parity][extra_cap]
 // Number of workgroups of the persistent batch launch for a given dynamic LDS size.
 int tiled_persistent_grid(size_t lds_bytes);
 // Allow the batch kernel variant lds_bytes of dynamic LDS (call before launching or
