@@ -343,6 +343,33 @@ __device__ __forceinline__ void gradient_2d(const F& f, const ConeRules& r, floa
     gradient_from_2d(p, corner_gradients_2d(p, r), gx, gy, value);
 }
 
+// Reverse of the interpolated central-difference gradient of one species at (x, y) with
+// respect to the field: the 12 cells that the sample read (cells repeat at walls; their
+// shares then add up) and their adjoints, for the adjoint (agx, agy) of the sampled gradient,
+// already weighted by the species sign.
+struct Scatter2D {
+    int i[12], j[12];
+    float v[12];
+};
+
+__device__ __forceinline__ Scatter2D sample_adjoint_2d(const ConeRules& r, float x, float y,
+                                                       float agx, float agy) {
+    int i0, j0;
+    float fx, fy;
+    corner(x, r.inv_dx, r.nx, i0, fx);
+    corner(y, r.inv_dx, r.ny, j0, fy);
+    const float w00 = (1.0f - fx) * (1.0f - fy), w10 = fx * (1.0f - fy);
+    const float w01 = (1.0f - fx) * fy, w11 = fx * fy;
+    const float hx = r.half_inv_dx * agx, hy = r.half_inv_dx * agy;
+    const int im = max(i0 - 1, 0), ip = min(i0 + 2, r.nx - 1);
+    const int jm = max(j0 - 1, 0), jp = min(j0 + 2, r.ny - 1);
+    return Scatter2D{{im, i0, i0 + 1, ip, im, i0, i0 + 1, ip, i0, i0 + 1, i0, i0 + 1},
+                     {j0, j0, j0, j0, j0 + 1, j0 + 1, j0 + 1, j0 + 1, jm, jm, jp, jp},
+                     {-w00 * hx, fmaf(-w10, hx, -(w01 * hy)), fmaf(w00, hx, -(w11 * hy)),
+                      w10 * hx, -w01 * hx, fmaf(-w11, hx, w00 * hy), fmaf(w01, hx, w10 * hy),
+                      w11 * hx, -w00 * hy, -w10 * hy, w01 * hy, w11 * hy}};
+}
+
 // The footprint of the interpolated 3D gradient: the lower corner (i0, j0, l0) of the 2x2x2
 // cell-centre block around the tip, the fractions along each axis, and the clamped indices
 // one beyond each face (ghost = own value at a wall).

@@ -150,23 +150,49 @@ __device__ __forceinline__ int fixed_exponent(uint32_t max_bits) {
     return e;
 }
 
-struct FixedStep {
-    const long long* q;   // one species' sums of the step, one per cell
-    double inv;           // 2^(e - kFixedBits)
-    __device__ __forceinline__ float operator[](size_t x) const {
-        return (float)((double)q[x] * inv);
-    }
+// Reverse pass of the 2D step, segment by segment (kernels_adjoint.hip for the cones,
+// kernels_reverse2d.hip for the fields).
+constexpr int kRevSteps = 8;   // reverse field steps per launch
+
+// One checkpoint segment of `len` steps from step seg0 and what its reverse works on.  Field
+// state c^t of species s (after t steps of the segment, t = 0 .. len) is
+// fields + (t * n_species + s) * cells.
+struct ReverseSegment {
+    ConeRules rules;
+    StencilCoef coef[2];
+    int nx, ny, n_species, M, len;
+    uint32_t seg0;
+    const float* fields;
+    const float4* tips;    // [len][M]: the cones' state (x, y, theta) at the start of each step
+    float2* ag;            // [len][M]: adjoint of the cone's sampled gradient, before the
+                           // species' signs
+    float* vmax;           // [len][M]: largest |adjoint| of a cell its samples read
+    // zero before the segment's launches: the step maxima and the tiles' cone counts
+    uint32_t* step_max;    // [len]
+    int32_t* count;        // [launch][tile]
+    int32_t* list;         // [launch][list_cap]
+    size_t list_cap;
+    // accumulators over the whole sweep: [species][tile], and one per source
+    double* acc_D;
+    double* acc_k;
+    double* acc_q;
+    const int32_t* q_start;   // [species][tile + 1] into q_entry (reverse_sources)
+    const int2* q_entry;
 };
-
-__device__ __forceinline__ FixedStep fixed_step(const long long* q, const uint32_t* step_max,
-                                                int t) {
-    return FixedStep{q, ldexp(1.0, fixed_exponent(step_max[t]) - kFixedBits)};
-}
-
-// Reverse pass of the 2D step (kernels_adjoint.hip).  Field adjoint grids have
-// adjoint_field_blocks(nx, ny) workgroups, each owning one slot of acc_D / acc_k.
-// A segment's fields are `fields + (t * n_species + s) * cells` for t = 0..len.
-int adjoint_field_blocks(int nx, int ny);
+int reverse_tiles(int nx, int ny);
+int reverse_launches(int len);
+// Entries that the list of one launch can need: M cones moving at most step_cells per step.
+size_t reverse_list_capacity(int nx, int ny, int M, double step_cells);
+// Append one species' sources, numbered from `first`, listed by the tile of their cell.
+void reverse_sources(int nx, int ny, const std::vector<int32_t>& cells, int first,
+                     std::vector<int32_t>& start, std::vector<int2>& entry);
+// The cones that can touch each tile, for every launch of the segment (after the cones'
+// reverse).
+hipError_t launch_reverse_lists(const ReverseSegment& g, hipStream_t stream);
+// Launch `launch` of reverse_launches(len): the field adjoint of every species from a_in to
+// a_out, kRevSteps steps back (fewer in the last launch).
+hipError_t launch_field_reverse2d(const ReverseSegment& g, int launch, const float* const* a_in,
+                                  float* const* a_out, hipStream_t stream);
 int adjoint_cone_blocks(int n);
 // Forward re-run of segments seg_first .. seg_first + n_seg - 1 of a run checkpointed every
 // `every` of its n_steps steps from step n0; run step t's fields are at
@@ -177,47 +203,10 @@ hipError_t launch_cones_segments2d(const ConeRules& rules, const float* fields, 
                                    int every, int n_steps, uint32_t n0, const float* ckpt_pos,
                                    const float* ckpt_dir, const int32_t* ckpt_int, int M,
                                    float4* tape, hipStream_t stream);
-// Reverse of a segment's cone steps: each cone's gradient samples' adjoints (12 cells per
-// species and step) are written to the segment's records, rec_at / rec_v
-// [len][n][n_species][12]; then the largest |contribution| of every step goes to
-// step_max[len] (cleared by the call).
-hipError_t launch_cone_adjoint_segment2d(const ConeRules& rules, const float* fields,
-                                         size_t cells, int n_species, uint32_t seg0, int len,
-                                         int32_t* rec_at, float* rec_v, uint32_t* step_max,
-                                         const float4* tape, const int32_t* status,
-                                         const int32_t* event_step, float* acone, int n,
+// Reverse of a segment's cone steps (ag, vmax), then every step's maximum (step_max).
+hipError_t launch_cone_adjoint_segment2d(const ReverseSegment& g, const int32_t* status,
+                                         const int32_t* event_step, float* acone,
                                          hipStream_t stream);
-// The records of segment steps t_lo .. t_lo + n_steps - 1 added into their fixed-point sums
-// with each step's scale: step t's sums of species s are e + ((t % ring) * n_species + s) *
-// cells, a ring of `ring` steps whose slots for these steps must hold zeros.
-hipError_t launch_sample_add2d(size_t cells, int n_species, uint32_t seg0, int len, int t_lo,
-                               int n_steps, int ring, const int32_t* rec_at, const float* rec_v,
-                               const uint32_t* step_max, long long* e, const int32_t* status,
-                               const int32_t* event_step, int n, hipStream_t stream);
-// One reverse field step with the sample adjoints of step t: e + (t * n_species) * cells
-// holds the species' fixed-point sums (e points at this species' first step).
-hipError_t launch_field_adjoint2d(int nx, int ny, const float* a_in, const long long* e_in,
-                                  const uint32_t* step_max, int t, const float* c,
-                                  float* a_out, StencilCoef coef, double* acc_D, double* acc_k,
-                                  const int32_t* q_cell, int n_q, double* acc_q,
-                                  hipStream_t stream);
-// Two reverse steps per launch (n, then n - 1): a_in = a^{n+1}, e1/e0 = e^{n+1}/e^n (the
-// fixed-point sums of segment steps t1 / t0),
-// c1/c0 = c^n/c^{n-1}, a_out = a^{n-1}; adjoint_pair_blocks(nx, ny) boxes own acc_D/acc_k
-// slots, and the sources are listed per box (adjoint_pair_sources: q_start[box] ..
-// q_start[box + 1] - 1 index q_index, the source numbers m of q_cell / acc_q).  z1 and z0
-// (may be null) are sums of other steps, which the launch sets to zero (each box its own
-// cells); neither may be e1 or e0.
-int adjoint_pair_blocks(int nx, int ny);
-void adjoint_pair_sources(int nx, int ny, const std::vector<int32_t>& cells,
-                          std::vector<int32_t>& start, std::vector<int32_t>& index);
-hipError_t launch_field_adjoint2d_pair(int nx, int ny, const float* a_in, const long long* e1,
-                                       const long long* e0, const uint32_t* step_max, int t1,
-                                       int t0, const float* c1, const float* c0, float* a_out,
-                                       StencilCoef coef, double* acc_D, double* acc_k,
-                                       const int32_t* q_start, const int32_t* q_index,
-                                       const int32_t* q_cell, double* acc_q,
-                                       long long* z1, long long* z0, hipStream_t stream);
 hipError_t launch_adjoint_seed2d(const float* pos, const float* tip_target, const float* weight,
                                  float* acone, double* partial, int n, hipStream_t stream);
 

@@ -13,24 +13,12 @@
 //                             once, one thread per segment and cone);
 //   k_cone_adjoint_segment2d  walks the steps backwards carrying each cone's adjoint of
 //                             (p, theta) through advance, capped turn and interpolated
-//                             gradient, and records its gradient samples' adjoints (12
-//                             cells and values per species, cone and step);
-//   k_sample_max, k_sample_add  add the records of every step into e^{n+1}, one buffer of
-//                             64-bit fixed-point sums per step and species, scaled by the
-//                             step's largest contribution: integer additions, so the sums
-//                             (and the whole gradient) do not depend on the order in which
-//                             the cones' contributions arrive.  The sums are added a few
-//                             steps at a time, just before those steps are reversed, into a
-//                             small ring of per-step buffers (the reverse field launches
-//                             clear the buffers they are done with);
-//   k_field_adjoint2d_pair    (kernels_field2d.hip) two reverse steps per launch, and
-//   k_field_adjoint2d_rows    one for the first step of a segment of odd length: with
-//                             b = a^{n+1} + e^{n+1}, a^n = b + r Lap b - k dt b (the
-//                             zero-flux Laplacian is symmetric, so the adjoint stencil is
-//                             the stencil), and
-//                             per-workgroup FP64 sums of b Lap c^n (for dL/dD) and b c^n (for
-//                             dL/dk) plus b at every source cell (dL/dq).
-// HBM bytes per cell of the reverse field step: a^{n+1}, e^{n+1} and c^n read, a^n written.
+//                             gradient, and records the adjoint of its sampled gradient
+//                             (two values per cone and step);
+//   k_sample_max              takes each step's largest contribution to a cell, the scale of
+//                             its fixed-point sums;
+//   kernels_reverse2d.hip     reverses the segment's field steps, eight per launch, adding
+//                             the samples' adjoints where the cones were.
 #include "internal.hpp"
 
 namespace cuesim {
@@ -57,63 +45,26 @@ __device__ double adj_block_sum(double v) {
     return t;
 }
 
-// The adjoints of one gradient sample's 12 loaded cells: adds to af[at[k]] of v[k].
-struct Scatter2D {
-    int at[12];
-    float v[12];
-};
-
-// Record of one sample's adjoints: rec_at / rec_v + ((t * n + i) * n_species + s) * 12.
-__device__ __forceinline__ void write_record(int32_t* __restrict__ at, float* __restrict__ v,
-                                             const Scatter2D& s) {
-#pragma unroll
-    for (int k = 0; k < 12; k += 4) {
-        *(int4*)(at + k) = make_int4(s.at[k], s.at[k + 1], s.at[k + 2], s.at[k + 3]);
-        *(float4*)(v + k) = make_float4(s.v[k], s.v[k + 1], s.v[k + 2], s.v[k + 3]);
-    }
-}
-
-// Reverse of the interpolated central-difference gradient of one species at (x, y), from
-// the footprint and corner gradients the forward sample used.  (agx, agy) is the adjoint of
-// the sampled gradient, already weighted by the species sign.  Adds the adjoint of the tip
-// position into (apx, apy) -- the interpolation weights depend on the tip; along an axis
-// where the tip is clamped to the outermost centres they do not -- and returns the adjoint
-// of the 12 loaded values (cells repeat at walls; their adds then combine).
-__device__ __forceinline__ Scatter2D gradient_2d_reverse(const Footprint2D& p,
-                                                         const CornerGradients2D& g,
-                                                         const ConeRules& r, float x, float y,
-                                                         float agx, float agy, float& apx,
-                                                         float& apy) {
+// Reverse of the interpolated central-difference gradient of one species at (x, y) with
+// respect to the tip, from the footprint and corner gradients the forward sample used:
+// (agx, agy) is the adjoint of the sampled gradient, already weighted by the species sign.
+// Adds into (apx, apy) -- the interpolation weights depend on the tip; along an axis where the
+// tip is clamped to the outermost centres they do not.  (The field's share is
+// sample_adjoint_2d.)
+__device__ __forceinline__ void sample_tip_adjoint_2d(const Footprint2D& p,
+                                                      const CornerGradients2D& g,
+                                                      const ConeRules& r, float x, float y,
+                                                      float agx, float agy, float& apx,
+                                                      float& apy) {
     const float fx = p.fx, fy = p.fy;
     const float ux = fmaf(x, r.inv_dx, -0.5f), uy = fmaf(y, r.inv_dx, -0.5f);
     const bool free_x = ux > 0.0f && ux < (float)(r.nx - 1);
     const bool free_y = uy > 0.0f && uy < (float)(r.ny - 1);
-    const int nx = r.nx, i0 = p.i0, j0 = p.j0;
-    const float w00 = (1.0f - fx) * (1.0f - fy), w10 = fx * (1.0f - fy);
-    const float w01 = (1.0f - fx) * fy, w11 = fx * fy;
-    // position: d w / d f along each axis, times d f / d p = 1 / dx where not clamped
+    // d w / d f along each axis, times d f / d p = 1 / dx where not clamped
     const float aw00 = fmaf(agy, g.gy00, agx * g.gx00), aw10 = fmaf(agy, g.gy10, agx * g.gx10);
     const float aw01 = fmaf(agy, g.gy01, agx * g.gx01), aw11 = fmaf(agy, g.gy11, agx * g.gx11);
     if (free_x) apx = fmaf(r.inv_dx, fmaf(fy, aw11 - aw01, (1.0f - fy) * (aw10 - aw00)), apx);
     if (free_y) apy = fmaf(r.inv_dx, fmaf(fx, aw11 - aw10, (1.0f - fx) * (aw01 - aw00)), apy);
-    // field: each loaded value's adjoint
-    const float h = r.half_inv_dx;
-    const float hx = h * agx, hy = h * agy;
-    const int r0 = j0 * nx, r1 = r0 + nx;
-    Scatter2D s;
-    s.at[0] = r0 + p.im;      s.v[0] = -w00 * hx;
-    s.at[1] = r0 + i0;        s.v[1] = fmaf(-w10, hx, -(w01 * hy));
-    s.at[2] = r0 + i0 + 1;    s.v[2] = fmaf(w00, hx, -(w11 * hy));
-    s.at[3] = r0 + p.ip;      s.v[3] = w10 * hx;
-    s.at[4] = r1 + p.im;      s.v[4] = -w01 * hx;
-    s.at[5] = r1 + i0;        s.v[5] = fmaf(-w11, hx, w00 * hy);
-    s.at[6] = r1 + i0 + 1;    s.v[6] = fmaf(w01, hx, w10 * hy);
-    s.at[7] = r1 + p.ip;      s.v[7] = w11 * hx;
-    s.at[8] = p.jm * nx + i0; s.v[8] = -w00 * hy;
-    s.at[9] = s.at[8] + 1;    s.v[9] = -w10 * hy;
-    s.at[10] = p.jp * nx + i0; s.v[10] = w01 * hy;
-    s.at[11] = s.at[10] + 1;  s.v[11] = w11 * hy;
-    return s;
 }
 
 struct Field2D {
@@ -124,9 +75,9 @@ struct Field2D {
 
 // Reverse of one cone step (step index `step`) of cone i from its state (x, y, theta) at
 // the start of the step, the footprints p0/p1 of its gradient samples in the fields after
-// the step's field update, their corner gradients and the weighted gradient (gx, gy).  (apx, apy, ath) holds the adjoint of the state after the
-// step on entry and of the state before it on exit; out[s] receives the adjoints of species
-// s's sampled cells.
+// the step's field update, their corner gradients and the weighted gradient (gx, gy).
+// (apx, apy, ath) holds the adjoint of the state after the step on entry and of the state
+// before it on exit; (agx, agy) receives the adjoint of the weighted gradient.
 template <int NS>
 __device__ __forceinline__ void cone_adjoint_step(const ConeRules& r, const Footprint2D& p0,
                                                   const Footprint2D& p1,
@@ -134,7 +85,7 @@ __device__ __forceinline__ void cone_adjoint_step(const ConeRules& r, const Foot
                                                   const CornerGradients2D& g1, float gx,
                                                   float gy, float4 st, int i, uint32_t step,
                                                   float& apx, float& apy, float& ath,
-                                                  Scatter2D* out) {
+                                                  float& agx, float& agy) {
     const float x = st.x, y = st.y, th = st.z;
     float s, c;
     sincos_angle(th, s, c);
@@ -152,7 +103,7 @@ __device__ __forceinline__ void cone_adjoint_step(const ConeRules& r, const Foot
     const float athn = fmaf(r.step_len, fmaf(cn, apy, -(sn * apx)), ath);
     // theta' = theta + turn(theta, g) + noise
     ath = athn;
-    float agx = 0.0f, agy = 0.0f;
+    agx = agy = 0.0f;
     if (!capped) {
         const float den = fmaf(along, along, cross * cross);
         const float a_cross = athn * along / den, a_along = -athn * cross / den;
@@ -161,10 +112,9 @@ __device__ __forceinline__ void cone_adjoint_step(const ConeRules& r, const Foot
         agx = r.gain * fmaf(a_along, c, -(a_cross * s));
         agy = r.gain * fmaf(a_cross, c, a_along * s);
     }
-    out[0] = gradient_2d_reverse(p0, g0, r, x, y, r.sign0 * agx, r.sign0 * agy, apx, apy);
+    sample_tip_adjoint_2d(p0, g0, r, x, y, r.sign0 * agx, r.sign0 * agy, apx, apy);
     if (NS > 1)
-        out[NS - 1] = gradient_2d_reverse(p1, g1, r, x, y, r.sign1 * agx, r.sign1 * agy, apx,
-                                          apy);
+        sample_tip_adjoint_2d(p1, g1, r, x, y, r.sign1 * agx, r.sign1 * agy, apx, apy);
 }
 
 // The forward gradient sample of a step from its footprints, computed exactly as the
@@ -269,20 +219,35 @@ __device__ __forceinline__ int last_step(const Segment2D& seg, const int32_t* st
     return (int)max<int64_t>(min<int64_t>(seg.len - 1, last - 1 - (int64_t)seg.seg0), -1);
 }
 
+// Largest |adjoint| of the cells that one species' sample read.
+__device__ __forceinline__ float sample_max(const ConeRules& r, float x, float y, float agx,
+                                            float agy) {
+    const Scatter2D c = sample_adjoint_2d(r, x, y, agx, agy);
+    float m = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 12; ++k) m = fmaxf(m, fabsf(c.v[k]));
+    return m;
+}
+
 // Reverse of one segment's cone steps, one thread per cone from the last step to the first;
-// the adjoints of step t's gradient samples are recorded (write_record) for k_sample_add.
+// the adjoint of step t's sampled gradient goes to ag[t * n + i] and the largest adjoint of a
+// cell it read to vmax (zero at steps the cone takes no part in).
 // The forward states come from the run's cone tape, so the gathers of the step before do
 // not wait for this step's adjoint: its footprints are loaded one step ahead and its state
 // two.
 template <int NS>
 __global__ __launch_bounds__(kSegThreads) void k_cone_adjoint_segment2d(
-    ConeRules r, Segment2D seg, int32_t* __restrict__ rec_at, float* __restrict__ rec_v,
+    ConeRules r, Segment2D seg, float2* __restrict__ ag, float* __restrict__ vmax,
     const float4* __restrict__ tape, const int32_t* __restrict__ status,
     const int32_t* __restrict__ event_step, float* __restrict__ acone, int n) {
     const int i = blockIdx.x * kSegThreads + threadIdx.x;
     if (i >= n) return;
     float apx = acone[3 * i], apy = acone[3 * i + 1], ath = acone[3 * i + 2];
     const int t_hi = last_step(seg, status, event_step, i);
+    for (int t = seg.len - 1; t > t_hi; --t) {
+        ag[(size_t)t * n + i] = make_float2(0.0f, 0.0f);
+        vmax[(size_t)t * n + i] = 0.0f;
+    }
     if (t_hi >= 0) {
         float4 st = tape[(size_t)t_hi * n + i];
         float4 next = tape[(size_t)max(t_hi - 1, 0) * n + i];
@@ -302,15 +267,14 @@ __global__ __launch_bounds__(kSegThreads) void k_cone_adjoint_segment2d(
                             : q0;
             }
             CornerGradients2D g0, g1;
-            float gx, gy;
+            float gx, gy, agx, agy;
             sample_2d<NS>(r, p0, p1, g0, g1, gx, gy);
-            Scatter2D out[NS];
             cone_adjoint_step<NS>(r, p0, p1, g0, g1, gx, gy, st, i, seg.seg0 + (uint32_t)t,
-                                  apx, apy, ath, out);
-            const size_t rec = (((size_t)t * n + i) * NS) * 12;
-#pragma unroll
-            for (int s = 0; s < NS; ++s) write_record(rec_at + rec + s * 12, rec_v + rec + s * 12,
-                                                      out[s]);
+                                  apx, apy, ath, agx, agy);
+            float m = sample_max(r, st.x, st.y, r.sign0 * agx, r.sign0 * agy);
+            if (NS > 1) m = fmaxf(m, sample_max(r, st.x, st.y, r.sign1 * agx, r.sign1 * agy));
+            ag[(size_t)t * n + i] = make_float2(agx, agy);
+            vmax[(size_t)t * n + i] = m;
             st = next;
             next = next2;
             p0 = q0;
@@ -322,78 +286,31 @@ __global__ __launch_bounds__(kSegThreads) void k_cone_adjoint_segment2d(
     acone[3 * i + 2] = ath;
 }
 
-constexpr int kRecThreads = 256;
-
 // Largest |contribution| of every step of the segment: a workgroup takes kMaxCones cones of
-// one step (kMaxCones / kRecThreads per thread), reduces their maximum through the wavefronts
+// one step (kMaxCones / kMaxThreads per thread), reduces their maximum through the wavefronts
 // and LDS, and applies one atomic maximum on the step's FP32 bits (non-negative floats order
 // like their bits).  Few atomics meet on each step's word: with one per wavefront (128 per
-// step at 8192 cones) they queued on those words, and a gradient's reverse sweep at 1024^2
-// took 23.5 instead of 22.5 ms.
-constexpr int kMaxCones = 8 * kRecThreads;
+// step at 8192 cones) they queued on those words.
+constexpr int kMaxThreads = 256;
+constexpr int kMaxCones = 8 * kMaxThreads;
 
-template <int NS>
-__global__ __launch_bounds__(kRecThreads) void k_sample_max(
-    Segment2D seg, const float* __restrict__ rec_v, const int32_t* __restrict__ status,
-    const int32_t* __restrict__ event_step, uint32_t* __restrict__ step_max, int n) {
+__global__ __launch_bounds__(kMaxThreads) void k_sample_max(const float* __restrict__ vmax,
+                                                            uint32_t* __restrict__ step_max,
+                                                            int n) {
     const int t = blockIdx.y;
     float m = 0.0f;
 #pragma unroll
-    for (int k = 0; k < kMaxCones / kRecThreads; ++k) {
-        const int i = blockIdx.x * kMaxCones + k * kRecThreads + threadIdx.x;
-        if (i < n && t <= last_step(seg, status, event_step, i)) {
-            const float4* v = (const float4*)(rec_v + (((size_t)t * n + i) * NS) * 12);
-#pragma unroll
-            for (int q = 0; q < 3 * NS; ++q) {
-                const float4 x = v[q];
-                m = fmaxf(m, fmaxf(fmaxf(fabsf(x.x), fabsf(x.y)), fmaxf(fabsf(x.z), fabsf(x.w))));
-            }
-        }
+    for (int k = 0; k < kMaxCones / kMaxThreads; ++k) {
+        const int i = blockIdx.x * kMaxCones + k * kMaxThreads + threadIdx.x;
+        if (i < n) m = fmaxf(m, vmax[(size_t)t * n + i]);
     }
     for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-    __shared__ float wave_max[kRecThreads / 64];
+    __shared__ float wave_max[kMaxThreads / 64];
     if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = m;
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int w = 1; w < kRecThreads / 64; ++w) m = fmaxf(m, wave_max[w]);
+        for (int w = 1; w < kMaxThreads / 64; ++w) m = fmaxf(m, wave_max[w]);
         if (m > 0.0f) atomicMax(&step_max[t], __float_as_uint(m));
-    }
-}
-
-// Every (cone, step) record of steps t_lo .. t_lo + gridDim.y - 1 added into the step's
-// fixed-point sums (slot t % ring of e): q = rint(v 2^(40 - e)) (the product is an exact
-// power-of-two scaling in FP64), |q| <= 2^40.
-template <int NS>
-__global__ __launch_bounds__(kRecThreads) void k_sample_add(
-    Segment2D seg, int t_lo, int ring, const int32_t* __restrict__ rec_at,
-    const float* __restrict__ rec_v, const int32_t* __restrict__ status,
-    const int32_t* __restrict__ event_step, const uint32_t* __restrict__ step_max,
-    unsigned long long* __restrict__ e, int n) {
-    const int i = blockIdx.x * kRecThreads + threadIdx.x;
-    const int t = t_lo + blockIdx.y;
-    if (i >= n || t > last_step(seg, status, event_step, i)) return;
-    const size_t rec = (((size_t)t * n + i) * NS) * 12;
-    // the whole record first (16-byte loads, all in flight together), then the additions
-    float4 v[3 * NS];
-    int4 at[3 * NS];
-#pragma unroll
-    for (int k = 0; k < 3 * NS; ++k) {
-        v[k] = ((const float4*)(rec_v + rec))[k];
-        at[k] = ((const int4*)(rec_at + rec))[k];
-    }
-    const double scale = ldexp(1.0, kFixedBits - fixed_exponent(step_max[t]));
-#pragma unroll
-    for (int k = 0; k < 12 * NS; ++k) {
-        unsigned long long* dst = e + ((size_t)(t % ring) * NS + k / 12) * seg.cells;
-        const float4 vq = v[k / 4];
-        const int4 aq = at[k / 4];
-        const float val = k % 4 == 0 ? vq.x : k % 4 == 1 ? vq.y : k % 4 == 2 ? vq.z : vq.w;
-        const int cell = k % 4 == 0 ? aq.x : k % 4 == 1 ? aq.y : k % 4 == 2 ? aq.z : aq.w;
-        const double x = (double)val * scale;
-        // (a non-finite contribution, possible only from non-finite fields, adds nothing
-        // rather than an undefined conversion)
-        const long long q = isfinite(x) ? (long long)rint(x) : 0;
-        if (q != 0) atomicAdd(dst + cell, (unsigned long long)q);
     }
 }
 
@@ -440,46 +357,22 @@ hipError_t launch_cones_segments2d(const ConeRules& rules, const float* fields, 
     return hipGetLastError();
 }
 
-hipError_t launch_cone_adjoint_segment2d(const ConeRules& rules, const float* fields,
-                                         size_t cells, int n_species, uint32_t seg0, int len,
-                                         int32_t* rec_at, float* rec_v, uint32_t* step_max,
-                                         const float4* tape, const int32_t* status,
-                                         const int32_t* event_step, float* acone, int n,
+hipError_t launch_cone_adjoint_segment2d(const ReverseSegment& g, const int32_t* status,
+                                         const int32_t* event_step, float* acone,
                                          hipStream_t stream) {
-    if (len == 0) return hipSuccess;
-    hipError_t err = hipMemsetAsync(step_max, 0, sizeof(uint32_t) * (size_t)len, stream);
-    if (err != hipSuccess || n == 0) return err;
-    const Segment2D seg{fields, cells, n_species, seg0, len};
+    const int n = g.M;
+    if (g.len == 0 || n == 0) return hipSuccess;
+    const Segment2D seg{g.fields, (size_t)g.nx * g.ny, g.n_species, g.seg0, g.len};
     const dim3 grid((n + kSegThreads - 1) / kSegThreads);
-    const dim3 max_grid((n + kMaxCones - 1) / kMaxCones, len);
-    if (n_species > 1) {
+    const dim3 max_grid((n + kMaxCones - 1) / kMaxCones, g.len);
+    if (g.n_species > 1)
         hipLaunchKernelGGL(k_cone_adjoint_segment2d<2>, grid, dim3(kSegThreads), 0, stream,
-                           rules, seg, rec_at, rec_v, tape, status, event_step, acone, n);
-        hipLaunchKernelGGL(k_sample_max<2>, max_grid, dim3(kRecThreads), 0, stream, seg, rec_v,
-                           status, event_step, step_max, n);
-    } else {
-        hipLaunchKernelGGL(k_cone_adjoint_segment2d<1>, grid, dim3(kSegThreads), 0, stream,
-                           rules, seg, rec_at, rec_v, tape, status, event_step, acone, n);
-        hipLaunchKernelGGL(k_sample_max<1>, max_grid, dim3(kRecThreads), 0, stream, seg, rec_v,
-                           status, event_step, step_max, n);
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_sample_add2d(size_t cells, int n_species, uint32_t seg0, int len, int t_lo,
-                               int n_steps, int ring, const int32_t* rec_at, const float* rec_v,
-                               const uint32_t* step_max, long long* e, const int32_t* status,
-                               const int32_t* event_step, int n, hipStream_t stream) {
-    if (n == 0 || n_steps <= 0) return hipSuccess;
-    const Segment2D seg{nullptr, cells, n_species, seg0, len};
-    const dim3 rec_grid((n + kRecThreads - 1) / kRecThreads, n_steps);
-    unsigned long long* eu = (unsigned long long*)e;
-    if (n_species > 1)
-        hipLaunchKernelGGL(k_sample_add<2>, rec_grid, dim3(kRecThreads), 0, stream, seg, t_lo,
-                           ring, rec_at, rec_v, status, event_step, step_max, eu, n);
+                           g.rules, seg, g.ag, g.vmax, g.tips, status, event_step, acone, n);
     else
-        hipLaunchKernelGGL(k_sample_add<1>, rec_grid, dim3(kRecThreads), 0, stream, seg, t_lo,
-                           ring, rec_at, rec_v, status, event_step, step_max, eu, n);
+        hipLaunchKernelGGL(k_cone_adjoint_segment2d<1>, grid, dim3(kSegThreads), 0, stream,
+                           g.rules, seg, g.ag, g.vmax, g.tips, status, event_step, acone, n);
+    hipLaunchKernelGGL(k_sample_max, max_grid, dim3(kMaxThreads), 0, stream, g.vmax, g.step_max,
+                       n);
     return hipGetLastError();
 }
 

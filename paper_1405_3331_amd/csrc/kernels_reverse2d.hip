@@ -1,0 +1,598 @@
+// kernels_reverse2d.hip -- the reverse field steps of the gradient sweep, up to kRevSteps per
+// launch: with b^t = a^{t+1} + e^t (e: the cone samples' adjoints of run step t),
+//   a^t = b + r Lap b - k dt b    (the zero-flux Laplacian is symmetric),
+// FP64 sums of b Lap c^t (for dL/dD) and b c^t (for dL/dk) over all cells, and b at every
+// source cell (for dL/dq).
+//
+// One workgroup takes one tile of one species: a core of kTX x kTY cells and a halo of
+// kRevSteps cells on every side, a^{t+1} loaded into LDS once; each sub-step adds the cones'
+// adjoints into the tile, updates it in place (the valid region shrinks by one cell) and adds
+// the core's share of the two sums, reading c^t from the run's recorded states, one sub-step
+// ahead of its use; the core's a goes back to memory after the last.
+//
+// The cones' adjoints of a step are added per cell as 64-bit fixed-point numbers (LDS integer
+// atomics, value = q 2^(e - kFixedBits), 2^e from the step's largest contribution) and enter
+// the tile as one float: integer additions, so the sum in a cell does not depend on the order
+// in which the contributions arrive and the gradient is bitwise reproducible.  Which cones can
+// touch a tile's loaded region during a launch is listed beforehand, per launch of a segment
+// (k_tile_count, k_tile_scan, k_tile_fill); a contribution is rebuilt where it is needed from
+// the cone's tip and the adjoint of its sampled gradient (20 bytes per cone and step, against
+// a 96-byte record of the 12 cells and values).
+//
+// Before, each step's contributions went into a buffer of sums over the whole grid in HBM by
+// global 64-bit atomics (3.9 us per step at 1024^2 and 8192 cones), which the reverse step
+// then read (8 B per cell and step), at two steps per launch (6.6 us per step).
+// HBM bytes per cell and step now: c^t once (4 B), and a in and out once per launch.
+// Bound: the VALU (about 12 instructions per row of two cells for the stencil, 22 for the
+// sums) and the barriers between sub-steps.
+#include <algorithm>
+#include <type_traits>
+
+#include "rows.hpp"
+
+namespace cuesim {
+
+namespace {
+
+constexpr int kWaves = 8;
+constexpr int kThreads = 64 * kWaves;
+constexpr int kCPL = 2;
+constexpr int kW = 64 * kCPL;             // loaded tile width
+constexpr int kH = kRevSteps;             // halo
+// Rows per wavefront, all in registers during a sub-step.  A core row costs three times a halo
+// row (the two sums), so the first and the last wavefront take the halo's rows and two of the
+// core's, the others three core rows each: tiles of 112 x 22 cells, 470 of them at 1024^2, so
+// that every workgroup of that grid is resident at once (two per CU).
+constexpr int kEdgeCore = 2, kMidCore = 3;
+constexpr int kTX = kW - 2 * kH, kTY = 2 * kEdgeCore + (kWaves - 2) * kMidCore;
+constexpr int kHL = kTY + 2 * kH;         // loaded height
+constexpr int kXcds = 8;
+constexpr int kTileCones = kThreads / 4;  // cones of a tile whose steps are held in LDS: one
+                                          // cone per four threads
+constexpr int kListThreads = 256;
+constexpr int kScanThreads = 1024;
+static_assert(kTX > 0 && kTY > 0 && kH % kCPL == 0, "tile shape");
+
+using V = float2;
+
+struct ReverseArgs {
+    const float* a_in[2];
+    float* a_out[2];
+    StencilCoef coef[2];
+    ConeRules rules;
+    const float* fields;       // c^t of species s: fields + (t * n_species + s) * cells
+    size_t cells;
+    int n_species, nx, ny, tiles_x, n_tiles, per_xcd;
+    uint32_t tiles_x_inv;      // ceil(2^32 / tiles_x)
+    int t_hi, steps;           // segment steps t_hi, t_hi - 1, .. are reversed
+    int M;
+    const float4* tips;        // [t][M]: the cones' state at the start of step t
+    const float2* ag;          // [t][M]: the adjoint of the cone's sampled gradient
+    const uint32_t* step_max;  // [t]
+    const int32_t* list_end;   // [tile]: where the tile's cones end in the list
+    const int32_t* list;
+    double* acc_D;             // [species][tile]
+    double* acc_k;
+    const int32_t* q_start;    // [species][tile + 1] into q_entry
+    const int2* q_entry;       // (LDS cell in its tile, source number)
+    double* acc_q;
+};
+
+// Sum of v over the wavefront, valid in lane 63: shifts within rows of 16 lanes, then the row
+// totals broadcast to the rows after them, without a trip through LDS.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double plus_dpp(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xF, false);
+    return v + __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double wave_sum(double v) {
+    v = plus_dpp<0x111, 0xF>(v);   // row_shr:1, 2, 4, 8
+    v = plus_dpp<0x112, 0xF>(v);
+    v = plus_dpp<0x114, 0xF>(v);
+    v = plus_dpp<0x118, 0xF>(v);
+    v = plus_dpp<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
+    return plus_dpp<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
+}
+
+// Three of the 12 cells of the sample of a cone p = (x, y, agx, agy), cells 3 q .. 3 q + 2: as
+// LDS cells of the tile (-1: outside the loaded region) and their adjoints.
+struct Share {
+    int at[3];
+    float v[3];
+};
+constexpr int kShares = kThreads / kTileCones;   // threads per cone
+static_assert(kShares == 4, "four threads share 12 cells");
+
+__device__ __forceinline__ Share share_of(const ConeRules& r, float sign, const float4& p, int q,
+                                          int x0, int y0) {
+    const Scatter2D s = sample_adjoint_2d(r, p.x, p.y, sign * p.z, sign * p.w);
+    Share c;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        int i = s.i[k], j = s.j[k];
+        c.v[k] = s.v[k];
+#pragma unroll
+        for (int m = 1; m < kShares; ++m) {
+            i = q == m ? s.i[3 * m + k] : i;
+            j = q == m ? s.j[3 * m + k] : j;
+            c.v[k] = q == m ? s.v[3 * m + k] : c.v[k];
+        }
+        const int lx = i - x0, ly = j - y0;
+        const bool in = (unsigned)lx < (unsigned)kW && (unsigned)ly < (unsigned)kHL;
+        c.at[k] = in ? ly * kW + lx : -1;
+    }
+    return c;
+}
+
+// One wavefront's strip of a tile: N rows from loaded row LY0, of which rows CORE0 ..
+// CORE0 + CORES - 1 of the strip belong to the core.  EDGE: the tile meets a wall of the grid,
+// so rows and columns outside it are skipped, clamped or replaced (else no test is needed).
+template <int N, int CORE0, int CORES, bool ALIGNED, bool EDGE>
+struct Strip {
+    V row[N + 2];        // b on the strip and a row to either side
+    V c[CORES + 2];      // c^t on the strip's core rows and a row to either side
+
+    __device__ __forceinline__ void load_c(GlobalPtr<const float> f, int nx, int ny, int gy0,
+                                           int gx0) {
+#pragma unroll
+        for (int r = 0; r < CORES + 2; ++r) {
+            const int gy = gy0 + CORE0 + r - 1;
+            if (EDGE || !ALIGNED) {
+                const RowVec<kCPL> v = load_row<kCPL, ALIGNED>(f, nx, ny, gy, gx0);
+                c[r] = make_float2(v[0], v[1]);
+            } else {
+                const RowVec<kCPL> v = *(GlobalPtr<const RowVec<kCPL>>)(f + (size_t)gy * nx + gx0);
+                c[r] = make_float2(v[0], v[1]);
+            }
+        }
+    }
+    __device__ __forceinline__ void read(const float* L, int ly0) {
+#pragma unroll
+        for (int r = 0; r < N + 2; ++r) row[r] = *(const V*)&L[(ly0 + r - 1) * kW];
+    }
+    // Sub-step k: the strip's new rows into the tile (rows that later sub-steps need) and the
+    // core rows' share of the sums.
+    __device__ __forceinline__ void step(float* L, int ly0, int k, int gy0, int gx0, int nx,
+                                         int ny, const StencilCoef& coef, bool core_col,
+                                         double& pD, double& pk) {
+        constexpr int COLS = EDGE ? kWallAny : kNoWall;
+#pragma unroll
+        for (int r = 0; r < N; ++r) {
+            const bool core = r >= CORE0 && r < CORE0 + CORES;
+            const int ly = ly0 + r, gy = gy0 + r;
+            if (!core && (ly <= k || ly >= kHL - 1 - k)) continue;
+            if (EDGE && (gy < 0 || gy >= ny)) continue;
+            const V mid = row[r + 1];
+            const V below = EDGE && gy == 0 ? mid : row[r];
+            const V above = EDGE && gy == ny - 1 ? mid : row[r + 2];
+            *(V*)&L[ly * kW] = row_update<kCPL, COLS>(below, mid, above, gx0, nx, coef);
+            if (!core) continue;
+            // c's rows are clamped into the grid: the zero-flux rule at its first and last
+            const int m = r - CORE0 + 1;
+            const V lap = row_laplacian<kCPL, COLS>(c[m - 1], c[m], c[m + 1], gx0, nx);
+            if (core_col && (!EDGE || gx0 < nx)) {
+                pD = fma((double)mid.x, (double)lap.x, pD);
+                pk = fma((double)mid.x, (double)c[m].x, pk);
+                if (!EDGE || ALIGNED || gx0 + 1 < nx) {
+                    pD = fma((double)mid.y, (double)lap.y, pD);
+                    pk = fma((double)mid.y, (double)c[m].y, pk);
+                }
+            }
+        }
+    }
+    // The strip's core rows of the finished tile to memory.
+    __device__ __forceinline__ void store(const float* L, GlobalPtr<float> out, int ly0, int gy0,
+                                          int gx0, int nx, int ny, bool core_col) const {
+        if (!core_col) return;
+#pragma unroll
+        for (int r = CORE0; r < CORE0 + CORES; ++r) {
+            const int gy = gy0 + r;
+            if (EDGE && gy >= ny) continue;
+            const V v = *(const V*)&L[(ly0 + r) * kW];
+            const GlobalPtr<float> dst = out + (size_t)gy * nx + gx0;
+            if (ALIGNED) {
+                if (!EDGE || gx0 < nx) *(GlobalPtr<RowVec<2>>)dst = RowVec<2>{v.x, v.y};
+            } else {
+                if (!EDGE || gx0 < nx) dst[0] = v.x;
+                if (!EDGE || gx0 + 1 < nx) dst[1] = v.y;
+            }
+        }
+    }
+};
+
+// ALIGNED: nx is even, so that a lane's two cells lie inside the grid's columns together and
+// are loaded and stored as one 8-byte value.
+template <bool ALIGNED>
+__global__ __launch_bounds__(kThreads, 4) void k_field_reverse2d(ReverseArgs a) {
+    __shared__ __align__(16) float tile_a[(kHL + 2) * kW];     // row ly at (ly + 1) * kW
+    __shared__ __align__(16) unsigned long long sums[kHL * kW];
+    __shared__ float4 cones[kRevSteps][kTileCones];   // (x, y, agx, agy), step t_hi - k in row k
+    __shared__ double part[2][kWaves];
+    const int tile = (blockIdx.x % kXcds) * a.per_xcd + blockIdx.x / kXcds, s = blockIdx.y;
+    if (tile >= a.n_tiles) return;   // whole workgroup: the barriers stay uniform
+    const int ty = a.tiles_x > 1 ? (int)__umulhi((uint32_t)tile, a.tiles_x_inv) : tile;
+    const int tx = tile - ty * a.tiles_x;
+    const int x0 = tx * kTX - kH, y0 = ty * kTY - kH;
+    const int nx = a.nx, ny = a.ny, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int cx = kCPL * lane, gx0 = x0 + cx;
+    const StencilCoef coef = a.coef[s];
+    const float sign = s == 0 ? a.rules.sign0 : a.rules.sign1;
+    float* const L = tile_a + kW + cx;   // the lane's cells of row 0
+
+    // the ranges of the tile's cones and sources, and the tile's a (indices clamped into the
+    // grid: cells outside are never read by cells inside)
+    const int list_lo = tile > 0 ? a.list_end[tile - 1] : 0;
+    const int n_list = a.list_end[tile] - list_lo;
+    const int q_lo = a.q_start[s * (a.n_tiles + 1) + tile];
+    const int n_q = a.q_start[s * (a.n_tiles + 1) + tile + 1] - q_lo;
+    // the steps' scales, step t_hi - k in lane k
+    const int max_bits = lane < a.steps ? (int)a.step_max[a.t_hi - lane] : 0;
+    constexpr int kLoad = (kHL + kWaves - 1) / kWaves;
+    RowVec<kCPL> in[kLoad];
+#pragma unroll
+    for (int r = 0; r < kLoad; ++r)
+        in[r] = load_row<kCPL, ALIGNED>(gbl(a.a_in[s]), nx, ny,
+                                        y0 + min(wave + r * kWaves, kHL - 1), gx0);
+    for (int k = tid; k < kHL * kW / 2; k += kThreads)
+        *(ulonglong2*)&sums[2 * k] = make_ulonglong2(0, 0);
+    // a cone's tip and sample adjoint at step t, as (x, y, agx, agy)
+    auto load_cone = [&](int i, int t) {
+        const size_t at = (size_t)t * a.M + i;
+        const float2 g = a.ag[at], x = *(const float2*)(a.tips + at);
+        return make_float4(x.x, x.y, g.x, g.y);
+    };
+    // every step of the tile's first kTileCones cones, and this thread's source
+    const int m0 = tid % kTileCones, k0 = tid / kTileCones;
+    const int cone = m0 < n_list ? a.list[list_lo + m0] : -1;
+    const int2 src = tid < n_q ? a.q_entry[q_lo + tid] : make_int2(-1, 0);
+    double q_sum = 0.0;
+    if (cone >= 0) {
+        float4 p[kRevSteps / kShares];
+#pragma unroll
+        for (int u = 0; u < kRevSteps / kShares; ++u)
+            p[u] = load_cone(cone, max(a.t_hi - (u * kShares + k0), 0));
+#pragma unroll
+        for (int u = 0; u < kRevSteps / kShares; ++u) cones[u * kShares + k0][m0] = p[u];
+    }
+#pragma unroll
+    for (int r = 0; r < kLoad; ++r)   // (past the tile: its last row again)
+        *(V*)&L[min(wave + r * kWaves, kHL - 1) * kW] = make_float2(in[r][0], in[r][1]);
+
+    // the cones' contributions of sub-step k's step into the sums, and from there into the
+    // tile: of all contributions to a cell the first to take its sum adds it, the others find
+    // zero (a crowded tile takes its further cones in turn)
+    auto exponent = [&](int k) {
+        return fixed_exponent((uint32_t)__builtin_amdgcn_readlane(max_bits, k));
+    };
+    // cells with a contribution of this thread waiting in the sums
+    int mine[3] = {-1, -1, -1};
+    const int my_cone = tid / kShares, my_share = tid % kShares;
+    auto add = [&](const float4& p, int q, double scale, int (&at)[3]) {
+        const Share c = share_of(a.rules, sign, p, q, x0, y0);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            // (a non-finite contribution, possible only from non-finite fields, adds nothing
+            // rather than an undefined conversion)
+            const double x = (double)c.v[k] * scale;
+            const long long n = isfinite(x) ? (long long)rint(x) : 0;
+            at[k] = n != 0 ? c.at[k] : -1;
+            if (at[k] >= 0) atomicAdd(&sums[at[k]], (unsigned long long)n);
+        }
+    };
+    auto take = [&](const int (&at)[3], double inv) {
+        long long n[3];
+        float v[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) n[k] = at[k] >= 0 ? (long long)atomicExch(&sums[at[k]], 0ull) : 0;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) v[k] = n[k] != 0 ? tile_a[kW + at[k]] : 0.0f;
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            if (n[k] != 0) tile_a[kW + at[k]] = v[k] + (float)((double)n[k] * inv);
+    };
+    auto moving = [](const float4& p) { return p.z != 0.0f || p.w != 0.0f; };
+    auto add_step = [&](int k) {
+        const double scale = ldexp(1.0, kFixedBits - exponent(k));
+        mine[0] = mine[1] = mine[2] = -1;
+        if (my_cone < n_list) {
+            const float4 p = cones[k][my_cone];
+            if (moving(p)) add(p, my_share, scale, mine);
+        }
+        for (int m = kTileCones * kShares + tid; m < n_list * kShares; m += kThreads) {
+            const float4 p = load_cone(a.list[list_lo + m / kShares], a.t_hi - k);
+            int at[3];
+            if (moving(p)) add(p, m % kShares, scale, at);
+        }
+    };
+    auto take_step = [&](int k) {
+        const double inv = ldexp(1.0, exponent(k) - kFixedBits);
+        take(mine, inv);
+        for (int m = kTileCones * kShares + tid; m < n_list * kShares; m += kThreads) {
+            const float4 p = load_cone(a.list[list_lo + m / kShares], a.t_hi - k);
+            if (moving(p)) take(share_of(a.rules, sign, p, m % kShares, x0, y0).at, inv);
+        }
+    };
+    const bool core_col = cx >= kH && cx < kH + kTX;   // both cells (kH and kTX are even)
+    double pD = 0.0, pk = 0.0;
+    auto fields_at = [&](int t) {
+        return gbl(a.fields + ((size_t)t * a.n_species + s) * a.cells);
+    };
+    // the sub-steps on this wavefront's strip, `ly0` its first row; every wavefront passes the
+    // same barriers
+    auto sweep = [&](auto strip, int ly0) {
+        const int gy0 = y0 + ly0;
+        strip.load_c(fields_at(a.t_hi), nx, ny, gy0, gx0);
+        __syncthreads();
+        if (n_list > 0) {
+            add_step(0);
+            __syncthreads();
+            take_step(0);
+            __syncthreads();
+        }
+        for (int k = 0; k < a.steps; ++k) {
+            const int t = a.t_hi - k;
+            // b^t is complete in the tile: its source cells, and this strip's rows
+            if (src.x >= 0) q_sum += (double)tile_a[kW + src.x];
+            for (int m = tid + kThreads; m < n_q; m += kThreads) {
+                const int2 e = a.q_entry[q_lo + m];
+                unsafeAtomicAdd(&a.acc_q[e.y], (double)tile_a[kW + e.x]);
+            }
+            strip.read(L, ly0);
+            __syncthreads();
+            strip.step(L, ly0, k, gy0, gx0, nx, ny, coef, core_col, pD, pk);
+            if (k + 1 == a.steps) break;
+            strip.load_c(fields_at(t - 1), nx, ny, gy0, gx0);   // one sub-step ahead of its use
+            if (n_list > 0) add_step(k + 1);
+            __syncthreads();
+            if (n_list > 0) {
+                take_step(k + 1);
+                __syncthreads();
+            }
+        }
+        strip.store(L, gbl(a.a_out[s]), ly0, gy0, gx0, nx, ny, core_col);
+    };
+    auto by_wave = [&](auto edge) {
+        constexpr bool EDGE = decltype(edge)::value;
+        constexpr int kEdgeRows = kH + kEdgeCore;
+        if (wave == 0)
+            sweep(Strip<kEdgeRows, kH, kEdgeCore, ALIGNED, EDGE>{}, 0);
+        else if (wave == kWaves - 1)
+            sweep(Strip<kEdgeRows, 0, kEdgeCore, ALIGNED, EDGE>{}, kHL - kEdgeRows);
+        else
+            sweep(Strip<kMidCore, 0, kMidCore, ALIGNED, EDGE>{},
+                  kEdgeRows + (wave - 1) * kMidCore);
+    };
+    if (x0 > 0 && x0 + kW < nx && y0 > 0 && y0 + kHL < ny)
+        by_wave(std::false_type{});
+    else
+        by_wave(std::true_type{});
+    pD = wave_sum(pD);
+    pk = wave_sum(pk);
+    if (lane == 63) {
+        part[0][wave] = pD;
+        part[1][wave] = pk;
+    }
+    __syncthreads();
+    // every accumulator has one writer at a time (its tile, or its source's tile)
+    if (tid < 2) {
+        double sum = 0.0;
+        for (int w = 0; w < kWaves; ++w) sum += part[tid][w];
+        unsafeAtomicAdd(&(tid == 0 ? a.acc_D : a.acc_k)[s * a.n_tiles + tile], sum);
+    }
+    if (src.x >= 0) unsafeAtomicAdd(&a.acc_q[src.y], q_sum);
+}
+
+// -- which cones can touch a tile during a launch -----------------------------------------
+// Launch g of a segment reverses its steps len - 1 - g kRevSteps downwards.
+
+struct ListArgs {
+    ConeRules rules;
+    int M, len, tiles_x, tiles_y, cap;
+    const float4* tips;   // [t][M]
+    const float2* ag;     // [t][M]
+    int32_t* count;       // [launch][tile]
+    int32_t* list;        // [launch][cap]
+};
+
+// Tiles x1 .. x2 by y1 .. y2.
+struct TileBox {
+    int x1, x2, y1, y2;
+    __device__ bool has(int tx, int ty) const {
+        return tx >= x1 && tx <= x2 && ty >= y1 && ty <= y2;
+    }
+};
+
+// Tiles along one axis whose loaded region holds a cell of [lo, hi].
+__device__ __forceinline__ void tile_range(int lo, int hi, int core, int tiles, int& first,
+                                           int& last) {
+    first = max(lo - kH, 0) / core;
+    last = min((hi + kH) / core, tiles - 1);
+}
+
+// Calls each(tile) once for every tile whose loaded region cone i's samples touch in launch g.
+template <class Each>
+__device__ __forceinline__ void for_touched_tiles(const ListArgs& a, int i, int g,
+                                                  const Each& each) {
+    const int t_hi = a.len - 1 - g * kRevSteps;
+    float2 ag[kRevSteps], tip[kRevSteps];   // all loads first
+#pragma unroll
+    for (int k = 0; k < kRevSteps; ++k) {
+        const size_t at = (size_t)max(t_hi - k, 0) * a.M + i;
+        ag[k] = a.ag[at];
+        tip[k] = *(const float2*)(a.tips + at);
+    }
+    TileBox seen[kRevSteps];
+#pragma unroll
+    for (int k = 0; k < kRevSteps; ++k) {
+        seen[k] = TileBox{1, 0, 1, 0};
+        if (t_hi - k < 0 || (ag[k].x == 0.0f && ag[k].y == 0.0f)) continue;
+        int i0, j0;
+        float f;
+        corner(tip[k].x, a.rules.inv_dx, a.rules.nx, i0, f);
+        corner(tip[k].y, a.rules.inv_dx, a.rules.ny, j0, f);
+        TileBox b;
+        tile_range(max(i0 - 1, 0), min(i0 + 2, a.rules.nx - 1), kTX, a.tiles_x, b.x1, b.x2);
+        tile_range(max(j0 - 1, 0), min(j0 + 2, a.rules.ny - 1), kTY, a.tiles_y, b.y1, b.y2);
+        seen[k] = b;
+        for (int ty = b.y1; ty <= b.y2; ++ty)
+            for (int tx = b.x1; tx <= b.x2; ++tx) {
+                bool before = false;
+#pragma unroll
+                for (int m = 0; m < kRevSteps; ++m)
+                    if (m < k) before = before || seen[m].has(tx, ty);
+                if (!before) each(ty * a.tiles_x + tx);
+            }
+    }
+}
+
+__global__ __launch_bounds__(kListThreads) void k_tile_count(ListArgs a) {
+    const int i = blockIdx.x * kListThreads + threadIdx.x, g = blockIdx.y;
+    if (i >= a.M) return;
+    int32_t* const count = a.count + (size_t)g * a.tiles_x * a.tiles_y;
+    for_touched_tiles(a, i, g, [&](int tile) { atomicAdd(&count[tile], 1); });
+}
+
+// Counts of one launch's tiles -> where each tile's cones start in the list.
+__global__ __launch_bounds__(kScanThreads) void k_tile_scan(int32_t* count, int n) {
+    __shared__ int32_t wave_total[kScanThreads / 64];
+    int32_t* const a = count + (size_t)blockIdx.x * n;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int32_t carry = 0;
+    for (int base = 0; base < n; base += kScanThreads) {
+        const int k = base + threadIdx.x;
+        const int32_t v = k < n ? a[k] : 0;
+        int32_t incl = v;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int32_t y = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += y;
+        }
+        if (lane == 63) wave_total[wave] = incl;
+        __syncthreads();
+        int32_t at = carry + incl - v, total = 0;
+        for (int w = 0; w < kScanThreads / 64; ++w) {
+            at += w < wave ? wave_total[w] : 0;
+            total += wave_total[w];
+        }
+        if (k < n) a[k] = at;
+        carry += total;
+        __syncthreads();   // every thread has read wave_total
+    }
+}
+
+// Cones into the tiles' lists; a tile's start becomes its end (the next tile's start).
+__global__ __launch_bounds__(kListThreads) void k_tile_fill(ListArgs a) {
+    const int i = blockIdx.x * kListThreads + threadIdx.x, g = blockIdx.y;
+    if (i >= a.M) return;
+    int32_t* const count = a.count + (size_t)g * a.tiles_x * a.tiles_y;
+    int32_t* const list = a.list + (size_t)g * a.cap;
+    for_touched_tiles(a, i, g, [&](int tile) {
+        const int at = atomicAdd(&count[tile], 1);
+        if (at < a.cap) list[at] = i;   // (the capacity holds every cone's most tiles)
+    });
+}
+
+int tiles_along(int n, int core) { return (n + core - 1) / core; }
+
+// Most tiles along one axis whose loaded regions meet a stretch of `cells` cells.
+int tiles_touched(double cells, int core, int tiles) {
+    const double n = (cells - 1.0 + 2.0 * kH) / core + 2.0;
+    return n < tiles ? (int)n : tiles;
+}
+
+}  // namespace
+
+int reverse_tiles(int nx, int ny) { return tiles_along(nx, kTX) * tiles_along(ny, kTY); }
+
+int reverse_launches(int len) { return (len + kRevSteps - 1) / kRevSteps; }
+
+size_t reverse_list_capacity(int nx, int ny, int M, double step_cells) {
+    const int tx = tiles_along(nx, kTX), ty = tiles_along(ny, kTY);
+    // the tiles that kRevSteps footprints of 4 x 4 cells touch, each on its own, or together:
+    // the footprints of a cone moving `span` cells cover at most span + 6 (one for rounding)
+    const size_t apart = (size_t)kRevSteps * tiles_touched(4, kTX, tx) * tiles_touched(4, kTY, ty);
+    const double span = (kRevSteps - 1) * step_cells;
+    const size_t together = (size_t)tiles_touched(span + 6, kTX, tx) *
+                            tiles_touched(span + 6, kTY, ty);
+    return (size_t)M * std::min(apart, together);
+}
+
+void reverse_sources(int nx, int ny, const std::vector<int32_t>& cells, int first,
+                     std::vector<int32_t>& start, std::vector<int2>& entry) {
+    const int tiles_x = tiles_along(nx, kTX), n = reverse_tiles(nx, ny);
+    std::vector<int32_t> at(n + 1, 0);
+    auto tile_of = [&](int32_t cell) { return cell / nx / kTY * tiles_x + cell % nx / kTX; };
+    for (int32_t cell : cells) at[tile_of(cell) + 1] += 1;
+    for (int t = 0; t < n; ++t) at[t + 1] += at[t];
+    const size_t base = entry.size();
+    for (int t = 0; t <= n; ++t) start.push_back((int32_t)base + at[t]);
+    entry.resize(base + cells.size());
+    for (size_t m = 0; m < cells.size(); ++m) {
+        const int x = cells[m] % nx % kTX + kH, y = cells[m] / nx % kTY + kH;
+        entry[base + at[tile_of(cells[m])]++] = make_int2(y * kW + x, first + (int32_t)m);
+    }
+}
+
+hipError_t launch_reverse_lists(const ReverseSegment& g, hipStream_t stream) {
+    const int launches = reverse_launches(g.len);
+    if (g.M == 0 || launches == 0) return hipSuccess;
+    ListArgs a = {};
+    a.rules = g.rules;
+    a.M = g.M;
+    a.len = g.len;
+    a.tiles_x = tiles_along(g.nx, kTX);
+    a.tiles_y = tiles_along(g.ny, kTY);
+    a.cap = (int)g.list_cap;
+    a.tips = g.tips;
+    a.ag = g.ag;
+    a.count = g.count;
+    a.list = g.list;
+    const dim3 grid((g.M + kListThreads - 1) / kListThreads, launches);
+    hipLaunchKernelGGL(k_tile_count, grid, dim3(kListThreads), 0, stream, a);
+    hipLaunchKernelGGL(k_tile_scan, dim3(launches), dim3(kScanThreads), 0, stream, g.count,
+                       a.tiles_x * a.tiles_y);
+    hipLaunchKernelGGL(k_tile_fill, grid, dim3(kListThreads), 0, stream, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_field_reverse2d(const ReverseSegment& g, int launch, const float* const* a_in,
+                                  float* const* a_out, hipStream_t stream) {
+    ReverseArgs a = {};
+    a.tiles_x = tiles_along(g.nx, kTX);
+    a.n_tiles = reverse_tiles(g.nx, g.ny);
+    for (int s = 0; s < g.n_species; ++s) {
+        a.a_in[s] = a_in[s];
+        a.a_out[s] = a_out[s];
+        a.coef[s] = g.coef[s];
+    }
+    a.rules = g.rules;
+    a.fields = g.fields;
+    a.cells = (size_t)g.nx * g.ny;
+    a.n_species = g.n_species;
+    a.nx = g.nx;
+    a.ny = g.ny;
+    a.per_xcd = (a.n_tiles + kXcds - 1) / kXcds;
+    a.tiles_x_inv = (uint32_t)(((1ull << 32) + a.tiles_x - 1) / a.tiles_x);
+    a.t_hi = g.len - 1 - launch * kRevSteps;
+    a.steps = std::min(kRevSteps, a.t_hi + 1);
+    a.M = g.M;
+    a.tips = g.tips;
+    a.ag = g.ag;
+    a.step_max = g.step_max;
+    a.list_end = g.count + (size_t)launch * a.n_tiles;
+    a.list = g.list + (size_t)launch * g.list_cap;
+    a.acc_D = g.acc_D;
+    a.acc_k = g.acc_k;
+    a.q_start = g.q_start;
+    a.q_entry = g.q_entry;
+    a.acc_q = g.acc_q;
+    const dim3 grid(a.per_xcd * kXcds, g.n_species);
+    if (g.nx % 2 == 0)
+        hipLaunchKernelGGL(k_field_reverse2d<true>, grid, dim3(kThreads), 0, stream, a);
+    else
+        hipLaunchKernelGGL(k_field_reverse2d<false>, grid, dim3(kThreads), 0, stream, a);
+    return hipGetLastError();
+}
+
+}  // namespace cuesim

@@ -26,17 +26,6 @@ thread_local std::string g_create_error;
 // Steps between refreshes of the spatial order of 3D cones (a cone moves step_len per step;
 // 8, 16, 32 and 64 were measured at 256^3, 32 was fastest).
 constexpr int kOrderRefresh = 32;
-// Gradient sweep: the samples' fixed-point sums are added kSumGroup steps at a time (an even
-// number, so that the two-step reverse launches stay within a group) into a ring of
-// kSumRing = 2 kSumGroup per-step buffers per species; each two-step launch clears the
-// buffers of the group before its own, which the group after it reuses.  At 1024^2 (one
-// species, 100-step segments) groups of 8 steps measured best: 24.1 ms per sweep against
-// 24.9 with 4, 27.0 with 2 and 24.6 with one buffer per step of the segment (800 MiB, cleared
-// per segment); the ring takes 128 MiB.
-constexpr int kSumGroup = 8;
-constexpr int kSumRing = 2 * kSumGroup;
-static_assert(kSumGroup >= 2 && kSumGroup % 2 == 0, "groups of whole step pairs");
-
 }  // namespace
 
 // Record of the last sim_adjoint_run: checkpoints every `every` steps of the forward run
@@ -61,16 +50,14 @@ struct AdjointRun {
         bool whole = false;             // the window is the whole run (else one segment)
         float* tape_own = nullptr;      // the window's field states when the run did not record
         float4* tape_cones = nullptr;   // the cone state at every step of the window
-        long long* scatter = nullptr;   // fixed-point sample adjoints, a ring of steps:
-                                        // [kSumRing][species][cells]
-        int32_t* rec_at = nullptr;      // one segment's sample records [K][M][species][12]
-        float* rec_v = nullptr;
-        uint32_t* step_max = nullptr;   // [K]
+        float2* ag = nullptr;           // one segment's sample adjoints [K][M], their largest
+        float* vmax = nullptr;          // shares [K][M]
+        uint32_t* step_max = nullptr;   // [K], and [launch][tile] cone counts: cleared together
+        int32_t* list = nullptr;        // the cones that touch each tile, per launch
         float* afield = nullptr;        // the field adjoint, ping-pong per species
         double* acc = nullptr;          // FP64 accumulators
-        int32_t* q_cell = nullptr;      // source cells, and the sources listed per box
-        int32_t* q_start = nullptr;
-        int32_t* q_index = nullptr;
+        int32_t* q_start = nullptr;     // the sources listed per tile
+        int2* q_entry = nullptr;
     } work;
 };
 
@@ -203,15 +190,14 @@ void drop_events(sim_handle* h) {
 static void adjoint_work_release(AdjointRun::Work& w) {
     dfree(w.tape_own);
     dfree(w.tape_cones);
-    dfree(w.scatter);
-    dfree(w.rec_at);
-    dfree(w.rec_v);
+    dfree(w.ag);
+    dfree(w.vmax);
     dfree(w.step_max);
+    dfree(w.list);
     dfree(w.afield);
     dfree(w.acc);
-    dfree(w.q_cell);
     dfree(w.q_start);
-    dfree(w.q_index);
+    dfree(w.q_entry);
     w = AdjointRun::Work();
 }
 
@@ -1081,12 +1067,10 @@ static sim_status adjoint_seed(sim_handle* h) {
     return SIM_OK;
 }
 
-// Bytes of every field state of a run of n_steps, of its cone states and of the ring of
-// sample sums: what the gradient needs to re-run the cones of the whole run once.
-static size_t adjoint_whole_bytes(const sim_handle* h, int64_t n_steps, int64_t every) {
-    (void)every;
+// Bytes of every field state of a run of n_steps and of its cone states.
+static size_t adjoint_whole_bytes(const sim_handle* h, int64_t n_steps) {
     const size_t ns = (size_t)h->n_species, cells = (size_t)h->n_cells;
-    return (size_t)(n_steps + 1) * ns * cells * 4 + (size_t)kSumRing * ns * cells * 8 +
+    return (size_t)(n_steps + 1) * ns * cells * 4 +
            (size_t)n_steps * std::max<size_t>((size_t)h->n_cones, 1) * 16;
 }
 
@@ -1166,7 +1150,7 @@ sim_status sim_adjoint_run(sim_handle* h, int64_t n_steps, int32_t checkpoint_ev
     // goes (the reverse sweep then re-runs only the cone steps); if the tape cannot be had,
     // the sweep re-runs the fields from the checkpoints instead.
     RecordGuard recording;
-    if (a->n_ckpt > 1 && adjoint_whole_bytes(h, n_steps, checkpoint_every) < adjoint_tape_limit(h)) {
+    if (a->n_ckpt > 1 && adjoint_whole_bytes(h, n_steps) < adjoint_tape_limit(h)) {
         if (dalloc(&a->tape, (size_t)(n_steps + 1) * ns * cells) != hipSuccess) {
             (void)hipGetLastError();
             a->tape = nullptr;
@@ -1231,17 +1215,16 @@ sim_status sim_adjoint_backward(sim_handle* h, double* dL_dq, double* dL_dD, dou
     const int ns = h->n_species, M = h->n_cones, nx = h->nx, ny = h->ny;
     const size_t cells = (size_t)h->n_cells, Ms = (size_t)M;
     const int K = (int)std::min<int64_t>(a->every, std::max<int64_t>(a->n_steps, 1));
-    // accumulator slots: enough for the boxes of the single- and the two-step reverse field
-    // kernels (both are used; the host sums every slot)
-    const int fb = std::max(adjoint_field_blocks(nx, ny), adjoint_pair_blocks(nx, ny));
+    const int fb = reverse_tiles(nx, ny);   // accumulator slots per species
     int n_q[SIM_MAX_SPECIES] = {0, 0}, q_off[SIM_MAX_SPECIES] = {0, 0};
     for (int s = 0; s < ns; ++s) n_q[s] = (int)h->src_caller_cell[s].size();
     q_off[1] = n_q[0];
     const int nq_all = n_q[0] + (ns > 1 ? n_q[1] : 0);
 
     // Workspace.  The field states of the reverse sweep (a window of steps), the cone state at
-    // every step of the window, one segment's per-step sample adjoints, the re-run's cones,
-    // the field adjoint (ping-pong per species) and FP64 accumulators.  When the whole run's
+    // every step of the window, one segment's per-step sample adjoints and the lists of the
+    // cones that touch each tile, the field adjoint (ping-pong per species) and FP64
+    // accumulators.  When the whole run's
     // fields fit comfortably (under half the free device memory), the window is the whole
     // run: the fields are re-run once and the cone steps of every segment are re-run at once,
     // one thread per (segment, cone), instead of segment after segment.
@@ -1253,47 +1236,39 @@ sim_status sim_adjoint_backward(sim_handle* h, double* dL_dq, double* dL_dD, dou
     const bool fresh = !w.ready;   // first sweep of this record: allocate the workspace
     if (fresh)
         w.whole = recorded || (n_seg > 1 &&
-                               adjoint_whole_bytes(h, n_run, a->every) < adjoint_tape_limit(h));
+                               adjoint_whole_bytes(h, n_run) < adjoint_tape_limit(h));
     const bool whole = w.whole;
     const int64_t window = whole ? n_run : K;
     float*& tape_own = w.tape_own;
     float4*& tape_cones = w.tape_cones;
-    long long*& scatter = w.scatter;
-    int32_t*& rec_at = w.rec_at;
-    float*& rec_v = w.rec_v;
     uint32_t*& step_max = w.step_max;
     float*& afield = w.afield;
     double*& acc = w.acc;
-    int32_t*& q_cell = w.q_cell;
     int32_t*& q_start = w.q_start;
-    int32_t*& q_index = w.q_index;
+    int2*& q_entry = w.q_entry;
     // on a device error the workspace is dropped (the next call allocates it again)
     auto free_all = [&]() { adjoint_work_release(w); };
-    // each species' sources listed by the box of the two-step kernel that holds their cell:
-    // q_start[s * (nbp + 1) + box] indexes q_index (source numbers within the species)
-    const int nbp = adjoint_pair_blocks(nx, ny);
-    std::vector<int32_t> q_start_h((size_t)ns * (nbp + 1)), q_index_h;
-    for (int s = 0; s < ns; ++s) {
-        std::vector<int32_t> st, ix;
-        adjoint_pair_sources(nx, ny, h->src_caller_cell[s], st, ix);
-        for (int b = 0; b <= nbp; ++b)
-            q_start_h[(size_t)s * (nbp + 1) + b] = st[b] + (int32_t)q_index_h.size();
-        q_index_h.insert(q_index_h.end(), ix.begin(), ix.end());
-    }
+    std::vector<int32_t> q_start_h;
+    std::vector<int2> q_entry_h;
+    for (int s = 0; s < ns; ++s)
+        reverse_sources(nx, ny, h->src_caller_cell[s], q_off[s], q_start_h, q_entry_h);
+    const size_t launches = (size_t)reverse_launches(K);
+    const size_t list_cap = reverse_list_capacity(nx, ny, std::max(M, 1),
+                                                  h->rules.step_len * h->rules.inv_dx);
+    const size_t cleared = (size_t)K + launches * fb;   // step_max and the counts
     hipError_t e = hipSuccess;
     const size_t acc_n = (size_t)2 * ns * fb + (size_t)std::max(nq_all, 1);
     if (fresh &&
         ((!recorded && (e = dalloc(&tape_own, (size_t)(window + 1) * ns * cells)) != hipSuccess) ||
         (e = dalloc(&tape_cones, (size_t)window * std::max<size_t>(Ms, 1))) != hipSuccess ||
-        (e = dalloc(&scatter, (size_t)kSumRing * ns * cells)) != hipSuccess ||
-        (e = dalloc(&rec_at, (size_t)K * std::max<size_t>(Ms, 1) * ns * 12)) != hipSuccess ||
-        (e = dalloc(&rec_v, (size_t)K * std::max<size_t>(Ms, 1) * ns * 12)) != hipSuccess ||
-        (e = dalloc(&step_max, (size_t)K)) != hipSuccess ||
+        (e = dalloc(&w.ag, (size_t)K * std::max<size_t>(Ms, 1))) != hipSuccess ||
+        (e = dalloc(&w.vmax, (size_t)K * std::max<size_t>(Ms, 1))) != hipSuccess ||
+        (e = dalloc(&step_max, cleared)) != hipSuccess ||
+        (e = dalloc(&w.list, launches * list_cap)) != hipSuccess ||
         (e = dalloc(&afield, (size_t)2 * ns * cells)) != hipSuccess ||
         (e = dalloc(&acc, acc_n)) != hipSuccess ||
-        (e = dalloc(&q_cell, (size_t)std::max(nq_all, 1))) != hipSuccess ||
         (e = dalloc(&q_start, q_start_h.size())) != hipSuccess ||
-        (e = dalloc(&q_index, std::max<size_t>(q_index_h.size(), 1))) != hipSuccess)) {
+        (e = dalloc(&q_entry, std::max<size_t>(q_entry_h.size(), 1))) != hipSuccess)) {
         free_all();
         if (e == hipErrorOutOfMemory)
             return fail(h, SIM_ENOMEM, "adjoint workspace: out of device memory");
@@ -1308,14 +1283,10 @@ sim_status sim_adjoint_backward(sim_handle* h, double* dL_dq, double* dL_dD, dou
         }                                                                   \
     } while (0)
     if (fresh) {
-        for (int s = 0; s < ns; ++s)
-            if (n_q[s] > 0)
-                ADJ_TRY(hipMemcpyAsync(q_cell + q_off[s], h->src_caller_cell[s].data(),
-                                       n_q[s] * 4, hipMemcpyHostToDevice, h->stream));
         ADJ_TRY(hipMemcpyAsync(q_start, q_start_h.data(), q_start_h.size() * 4,
                                hipMemcpyHostToDevice, h->stream));
-        if (!q_index_h.empty())
-            ADJ_TRY(hipMemcpyAsync(q_index, q_index_h.data(), q_index_h.size() * 4,
+        if (!q_entry_h.empty())
+            ADJ_TRY(hipMemcpyAsync(q_entry, q_entry_h.data(), q_entry_h.size() * sizeof(int2),
                                    hipMemcpyHostToDevice, h->stream));
         w.ready = true;
     }
@@ -1333,9 +1304,6 @@ sim_status sim_adjoint_backward(sim_handle* h, double* dL_dq, double* dL_dD, dou
     float* const tape = recorded ? a->tape : tape_own;
     auto field_at = [&](int64_t t, int s) {
         return tape + ((size_t)(t - t_base) * ns + s) * cells;
-    };
-    auto scatter_at = [&](int t, int s) {
-        return scatter + ((size_t)(t % kSumRing) * ns + s) * cells;
     };
     int cur = 0;
     auto afield_at = [&](int s, int half) { return afield + ((size_t)s * 2 + half) * cells; };
@@ -1377,48 +1345,38 @@ sim_status sim_adjoint_backward(sim_handle* h, double* dL_dq, double* dL_dD, dou
             t_base = t0;
             ADJ_TRY(rerun(j, t0, len, 1));
         }
-        // the segment's cone adjoints (their samples' adjoints recorded per step)
-        ADJ_TRY(launch_cone_adjoint_segment2d(h->rules, field_at(t0, 0), cells, ns,
-                                              (uint32_t)(a->n0 + t0), len, rec_at, rec_v,
-                                              step_max,
-                                              tape_cones + (size_t)(t0 - t_base) * Ms,
-                                              h->cones.status, h->cones.event_step, a->acone,
-                                              M, h->stream));
-        ADJ_TRY(hipMemsetAsync(scatter, 0, (size_t)kSumRing * ns * cells * sizeof(long long),
-                               h->stream));
-        // reverse the segment's field steps, two per launch while two remain, in groups of
-        // kSumGroup steps from the last one down: the group's sample sums first
-        int t = len - 1;
-        while (t >= 0) {
-            const int g_lo = std::max(t - kSumGroup + 1, 0);
-            ADJ_TRY(launch_sample_add2d(cells, ns, (uint32_t)(a->n0 + t0), len, g_lo,
-                                        t - g_lo + 1, kSumRing, rec_at, rec_v, step_max,
-                                        scatter, h->cones.status, h->cones.event_step, M,
-                                        h->stream));
-            for (; t >= g_lo + 1; t -= 2) {
-                // the sums of steps t + kSumGroup and t + kSumGroup - 1 (the group before,
-                // already reversed) are cleared for the group after this one
-                for (int s = 0; s < ns; ++s)
-                    ADJ_TRY(launch_field_adjoint2d_pair(
-                        nx, ny, afield_at(s, cur), scatter_at(t, s), scatter_at(t - 1, s),
-                        step_max, t, t - 1, field_at(t0 + t, s), field_at(t0 + t - 1, s),
-                        afield_at(s, cur ^ 1), h->coef[s], acc_D + (size_t)s * fb,
-                        acc_k + (size_t)s * fb, q_start + (size_t)s * (nbp + 1), q_index,
-                        q_cell + q_off[s], acc_q + q_off[s], scatter_at(t + kSumGroup, s),
-                        scatter_at(t + kSumGroup - 1, s), h->stream));
-                cur ^= 1;
-            }
-            if (t == g_lo) {   // the segment's first step, when its length is odd
-                for (int s = 0; s < ns; ++s)
-                    ADJ_TRY(launch_field_adjoint2d(nx, ny, afield_at(s, cur), scatter_at(t, s),
-                                                   step_max, t, field_at(t0 + t, s),
-                                                   afield_at(s, cur ^ 1), h->coef[s],
-                                                   acc_D + (size_t)s * fb,
-                                                   acc_k + (size_t)s * fb, q_cell + q_off[s],
-                                                   n_q[s], acc_q + q_off[s], h->stream));
-                cur ^= 1;
-                --t;
-            }
+        ReverseSegment g = {};
+        g.rules = h->rules;
+        for (int s = 0; s < ns; ++s) g.coef[s] = h->coef[s];
+        g.nx = nx;
+        g.ny = ny;
+        g.n_species = ns;
+        g.M = M;
+        g.len = len;
+        g.seg0 = (uint32_t)(a->n0 + t0);
+        g.fields = field_at(t0, 0);
+        g.tips = tape_cones + (size_t)(t0 - t_base) * Ms;
+        g.ag = w.ag;
+        g.vmax = w.vmax;
+        g.step_max = step_max;
+        g.count = (int32_t*)step_max + K;
+        g.list = w.list;
+        g.list_cap = list_cap;
+        g.acc_D = acc_D;
+        g.acc_k = acc_k;
+        g.acc_q = acc_q;
+        g.q_start = q_start;
+        g.q_entry = q_entry;
+        ADJ_TRY(hipMemsetAsync(step_max, 0, cleared * sizeof(uint32_t), h->stream));
+        // the segment's cone adjoints, the tiles they touch, then the field steps
+        ADJ_TRY(launch_cone_adjoint_segment2d(g, h->cones.status, h->cones.event_step, a->acone,
+                                              h->stream));
+        ADJ_TRY(launch_reverse_lists(g, h->stream));
+        for (int l = 0; l < reverse_launches(len); ++l) {
+            const float* in[SIM_MAX_SPECIES] = {afield_at(0, cur), afield_at(ns - 1, cur)};
+            float* out[SIM_MAX_SPECIES] = {afield_at(0, cur ^ 1), afield_at(ns - 1, cur ^ 1)};
+            ADJ_TRY(launch_field_reverse2d(g, l, in, out, h->stream));
+            cur ^= 1;
         }
     }
     std::vector<double> host(acc_n);
