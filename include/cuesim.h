@@ -215,8 +215,8 @@ const char* sim_last_error(const sim_handle* h);
  * side of the turn cap are held as the run took them (the cone rules of Sec. 3.4-3.5 are
  * not differentiable at those switches).  Memory: checkpoints of the fields and cone state
  * every checkpoint_every steps.  When every field state of the run fits within the tape
- * limit (sim_adjoint_set_tape_limit), the run records them all as it goes and the reverse
- * sweep re-runs only the cone steps; otherwise the sweep re-runs each segment of
+ * limit (sim_adjoint_set_tape_limit), the run records them and its cone steps as it goes and
+ * the reverse sweep re-runs nothing; otherwise the sweep re-runs each segment of
  * checkpoint_every + 1 fields per species from its checkpoint just before reversing it.
  * Both ways give the same gradient, bit for bit.
  * ---------------------------------------------------------------------------------------- */

@@ -343,6 +343,27 @@ __device__ __forceinline__ void gradient_2d(const F& f, const ConeRules& r, floa
     gradient_from_2d(p, corner_gradients_2d(p, r), gx, gy, value);
 }
 
+// What the reverse of a cone step needs of the forward step, recorded as it runs: planes of one
+// float4 per step and cone, plane j of step t at base + j * plane + t * M (M cones).
+//   0  tip before the step, sine and cosine of the heading after it
+//   1  cross and along of the turn, sine and cosine of the heading before the step
+//   2  weighted gradient, fractions of the tip within its cell-centre block
+//   3 + 2 s, 4 + 2 s  corner gradients of species s, along x and along y
+constexpr int kConePlanes = 3;   // and two per species
+struct ConeTape {
+    float4* base;
+    size_t plane;
+    int M;
+    __device__ __forceinline__ void put(int j, size_t t, int i, float4 v) const {
+        base[j * plane + t * M + i] = v;
+    }
+    __device__ __forceinline__ void sample(int s, size_t t, int i,
+                                           const CornerGradients2D& g) const {
+        put(kConePlanes + 2 * s, t, i, make_float4(g.gx00, g.gx10, g.gx01, g.gx11));
+        put(kConePlanes + 2 * s + 1, t, i, make_float4(g.gy00, g.gy10, g.gy01, g.gy11));
+    }
+};
+
 // Reverse of the interpolated central-difference gradient of one species at (x, y) with
 // respect to the field: the 12 cells that the sample read (cells repeat at walls; their
 // shares then add up) and their adjoints, for the adjoint (agx, agy) of the sampled gradient,
@@ -492,6 +513,13 @@ __device__ __forceinline__ float capped_turn(const ConeRules& r, float cross, fl
     return fminf(fmaxf(turn, -r.max_turn), r.max_turn);
 }
 
+// Whether the clamp applies, by the same tests.
+__device__ __forceinline__ bool turn_capped(const ConeRules& r, float cross, float along) {
+    if (r.tan_max > 0.0f) return !(along > 0.0f && fabsf(cross) < along * r.tan_max);
+    const float turn = atan2f(cross, along);
+    return turn > r.max_turn || turn < -r.max_turn;
+}
+
 // The SNR turn law (Sec. 3.5, Eq. 5): inside the detection window [c_min, c_max] of the
 // concentration c at the tip, turn by max_turn to the right (clockwise) when SNR + z0 > 0,
 // else to the left, with SNR = A w / c * sqrt(gamma / (1 + gamma)^3) * |g| sin(theta -
@@ -516,6 +544,17 @@ __device__ __forceinline__ void turn_terms(const ConeRules& r, float s, float c,
     cross = r.gain * fmaf(c, gy, -(s * gx));
     along = fmaf(r.gain, fmaf(c, gx, s * gy), 1.0f);
     if (cross == 0.0f) cross = 0.0f;
+}
+
+// The turn's part of a cone's record at step t: from the tip (x, y) and heading (s, c) before
+// the step and the heading (sn, cn) after it.
+__device__ __forceinline__ void record_turn(const ConeTape& tape, size_t t, int i,
+                                            const ConeRules& r, float x, float y, float s,
+                                            float c, float gx, float gy, float sn, float cn) {
+    float cross, along;
+    turn_terms(r, s, c, gx, gy, cross, along);
+    tape.put(0, t, i, make_float4(x, y, sn, cn));
+    tape.put(1, t, i, make_float4(cross, along, s, c));
 }
 
 // A heading wrapped back into [-pi, pi).

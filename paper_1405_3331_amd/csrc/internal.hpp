@@ -32,9 +32,11 @@ struct ConeArrays {
     int n;
 };
 
-// One 2D step's cones in the caller's order (kernels_plain.hip).
+// One 2D step's cones in the caller's order (kernels_plain.hip); with `tape` they are recorded
+// as its step t.
 hipError_t launch_cones2d(const ConeRules& rules, const float* f0, const float* f1,
-                          ConeArrays cones, uint32_t step, hipStream_t stream);
+                          ConeArrays cones, uint32_t step, hipStream_t stream,
+                          const ConeTape* tape = nullptr, size_t t = 0);
 
 // 2D field step of every species in one launch, sources included (kernels_field2d.hip).
 // Field2DStep holds the per-box source lists (row, column in the box, amount) built once by
@@ -163,13 +165,13 @@ struct ReverseSegment {
     int nx, ny, n_species, M, len;
     uint32_t seg0;
     const float* fields;
-    const float4* tips;    // [len][M]: the cones' state (x, y, theta) at the start of each step
+    ConeTape tape;         // the segment's cone steps
     float2* ag;            // [len][M]: adjoint of the cone's sampled gradient, before the
                            // species' signs
-    float* vmax;           // [len][M]: largest |adjoint| of a cell its samples read
-    // zero before the segment's launches: the step maxima and the tiles' cone counts
-    uint32_t* step_max;    // [len]
-    int32_t* count;        // [launch][tile]
+    float4* boxes;         // [launch][M]: box of the tips (x from, x to, y from, y to) whose
+                           // samples have an adjoint in the launch's steps
+    uint32_t* step_max;    // [len], zero before the segment's launches
+    int32_t* list_end;     // [launch][tile]: where the tile's cones end in the launch's list
     int32_t* list;         // [launch][list_cap]
     size_t list_cap;
     // accumulators over the whole sweep: [species][tile], and one per source
@@ -188,7 +190,7 @@ void reverse_sources(int nx, int ny, const std::vector<int32_t>& cells, int firs
                      std::vector<int32_t>& start, std::vector<int2>& entry);
 // The cones that can touch each tile, for every launch of the segment (after the cones'
 // reverse).
-hipError_t launch_reverse_lists(const ReverseSegment& g, hipStream_t stream);
+hipError_t launch_reverse_lists(const ReverseSegment& g, double step_cells, hipStream_t stream);
 // Launch `launch` of reverse_launches(len): the field adjoint of every species from a_in to
 // a_out, kRevSteps steps back (fewer in the last launch).
 hipError_t launch_field_reverse2d(const ReverseSegment& g, int launch, const float* const* a_in,
@@ -196,15 +198,17 @@ hipError_t launch_field_reverse2d(const ReverseSegment& g, int launch, const flo
 int adjoint_cone_blocks(int n);
 // Forward re-run of segments seg_first .. seg_first + n_seg - 1 of a run checkpointed every
 // `every` of its n_steps steps from step n0; run step t's fields are at
-// fields + ((t - t_base) * n_species + s) * cells and its cone states go to
-// tape[(t - t_base) * M + i].
+// fields + ((t - t_base) * n_species + s) * cells and its cone steps are recorded as step
+// t - t_base of `tape`.
 hipError_t launch_cones_segments2d(const ConeRules& rules, const float* fields, size_t cells,
                                    int n_species, int t_base, int seg_first, int n_seg,
                                    int every, int n_steps, uint32_t n0, const float* ckpt_pos,
                                    const float* ckpt_dir, const int32_t* ckpt_int, int M,
-                                   float4* tape, hipStream_t stream);
-// Reverse of a segment's cone steps (ag, vmax), then every step's maximum (step_max).
-hipError_t launch_cone_adjoint_segment2d(const ReverseSegment& g, const int32_t* status,
+                                   const ConeTape& tape, hipStream_t stream);
+// Reverse of a segment's cone steps (ag, boxes), then every step's largest contribution to a cell
+// (step_max).  start_status: the cones' status at the segment's first step.
+hipError_t launch_cone_adjoint_segment2d(const ReverseSegment& g, const int32_t* start_status,
+                                         const int32_t* status,
                                          const int32_t* event_step, float* acone,
                                          hipStream_t stream);
 hipError_t launch_adjoint_seed2d(const float* pos, const float* tip_target, const float* weight,

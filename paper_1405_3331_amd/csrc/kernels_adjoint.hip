@@ -7,10 +7,9 @@
 //
 // The fields never depend on the cones, so within a checkpoint segment the cones can be
 // handled apart from the fields, each cone by one thread over all the segment's steps:
-//   k_cones_segments2d        re-runs the segment's cone steps against the re-run fields and
-//                             records (x, y, theta) of every cone at the start of each step
-//                             (when the whole run's fields fit in memory, every segment at
-//                             once, one thread per segment and cone);
+//   the forward run (or, where it did not record its states, k_cones_segments2d, which re-runs
+//                             the segment's cone steps against the re-run fields) records what
+//                             the reverse of each cone step needs of it (ConeTape);
 //   k_cone_adjoint_segment2d  walks the steps backwards carrying each cone's adjoint of
 //                             (p, theta) through advance, capped turn and interpolated
 //                             gradient, and records the adjoint of its sampled gradient
@@ -26,11 +25,8 @@ namespace cuesim {
 namespace {
 
 constexpr int kAdjThreads = 256;
-constexpr int kSegThreads = 64;   // segment kernels: one wavefront per workgroup.  With the
-                                  // reverse walk loading footprints a step ahead, a gradient's
-                                  // reverse sweep at 1024^2 (8192 cones) takes 21.4-21.6 ms,
-                                  // against 21.7-21.8 with 32 threads and 23.0 with 16; half-wave
-                                  // workgroups were ~1.5% faster before that prefetch
+constexpr int kSegThreads = 64;   // segment kernels: one wavefront per workgroup, so that the
+                                  // cones of a small run spread over as many CUs as they can
 
 __device__ double adj_block_sum(double v) {
     __shared__ double part[kAdjThreads / 64];
@@ -46,23 +42,21 @@ __device__ double adj_block_sum(double v) {
 }
 
 // Reverse of the interpolated central-difference gradient of one species at (x, y) with
-// respect to the tip, from the footprint and corner gradients the forward sample used:
+// respect to the tip, from the fractions and corner gradients of the forward sample:
 // (agx, agy) is the adjoint of the sampled gradient, already weighted by the species sign.
 // Adds into (apx, apy) -- the interpolation weights depend on the tip; along an axis where the
 // tip is clamped to the outermost centres they do not.  (The field's share is
 // sample_adjoint_2d.)
-__device__ __forceinline__ void sample_tip_adjoint_2d(const Footprint2D& p,
-                                                      const CornerGradients2D& g,
-                                                      const ConeRules& r, float x, float y,
-                                                      float agx, float agy, float& apx,
-                                                      float& apy) {
-    const float fx = p.fx, fy = p.fy;
+__device__ __forceinline__ void sample_tip_adjoint_2d(float fx, float fy, const float4& gx,
+                                                      const float4& gy, const ConeRules& r,
+                                                      float x, float y, float agx, float agy,
+                                                      float& apx, float& apy) {
     const float ux = fmaf(x, r.inv_dx, -0.5f), uy = fmaf(y, r.inv_dx, -0.5f);
     const bool free_x = ux > 0.0f && ux < (float)(r.nx - 1);
     const bool free_y = uy > 0.0f && uy < (float)(r.ny - 1);
     // d w / d f along each axis, times d f / d p = 1 / dx where not clamped
-    const float aw00 = fmaf(agy, g.gy00, agx * g.gx00), aw10 = fmaf(agy, g.gy10, agx * g.gx10);
-    const float aw01 = fmaf(agy, g.gy01, agx * g.gx01), aw11 = fmaf(agy, g.gy11, agx * g.gx11);
+    const float aw00 = fmaf(agy, gy.x, agx * gx.x), aw10 = fmaf(agy, gy.y, agx * gx.y);
+    const float aw01 = fmaf(agy, gy.z, agx * gx.z), aw11 = fmaf(agy, gy.w, agx * gx.w);
     if (free_x) apx = fmaf(r.inv_dx, fmaf(fy, aw11 - aw01, (1.0f - fy) * (aw10 - aw00)), apx);
     if (free_y) apy = fmaf(r.inv_dx, fmaf(fx, aw11 - aw10, (1.0f - fx) * (aw01 - aw00)), apy);
 }
@@ -73,38 +67,33 @@ struct Field2D {
     __device__ float operator()(int i, int j) const { return f[j * nx + i]; }
 };
 
-// Reverse of one cone step (step index `step`) of cone i from its state (x, y, theta) at
-// the start of the step, the footprints p0/p1 of its gradient samples in the fields after
-// the step's field update, their corner gradients and the weighted gradient (gx, gy).
-// (apx, apy, ath) holds the adjoint of the state after the step on entry and of the state
-// before it on exit; (agx, agy) receives the adjoint of the weighted gradient.
+// A cone step's record (ConeTape).
 template <int NS>
-__device__ __forceinline__ void cone_adjoint_step(const ConeRules& r, const Footprint2D& p0,
-                                                  const Footprint2D& p1,
-                                                  const CornerGradients2D& g0,
-                                                  const CornerGradients2D& g1, float gx,
-                                                  float gy, float4 st, int i, uint32_t step,
+struct ConeTerms {
+    float4 v[kConePlanes + 2 * NS];
+    __device__ __forceinline__ void load(const ConeTape& tape, int t, int i) {
+#pragma unroll
+        for (int j = 0; j < kConePlanes + 2 * NS; ++j)
+            v[j] = tape.base[j * tape.plane + (size_t)t * tape.M + i];
+    }
+};
+
+// Reverse of one cone step from its record.  (apx, apy, ath) holds the adjoint of the state
+// after the step on entry and of the state before it on exit; (agx, agy) receives the adjoint
+// of the weighted gradient.
+template <int NS>
+__device__ __forceinline__ void cone_adjoint_step(const ConeRules& r, const ConeTerms<NS>& m,
                                                   float& apx, float& apy, float& ath,
                                                   float& agx, float& agy) {
-    const float x = st.x, y = st.y, th = st.z;
-    float s, c;
-    sincos_angle(th, s, c);
-    float cross, along;
-    turn_terms(r, s, c, gx, gy, cross, along);
-    bool capped;
-    const float turn = capped_turn(r, cross, along, &capped);
-    float z[2];
-    noise_2d(r.key, (uint32_t)i, step, z);
-    const float thn = wrap_heading(fmaf(r.sigma, z[0], th + turn));
-    float sn, cn;
-    sincos_angle(thn, sn, cn);
-
+    const float x = m.v[0].x, y = m.v[0].y, sn = m.v[0].z, cn = m.v[0].w;
+    const float cross = m.v[1].x, along = m.v[1].y, s = m.v[1].z, c = m.v[1].w;
+    const float gx = m.v[2].x, gy = m.v[2].y, fx = m.v[2].z, fy = m.v[2].w;
     // reverse: p' = p + s (cos theta', sin theta')
     const float athn = fmaf(r.step_len, fmaf(cn, apy, -(sn * apx)), ath);
     // theta' = theta + turn(theta, g) + noise
     ath = athn;
     agx = agy = 0.0f;
-    if (!capped) {
+    if (!turn_capped(r, cross, along)) {
         const float den = fmaf(along, along, cross * cross);
         const float a_cross = athn * along / den, a_along = -athn * cross / den;
         const float dot = fmaf(c, gx, s * gy);
@@ -112,32 +101,14 @@ __device__ __forceinline__ void cone_adjoint_step(const ConeRules& r, const Foot
         agx = r.gain * fmaf(a_along, c, -(a_cross * s));
         agy = r.gain * fmaf(a_cross, c, a_along * s);
     }
-    sample_tip_adjoint_2d(p0, g0, r, x, y, r.sign0 * agx, r.sign0 * agy, apx, apy);
+    sample_tip_adjoint_2d(fx, fy, m.v[3], m.v[4], r, x, y, r.sign0 * agx, r.sign0 * agy, apx,
+                          apy);
     if (NS > 1)
-        sample_tip_adjoint_2d(p1, g1, r, x, y, r.sign1 * agx, r.sign1 * agy, apx, apy);
+        sample_tip_adjoint_2d(fx, fy, m.v[kConePlanes + 2 * NS - 2],
+                              m.v[kConePlanes + 2 * NS - 1], r, x, y, r.sign1 * agx,
+                              r.sign1 * agy, apx, apy);
 }
 
-// The forward gradient sample of a step from its footprints, computed exactly as the
-// forward step computes it.
-template <int NS>
-__device__ __forceinline__ void sample_2d(const ConeRules& r, const Footprint2D& p0,
-                                          const Footprint2D& p1, CornerGradients2D& g0,
-                                          CornerGradients2D& g1, float& gx, float& gy) {
-    g0 = corner_gradients_2d(p0, r);
-    g1 = NS > 1 ? corner_gradients_2d(p1, r) : g0;
-    gradient_from_2d(p0, g0, gx, gy, nullptr);
-    gx *= r.sign0;
-    gy *= r.sign0;
-    if (NS > 1) {
-        float hx, hy;
-        gradient_from_2d(p1, g1, hx, hy, nullptr);
-        gx = fmaf(r.sign1, hx, gx);
-        gy = fmaf(r.sign1, hy, gy);
-    }
-}
-
-// A checkpoint segment of `len` steps from step seg0: fields[t] (species-major, `cells`
-// each) is the field state after t steps of the segment, t = 0..len.
 // Segments of a checkpointed run of n_steps steps from step n0, every `every` steps: run
 // step t's field state (after t steps) is fields + ((t - t_base) * n_species + s) * cells;
 // the checkpoint arrays hold each segment's cone state at its first step.
@@ -157,25 +128,13 @@ struct SegmentSet2D {
     }
 };
 
-struct Segment2D {
-    const float* fields;
-    size_t cells;
-    int n_species;
-    uint32_t seg0;
-    int len;
-    __device__ const float* field(int t, int s) const {
-        return fields + ((size_t)t * n_species + s) * cells;
-    }
-};
-
 // Forward re-run of the cone steps of segments seg_first .. seg_first + gridDim.y - 1, one
 // thread per (segment, cone) over all the segment's steps, each starting from its
-// checkpoint; the state at the start of run step t goes to tape[t - t_base][i] whether or
-// not the cone is still active.  Same arithmetic as the forward step (gradient, turn,
-// noise, advance, exit, contact).
+// checkpoint; the cone's step t is recorded as step t - t_base of the tape while it is active.
+// Same arithmetic as the forward step (gradient, turn, noise, advance, exit, contact).
 template <int NS>
 __global__ __launch_bounds__(kSegThreads) void k_cones_segments2d(ConeRules r, SegmentSet2D set,
-                                                                  float4* __restrict__ tape) {
+                                                                  ConeTape tape) {
     const int i = blockIdx.x * kSegThreads + threadIdx.x;
     if (i >= set.M) return;
     const int seg = set.seg_first + (int)blockIdx.y;
@@ -186,104 +145,111 @@ __global__ __launch_bounds__(kSegThreads) void k_cones_segments2d(ConeRules r, S
     float y = set.ckpt_pos[((size_t)seg * M + i) * 2 + 1];
     float th = set.ckpt_dir[(size_t)seg * M + i];
     int status = set.ckpt_status[(size_t)seg * 3 * M + i];
-    for (int t = t0; t < t1; ++t) {
-        tape[(size_t)(t - set.t_base) * M + i] = make_float4(x, y, th, 0.0f);
-        if (status != kActive) continue;
-        const float* f0 = set.field(t + 1, 0);
+    float sn, cs;
+    sincos_angle(th, sn, cs);
+    for (int t = t0; t < t1 && status == kActive; ++t) {
+        const size_t rec = (size_t)(t - set.t_base);
         float gx, gy;
-        gradient_2d(Field2D{f0, r.nx}, r, x, y, gx, gy);
+        const Footprint2D p0 = footprint_2d(Field2D{set.field(t + 1, 0), r.nx}, r, x, y);
+        const CornerGradients2D g0 = corner_gradients_2d(p0, r);
+        gradient_from_2d(p0, g0, gx, gy, nullptr);
+        tape.sample(0, rec, i, g0);
         gx *= r.sign0;
         gy *= r.sign0;
         if (NS > 1) {
             float hx, hy;
-            gradient_2d(Field2D{set.field(t + 1, NS - 1), r.nx}, r, x, y, hx, hy);
+            const Footprint2D p1 = footprint_2d(Field2D{set.field(t + 1, NS - 1), r.nx}, r, x, y);
+            const CornerGradients2D g1 = corner_gradients_2d(p1, r);
+            gradient_from_2d(p1, g1, hx, hy, nullptr);
+            tape.sample(1, rec, i, g1);
             gx = fmaf(r.sign1, hx, gx);
             gy = fmaf(r.sign1, hy, gy);
         }
-        float sn, cs;
-        sincos_angle(th, sn, cs);
+        tape.put(2, rec, i, make_float4(gx, gy, p0.fx, p0.fy));
+        const float x0 = x, y0 = y, s0 = sn, c0 = cs;
         float z[2];
         noise_2d(r.key, (uint32_t)i, set.n0 + (uint32_t)t, z);
         const ConeEvent ev = cone_step_2d(r, gx, gy, 0.0f, z, x, y, th, sn, cs,
                                           GridContact{&r.targets});
+        record_turn(tape, rec, i, r, x0, y0, s0, c0, gx, gy, sn, cs);
         status = ev.status;
     }
 }
 
-// Last step of a segment (from step seg0, len steps) in which cone i takes part: status and
-// event_step are the run's final ones, and a cone stopped at step n takes part in steps < n
-// only (-1: none of the segment's).
-__device__ __forceinline__ int last_step(const Segment2D& seg, const int32_t* status,
-                                         const int32_t* event_step, int i) {
+// Last step of a segment (from step seg0, len steps) in which cone i takes part (-1: none):
+// none if it had stopped before the segment; status and event_step are the run's final ones,
+// and a cone stopped at step n takes part in steps < n only.
+__device__ __forceinline__ int last_step(uint32_t seg0, int len, const int32_t* start_status,
+                                         const int32_t* status, const int32_t* event_step,
+                                         int i) {
+    if (start_status[i] != kActive) return -1;
     const int64_t last = status[i] == kActive ? INT64_MAX : (int64_t)event_step[i];
-    return (int)max<int64_t>(min<int64_t>(seg.len - 1, last - 1 - (int64_t)seg.seg0), -1);
-}
-
-// Largest |adjoint| of the cells that one species' sample read.
-__device__ __forceinline__ float sample_max(const ConeRules& r, float x, float y, float agx,
-                                            float agy) {
-    const Scatter2D c = sample_adjoint_2d(r, x, y, agx, agy);
-    float m = 0.0f;
-#pragma unroll
-    for (int k = 0; k < 12; ++k) m = fmaxf(m, fabsf(c.v[k]));
-    return m;
+    return (int)max<int64_t>(min<int64_t>(len - 1, last - 1 - (int64_t)seg0), -1);
 }
 
 // Reverse of one segment's cone steps, one thread per cone from the last step to the first;
-// the adjoint of step t's sampled gradient goes to ag[t * n + i] and the largest adjoint of a
-// cell it read to vmax (zero at steps the cone takes no part in).
-// The forward states come from the run's cone tape, so the gathers of the step before do
-// not wait for this step's adjoint: its footprints are loaded one step ahead and its state
-// two.
+// the adjoint of step t's sampled gradient goes to ag[t * n + i] (zero at steps the cone takes
+// no part in).  The forward steps come from the cone tape, a streaming read kAhead steps
+// ahead, so that only what depends on the adjoint is left in the chain from step to step: 65
+// VALU instructions, two of them divisions.  (Before, each step gathered its 12 cells per
+// species from the run's fields, a 128-byte line for a few bytes, and computed the forward
+// step again: 115 us per 100 steps of 8192 cones.)
+// For every reverse launch (kRevSteps steps, from the segment's end) the box of the tips whose
+// samples have an adjoint goes to boxes[launch * n + i] (empty: x from above x to).
+constexpr int kAhead = 4;
+
 template <int NS>
 __global__ __launch_bounds__(kSegThreads) void k_cone_adjoint_segment2d(
-    ConeRules r, Segment2D seg, float2* __restrict__ ag, float* __restrict__ vmax,
-    const float4* __restrict__ tape, const int32_t* __restrict__ status,
-    const int32_t* __restrict__ event_step, float* __restrict__ acone, int n) {
+    ConeRules r, ConeTape tape, uint32_t seg0, int len, float2* __restrict__ ag,
+    float4* __restrict__ boxes, const int32_t* __restrict__ start_status,
+    const int32_t* __restrict__ status, const int32_t* __restrict__ event_step,
+    float* __restrict__ acone) {
+    const int n = tape.M;
     const int i = blockIdx.x * kSegThreads + threadIdx.x;
     if (i >= n) return;
     float apx = acone[3 * i], apy = acone[3 * i + 1], ath = acone[3 * i + 2];
-    const int t_hi = last_step(seg, status, event_step, i);
-    for (int t = seg.len - 1; t > t_hi; --t) {
-        ag[(size_t)t * n + i] = make_float2(0.0f, 0.0f);
-        vmax[(size_t)t * n + i] = 0.0f;
-    }
-    if (t_hi >= 0) {
-        float4 st = tape[(size_t)t_hi * n + i];
-        float4 next = tape[(size_t)max(t_hi - 1, 0) * n + i];
-        Footprint2D p0 = footprint_2d(Field2D{seg.field(t_hi + 1, 0), r.nx}, r, st.x, st.y);
-        Footprint2D p1 =
-            NS > 1 ? footprint_2d(Field2D{seg.field(t_hi + 1, NS - 1), r.nx}, r, st.x, st.y)
-                   : p0;
-        for (int t = t_hi; t >= 0; --t) {
-            // the step before: its state two steps ahead and its footprints one step ahead,
-            // requested before this step's arithmetic (the samples do not depend on it)
-            const float4 next2 = tape[(size_t)max(t - 2, 0) * n + i];
-            Footprint2D q0 = p0, q1 = p1;
-            if (t > 0) {
-                q0 = footprint_2d(Field2D{seg.field(t, 0), r.nx}, r, next.x, next.y);
-                q1 = NS > 1 ? footprint_2d(Field2D{seg.field(t, NS - 1), r.nx}, r, next.x,
-                                           next.y)
-                            : q0;
+    const int t_hi = last_step(seg0, len, start_status, status, event_step, i);
+    const float4 none = make_float4(INFINITY, -INFINITY, INFINITY, -INFINITY);
+    float4 box = none;   // x from, x to, y from, y to
+    ConeTerms<NS> terms[kAhead];
+#pragma unroll
+    for (int a = 0; a < kAhead; ++a) terms[a].load(tape, max(len - 1 - a, 0), i);
+    // every cone walks all the steps (t is the same for the whole wavefront, so addresses are
+    // scalar work); a step it takes no part in leaves its adjoint alone
+    for (int t0 = len - 1; t0 >= 0; t0 -= kAhead) {
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a) {
+            const int t = t0 - a;
+            if (t < 0) break;
+            const ConeTerms<NS> here = terms[a];
+            terms[a].load(tape, max(t - kAhead, 0), i);
+            float agx = 0.0f, agy = 0.0f;
+            if (t <= t_hi) {
+                cone_adjoint_step<NS>(r, here, apx, apy, ath, agx, agy);
+                if (agx != 0.0f || agy != 0.0f)
+                    box = make_float4(fminf(box.x, here.v[0].x), fmaxf(box.y, here.v[0].x),
+                                      fminf(box.z, here.v[0].y), fmaxf(box.w, here.v[0].y));
             }
-            CornerGradients2D g0, g1;
-            float gx, gy, agx, agy;
-            sample_2d<NS>(r, p0, p1, g0, g1, gx, gy);
-            cone_adjoint_step<NS>(r, p0, p1, g0, g1, gx, gy, st, i, seg.seg0 + (uint32_t)t,
-                                  apx, apy, ath, agx, agy);
-            float m = sample_max(r, st.x, st.y, r.sign0 * agx, r.sign0 * agy);
-            if (NS > 1) m = fmaxf(m, sample_max(r, st.x, st.y, r.sign1 * agx, r.sign1 * agy));
             ag[(size_t)t * n + i] = make_float2(agx, agy);
-            vmax[(size_t)t * n + i] = m;
-            st = next;
-            next = next2;
-            p0 = q0;
-            p1 = q1;
+            const int k = len - 1 - t;
+            if (k % kRevSteps == kRevSteps - 1 || t == 0) {
+                boxes[(size_t)(k / kRevSteps) * n + i] = box;
+                box = none;
+            }
         }
     }
     acone[3 * i] = apx;
     acone[3 * i + 1] = apy;
     acone[3 * i + 2] = ath;
+}
+
+// Largest |adjoint| of the cells that one species' sample read.
+__device__ __forceinline__ float sample_max(const ConeRules& r, float2 p, float agx, float agy) {
+    const Scatter2D c = sample_adjoint_2d(r, p.x, p.y, agx, agy);
+    float m = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 12; ++k) m = fmaxf(m, fabsf(c.v[k]));
+    return m;
 }
 
 // Largest |contribution| of every step of the segment: a workgroup takes kMaxCones cones of
@@ -294,7 +260,9 @@ __global__ __launch_bounds__(kSegThreads) void k_cone_adjoint_segment2d(
 constexpr int kMaxThreads = 256;
 constexpr int kMaxCones = 8 * kMaxThreads;
 
-__global__ __launch_bounds__(kMaxThreads) void k_sample_max(const float* __restrict__ vmax,
+__global__ __launch_bounds__(kMaxThreads) void k_sample_max(ConeRules r,
+                                                            const float4* __restrict__ tips,
+                                                            const float2* __restrict__ ag,
                                                             uint32_t* __restrict__ step_max,
                                                             int n) {
     const int t = blockIdx.y;
@@ -302,7 +270,12 @@ __global__ __launch_bounds__(kMaxThreads) void k_sample_max(const float* __restr
 #pragma unroll
     for (int k = 0; k < kMaxCones / kMaxThreads; ++k) {
         const int i = blockIdx.x * kMaxCones + k * kMaxThreads + threadIdx.x;
-        if (i < n) m = fmaxf(m, vmax[(size_t)t * n + i]);
+        if (i >= n) break;
+        const float2 g = ag[(size_t)t * n + i];
+        if (g.x == 0.0f && g.y == 0.0f) continue;
+        const float2 p = *(const float2*)(tips + (size_t)t * n + i);
+        m = fmaxf(m, sample_max(r, p, r.sign0 * g.x, r.sign0 * g.y));
+        if (r.n_species > 1) m = fmaxf(m, sample_max(r, p, r.sign1 * g.x, r.sign1 * g.y));
     }
     for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
     __shared__ float wave_max[kMaxThreads / 64];
@@ -343,7 +316,7 @@ hipError_t launch_cones_segments2d(const ConeRules& rules, const float* fields, 
                                    int n_species, int t_base, int seg_first, int n_seg,
                                    int every, int n_steps, uint32_t n0, const float* ckpt_pos,
                                    const float* ckpt_dir, const int32_t* ckpt_int, int M,
-                                   float4* tape, hipStream_t stream) {
+                                   const ConeTape& tape, hipStream_t stream) {
     if (M == 0 || n_seg == 0) return hipSuccess;
     const SegmentSet2D set{fields, cells, n_species, t_base, seg_first, every, n_steps, n0,
                            ckpt_pos, ckpt_dir, ckpt_int, M};
@@ -357,22 +330,23 @@ hipError_t launch_cones_segments2d(const ConeRules& rules, const float* fields, 
     return hipGetLastError();
 }
 
-hipError_t launch_cone_adjoint_segment2d(const ReverseSegment& g, const int32_t* status,
-                                         const int32_t* event_step, float* acone,
-                                         hipStream_t stream) {
+hipError_t launch_cone_adjoint_segment2d(const ReverseSegment& g, const int32_t* start_status,
+                                         const int32_t* status, const int32_t* event_step,
+                                         float* acone, hipStream_t stream) {
     const int n = g.M;
     if (g.len == 0 || n == 0) return hipSuccess;
-    const Segment2D seg{g.fields, (size_t)g.nx * g.ny, g.n_species, g.seg0, g.len};
     const dim3 grid((n + kSegThreads - 1) / kSegThreads);
     const dim3 max_grid((n + kMaxCones - 1) / kMaxCones, g.len);
     if (g.n_species > 1)
         hipLaunchKernelGGL(k_cone_adjoint_segment2d<2>, grid, dim3(kSegThreads), 0, stream,
-                           g.rules, seg, g.ag, g.vmax, g.tips, status, event_step, acone, n);
+                           g.rules, g.tape, g.seg0, g.len, g.ag, g.boxes, start_status,
+                           status, event_step, acone);
     else
         hipLaunchKernelGGL(k_cone_adjoint_segment2d<1>, grid, dim3(kSegThreads), 0, stream,
-                           g.rules, seg, g.ag, g.vmax, g.tips, status, event_step, acone, n);
-    hipLaunchKernelGGL(k_sample_max, max_grid, dim3(kMaxThreads), 0, stream, g.vmax, g.step_max,
-                       n);
+                           g.rules, g.tape, g.seg0, g.len, g.ag, g.boxes, start_status,
+                           status, event_step, acone);
+    hipLaunchKernelGGL(k_sample_max, max_grid, dim3(kMaxThreads), 0, stream, g.rules,
+                       g.tape.base, g.ag, g.step_max, n);
     return hipGetLastError();
 }
 

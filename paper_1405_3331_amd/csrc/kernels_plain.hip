@@ -17,28 +17,39 @@ struct Global2D {
     __device__ float operator()(int i, int j) const { return f[j * nx + i]; }
 };
 
+// RECORD: what the reverse needs of the step goes to step t of the run's cone tape.
+template <bool RECORD>
 __global__ __launch_bounds__(256) void k_cones2d(ConeRules r, const float* __restrict__ f0,
                                                  const float* __restrict__ f1, ConeArrays c,
-                                                 uint32_t step) {
+                                                 uint32_t step, ConeTape tape, size_t t) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= c.n || c.status[i] != kActive) return;
     float x = c.pos[2 * i], y = c.pos[2 * i + 1], th = c.dir[i];
     float gx, gy, conc = 0.0f;
-    gradient_2d(Global2D{f0, r.nx}, r, x, y, gx, gy, r.turn_law == 1 ? &conc : nullptr);
+    const Footprint2D p0 = footprint_2d(Global2D{f0, r.nx}, r, x, y);
+    const CornerGradients2D g0 = corner_gradients_2d(p0, r);
+    gradient_from_2d(p0, g0, gx, gy, r.turn_law == 1 ? &conc : nullptr);
+    if (RECORD) tape.sample(0, t, i, g0);
     gx *= r.sign0;
     gy *= r.sign0;
     if (r.n_species > 1) {
         float hx, hy;
-        gradient_2d(Global2D{f1, r.nx}, r, x, y, hx, hy);
+        const Footprint2D p1 = footprint_2d(Global2D{f1, r.nx}, r, x, y);
+        const CornerGradients2D g1 = corner_gradients_2d(p1, r);
+        gradient_from_2d(p1, g1, hx, hy, nullptr);
+        if (RECORD) tape.sample(1, t, i, g1);
         gx = fmaf(r.sign1, hx, gx);
         gy = fmaf(r.sign1, hy, gy);
     }
+    if (RECORD) tape.put(2, t, i, make_float4(gx, gy, p0.fx, p0.fy));
     float sn, cs;
     sincos_angle(th, sn, cs);
+    const float x0 = x, y0 = y, s0 = sn, c0 = cs;
     float z[2];
     noise_2d(r.key, (uint32_t)i, step, z);
     const ConeEvent ev = cone_step_2d(r, gx, gy, conc, z, x, y, th, sn, cs,
                                       GridContact{&r.targets});
+    if (RECORD) record_turn(tape, t, i, r, x0, y0, s0, c0, gx, gy, sn, cs);
     c.pos[2 * i] = x;
     c.pos[2 * i + 1] = y;
     c.dir[i] = th;
@@ -113,10 +124,16 @@ hipError_t launch_copy_spans(const CopySpans& c, hipStream_t stream) {
 }
 
 hipError_t launch_cones2d(const ConeRules& rules, const float* f0, const float* f1,
-                          ConeArrays cones, uint32_t step, hipStream_t stream) {
+                          ConeArrays cones, uint32_t step, hipStream_t stream,
+                          const ConeTape* tape, size_t t) {
     if (cones.n == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_cones2d, dim3((cones.n + 255) / 256), dim3(256), 0, stream, rules, f0,
-                       f1, cones, step);
+    const dim3 grid((cones.n + 255) / 256);
+    if (tape)
+        hipLaunchKernelGGL(k_cones2d<true>, grid, dim3(256), 0, stream, rules, f0, f1, cones,
+                           step, *tape, t);
+    else
+        hipLaunchKernelGGL(k_cones2d<false>, grid, dim3(256), 0, stream, rules, f0, f1, cones,
+                           step, ConeTape{}, (size_t)0);
     return hipGetLastError();
 }
 

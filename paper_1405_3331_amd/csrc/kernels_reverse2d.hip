@@ -15,7 +15,7 @@
 // the tile as one float: integer additions, so the sum in a cell does not depend on the order
 // in which the contributions arrive and the gradient is bitwise reproducible.  Which cones can
 // touch a tile's loaded region during a launch is listed beforehand, per launch of a segment
-// (k_tile_count, k_tile_scan, k_tile_fill); a contribution is rebuilt where it is needed from
+// (k_tile_lists); a contribution is rebuilt where it is needed from
 // the cone's tip and the adjoint of its sampled gradient (20 bytes per cone and step, against
 // a 96-byte record of the 12 cells and values).
 //
@@ -49,8 +49,8 @@ constexpr int kHL = kTY + 2 * kH;         // loaded height
 constexpr int kXcds = 8;
 constexpr int kTileCones = kThreads / 4;  // cones of a tile whose steps are held in LDS: one
                                           // cone per four threads
-constexpr int kListThreads = 256;
-constexpr int kScanThreads = 1024;
+constexpr int kListThreads = 1024;
+constexpr int kListTiles = 24 * 1024;     // most tiles counted in LDS
 static_assert(kTX > 0 && kTY > 0 && kH % kCPL == 0, "tile shape");
 
 using V = float2;
@@ -66,7 +66,7 @@ struct ReverseArgs {
     uint32_t tiles_x_inv;      // ceil(2^32 / tiles_x)
     int t_hi, steps;           // segment steps t_hi, t_hi - 1, .. are reversed
     int M;
-    const float4* tips;        // [t][M]: the cones' state at the start of step t
+    const float4* tips;        // [t][M]: tip (x, y, ..) at the start of step t
     const float2* ag;          // [t][M]: the adjoint of the cone's sampled gradient
     const uint32_t* step_max;  // [t]
     const int32_t* list_end;   // [tile]: where the tile's cones end in the list
@@ -390,10 +390,12 @@ __global__ __launch_bounds__(kThreads, 4) void k_field_reverse2d(ReverseArgs a) 
 struct ListArgs {
     ConeRules rules;
     int M, len, tiles_x, tiles_y, cap;
-    const float4* tips;   // [t][M]
-    const float2* ag;     // [t][M]
-    int32_t* count;       // [launch][tile]
-    int32_t* list;        // [launch][cap]
+    bool boxed;            // list the tiles of a cone's box (else of each of its samples)
+    const float4* tips;    // [t][M]
+    const float2* ag;      // [t][M]
+    const float4* boxes;   // [launch][M]
+    int32_t* list_end;     // [launch][tile]
+    int32_t* list;         // [launch][cap]
 };
 
 // Tiles x1 .. x2 by y1 .. y2.
@@ -411,30 +413,45 @@ __device__ __forceinline__ void tile_range(int lo, int hi, int core, int tiles, 
     last = min((hi + kH) / core, tiles - 1);
 }
 
-// Calls each(tile) once for every tile whose loaded region cone i's samples touch in launch g.
+// Tiles whose loaded region meets the samples of tips from (xa, ya) to (xb, yb).
+__device__ __forceinline__ TileBox tiles_of(const ListArgs& a, float xa, float xb, float ya,
+                                            float yb) {
+    int i0, i1, j0, j1;
+    float f;
+    corner(xa, a.rules.inv_dx, a.rules.nx, i0, f);
+    corner(xb, a.rules.inv_dx, a.rules.nx, i1, f);
+    corner(ya, a.rules.inv_dx, a.rules.ny, j0, f);
+    corner(yb, a.rules.inv_dx, a.rules.ny, j1, f);
+    TileBox b;
+    tile_range(max(i0 - 1, 0), min(i1 + 2, a.rules.nx - 1), kTX, a.tiles_x, b.x1, b.x2);
+    tile_range(max(j0 - 1, 0), min(j1 + 2, a.rules.ny - 1), kTY, a.tiles_y, b.y1, b.y2);
+    return b;
+}
+
+// Calls each(tile) once for every tile that cone i is listed for in launch g: the tiles of its
+// box, or, where cones move so far that a box would cover many tiles that no sample touches,
+// those of each sample.
 template <class Each>
 __device__ __forceinline__ void for_touched_tiles(const ListArgs& a, int i, int g,
                                                   const Each& each) {
-    const int t_hi = a.len - 1 - g * kRevSteps;
-    float2 ag[kRevSteps], tip[kRevSteps];   // all loads first
-#pragma unroll
-    for (int k = 0; k < kRevSteps; ++k) {
-        const size_t at = (size_t)max(t_hi - k, 0) * a.M + i;
-        ag[k] = a.ag[at];
-        tip[k] = *(const float2*)(a.tips + at);
+    if (a.boxed) {
+        const float4 p = a.boxes[(size_t)g * a.M + i];
+        if (!(p.x <= p.y)) return;
+        const TileBox b = tiles_of(a, p.x, p.y, p.z, p.w);
+        for (int ty = b.y1; ty <= b.y2; ++ty)
+            for (int tx = b.x1; tx <= b.x2; ++tx) each(ty * a.tiles_x + tx);
+        return;
     }
+    const int t_hi = a.len - 1 - g * kRevSteps;
     TileBox seen[kRevSteps];
 #pragma unroll
     for (int k = 0; k < kRevSteps; ++k) {
         seen[k] = TileBox{1, 0, 1, 0};
-        if (t_hi - k < 0 || (ag[k].x == 0.0f && ag[k].y == 0.0f)) continue;
-        int i0, j0;
-        float f;
-        corner(tip[k].x, a.rules.inv_dx, a.rules.nx, i0, f);
-        corner(tip[k].y, a.rules.inv_dx, a.rules.ny, j0, f);
-        TileBox b;
-        tile_range(max(i0 - 1, 0), min(i0 + 2, a.rules.nx - 1), kTX, a.tiles_x, b.x1, b.x2);
-        tile_range(max(j0 - 1, 0), min(j0 + 2, a.rules.ny - 1), kTY, a.tiles_y, b.y1, b.y2);
+        if (t_hi - k < 0) continue;
+        const size_t at = (size_t)(t_hi - k) * a.M + i;
+        const float2 ag = a.ag[at], p = *(const float2*)(a.tips + at);
+        if (ag.x == 0.0f && ag.y == 0.0f) continue;
+        const TileBox b = tiles_of(a, p.x, p.x, p.y, p.y);
         seen[k] = b;
         for (int ty = b.y1; ty <= b.y2; ++ty)
             for (int tx = b.x1; tx <= b.x2; ++tx) {
@@ -447,22 +464,39 @@ __device__ __forceinline__ void for_touched_tiles(const ListArgs& a, int i, int 
     }
 }
 
-__global__ __launch_bounds__(kListThreads) void k_tile_count(ListArgs a) {
-    const int i = blockIdx.x * kListThreads + threadIdx.x, g = blockIdx.y;
-    if (i >= a.M) return;
-    int32_t* const count = a.count + (size_t)g * a.tiles_x * a.tiles_y;
-    for_touched_tiles(a, i, g, [&](int tile) { atomicAdd(&count[tile], 1); });
-}
-
-// Counts of one launch's tiles -> where each tile's cones start in the list.
-__global__ __launch_bounds__(kScanThreads) void k_tile_scan(int32_t* count, int n) {
-    __shared__ int32_t wave_total[kScanThreads / 64];
-    int32_t* const a = count + (size_t)blockIdx.x * n;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// The lists of launch blockIdx.x, by one workgroup: cones counted per tile (in LDS where the
+// tiles fit: device-wide atomics and a scan of their own took 37 us per 100-step segment at
+// 8192 cones, this 22), the counts scanned to where each tile's cones start, and the cones put
+// there; a tile's start becomes its end (the next tile's start).  The order of a tile's cones
+// does not matter: their contributions are added as integers.
+template <bool LDS>
+__global__ __launch_bounds__(kListThreads) void k_tile_lists(ListArgs a) {
+    extern __shared__ int32_t lds_count[];
+    __shared__ int32_t wave_total[kListThreads / 64];
+    const int g = blockIdx.x, n = a.tiles_x * a.tiles_y, tid = threadIdx.x;
+    int32_t* const out = a.list_end + (size_t)g * n;
+    int32_t* const count = LDS ? lds_count : out;
+    int32_t* const list = a.list + (size_t)g * a.cap;
+    auto get = [&](int k) {
+        return LDS ? count[k]
+                   : __hip_atomic_load(count + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    auto set = [&](int k, int32_t v) {
+        if (LDS)
+            count[k] = v;
+        else
+            __hip_atomic_store(count + k, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    for (int k = tid; k < n; k += kListThreads) set(k, 0);
+    __syncthreads();
+    for (int i = tid; i < a.M; i += kListThreads)
+        for_touched_tiles(a, i, g, [&](int tile) { atomicAdd(&count[tile], 1); });
+    __syncthreads();
+    const int lane = tid & 63, wave = tid >> 6;
     int32_t carry = 0;
-    for (int base = 0; base < n; base += kScanThreads) {
-        const int k = base + threadIdx.x;
-        const int32_t v = k < n ? a[k] : 0;
+    for (int base = 0; base < n; base += kListThreads) {
+        const int k = base + tid;
+        const int32_t v = k < n ? get(k) : 0;
         int32_t incl = v;
         for (int off = 1; off < 64; off <<= 1) {
             const int32_t y = __shfl_up(incl, off, 64);
@@ -471,26 +505,23 @@ __global__ __launch_bounds__(kScanThreads) void k_tile_scan(int32_t* count, int 
         if (lane == 63) wave_total[wave] = incl;
         __syncthreads();
         int32_t at = carry + incl - v, total = 0;
-        for (int w = 0; w < kScanThreads / 64; ++w) {
+        for (int w = 0; w < kListThreads / 64; ++w) {
             at += w < wave ? wave_total[w] : 0;
             total += wave_total[w];
         }
-        if (k < n) a[k] = at;
+        if (k < n) set(k, at);
         carry += total;
         __syncthreads();   // every thread has read wave_total
     }
-}
-
-// Cones into the tiles' lists; a tile's start becomes its end (the next tile's start).
-__global__ __launch_bounds__(kListThreads) void k_tile_fill(ListArgs a) {
-    const int i = blockIdx.x * kListThreads + threadIdx.x, g = blockIdx.y;
-    if (i >= a.M) return;
-    int32_t* const count = a.count + (size_t)g * a.tiles_x * a.tiles_y;
-    int32_t* const list = a.list + (size_t)g * a.cap;
-    for_touched_tiles(a, i, g, [&](int tile) {
-        const int at = atomicAdd(&count[tile], 1);
-        if (at < a.cap) list[at] = i;   // (the capacity holds every cone's most tiles)
-    });
+    for (int i = tid; i < a.M; i += kListThreads)
+        for_touched_tiles(a, i, g, [&](int tile) {
+            const int at = atomicAdd(&count[tile], 1);
+            if (at < a.cap) list[at] = i;   // (the capacity holds every cone's most tiles)
+        });
+    if (LDS) {
+        __syncthreads();
+        for (int k = tid; k < n; k += kListThreads) out[k] = count[k];
+    }
 }
 
 int tiles_along(int n, int core) { return (n + core - 1) / core; }
@@ -507,15 +538,20 @@ int reverse_tiles(int nx, int ny) { return tiles_along(nx, kTX) * tiles_along(ny
 
 int reverse_launches(int len) { return (len + kRevSteps - 1) / kRevSteps; }
 
-size_t reverse_list_capacity(int nx, int ny, int M, double step_cells) {
+// Most tiles a cone is listed for in one launch: the tiles that kRevSteps footprints of 4 x 4
+// cells touch, each on its own (apart), or their box, which covers at most span + 6 cells
+// along an axis (one for rounding) when the cone moves `span` cells.
+static void tiles_per_cone(int nx, int ny, double step_cells, size_t& apart, size_t& boxed) {
     const int tx = tiles_along(nx, kTX), ty = tiles_along(ny, kTY);
-    // the tiles that kRevSteps footprints of 4 x 4 cells touch, each on its own, or together:
-    // the footprints of a cone moving `span` cells cover at most span + 6 (one for rounding)
-    const size_t apart = (size_t)kRevSteps * tiles_touched(4, kTX, tx) * tiles_touched(4, kTY, ty);
-    const double span = (kRevSteps - 1) * step_cells;
-    const size_t together = (size_t)tiles_touched(span + 6, kTX, tx) *
-                            tiles_touched(span + 6, kTY, ty);
-    return (size_t)M * std::min(apart, together);
+    const double cells = (kRevSteps - 1) * step_cells + 6;
+    apart = (size_t)kRevSteps * tiles_touched(4, kTX, tx) * tiles_touched(4, kTY, ty);
+    boxed = (size_t)tiles_touched(cells, kTX, tx) * tiles_touched(cells, kTY, ty);
+}
+
+size_t reverse_list_capacity(int nx, int ny, int M, double step_cells) {
+    size_t apart, boxed;
+    tiles_per_cone(nx, ny, step_cells, apart, boxed);
+    return (size_t)M * std::min(apart, boxed);
 }
 
 void reverse_sources(int nx, int ny, const std::vector<int32_t>& cells, int first,
@@ -534,9 +570,11 @@ void reverse_sources(int nx, int ny, const std::vector<int32_t>& cells, int firs
     }
 }
 
-hipError_t launch_reverse_lists(const ReverseSegment& g, hipStream_t stream) {
+hipError_t launch_reverse_lists(const ReverseSegment& g, double step_cells, hipStream_t stream) {
     const int launches = reverse_launches(g.len);
-    if (g.M == 0 || launches == 0) return hipSuccess;
+    if (launches == 0) return hipSuccess;
+    size_t apart, boxed;
+    tiles_per_cone(g.nx, g.ny, step_cells, apart, boxed);
     ListArgs a = {};
     a.rules = g.rules;
     a.M = g.M;
@@ -544,15 +582,24 @@ hipError_t launch_reverse_lists(const ReverseSegment& g, hipStream_t stream) {
     a.tiles_x = tiles_along(g.nx, kTX);
     a.tiles_y = tiles_along(g.ny, kTY);
     a.cap = (int)g.list_cap;
-    a.tips = g.tips;
+    a.boxed = boxed <= apart;
+    a.tips = g.tape.base;   // plane 0
     a.ag = g.ag;
-    a.count = g.count;
+    a.boxes = g.boxes;
+    a.list_end = g.list_end;
     a.list = g.list;
-    const dim3 grid((g.M + kListThreads - 1) / kListThreads, launches);
-    hipLaunchKernelGGL(k_tile_count, grid, dim3(kListThreads), 0, stream, a);
-    hipLaunchKernelGGL(k_tile_scan, dim3(launches), dim3(kScanThreads), 0, stream, g.count,
-                       a.tiles_x * a.tiles_y);
-    hipLaunchKernelGGL(k_tile_fill, grid, dim3(kListThreads), 0, stream, a);
+    const int n = a.tiles_x * a.tiles_y;
+    if (n <= kListTiles) {
+        const size_t bytes = (size_t)n * sizeof(int32_t);
+        const hipError_t e = hipFuncSetAttribute((const void*)k_tile_lists<true>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 (int)(kListTiles * sizeof(int32_t)));
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_tile_lists<true>, dim3(launches), dim3(kListThreads), bytes, stream,
+                           a);
+    } else {
+        hipLaunchKernelGGL(k_tile_lists<false>, dim3(launches), dim3(kListThreads), 0, stream, a);
+    }
     return hipGetLastError();
 }
 
@@ -577,10 +624,10 @@ hipError_t launch_field_reverse2d(const ReverseSegment& g, int launch, const flo
     a.t_hi = g.len - 1 - launch * kRevSteps;
     a.steps = std::min(kRevSteps, a.t_hi + 1);
     a.M = g.M;
-    a.tips = g.tips;
+    a.tips = g.tape.base;   // plane 0
     a.ag = g.ag;
     a.step_max = g.step_max;
-    a.list_end = g.count + (size_t)launch * a.n_tiles;
+    a.list_end = g.list_end + (size_t)launch * a.n_tiles;
     a.list = g.list + (size_t)launch * g.list_cap;
     a.acc_D = g.acc_D;
     a.acc_k = g.acc_k;

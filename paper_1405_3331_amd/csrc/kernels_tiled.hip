@@ -84,6 +84,7 @@ struct TiledArgs2D {
     float* record;             // non-null: every sub-step's field also goes to
                                // record + ((step - record_n0) * NS + s) * cells (a tape of
                                // every state of a run, for the trajectory-loss gradient)
+    ConeTape cone_record;      // and what the reverse needs of every cone step
     uint32_t record_n0;
 };
 
@@ -288,24 +289,31 @@ __device__ __forceinline__ Footprint2D footprint_lds(const LdsField2D& f, const 
 // and tests exit and contact using g and registers only, so it may run while the next
 // sub-step already overwrites the field.
 // The sample is (g_x, g_y, concentration of species 0; the last only under the SNR law).
-template <int NS>
+// RECORD: the sample's part of the cone's record goes to the run's cone tape (step t of it).
+template <int NS, bool RECORD>
 __device__ __forceinline__ float3 tile_cone_gradient(const float4& st, const LdsField2D& f0,
                                                      const LdsField2D& f1,
-                                                     const ConeRules& rules) {
+                                                     const ConeRules& rules,
+                                                     const ConeTape& tape, size_t t) {
     float gxv = 0.0f, gyv = 0.0f, conc = 0.0f;
-    if (__float_as_int(st.w) < 0) return make_float3(gxv, gyv, conc);
+    const int id = __float_as_int(st.w);
+    if (id < 0) return make_float3(gxv, gyv, conc);
     const Footprint2D p0 = footprint_lds(f0, rules, st.x, st.y);
-    gradient_from_2d(p0, corner_gradients_2d(p0, rules), gxv, gyv,
-                     rules.turn_law == 1 ? &conc : nullptr);
+    const CornerGradients2D g0 = corner_gradients_2d(p0, rules);
+    if (RECORD) tape.sample(0, t, id, g0);
+    gradient_from_2d(p0, g0, gxv, gyv, rules.turn_law == 1 ? &conc : nullptr);
     gxv *= rules.sign0;
     gyv *= rules.sign0;
     if (NS > 1) {
         float hx, hy;
         const Footprint2D p1 = footprint_lds(f1, rules, st.x, st.y);
-        gradient_from_2d(p1, corner_gradients_2d(p1, rules), hx, hy, nullptr);
+        const CornerGradients2D g1 = corner_gradients_2d(p1, rules);
+        if (RECORD) tape.sample(1, t, id, g1);
+        gradient_from_2d(p1, g1, hx, hy, nullptr);
         gxv = fmaf(rules.sign1, hx, gxv);
         gyv = fmaf(rules.sign1, hy, gyv);
     }
+    if (RECORD) tape.put(2, t, id, make_float4(gxv, gyv, p0.fx, p0.fy));
     return make_float3(gxv, gyv, conc);
 }
 
@@ -313,11 +321,13 @@ __device__ __forceinline__ float3 tile_cone_gradient(const float4& st, const Lds
 // the sign bit of its id set.  One Philox block serves an even step and the next odd one:
 // the odd step's two words wait in `spare` (`fresh`: no even step of this launch has
 // filled them yet).
+template <bool RECORD>
 __device__ __forceinline__ void tile_cone_advance(float4& st, float2& sc, uint2& spare,
                                                   float3 g, const ConeRules& rules,
                                                   uint32_t step, bool fresh,
                                                   const TileContact& contact,
-                                                  const ConeArrays& cones) {
+                                                  const ConeArrays& cones,
+                                                  const ConeTape& tape, size_t t) {
     int id = __float_as_int(st.w);
     if (id < 0) return;
     float z[2];
@@ -333,8 +343,11 @@ __device__ __forceinline__ void tile_cone_advance(float4& st, float2& sc, uint2&
         normal_pair(spare.x, spare.y, z);
     }
     float x = st.x, y = st.y, th = st.z;
+    const float2 before = sc;
     const ConeEvent ev =
         cone_step_2d(rules, g.x, g.y, g.z, z, x, y, th, sc.x, sc.y, contact);
+    if (RECORD)
+        record_turn(tape, t, id, rules, st.x, st.y, before.x, before.y, g.x, g.y, sc.x, sc.y);
     if (ev.status != kActive) {
         cones.pos[2 * id] = x;
         cones.pos[2 * id + 1] = y;
@@ -701,15 +714,17 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& 
         //    happens before the barrier; the cones then finish their step after it,
         //    overlapping the next sub-step's in-place stencil, which they no longer read.
         const uint32_t step = first_step + (uint32_t)b;
+        const size_t rec = RECORD ? step - a.record_n0 : 0;
         if (n_cones > 0) {
             float3 g[kConeSlots];
 #pragma unroll
-            for (int k = 0; k < kConeSlots; ++k) g[k] = tile_cone_gradient<NS>(mine[k], f0, f1, rules);
+            for (int k = 0; k < kConeSlots; ++k) 
+                g[k] = tile_cone_gradient<NS, RECORD>(mine[k], f0, f1, rules, a.cone_record, rec);
             __syncthreads();
 #pragma unroll
             for (int k = 0; k < kConeSlots; ++k)
-                tile_cone_advance(mine[k], trig[k], spare[k], g[k], rules, step, b == 0,
-                                  contact, a.cones);
+                tile_cone_advance<RECORD>(mine[k], trig[k], spare[k], g[k], rules, step, b == 0,
+                                          contact, a.cones, a.cone_record, rec);
         }
     }
 
@@ -1154,8 +1169,9 @@ hipError_t tiled_allocate(const TiledPlan& plan, TiledState& st, int n_cones,
     return hipSuccess;
 }
 
-void tiled_set_record(TiledState& st, float* tape, uint32_t n0) {
+void tiled_set_record(TiledState& st, float* tape, const ConeTape& cones, uint32_t n0) {
     st.args->record = tape;
+    st.args->cone_record = cones;
     st.args->record_n0 = n0;
 }
 

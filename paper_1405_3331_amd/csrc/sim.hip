@@ -43,17 +43,19 @@ struct AdjointRun {
     double* loss_partial = nullptr;     // [cone workgroups]
     float* tape = nullptr;              // [n_steps + 1][n_species][n_cells]: every field state
                                         // of the run, recorded as it ran (null: not recorded)
+    float4* cone_tape = nullptr;        // and every cone step (ConeTape)
     // The reverse sweep's workspace, allocated by its first call and kept for further calls
     // on the same record (freed with the record).
     struct Work {
         bool ready = false;
         bool whole = false;             // the window is the whole run (else one segment)
         float* tape_own = nullptr;      // the window's field states when the run did not record
-        float4* tape_cones = nullptr;   // the cone state at every step of the window
-        float2* ag = nullptr;           // one segment's sample adjoints [K][M], their largest
-        float* vmax = nullptr;          // shares [K][M]
-        uint32_t* step_max = nullptr;   // [K], and [launch][tile] cone counts: cleared together
-        int32_t* list = nullptr;        // the cones that touch each tile, per launch
+        float4* tape_cones = nullptr;   // the window's cone steps when the run did not record
+        float2* ag = nullptr;           // one segment's sample adjoints [K][M]
+        uint32_t* step_max = nullptr;   // [K]
+        float4* boxes = nullptr;        // the cones' tips per launch, and the cones that touch
+        int32_t* list_end = nullptr;    // each tile
+        int32_t* list = nullptr;
         float* afield = nullptr;        // the field adjoint, ping-pong per species
         double* acc = nullptr;          // FP64 accumulators
         int32_t* q_start = nullptr;     // the sources listed per tile
@@ -123,6 +125,7 @@ struct sim_handle {
     AdjointRun* adj = nullptr;
     int64_t adj_tape_limit = 0;   // bytes the gradient may record (0: half the free memory)
     float* record = nullptr;      // recording a run (per-step path): tape of its field states
+    ConeTape cone_record = {};    // and of its cone steps
     int64_t record_n0 = 0;        // step of the tape's first state
     GraphBuffers graph = {};                                 // last sim_connectivity
     int graph_cones = 0;
@@ -191,8 +194,9 @@ static void adjoint_work_release(AdjointRun::Work& w) {
     dfree(w.tape_own);
     dfree(w.tape_cones);
     dfree(w.ag);
-    dfree(w.vmax);
     dfree(w.step_max);
+    dfree(w.boxes);
+    dfree(w.list_end);
     dfree(w.list);
     dfree(w.afield);
     dfree(w.acc);
@@ -213,6 +217,7 @@ void adjoint_release(sim_handle* h) {
     dfree(a->acone);
     dfree(a->loss_partial);
     dfree(a->tape);
+    dfree(a->cone_tape);
     adjoint_work_release(a->work);
     delete a;
     h->adj = nullptr;
@@ -456,7 +461,9 @@ sim_status plain_step(sim_handle* h) {
     const float* f0 = h->field[0][h->cur[0]];
     const float* f1 = h->n_species > 1 ? h->field[1][h->cur[1]] : f0;
     if (h->dim == 2) {
-        HIP_TRY(h, launch_cones2d(h->rules, f0, f1, h->cones, (uint32_t)h->step, h->stream));
+        HIP_TRY(h, launch_cones2d(h->rules, f0, f1, h->cones, (uint32_t)h->step, h->stream,
+                                  h->record ? &h->cone_record : nullptr,
+                                  (size_t)(h->step - h->record_n0)));
     } else if (h->order3d.n > 0) {
         if (!h->cones_ordered) {
             HIP_TRY(h, order3d_begin(h->order3d, h->rules, h->cones, h->stream));
@@ -1067,11 +1074,19 @@ static sim_status adjoint_seed(sim_handle* h) {
     return SIM_OK;
 }
 
-// Bytes of every field state of a run of n_steps and of its cone states.
+// Cone tape entries of a window of n_steps steps.
+static size_t cone_tape_size(const sim_handle* h, int64_t n_steps) {
+    return (size_t)(kConePlanes + 2 * h->n_species) * (size_t)n_steps *
+           std::max<size_t>((size_t)h->n_cones, 1);
+}
+static ConeTape cone_tape_view(const sim_handle* h, float4* base, int64_t n_steps) {
+    return ConeTape{base, (size_t)n_steps * (size_t)h->n_cones, h->n_cones};
+}
+
+// Bytes of every field state of a run of n_steps and of its cone steps.
 static size_t adjoint_whole_bytes(const sim_handle* h, int64_t n_steps) {
     const size_t ns = (size_t)h->n_species, cells = (size_t)h->n_cells;
-    return (size_t)(n_steps + 1) * ns * cells * 4 +
-           (size_t)n_steps * std::max<size_t>((size_t)h->n_cones, 1) * 16;
+    return (size_t)(n_steps + 1) * ns * cells * 4 + cone_tape_size(h, n_steps) * sizeof(float4);
 }
 
 // The handle's tape limit (sim_adjoint_set_tape_limit), or half the free device memory.
@@ -1088,7 +1103,7 @@ struct RecordGuard {
     ~RecordGuard() {
         if (!h) return;
         h->record = nullptr;
-        if (h->block_steps > 1) tiled_set_record(h->tiled, nullptr, 0);
+        if (h->block_steps > 1) tiled_set_record(h->tiled, nullptr, ConeTape{}, 0);
     }
 };
 
@@ -1146,14 +1161,15 @@ sim_status sim_adjoint_run(sim_handle* h, int64_t n_steps, int32_t checkpoint_ev
                                   h->stream));
         HIP_TRY(h, hipMemcpyAsync(a->weight, weight, Ms * 4, hipMemcpyHostToDevice, h->stream));
     }
-    // When the whole run's states fit the tape limit, record every field state as the run
-    // goes (the reverse sweep then re-runs only the cone steps); if the tape cannot be had,
-    // the sweep re-runs the fields from the checkpoints instead.
+    // When the whole run's states fit the tape limit, record every field state and cone step
+    // as the run goes; if the tape cannot be had, the sweep re-runs them from the checkpoints
+    // instead.
     RecordGuard recording;
     if (a->n_ckpt > 1 && adjoint_whole_bytes(h, n_steps) < adjoint_tape_limit(h)) {
-        if (dalloc(&a->tape, (size_t)(n_steps + 1) * ns * cells) != hipSuccess) {
+        if (dalloc(&a->tape, (size_t)(n_steps + 1) * ns * cells) != hipSuccess ||
+            dalloc(&a->cone_tape, cone_tape_size(h, n_steps)) != hipSuccess) {
             (void)hipGetLastError();
-            a->tape = nullptr;
+            dfree(a->tape);
         } else {
             for (size_t s = 0; s < ns; ++s)
                 HIP_TRY(h, hipMemcpyAsync(a->tape + s * cells, h->field[s][h->cur[s]], cells * 4,
@@ -1161,7 +1177,9 @@ sim_status sim_adjoint_run(sim_handle* h, int64_t n_steps, int32_t checkpoint_ev
             recording.h = h;
             h->record = a->tape;
             h->record_n0 = h->step;
-            if (h->block_steps > 1) tiled_set_record(h->tiled, a->tape, (uint32_t)h->step);
+            h->cone_record = cone_tape_view(h, a->cone_tape, n_steps);
+            if (h->block_steps > 1)
+                tiled_set_record(h->tiled, a->tape, h->cone_record, (uint32_t)h->step);
         }
     }
     for (int j = 0; j < a->n_ckpt; ++j) {
@@ -1221,16 +1239,14 @@ sim_status sim_adjoint_backward(sim_handle* h, double* dL_dq, double* dL_dD, dou
     q_off[1] = n_q[0];
     const int nq_all = n_q[0] + (ns > 1 ? n_q[1] : 0);
 
-    // Workspace.  The field states of the reverse sweep (a window of steps), the cone state at
-    // every step of the window, one segment's per-step sample adjoints and the lists of the
-    // cones that touch each tile, the field adjoint (ping-pong per species) and FP64
-    // accumulators.  When the whole run's
-    // fields fit comfortably (under half the free device memory), the window is the whole
-    // run: the fields are re-run once and the cone steps of every segment are re-run at once,
-    // one thread per (segment, cone), instead of segment after segment.
+    // Workspace.  One segment's per-step sample adjoints and the lists of the cones that touch
+    // each tile, the field adjoint (ping-pong per species), FP64 accumulators and, when the run
+    // did not record them, the field states and cone steps of a window of steps: the whole run
+    // if it fits the limit after all (the fields are re-run once and the cone steps of every
+    // segment at once, one thread per segment and cone), else a segment after the other.
     const int n_seg = a->n_ckpt;
     const int64_t n_run = a->n_steps;
-    // the run recorded its field states (sim_adjoint_run): only the cone steps are re-run
+    // the run recorded its field states and cone steps (sim_adjoint_run)
     const bool recorded = a->tape != nullptr;
     AdjointRun::Work& w = a->work;
     const bool fresh = !w.ready;   // first sweep of this record: allocate the workspace
@@ -1253,17 +1269,18 @@ sim_status sim_adjoint_backward(sim_handle* h, double* dL_dq, double* dL_dD, dou
     for (int s = 0; s < ns; ++s)
         reverse_sources(nx, ny, h->src_caller_cell[s], q_off[s], q_start_h, q_entry_h);
     const size_t launches = (size_t)reverse_launches(K);
-    const size_t list_cap = reverse_list_capacity(nx, ny, std::max(M, 1),
-                                                  h->rules.step_len * h->rules.inv_dx);
-    const size_t cleared = (size_t)K + launches * fb;   // step_max and the counts
+    const double step_cells = h->rules.step_len * h->rules.inv_dx;
+    const size_t list_cap = reverse_list_capacity(nx, ny, std::max(M, 1), step_cells);
     hipError_t e = hipSuccess;
     const size_t acc_n = (size_t)2 * ns * fb + (size_t)std::max(nq_all, 1);
     if (fresh &&
-        ((!recorded && (e = dalloc(&tape_own, (size_t)(window + 1) * ns * cells)) != hipSuccess) ||
-        (e = dalloc(&tape_cones, (size_t)window * std::max<size_t>(Ms, 1))) != hipSuccess ||
+        ((!recorded &&
+          ((e = dalloc(&tape_own, (size_t)(window + 1) * ns * cells)) != hipSuccess ||
+           (e = dalloc(&tape_cones, cone_tape_size(h, window))) != hipSuccess)) ||
         (e = dalloc(&w.ag, (size_t)K * std::max<size_t>(Ms, 1))) != hipSuccess ||
-        (e = dalloc(&w.vmax, (size_t)K * std::max<size_t>(Ms, 1))) != hipSuccess ||
-        (e = dalloc(&step_max, cleared)) != hipSuccess ||
+        (e = dalloc(&step_max, (size_t)K)) != hipSuccess ||
+        (e = dalloc(&w.boxes, launches * std::max<size_t>(Ms, 1))) != hipSuccess ||
+        (e = dalloc(&w.list_end, launches * fb)) != hipSuccess ||
         (e = dalloc(&w.list, launches * list_cap)) != hipSuccess ||
         (e = dalloc(&afield, (size_t)2 * ns * cells)) != hipSuccess ||
         (e = dalloc(&acc, acc_n)) != hipSuccess ||
@@ -1307,14 +1324,11 @@ sim_status sim_adjoint_backward(sim_handle* h, double* dL_dq, double* dL_dD, dou
     };
     int cur = 0;
     auto afield_at = [&](int s, int half) { return afield + ((size_t)s * 2 + half) * cells; };
+    const ConeTape tape_of_cones =
+        recorded ? cone_tape_view(h, a->cone_tape, n_run) : cone_tape_view(h, tape_cones, window);
     // re-run the fields of run steps [t0, t0 + len) from the checkpoint of segment j, and
-    // the cone steps of segments j .. j + n - 1
-    // (the fields only when the run did not record them)
+    // the cone steps of segments j .. j + n - 1 (a run that recorded them needs neither)
     auto rerun = [&](int j, int64_t t0, int64_t len, int n) -> hipError_t {
-        if (recorded)
-            return launch_cones_segments2d(h->rules, tape, cells, ns, (int)t_base, j, n,
-                                           a->every, (int)n_run, (uint32_t)a->n0, a->ckpt_pos,
-                                           a->ckpt_dir, a->ckpt_int, M, tape_cones, h->stream);
         hipError_t r = hipMemcpyAsync(field_at(t0, 0), a->ckpt_field + (size_t)j * ns * cells,
                                       (size_t)ns * cells * 4, hipMemcpyDeviceToDevice,
                                       h->stream);
@@ -1334,10 +1348,10 @@ sim_status sim_adjoint_backward(sim_handle* h, double* dL_dq, double* dL_dD, dou
         if (r == hipSuccess)
             r = launch_cones_segments2d(h->rules, tape, cells, ns, (int)t_base, j, n, a->every,
                                         (int)n_run, (uint32_t)a->n0, a->ckpt_pos, a->ckpt_dir,
-                                        a->ckpt_int, M, tape_cones, h->stream);
+                                        a->ckpt_int, M, tape_of_cones, h->stream);
         return r;
     };
-    if (whole) ADJ_TRY(rerun(0, 0, n_run, n_seg));
+    if (whole && !recorded) ADJ_TRY(rerun(0, 0, n_run, n_seg));
     for (int j = n_seg - 1; j >= 0; --j) {
         const int64_t t0 = (int64_t)j * a->every;
         const int len = (int)std::min<int64_t>(a->every, n_run - t0);
@@ -1355,11 +1369,12 @@ sim_status sim_adjoint_backward(sim_handle* h, double* dL_dq, double* dL_dD, dou
         g.len = len;
         g.seg0 = (uint32_t)(a->n0 + t0);
         g.fields = field_at(t0, 0);
-        g.tips = tape_cones + (size_t)(t0 - t_base) * Ms;
+        g.tape = tape_of_cones;
+        g.tape.base += (size_t)(t0 - t_base) * Ms;
         g.ag = w.ag;
-        g.vmax = w.vmax;
         g.step_max = step_max;
-        g.count = (int32_t*)step_max + K;
+        g.boxes = w.boxes;
+        g.list_end = w.list_end;
         g.list = w.list;
         g.list_cap = list_cap;
         g.acc_D = acc_D;
@@ -1367,11 +1382,12 @@ sim_status sim_adjoint_backward(sim_handle* h, double* dL_dq, double* dL_dD, dou
         g.acc_q = acc_q;
         g.q_start = q_start;
         g.q_entry = q_entry;
-        ADJ_TRY(hipMemsetAsync(step_max, 0, cleared * sizeof(uint32_t), h->stream));
+        ADJ_TRY(hipMemsetAsync(step_max, 0, (size_t)K * sizeof(uint32_t), h->stream));
         // the segment's cone adjoints, the tiles they touch, then the field steps
-        ADJ_TRY(launch_cone_adjoint_segment2d(g, h->cones.status, h->cones.event_step, a->acone,
+        ADJ_TRY(launch_cone_adjoint_segment2d(g, a->ckpt_int + (size_t)j * 3 * Ms,
+                                              h->cones.status, h->cones.event_step, a->acone,
                                               h->stream));
-        ADJ_TRY(launch_reverse_lists(g, h->stream));
+        ADJ_TRY(launch_reverse_lists(g, step_cells, h->stream));
         for (int l = 0; l < reverse_launches(len); ++l) {
             const float* in[SIM_MAX_SPECIES] = {afield_at(0, cur), afield_at(ns - 1, cur)};
             float* out[SIM_MAX_SPECIES] = {afield_at(0, cur ^ 1), afield_at(ns - 1, cur ^ 1)};
