@@ -43,6 +43,7 @@ hipError_t launch_cones2d(const ConeRules& rules, const float* f0, const float* 
 // field2d_prepare from the merged, pre-scaled sources of each species.
 struct Field2DStep {
     int nx = 0, ny = 0, n_species = 0, n_boxes = 0;
+    char* memory = nullptr;         // every list below
     int32_t* src_start = nullptr;   // [n_boxes + 1]
     int32_t* src_row = nullptr;     // per entry: row j
     int32_t* src_col = nullptr;     // per entry: thread of the box owning the cell
@@ -81,6 +82,7 @@ hipError_t launch_field2d_rows(const Field2DStep& f, const float* const* in, flo
 // field3d_prepare from the merged, pre-scaled sources of each species.
 struct Field3D {
     int nx = 0, ny = 0, nz = 0, n_species = 0, n_boxes = 0;
+    char* memory = nullptr;          // every list below
     int32_t* src_start = nullptr;    // [n_boxes + 1]
     int32_t* src_plane = nullptr;    // per entry: plane index l
     int32_t* src_thread = nullptr;   // per entry: thread of the box owning the cell
@@ -110,6 +112,7 @@ hipError_t launch_field3d(const Field3D& f, const float* const* in, float* const
 // Keys are Morton codes of the tip cell coarsened by `shift` bits per axis; stopped cones
 // carry id -1 and the key `inactive`, past every active one.
 struct ConeOrder3D {
+    char* memory = nullptr;   // every array below
     float4* tip[2] = {};
     float4* dir[2] = {};
     uint32_t* key[2] = {};

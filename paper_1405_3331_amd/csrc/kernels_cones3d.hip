@@ -15,6 +15,7 @@
 // a refresh moves them behind the active ones.  The caller-order tips and headings of the
 // active cones are brought up to date only when the state is read (order3d_end).
 #include "internal.hpp"
+#include "memory.hpp"
 
 namespace cuesim {
 
@@ -267,25 +268,28 @@ hipError_t order3d_allocate(ConeOrder3D& o, int n, int nx, int ny, int nz) {
     o.inactive = 1u << (3 * bits);
     o.end_bit = 3 * bits + 1;
     if (n == 0) return hipSuccess;
-    hipError_t e;
+    auto padded = [](size_t bytes) { return (bytes + 255) / 256 * 256; };
+    const size_t state = padded((size_t)n * sizeof(float4)), word = padded((size_t)n * 4);
+    const hipError_t e = device_malloc((void**)&o.memory, 4 * state + 4 * word +
+                                                              sort_pairs_scratch_bytes(n));
+    if (e != hipSuccess) return e;
+    char* at = o.memory;
     for (int b = 0; b < 2; ++b) {
-        if ((e = hipMalloc((void**)&o.tip[b], (size_t)n * sizeof(float4))) != hipSuccess ||
-            (e = hipMalloc((void**)&o.dir[b], (size_t)n * sizeof(float4))) != hipSuccess ||
-            (e = hipMalloc((void**)&o.key[b], (size_t)n * sizeof(uint32_t))) != hipSuccess ||
-            (e = hipMalloc((void**)&o.slot[b], (size_t)n * sizeof(int32_t))) != hipSuccess)
-            return e;
+        o.tip[b] = (float4*)at;
+        o.dir[b] = (float4*)(at + state);
+        at += 2 * state;
     }
-    return hipMalloc((void**)&o.scratch, sort_pairs_scratch_bytes(n));
+    for (int b = 0; b < 2; ++b) {
+        o.key[b] = (uint32_t*)at;
+        o.slot[b] = (int32_t*)(at + word);
+        at += 2 * word;
+    }
+    o.scratch = (int32_t*)at;
+    return hipSuccess;
 }
 
 void order3d_release(ConeOrder3D& o) {
-    for (int b = 0; b < 2; ++b) {
-        if (o.tip[b]) (void)hipFree(o.tip[b]);
-        if (o.dir[b]) (void)hipFree(o.dir[b]);
-        if (o.key[b]) (void)hipFree(o.key[b]);
-        if (o.slot[b]) (void)hipFree(o.slot[b]);
-    }
-    if (o.scratch) (void)hipFree(o.scratch);
+    device_free(o.memory);
     o = ConeOrder3D{};
 }
 

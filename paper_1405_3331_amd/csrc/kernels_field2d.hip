@@ -22,6 +22,7 @@
 #include <vector>
 
 #include "internal.hpp"
+#include "memory.hpp"
 
 namespace cuesim {
 
@@ -242,24 +243,6 @@ hipError_t field2d_prepare(Field2DStep& f, int nx, int ny, int n_species,
         }
         start[box + 1] = (int32_t)row_of.size();
     }
-    const size_t n_src = std::max<size_t>(row_of.size(), 1);
-    hipError_t e;
-    if ((e = hipMalloc((void**)&f.src_start, start.size() * sizeof(int32_t))) != hipSuccess ||
-        (e = hipMalloc((void**)&f.src_row, n_src * sizeof(int32_t))) != hipSuccess ||
-        (e = hipMalloc((void**)&f.src_col, n_src * sizeof(int32_t))) != hipSuccess ||
-        (e = hipMalloc((void**)&f.src_q, n_src * sizeof(float))) != hipSuccess)
-        return e;
-    if ((e = hipMemcpy(f.src_start, start.data(), start.size() * sizeof(int32_t),
-                       hipMemcpyHostToDevice)) != hipSuccess)
-        return e;
-    if (!row_of.empty() &&
-        ((e = hipMemcpy(f.src_row, row_of.data(), row_of.size() * sizeof(int32_t),
-                        hipMemcpyHostToDevice)) != hipSuccess ||
-         (e = hipMemcpy(f.src_col, col_of.data(), col_of.size() * sizeof(int32_t),
-                        hipMemcpyHostToDevice)) != hipSuccess ||
-         (e = hipMemcpy(f.src_q, amount.data(), amount.size() * sizeof(float),
-                        hipMemcpyHostToDevice)) != hipSuccess))
-        return e;
     // two-step boxes: the sources on each box and its one-cell ring (a cell near a box edge
     // is listed by up to four boxes)
     const Tiles2D p = tiles_for(nx, ny, kPY);
@@ -285,20 +268,19 @@ hipError_t field2d_prepare(Field2DStep& f, int nx, int ny, int n_species,
         }
         pstart[b + 1] = (int32_t)ppos.size();
     }
-    const size_t n_p = std::max<size_t>(ppos.size(), 1);
-    if ((e = hipMalloc((void**)&f.pair_start, pstart.size() * sizeof(int32_t))) != hipSuccess ||
-        (e = hipMalloc((void**)&f.pair_pos, n_p * sizeof(int32_t))) != hipSuccess ||
-        (e = hipMalloc((void**)&f.pair_q, n_p * sizeof(float))) != hipSuccess)
-        return e;
-    if ((e = hipMemcpy(f.pair_start, pstart.data(), pstart.size() * sizeof(int32_t),
-                       hipMemcpyHostToDevice)) != hipSuccess)
-        return e;
-    if (!ppos.empty() &&
-        ((e = hipMemcpy(f.pair_pos, ppos.data(), ppos.size() * sizeof(int32_t),
-                        hipMemcpyHostToDevice)) != hipSuccess ||
-         (e = hipMemcpy(f.pair_q, pq.data(), pq.size() * sizeof(float),
-                        hipMemcpyHostToDevice)) != hipSuccess))
-        return e;
+    UploadBlock up;
+    const size_t at_start = up.add(start), at_row = up.add(row_of), at_col = up.add(col_of),
+                 at_q = up.add(amount), at_pstart = up.add(pstart), at_ppos = up.add(ppos),
+                 at_pq = up.add(pq);
+    const hipError_t e = up.upload(&f.memory);
+    if (e != hipSuccess) return e;
+    f.src_start = (int32_t*)(f.memory + at_start);
+    f.src_row = (int32_t*)(f.memory + at_row);
+    f.src_col = (int32_t*)(f.memory + at_col);
+    f.src_q = (float*)(f.memory + at_q);
+    f.pair_start = (int32_t*)(f.memory + at_pstart);
+    f.pair_pos = (int32_t*)(f.memory + at_ppos);
+    f.pair_q = (float*)(f.memory + at_pq);
     f.n_pair_boxes = n_pair;
     f.nx = nx;
     f.ny = ny;
@@ -308,13 +290,7 @@ hipError_t field2d_prepare(Field2DStep& f, int nx, int ny, int n_species,
 }
 
 void field2d_release(Field2DStep& f) {
-    if (f.src_start) (void)hipFree(f.src_start);
-    if (f.src_row) (void)hipFree(f.src_row);
-    if (f.src_col) (void)hipFree(f.src_col);
-    if (f.src_q) (void)hipFree(f.src_q);
-    if (f.pair_start) (void)hipFree(f.pair_start);
-    if (f.pair_pos) (void)hipFree(f.pair_pos);
-    if (f.pair_q) (void)hipFree(f.pair_q);
+    device_free(f.memory);
     f = Field2DStep{};
 }
 

@@ -24,6 +24,7 @@
 #include <vector>
 
 #include "internal.hpp"
+#include "memory.hpp"
 
 namespace cuesim {
 
@@ -151,24 +152,15 @@ hipError_t field3d_prepare(Field3D& f, int nx, int ny, int nz, int n_species,
         }
         start[box + 1] = (int32_t)plane_of.size();
     }
-    const size_t n_src = std::max<size_t>(plane_of.size(), 1);
-    hipError_t e;
-    if ((e = hipMalloc((void**)&f.src_start, start.size() * sizeof(int32_t))) != hipSuccess ||
-        (e = hipMalloc((void**)&f.src_plane, n_src * sizeof(int32_t))) != hipSuccess ||
-        (e = hipMalloc((void**)&f.src_thread, n_src * sizeof(int32_t))) != hipSuccess ||
-        (e = hipMalloc((void**)&f.src_q, n_src * sizeof(float))) != hipSuccess)
-        return e;
-    if ((e = hipMemcpy(f.src_start, start.data(), start.size() * sizeof(int32_t),
-                       hipMemcpyHostToDevice)) != hipSuccess)
-        return e;
-    if (!plane_of.empty() &&
-        ((e = hipMemcpy(f.src_plane, plane_of.data(), plane_of.size() * sizeof(int32_t),
-                        hipMemcpyHostToDevice)) != hipSuccess ||
-         (e = hipMemcpy(f.src_thread, thread_of.data(), thread_of.size() * sizeof(int32_t),
-                        hipMemcpyHostToDevice)) != hipSuccess ||
-         (e = hipMemcpy(f.src_q, amount.data(), amount.size() * sizeof(float),
-                        hipMemcpyHostToDevice)) != hipSuccess))
-        return e;
+    UploadBlock up;
+    const size_t at_start = up.add(start), at_plane = up.add(plane_of),
+                 at_thread = up.add(thread_of), at_q = up.add(amount);
+    const hipError_t e = up.upload(&f.memory);
+    if (e != hipSuccess) return e;
+    f.src_start = (int32_t*)(f.memory + at_start);
+    f.src_plane = (int32_t*)(f.memory + at_plane);
+    f.src_thread = (int32_t*)(f.memory + at_thread);
+    f.src_q = (float*)(f.memory + at_q);
     f.nx = nx;
     f.ny = ny;
     f.nz = nz;
@@ -178,10 +170,7 @@ hipError_t field3d_prepare(Field3D& f, int nx, int ny, int nz, int n_species,
 }
 
 void field3d_release(Field3D& f) {
-    if (f.src_start) (void)hipFree(f.src_start);
-    if (f.src_plane) (void)hipFree(f.src_plane);
-    if (f.src_thread) (void)hipFree(f.src_thread);
-    if (f.src_q) (void)hipFree(f.src_q);
+    device_free(f.memory);
     f = Field3D{};
 }
 

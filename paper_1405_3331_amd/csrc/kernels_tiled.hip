@@ -22,6 +22,7 @@
 // instead of B reads and B writes of every cell.
 #include <hip/hip_ext.h>
 
+#include "memory.hpp"
 #include "rows.hpp"
 #include "tiled.hpp"
 
@@ -1019,7 +1020,7 @@ hipError_t tiled_allocate(const TiledPlan& plan, TiledState& st, int n_cones,
     const int W = 64 * plan.cpl;
     st.capacity = std::max(1, n_cones);
     const size_t slots = (size_t)plan.n_tiles * st.capacity;
-    if ((e = hipMalloc(&st.bucket[0], 2 * slots * sizeof(float4))) != hipSuccess) return e;
+    if ((e = device_malloc((void**)&st.bucket[0], 2 * slots * sizeof(float4))) != hipSuccess) return e;
     st.bucket[1] = st.bucket[0] + slots;
     st.cur = 0;
     st.phase = 0;
@@ -1121,7 +1122,7 @@ hipError_t tiled_allocate(const TiledPlan& plan, TiledState& st, int n_cones,
     };
     const size_t at_head = table(head), at_entry = table(entry), at_amount = table(amount),
                  at_tgt = table(tpts), at_hsrc = table(head_src), at_htgt = table(head_tgt);
-    if ((e = hipMalloc(&st.memory, bytes)) != hipSuccess ||
+    if ((e = device_malloc((void**)&st.memory, bytes)) != hipSuccess ||
         (e = hipMemsetAsync(st.memory, 0, zeroed, stream)) != hipSuccess ||
         (e = hipMemcpy(st.memory + zeroed, tables.data(), tables.size(),
                        hipMemcpyHostToDevice)) != hipSuccess)
@@ -1189,8 +1190,8 @@ int tiled_extra_capacity(int64_t n_cones) {
 }
 
 void tiled_release(TiledState& st) {
-    (void)hipFree(st.bucket[0]);
-    (void)hipFree(st.memory);
+    device_free(st.bucket[0]);
+    device_free(st.memory);
     delete st.args;
     st = TiledState();
 }

@@ -14,6 +14,7 @@
 
 #include "cuesim.h"
 #include "internal.hpp"
+#include "memory.hpp"
 #include "validate.hpp"
 #include "tiled.hpp"
 
@@ -83,8 +84,8 @@ struct sim_handle {
     int cur[SIM_MAX_SPECIES] = {0, 0};
     Field2DStep field2d = {};   // 2D un-blocked field step with its per-box source lists
     ConeArrays cones = {};
-    float4* target_pts = nullptr;
-    int32_t* target_cells = nullptr;
+    char* cone_memory = nullptr;     // the arrays of `cones`
+    char* target_memory = nullptr;   // the target grid
     double* mass_partial = nullptr;
     double* mass_out = nullptr;
     // periodic mass check: every mass_every steps (0: off) sim_step enqueues the FP64 mass of
@@ -173,12 +174,12 @@ template <class T>
 hipError_t dalloc(T** p, size_t count) {
     *p = nullptr;
     if (count == 0) return hipSuccess;
-    return hipMalloc((void**)p, count * sizeof(T));
+    return device_malloc((void**)p, count * sizeof(T));
 }
 
 template <class T>
 void dfree(T*& p) {
-    if (p) (void)hipFree(p);
+    device_free(p);
     p = nullptr;
 }
 
@@ -205,9 +206,11 @@ static void adjoint_work_release(AdjointRun::Work& w) {
     w = AdjointRun::Work();
 }
 
+// (the handle's stream may still be at work on what is given back: wait for it)
 void adjoint_release(sim_handle* h) {
     AdjointRun* a = h->adj;
     if (!a) return;
+    (void)hipStreamSynchronize(h->stream);
     dfree(a->ckpt_field);
     dfree(a->ckpt_pos);
     dfree(a->ckpt_dir);
@@ -225,6 +228,7 @@ void adjoint_release(sim_handle* h) {
 
 void graph_release(sim_handle* h) {
     GraphBuffers& g = h->graph;
+    if (g.row_start) (void)hipStreamSynchronize(h->stream);
     dfree(g.owner);
     dfree(g.target_owner);
     dfree(g.key);
@@ -236,23 +240,25 @@ void graph_release(sim_handle* h) {
     dfree(g.edges);
     dfree(g.level);
     dfree(g.grew);
-    if (g.scratch) (void)hipFree(g.scratch);
+    dfree(g.scratch);
     g = GraphBuffers{};
 }
 
 void release(sim_handle* h) {
+    // what is given back may be reused at once: wait for all work on the device, the caller's
+    // on a view of a field among it
+    int current = h->device;
+    (void)hipGetDevice(&current);
+    if (current != h->device) (void)hipSetDevice(h->device);
+    (void)hipDeviceSynchronize();
+    if (current != h->device) (void)hipSetDevice(current);
     adjoint_release(h);
     graph_release(h);
     for (int s = 0; s < SIM_MAX_SPECIES; ++s) {
         for (int b = 0; b < 2; ++b) dfree(h->field[s][b]);
     }
-    dfree(h->cones.pos);
-    dfree(h->cones.dir);
-    dfree(h->cones.status);
-    dfree(h->cones.target);
-    dfree(h->cones.event_step);
-    dfree(h->target_pts);
-    dfree(h->target_cells);
+    dfree(h->cone_memory);
+    dfree(h->target_memory);
     dfree(h->mass_partial);
     dfree(h->mass_out);
     dfree(h->mass_flag);
@@ -267,6 +273,7 @@ void release(sim_handle* h) {
     drop_events(h);
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
     h->stream = nullptr;
+    device_memory_user(-1);
 }
 
 // Fold a finished periodic mass check into the sticky flag (never waits).
@@ -274,6 +281,24 @@ void poll_mass_check(sim_handle* h) {
     if (!h->mass_pending || hipEventQuery(h->mass_event) != hipSuccess) return;
     h->mass_pending = false;
     if (*(volatile int32_t*)h->mass_flag_host) h->nonfinite = true;
+}
+
+// The mass check's buffers, made by its first use.
+sim_status mass_prepare(sim_handle* h) {
+    if (h->mass_event) return SIM_OK;
+    dfree(h->mass_partial);   // (left by an earlier attempt)
+    dfree(h->mass_out);
+    dfree(h->mass_flag);
+    if (h->mass_flag_host) (void)hipHostFree(h->mass_flag_host);
+    h->mass_flag_host = nullptr;
+    HIP_TRY(h, dalloc(&h->mass_partial, kMassPartials));
+    HIP_TRY(h, dalloc(&h->mass_out, SIM_MAX_SPECIES));
+    HIP_TRY(h, dalloc(&h->mass_flag, 1));
+    HIP_TRY(h, hipMemsetAsync(h->mass_flag, 0, sizeof(int32_t), h->stream));
+    HIP_TRY(h, hipHostMalloc((void**)&h->mass_flag_host, sizeof(int32_t)));
+    *h->mass_flag_host = 0;
+    HIP_TRY(h, hipEventCreateWithFlags(&h->mass_event, hipEventDisableTiming));
+    return SIM_OK;
 }
 
 sim_status nonfinite_fail(sim_handle* h) {
@@ -328,15 +353,12 @@ sim_status build_targets(sim_handle* h, const sim_params* p) {
         std::memcpy(&v.w, &idx, sizeof idx);
         pts[fill[key[t]]++] = v;
     }
-    HIP_TRY(h, dalloc(&h->target_pts, pts.size()));
-    HIP_TRY(h, dalloc(&h->target_cells, start.size()));
-    HIP_TRY(h, hipMemcpy(h->target_pts, pts.data(), pts.size() * sizeof(float4),
-                         hipMemcpyHostToDevice));
-    HIP_TRY(h, hipMemcpy(h->target_cells, start.data(), start.size() * sizeof(int32_t),
-                         hipMemcpyHostToDevice));
+    UploadBlock up;
+    const size_t at_pts = up.add(pts), at_start = up.add(start);
+    HIP_TRY(h, up.upload(&h->target_memory));
     TargetGrid& tg = h->rules.targets;
-    tg.pts = h->target_pts;
-    tg.cell_start = h->target_cells;
+    tg.pts = (const float4*)(h->target_memory + at_pts);
+    tg.cell_start = (const int32_t*)(h->target_memory + at_start);
     tg.gx = g[0];
     tg.gy = g[1];
     tg.gz = g[2];
@@ -509,6 +531,7 @@ sim_status create_impl(const sim_params* p, void* hip_stream, int force_cpl, sim
     if (st != SIM_OK) return st;
     sim_handle* h = new (std::nothrow) sim_handle();
     if (!h) return fail(nullptr, SIM_ENOMEM, "host allocation failed");
+    device_memory_user(1);
     auto bail = [&](sim_status s) {
         g_create_error = h->err;
         release(h);
@@ -583,21 +606,20 @@ sim_status create_impl(const sim_params* p, void* hip_stream, int force_cpl, sim
     // cones (caller order)
     const size_t M = (size_t)p->n_cones;
     h->cones.n = p->n_cones;
-    if ((e = dalloc(&h->cones.pos, M * p->dim)) != hipSuccess ||
-        (e = dalloc(&h->cones.dir, M * dir_width(p->dim))) != hipSuccess ||
-        (e = dalloc(&h->cones.status, M)) != hipSuccess ||
-        (e = dalloc(&h->cones.target, M)) != hipSuccess ||
-        (e = dalloc(&h->cones.event_step, M)) != hipSuccess)
-        return bail(device_fail(h, e, "cone allocation"));
-    if (M > 0) {
-        std::vector<int32_t> minus1(M, -1);
-        if ((e = hipMemcpy(h->cones.pos, p->cone_pos, M * p->dim * 4, hipMemcpyHostToDevice)) ||
-            (e = hipMemcpy(h->cones.dir, p->cone_dir, M * dir_width(p->dim) * 4,
-                           hipMemcpyHostToDevice)) ||
-            (e = hipMemset(h->cones.status, 0, M * 4)) ||
-            (e = hipMemcpy(h->cones.target, minus1.data(), M * 4, hipMemcpyHostToDevice)) ||
-            (e = hipMemcpy(h->cones.event_step, minus1.data(), M * 4, hipMemcpyHostToDevice)))
-            return bail(device_fail(h, e, "cone upload"));
+    {
+        const std::vector<int32_t> active(M, kActive), minus1(M, -1);
+        UploadBlock up;
+        const size_t at_pos = up.add(p->cone_pos, M * p->dim),
+                     at_dir = up.add(p->cone_dir, M * dir_width(p->dim)),
+                     at_status = up.add(active), at_target = up.add(minus1),
+                     at_event = up.add(minus1);
+        e = up.upload(&h->cone_memory);
+        if (e != hipSuccess) return bail(device_fail(h, e, "cone upload"));
+        h->cones.pos = (float*)(h->cone_memory + at_pos);
+        h->cones.dir = (float*)(h->cone_memory + at_dir);
+        h->cones.status = (int32_t*)(h->cone_memory + at_status);
+        h->cones.target = (int32_t*)(h->cone_memory + at_target);
+        h->cones.event_step = (int32_t*)(h->cone_memory + at_event);
     }
     if (p->dim == 3)
         e = field3d_prepare(h->field3d, h->nx, h->ny, h->nz, h->n_species, h->src_merged_cell,
@@ -613,15 +635,6 @@ sim_status create_impl(const sim_params* p, void* hip_stream, int force_cpl, sim
     st = build_targets(h, p);
     if (st != SIM_OK) return bail(st);
     h->target_host.assign(p->target_pos, p->target_pos + (size_t)p->n_targets * p->dim);
-    if ((e = dalloc(&h->mass_partial, kMassPartials)) != hipSuccess ||
-        (e = dalloc(&h->mass_out, SIM_MAX_SPECIES)) != hipSuccess ||
-        (e = dalloc(&h->mass_flag, 1)) != hipSuccess ||
-        (e = hipMemset(h->mass_flag, 0, sizeof(int32_t))) != hipSuccess ||
-        (e = hipHostMalloc((void**)&h->mass_flag_host, sizeof(int32_t))) != hipSuccess ||
-        (e = hipEventCreateWithFlags(&h->mass_event, hipEventDisableTiming)) != hipSuccess)
-        return bail(device_fail(h, e, "mass buffers"));
-    *h->mass_flag_host = 0;
-
     // temporal blocking plan
     h->block_steps = p->block_steps == 0 ? kDefaultBlockSteps : p->block_steps;
     if (h->block_steps > 1) {
@@ -696,10 +709,10 @@ void batch_release(sim_batch* b) {
         delete h;
     }
     b->sims.clear();
-    if (b->table) (void)hipFree(b->table);
-    if (b->extra) (void)hipFree(b->extra);
-    if (b->base) (void)hipFree(b->base);
-    if (b->launch) (void)hipFree(b->launch);
+    device_free(b->table);
+    device_free(b->extra);
+    device_free(b->base);
+    device_free(b->launch);
     b->table = nullptr;
     b->extra = nullptr;
     b->base = nullptr;
@@ -839,6 +852,10 @@ sim_status sim_set_mass_check(sim_handle* h, int64_t every) {
     if (!h) return fail(nullptr, SIM_EINVAL, "handle is NULL");
     if (h->poisoned) return fail(h, SIM_ESTATE, "handle poisoned by an earlier device error");
     if (every < 0) return fail(h, SIM_EINVAL, "every < 0");
+    if (every > 0) {
+        const sim_status st = mass_prepare(h);
+        if (st != SIM_OK) return st;
+    }
     h->mass_every = every;
     return SIM_OK;
 }
@@ -915,6 +932,8 @@ sim_status sim_read_state(sim_handle* h, sim_item what, int32_t index, void* dst
             return SIM_OK;
         }
         case SIM_MASS: {
+            st = mass_prepare(h);
+            if (st != SIM_OK) return st;
             for (int s = 0; s < h->n_species; ++s)
                 HIP_TRY(h, launch_mass(h->field[s][h->cur[s]], h->n_cells, h->mass_partial,
                                        kMassPartials, h->mass_out + s, h->stream));
@@ -1094,7 +1113,7 @@ static size_t adjoint_tape_limit(const sim_handle* h) {
     if (h->adj_tape_limit > 0) return (size_t)h->adj_tape_limit;
     size_t free_bytes = 0, total_bytes = 0;
     if (hipMemGetInfo(&free_bytes, &total_bytes) != hipSuccess) free_bytes = 0;
-    return free_bytes / 2;
+    return (free_bytes + device_idle_bytes(h->device)) / 2;
 }
 
 // Ends the recording of a run's field states (both paths) when it goes out of scope.
@@ -1263,7 +1282,10 @@ sim_status sim_adjoint_backward(sim_handle* h, double* dL_dq, double* dL_dD, dou
     int32_t*& q_start = w.q_start;
     int2*& q_entry = w.q_entry;
     // on a device error the workspace is dropped (the next call allocates it again)
-    auto free_all = [&]() { adjoint_work_release(w); };
+    auto free_all = [&]() {
+        (void)hipStreamSynchronize(h->stream);
+        adjoint_work_release(w);
+    };
     std::vector<int32_t> q_start_h;
     std::vector<int2> q_entry_h;
     for (int s = 0; s < ns; ++s)
@@ -1444,7 +1466,7 @@ sim_status sim_connectivity(sim_handle* h, int32_t n_neurons, const int32_t* con
         (e = dalloc(&g.degree, N)) != hipSuccess || (e = dalloc(&g.row_start, N + 1)) != hipSuccess ||
         (e = dalloc(&g.edges, Ms)) != hipSuccess || (e = dalloc(&g.level, N)) != hipSuccess ||
         (e = dalloc(&g.grew, 1)) != hipSuccess ||
-        (e = hipMalloc((void**)&g.scratch, sort_pairs_scratch_bytes(M))) != hipSuccess) {
+        (e = device_malloc((void**)&g.scratch, sort_pairs_scratch_bytes(M))) != hipSuccess) {
         graph_release(h);
         if (e == hipErrorOutOfMemory) return fail(h, SIM_ENOMEM, "connectivity buffers");
         return device_fail(h, e, "connectivity allocation");
@@ -1549,11 +1571,11 @@ sim_status sim_batch_create(const sim_params* const* params, int32_t n, void* hi
         return b->sims[x.x]->plan.height * b->sims[x.x]->n_cones >
                b->sims[y.x]->plan.height * b->sims[y.x]->n_cones;
     });
-    if ((e = hipMalloc(&b->table, entry * n)) != hipSuccess ||
-        (e = hipMalloc(&b->base, sizeof(int2) * items.size())) != hipSuccess ||
-        (e = hipMalloc(&b->extra, sizeof(int4) * 2 * kBatchPartLists * b->extra_cap)) !=
+    if ((e = device_malloc(&b->table, entry * n)) != hipSuccess ||
+        (e = device_malloc((void**)&b->base, sizeof(int2) * items.size())) != hipSuccess ||
+        (e = device_malloc((void**)&b->extra, sizeof(int4) * 2 * kBatchPartLists * b->extra_cap)) !=
             hipSuccess ||
-        (e = hipMalloc(&b->launch, sizeof(LaunchState))) != hipSuccess)
+        (e = device_malloc((void**)&b->launch, sizeof(LaunchState))) != hipSuccess)
         return bail(batch_fail(b, SIM_ENOMEM, "batch allocation failed"));
     for (int i = 0; i < n; ++i)
         if ((e = hipMemcpy((char*)b->table + entry * i, b->sims[i]->tiled.args, entry,
