@@ -38,6 +38,10 @@ hipError_t launch_cones2d(const ConeRules& rules, const float* f0, const float* 
                           ConeArrays cones, uint32_t step, hipStream_t stream,
                           const ConeTape* tape = nullptr, size_t t = 0);
 
+// Fill the near map of a target grid (its dimensions and targets set) of `words` words.
+hipError_t launch_near_map(int dim, const TargetGrid& tg, uint32_t* near, size_t words,
+                           int n_targets, hipStream_t stream);
+
 // 2D field step of every species in one launch, sources included (kernels_field2d.hip).
 // Field2DStep holds the per-box source lists (row, column in the box, amount) built once by
 // field2d_prepare from the merged, pre-scaled sources of each species.

@@ -60,6 +60,39 @@ __global__ __launch_bounds__(256) void k_cones2d(ConeRules r, const float* __res
     }
 }
 
+// Marks in the near map every cell that a tip in range of target blockIdx.x * 256 + threadIdx.x
+// can lie in: the cells that meet the contact ball, widened by kCellSlack cells for the FP32
+// rounding of a tip's cell and distance.
+template <int dim>
+__global__ __launch_bounds__(256) void k_near_map(TargetGrid tg, uint32_t* near, int n_targets) {
+    const int t = blockIdx.x * 256 + threadIdx.x;
+    if (t >= n_targets) return;
+    const float4 p = tg.pts[t];
+    const double inv = tg.near_inv, reach = (double)tg.r * inv + kCellSlack;
+    const double c[3] = {p.x * inv, p.y * inv, dim == 3 ? p.z * inv : 0.0};
+    const int n[3] = {tg.near_nx, tg.near_ny, tg.near_nz};
+    int lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};
+    for (int a = 0; a < dim; ++a) {
+        lo[a] = (int)fmin(fmax(floor(c[a] - reach - kCellSlack), 0.0), (double)n[a]);
+        hi[a] = (int)fmin(fmax(floor(c[a] + reach + kCellSlack), -1.0), (double)(n[a] - 1));
+    }
+    for (int z = lo[2]; z <= hi[2]; ++z)
+        for (int y = lo[1]; y <= hi[1]; ++y)
+            for (int x = lo[0]; x <= hi[0]; ++x) {
+                const int cell[3] = {x, y, z};
+                double d2 = 0.0;   // squared distance of the widened cell from the target
+                for (int a = 0; a < dim; ++a) {
+                    const double d = fmax(fmax(cell[a] - kCellSlack - c[a],
+                                               c[a] - (cell[a] + 1 + kCellSlack)), 0.0);
+                    d2 += d * d;
+                }
+                if (d2 > reach * reach) continue;
+                uint32_t bit;
+                const size_t word = near_word<dim>(tg, x, y, z, bit);
+                atomicOr(&near[word], bit);
+            }
+}
+
 // FP64 sum: each block reduces a grid-stride slice (wavefront shuffles, then LDS), the
 // second pass adds the block partials in a fixed order, so the result is deterministic.
 constexpr int kMassThreads = 256;
@@ -134,6 +167,18 @@ hipError_t launch_cones2d(const ConeRules& rules, const float* f0, const float* 
     else
         hipLaunchKernelGGL(k_cones2d<false>, grid, dim3(256), 0, stream, rules, f0, f1, cones,
                            step, ConeTape{}, (size_t)0);
+    return hipGetLastError();
+}
+
+hipError_t launch_near_map(int dim, const TargetGrid& tg, uint32_t* near, size_t words,
+                           int n_targets, hipStream_t stream) {
+    hipError_t e = hipMemsetAsync(near, 0, words * sizeof(uint32_t), stream);
+    if (e != hipSuccess || n_targets == 0) return e;
+    const dim3 grid((n_targets + 255) / 256);
+    if (dim == 2)
+        hipLaunchKernelGGL(k_near_map<2>, grid, dim3(256), 0, stream, tg, near, n_targets);
+    else
+        hipLaunchKernelGGL(k_near_map<3>, grid, dim3(256), 0, stream, tg, near, n_targets);
     return hipGetLastError();
 }
 

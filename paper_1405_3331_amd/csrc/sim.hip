@@ -86,6 +86,7 @@ struct sim_handle {
     ConeArrays cones = {};
     char* cone_memory = nullptr;     // the arrays of `cones`
     char* target_memory = nullptr;   // the target grid
+    uint32_t* near_map = nullptr;    // and its near map
     double* mass_partial = nullptr;
     double* mass_out = nullptr;
     // periodic mass check: every mass_every steps (0: off) sim_step enqueues the FP64 mass of
@@ -259,6 +260,7 @@ void release(sim_handle* h) {
     }
     dfree(h->cone_memory);
     dfree(h->target_memory);
+    dfree(h->near_map);
     dfree(h->mass_partial);
     dfree(h->mass_out);
     dfree(h->mass_flag);
@@ -365,6 +367,21 @@ sim_status build_targets(sim_handle* h, const sim_params* p) {
     tg.inv_cell = (float)(1.0 / cell);
     tg.r = (float)p->contact_radius;
     tg.r2 = (float)(p->contact_radius * p->contact_radius);
+    // the near map: cells of the contact radius where that gives at most 2048 (3D: 256) per
+    // axis (512 KB, 2 MB), so that few tips share a cell with a target's reach
+    const double near = std::max(p->contact_radius, longest / (dim == 2 ? 2048 : 256));
+    int n[3] = {1, 1, 1};
+    for (int a = 0; a < dim; ++a) n[a] = std::max(1, (int)std::ceil(L[a] / near));
+    tg.near_nx = n[0];
+    tg.near_ny = n[1];
+    tg.near_nz = n[2];
+    tg.near_inv = (float)(1.0 / near);
+    tg.near_wx = (n[0] + (dim == 2 ? 7 : 3)) / (dim == 2 ? 8 : 4);
+    tg.near_wy = (n[1] + 3) / 4;
+    const size_t words = (size_t)tg.near_wx * tg.near_wy * (size_t)((n[2] + 1) / 2);
+    HIP_TRY(h, dalloc(&h->near_map, words));
+    tg.near = h->near_map;
+    HIP_TRY(h, launch_near_map(dim, tg, h->near_map, words, p->n_targets, h->stream));
     return SIM_OK;
 }
 
