@@ -23,11 +23,13 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kXcds = 8;   // workgroups are dealt to the accelerator dies round-robin
-// workgroups per die of the cone step: two per CU (32 CUs per die), each walking several
-// blocks of its die's stretch, so a die works on a region of the fields its L2 can hold
-// (256^3 workload: 62 us and 247 MB fetched per step, against 70 us and 336 MB with every
-// block resident at once; one per CU fetched least, 186 MB, but took 67 us)
-constexpr int kConeWgsPerXcd = 32 * 2;
+// The cone step's workgroups are single wavefronts (nothing is shared between them), eight per
+// CU (32 CUs per die), each walking several blocks of its die's stretch, so that a die works
+// on a region of the fields its L2 can hold.  Per 256^3 step (field 49 us): 108-110 us, against
+// 112 with four, 112 with twelve and 115 with sixteen per CU, and 112 with two workgroups of
+// four wavefronts per CU.
+constexpr int kConeThreads = 64;
+constexpr int kConeWgsPerXcd = 32 * 8;
 
 __device__ __forceinline__ uint32_t spread3(uint32_t v) {   // 10 bits -> every third bit
     v &= 0x3ffu;
@@ -196,14 +198,14 @@ __device__ __forceinline__ void step_ordered_cone(const ConeRules& r, const floa
     c.event_step[id] = (int32_t)(step + 1);
 }
 
-// One step of every ordered cone.  The blocks of kThreads cones are split into one
+// One step of every ordered cone.  The blocks of kConeThreads cones are split into one
 // contiguous stretch of the order per accelerator die (workgroups are dealt to the dies
 // round-robin), so a die works on one compact region of the fields; when there are more
 // blocks than workgroups, the workgroups of a die walk its stretch block after block.  (Loading
 // both species' footprints before combining either was measured slower: the wider register
 // live range costs more than the extra loads in flight gain.)
 template <int NS>
-__global__ __launch_bounds__(kThreads) void k_cones3d_ordered(ConeRules r,
+__global__ __launch_bounds__(kConeThreads) void k_cones3d_ordered(ConeRules r,
                                                               const float* __restrict__ f0,
                                                               const float* __restrict__ f1,
                                                               float4* tip, float4* dir, int n,
@@ -212,7 +214,7 @@ __global__ __launch_bounds__(kThreads) void k_cones3d_ordered(ConeRules r,
     const int xcd = blockIdx.x % kXcds;
     const int wgs_per_xcd = gridDim.x / kXcds;
     for (int b = blockIdx.x / kXcds; b < per_xcd; b += wgs_per_xcd) {
-        const int t = (xcd * per_xcd + b) * kThreads + threadIdx.x;
+        const int t = (xcd * per_xcd + b) * kConeThreads + threadIdx.x;
         if (t < n) step_ordered_cone<NS>(r, f0, f1, tip, dir, c, step, t);
     }
 }
@@ -316,15 +318,15 @@ hipError_t launch_cones3d_ordered(const ConeRules& r, const float* f0, const flo
                                   ConeOrder3D& o, ConeArrays cones, uint32_t step,
                                   hipStream_t stream) {
     if (o.n == 0) return hipSuccess;
-    const int blocks = blocks_for(o.n);
+    const int blocks = (o.n + kConeThreads - 1) / kConeThreads;
     const int per_xcd = (blocks + kXcds - 1) / kXcds;
     const int wgs_per_xcd = std::min(per_xcd, kConeWgsPerXcd);
     if (r.n_species > 1)
-        hipLaunchKernelGGL(k_cones3d_ordered<2>, dim3(wgs_per_xcd * kXcds), dim3(kThreads), 0,
+        hipLaunchKernelGGL(k_cones3d_ordered<2>, dim3(wgs_per_xcd * kXcds), dim3(kConeThreads), 0,
                            stream, r, f0, f1, o.tip[o.cur], o.dir[o.cur], o.n, per_xcd, cones,
                            step);
     else
-        hipLaunchKernelGGL(k_cones3d_ordered<1>, dim3(wgs_per_xcd * kXcds), dim3(kThreads), 0,
+        hipLaunchKernelGGL(k_cones3d_ordered<1>, dim3(wgs_per_xcd * kXcds), dim3(kConeThreads), 0,
                            stream, r, f0, f1, o.tip[o.cur], o.dir[o.cur], o.n, per_xcd, cones,
                            step);
     return hipGetLastError();
