@@ -97,7 +97,7 @@ struct Field3DArgs {
     float* out[2];
     StencilCoef coef[2];
     int nx, ny, nz, n_species;
-    int tx, ty, tz, per_xcd;
+    int tx, ty, tz, planes, per_xcd;
     const int32_t* src_start;
     const int32_t* src_plane;
     const int32_t* src_thread;

@@ -2,9 +2,8 @@
 //
 // 7-point stencil with first-order decay, zero-flux walls (a missing neighbour is the cell
 // itself), then the point sources of the step (c' += q / dx^3).  One launch covers every
-// species.  A workgroup owns a box of kTX x kTY columns and kTZ consecutive planes of one
-// species (64 x 8 x 16, the fastest of the shapes measured) and marches up the planes; each
-// thread keeps the planes below, at and above its cell in registers and reads the four
+// species.  A workgroup owns a box of kTX x kTY columns and 8 or 4
+// consecutive planes of one species and marches up the planes; each thread keeps the planes below, at and above its cell in registers and reads the four
 // in-plane neighbours from lines the workgroup has just brought into L1/L2, so a cell is
 // fetched from HBM about once per step: 8 algorithmic bytes per species-cell-update.
 // Planes are taken kUnroll at a time with every load of the group issued before the
@@ -30,17 +29,29 @@ namespace cuesim {
 
 namespace {
 
-constexpr int kTX = 64, kTY = 8, kTZ = 16, kUnroll = 4;
+constexpr int kTX = 64, kTY = 8, kUnroll = 4;
 constexpr int kThreads = kTX * kTY;
 constexpr int kXcds = 8;
+// Planes per box: kDeep, or kUnroll where that leaves CUs without a box.  More planes per box
+// read fewer planes twice, fewer put more boxes in flight and keep a die's boxes closer
+// together.  Per step, 4 / 8 / 16 planes: 97 x 64 x 51 4.0 / 4.3 / 5.6 us; 128^3 6.4 / 6.1 /
+// 6.3; 160^3 10.1 / 8.5 / 9.0; 200^3 17.3 / 13.5 / 15.6; 256^3 25.5 / 21.5 / 23.5, with two
+// species 50.4 / 41.4 / 43.4.
+constexpr int kDeep = 8;
+constexpr int kDeepBoxes = 256;   // CUs
 
 struct Boxes {
-    int tx, ty, tz;   // boxes per axis
+    int tx, ty, tz, planes;   // boxes per axis, planes per box
     int per_species() const { return tx * ty * tz; }
 };
 
-Boxes boxes_for(int nx, int ny, int nz) {
-    return Boxes{(nx + kTX - 1) / kTX, (ny + kTY - 1) / kTY, (nz + kTZ - 1) / kTZ};
+Boxes boxes_for(int nx, int ny, int nz, int n_species) {
+    Boxes b{(nx + kTX - 1) / kTX, (ny + kTY - 1) / kTY, (nz + kDeep - 1) / kDeep, kDeep};
+    if (n_species * b.per_species() < kDeepBoxes) {
+        b.planes = kUnroll;
+        b.tz = (nz + kUnroll - 1) / kUnroll;
+    }
+    return b;
 }
 
 __device__ __forceinline__ float stencil(float c, float w, float e, float s, float n,
@@ -77,7 +88,7 @@ __global__ __launch_bounds__(kThreads) void k_field3d(Field3DArgs a) {
     const int dw = i > 0 ? -1 : 0, de = i < a.nx - 1 ? 1 : 0;
     const int ds = j > 0 ? -a.nx : 0, dn = j < a.ny - 1 ? a.nx : 0;
     const int nz = a.nz;
-    const int z0 = bz * kTZ, z1 = min(z0 + kTZ, nz);
+    const int z0 = bz * a.planes, z1 = min(z0 + a.planes, nz);
 
     float c = col[(size_t)z0 * plane];
     float below = col[(size_t)max(z0 - 1, 0) * plane];
@@ -124,7 +135,7 @@ __global__ __launch_bounds__(kThreads) void k_field3d(Field3DArgs a) {
 hipError_t field3d_prepare(Field3D& f, int nx, int ny, int nz, int n_species,
                            const std::vector<int32_t>* cells, const std::vector<float>* q) {
     field3d_release(f);
-    const Boxes b = boxes_for(nx, ny, nz);
+    const Boxes b = boxes_for(nx, ny, nz, n_species);
     const int n_boxes = n_species * b.per_species();
     // source entries per box, in plane order (cells are unique per species)
     std::vector<std::vector<std::pair<int64_t, float>>> per_box(n_boxes);
@@ -133,7 +144,7 @@ hipError_t field3d_prepare(Field3D& f, int nx, int ny, int nz, int n_species,
             const int64_t cell = cells[s][m];
             const int i = (int)(cell % nx), j = (int)((cell / nx) % ny),
                       l = (int)(cell / ((int64_t)nx * ny));
-            const int box = ((s * b.tz + l / kTZ) * b.ty + j / kTY) * b.tx + i / kTX;
+            const int box = ((s * b.tz + l / b.planes) * b.ty + j / kTY) * b.tx + i / kTX;
             const int tid = (j % kTY) * kTX + i % kTX;
             per_box[box].push_back({(int64_t)l * kThreads + tid, q[s][m]});
         }
@@ -177,7 +188,7 @@ void field3d_release(Field3D& f) {
 hipError_t launch_field3d(const Field3D& f, const float* const* in, float* const* out,
                           const StencilCoef* coef, hipStream_t stream, hipEvent_t start,
                           hipEvent_t stop) {
-    const Boxes b = boxes_for(f.nx, f.ny, f.nz);
+    const Boxes b = boxes_for(f.nx, f.ny, f.nz, f.n_species);
     Field3DArgs a = {};
     for (int s = 0; s < f.n_species; ++s) {
         a.in[s] = in[s];
@@ -191,6 +202,7 @@ hipError_t launch_field3d(const Field3D& f, const float* const* in, float* const
     a.tx = b.tx;
     a.ty = b.ty;
     a.tz = b.tz;
+    a.planes = b.planes;
     a.per_xcd = (f.n_boxes + kXcds - 1) / kXcds;
     a.src_start = f.src_start;
     a.src_plane = f.src_plane;
