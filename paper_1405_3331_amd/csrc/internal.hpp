@@ -32,12 +32,6 @@ struct ConeArrays {
     int n;
 };
 
-// One 2D step's cones in the caller's order (kernels_plain.hip); with `tape` they are recorded
-// as its step t.
-hipError_t launch_cones2d(const ConeRules& rules, const float* f0, const float* f1,
-                          ConeArrays cones, uint32_t step, hipStream_t stream,
-                          const ConeTape* tape = nullptr, size_t t = 0);
-
 // Fill the near map of a target grid (its dimensions and targets set) of `words` words.
 hipError_t launch_near_map(int dim, const TargetGrid& tg, uint32_t* near, size_t words,
                            int n_targets, hipStream_t stream);
@@ -70,6 +64,8 @@ struct Field2DStepArgs {
     const int32_t* src_col;
     const float* src_q;
 };
+Field2DStepArgs field2d_args(const Field2DStep& f, const float* const* in, float* const* out,
+                             const StencilCoef* coef);
 hipError_t field2d_prepare(Field2DStep& f, int nx, int ny, int n_species,
                            const std::vector<int32_t>* cells, const std::vector<float>* q);
 void field2d_release(Field2DStep& f);
@@ -80,6 +76,16 @@ hipError_t launch_field2d_pair(const Field2DStep& f, const float* const* in, flo
 hipError_t launch_field2d_rows(const Field2DStep& f, const float* const* in, float* const* out,
                                const StencilCoef* coef, hipStream_t stream,
                                hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
+
+// One 2D step's cones in the caller's order (kernels_plain.hip); with `tape` they are recorded
+// as its step t.
+hipError_t launch_cones2d(const ConeRules& rules, const float* f0, const float* f1,
+                          ConeArrays cones, uint32_t step, hipStream_t stream,
+                          const ConeTape* tape = nullptr, size_t t = 0);
+// The same (unrecorded), and in the same launch the next field step, from the fields that the
+// cones read.
+hipError_t launch_step2d(const ConeRules& rules, ConeArrays cones, uint32_t step,
+                         const Field2DStepArgs& next, hipStream_t stream);
 
 // 3D field step of every species in one launch, sources included (kernels_field3d.hip).
 // Field3D holds the per-box source lists (plane, thread, amount) built once by
@@ -103,6 +109,8 @@ struct Field3DArgs {
     const int32_t* src_thread;
     const float* src_q;
 };
+Field3DArgs field3d_args(const Field3D& f, const float* const* in, float* const* out,
+                         const StencilCoef* coef);
 hipError_t field3d_prepare(Field3D& f, int nx, int ny, int nz, int n_species,
                            const std::vector<int32_t>* cells, const std::vector<float>* q);
 void field3d_release(Field3D& f);
@@ -113,8 +121,7 @@ hipError_t launch_field3d(const Field3D& f, const float* const* in, float* const
 
 // Active 3D cones in spatial order (kernels_cones3d.hip): per cone the tip (x, y, z, id)
 // and heading (hx, hy, hz, 0), ping-pong halves, with the radix-sort keys, slots and scratch.
-// Keys are Morton codes of the tip cell coarsened by `shift` bits per axis; stopped cones
-// carry id -1 and the key `inactive`, past every active one.
+// Stopped cones carry id -1 and the key `inactive`, past every active one.
 struct ConeOrder3D {
     char* memory = nullptr;   // every array below
     float4* tip[2] = {};
@@ -124,9 +131,7 @@ struct ConeOrder3D {
     int32_t* scratch = nullptr;   // counting-sort histograms (sort_pairs)
     int cur = 0;
     int n = 0;
-    int shift = 3;   // 8-cell Morton cells: 118.2 us per 256^3 step, against 119.1 with 4-cell
-                     // and 118.3 / 119.5 with 16- / 32-cell ones (fewer sort passes, same order
-                     // at the scale of a workgroup's block)
+    int x_bits = 0;   // of the key
     uint32_t inactive = 0;
     int end_bit = 1;
 };
@@ -141,6 +146,9 @@ hipError_t order3d_refresh(ConeOrder3D& o, const ConeRules& r, hipStream_t strea
 hipError_t launch_cones3d_ordered(const ConeRules& r, const float* f0, const float* f1,
                                   ConeOrder3D& o, ConeArrays cones, uint32_t step,
                                   hipStream_t stream);
+// The same, and in the same launch the next field step, from the fields that the cones read.
+hipError_t launch_step3d(const ConeRules& r, ConeOrder3D& o, ConeArrays cones, uint32_t step,
+                         const Field3DArgs& next, hipStream_t stream);
 // Tips and headings of the still-active ordered cones back into the caller-order arrays.
 hipError_t order3d_end(const ConeOrder3D& o, ConeArrays cones, hipStream_t stream);
 

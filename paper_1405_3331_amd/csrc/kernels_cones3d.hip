@@ -3,9 +3,8 @@
 // A 3D cone samples 32 cells per species around its tip (Sec. 3.5 gradient steering; trilinear).  In
 // the caller's order neighbouring threads sit anywhere in the volume, so a wavefront touches
 // a separate set of cache lines per cone and uses a few bytes of each.  Here the active
-// cones are kept sorted by the Morton code of their tip cell (coarsened by `shift` bits per
-// axis): a workgroup then covers one compact region, its gathers share lines in L1/L2, and
-// the cone state itself streams as two aligned float4 per cone (tip x, y, z, id; heading).
+// cones are kept sorted by where their tips are (order_key): a workgroup then covers one
+// compact region, its gathers share lines in L1/L2, and the cone state itself streams as two aligned float4 per cone (tip x, y, z, id; heading).
 // Cones move at most step_len per step, so the order is refreshed every few steps (the
 // project's stable counting sort of the keys, kernels_sort.hip, then a gather of the state),
 // not every step.
@@ -14,6 +13,7 @@
 // and event step straight into the caller-order arrays and marks the ordered copy id = -1;
 // a refresh moves them behind the active ones.  The caller-order tips and headings of the
 // active cones are brought up to date only when the state is read (order3d_end).
+#include "field_step.hpp"
 #include "internal.hpp"
 #include "memory.hpp"
 
@@ -22,7 +22,6 @@ namespace cuesim {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kXcds = 8;   // workgroups are dealt to the accelerator dies round-robin
 // The cone step's workgroups are single wavefronts (nothing is shared between them), eight per
 // CU (32 CUs per die), each walking several blocks of its die's stretch, so that a die works
 // on a region of the fields its L2 can hold.  Per 256^3 step (field 49 us): 108-110 us, against
@@ -31,12 +30,19 @@ constexpr int kXcds = 8;   // workgroups are dealt to the accelerator dies round
 constexpr int kConeThreads = 64;
 constexpr int kConeWgsPerXcd = 32 * 8;
 
-__device__ __forceinline__ uint32_t spread3(uint32_t v) {   // 10 bits -> every third bit
-    v &= 0x3ffu;
-    v = (v | (v << 16)) & 0x030000ffu;
-    v = (v | (v << 8)) & 0x0300f00fu;
-    v = (v | (v << 4)) & 0x030c30c3u;
-    v = (v | (v << 2)) & 0x09249249u;
+// Order key of a tip: the Morton code of its (y, z) block of 8 x 8 cells, then its 32-cell run
+// along x, a line of the field: a wavefront's cones share lines.  Step against 8-cell Morton
+// cubes: 128^3, two species, 262,144 cones 28.5 us (30.4), 160^3 39.1 (41.3), 256^3 95.3 (95.8);
+// with 64-cell runs 30.3, 40.2 and 95.3.  Bits past kXBits, kYZBits are dropped: the order of
+// a larger volume is only less compact.
+constexpr int kRunShift = 5, kBlockShift = 3, kXBits = 6, kYZBits = 12;
+
+__device__ __forceinline__ uint32_t spread2(uint32_t v) {   // kYZBits bits -> every second bit
+    v &= (1u << kYZBits) - 1u;
+    v = (v | (v << 8)) & 0x00ff00ffu;
+    v = (v | (v << 4)) & 0x0f0f0f0fu;
+    v = (v | (v << 2)) & 0x33333333u;
+    v = (v | (v << 1)) & 0x55555555u;
     return v;
 }
 
@@ -46,34 +52,35 @@ __device__ __forceinline__ uint32_t cell_coord(float p, float inv_dx, int n) {
 }
 
 __device__ __forceinline__ uint32_t order_key(const ConeRules& r, float x, float y, float z,
-                                              int shift) {
-    return spread3(cell_coord(x, r.inv_dx, r.nx) >> shift) |
-           (spread3(cell_coord(y, r.inv_dx, r.ny) >> shift) << 1) |
-           (spread3(cell_coord(z, r.inv_dx, r.nz) >> shift) << 2);
+                                              int x_bits) {
+    const uint32_t run = cell_coord(x, r.inv_dx, r.nx) >> kRunShift;
+    return (spread2(cell_coord(y, r.inv_dx, r.ny) >> kBlockShift) |
+            spread2(cell_coord(z, r.inv_dx, r.nz) >> kBlockShift) << 1) << x_bits |
+           (run & ((1u << x_bits) - 1u));
 }
 
 // Caller order -> (tip, heading) with keys; inactive cones get id -1 and the key past every
 // active one.
 __global__ __launch_bounds__(kThreads) void k_pack3d(ConeRules r, ConeArrays c, float4* tip,
                                                      float4* dir, uint32_t* key, int32_t* slot,
-                                                     int shift, uint32_t inactive) {
+                                                     int x_bits, uint32_t inactive) {
     const int i = blockIdx.x * kThreads + threadIdx.x;
     if (i >= c.n) return;
     const float x = c.pos[3 * i], y = c.pos[3 * i + 1], z = c.pos[3 * i + 2];
     const bool active = c.status[i] == kActive;
     tip[i] = make_float4(x, y, z, __int_as_float(active ? i : -1));
     dir[i] = make_float4(c.dir[3 * i], c.dir[3 * i + 1], c.dir[3 * i + 2], 0.0f);
-    key[i] = active ? order_key(r, x, y, z, shift) : inactive;
+    key[i] = active ? order_key(r, x, y, z, x_bits) : inactive;
     slot[i] = i;
 }
 
 __global__ __launch_bounds__(kThreads) void k_keys3d(ConeRules r, const float4* __restrict__ tip,
                                                      int n, uint32_t* key, int32_t* slot,
-                                                     int shift, uint32_t inactive) {
+                                                     int x_bits, uint32_t inactive) {
     const int t = blockIdx.x * kThreads + threadIdx.x;
     if (t >= n) return;
     const float4 p = tip[t];
-    key[t] = __float_as_int(p.w) >= 0 ? order_key(r, p.x, p.y, p.z, shift) : inactive;
+    key[t] = __float_as_int(p.w) >= 0 ? order_key(r, p.x, p.y, p.z, x_bits) : inactive;
     slot[t] = t;
 }
 
@@ -219,6 +226,37 @@ __global__ __launch_bounds__(kConeThreads) void k_cones3d_ordered(ConeRules r,
     }
 }
 
+// Cones per workgroup of k_step3d: one wavefront of its eight where the cones are few, so that
+// every CU gets some (a wavefront's loads go to 64 lines each, and through one CU one after the
+// other), or where the fields are past the L2s, which more cones at once would thrash; every
+// wavefront where neither holds.  Step with one / eight: 128^3, one species, 32,768 cones 10.9 /
+// 13.5 us; 160^3, 65,536 14.6 / 15.3; 128^3, two species, 262,144 34.9 / 30.3; 256^3 98.5 / 108.
+constexpr int kSpreadCones = 4 * 256 * 64;
+constexpr int64_t kL2Bytes = (int64_t)kXcds * 4 << 20;
+
+// One step's cones and the next field step, which only read the fields as they are between
+// them, so one launch and one round of latency serve both.  A die's first cone_wgs workgroups
+// take its stretch of the cones, per_wg at a time, and start while all its CUs are free; its
+// boxes follow (spread evenly among them they took 120 us of a 256^3 step instead of 107).  At
+// 80 registers, for the boxes' occupancy.  Against two launches per step: 97 x 64 x 51, 3000
+// cones 12.7 -> 9.7 us; 128^3, one species, 32,768 cones 16.3 -> 10.6; 200^3, 4096 22.5 -> 16.7;
+// 256^3, two species, 262,144 100.5 -> 95.3, where the cones are bound by the lines they miss in
+// L2 (250 to 330 MB, beside the field's 270 MB).
+template <int NS>
+__global__ __launch_bounds__(kBoxThreads3D, 6) void k_step3d(ConeRules r, float4* tip,
+                                                             float4* dir, int n, int cone_wgs,
+                                                             int per_wg, ConeArrays c,
+                                                             uint32_t step, Field3DArgs a) {
+    const int xcd = blockIdx.x % kXcds, k = blockIdx.x / kXcds;
+    if (k < cone_wgs) {
+        const int t = (xcd * cone_wgs + k) * per_wg + threadIdx.x;
+        if ((int)threadIdx.x < per_wg && t < n) step_ordered_cone<NS>(r, a.in[0], a.in[NS - 1], tip, dir, c, step, t);
+        return;
+    }
+    const int box = xcd * a.per_xcd + (k - cone_wgs);
+    if (box < a.n_species * a.tx * a.ty * a.tz) field3d_box(a, box, threadIdx.x);
+}
+
 __global__ __launch_bounds__(kThreads) void k_unpack3d(const float4* __restrict__ tip,
                                                        const float4* __restrict__ dir, int n,
                                                        ConeArrays c) {
@@ -238,9 +276,9 @@ __global__ __launch_bounds__(kThreads) void k_unpack3d(const float4* __restrict_
 
 int blocks_for(int n) { return (n + kThreads - 1) / kThreads; }
 
-int axis_bits(int n, int shift) {
-    int bits = 1;
-    while (bits < 10 && ((n - 1) >> shift) >= (1 << bits)) ++bits;
+int axis_bits(int n, int shift, int most) {
+    int bits = 0;
+    while (bits < most && ((n - 1) >> shift) >= (1 << bits)) ++bits;
     return bits;
 }
 
@@ -265,10 +303,11 @@ hipError_t sort_and_gather(ConeOrder3D& o, hipStream_t stream) {
 hipError_t order3d_allocate(ConeOrder3D& o, int n, int nx, int ny, int nz) {
     o = ConeOrder3D{};
     o.n = n;
-    const int bits = std::max(axis_bits(nx, o.shift), std::max(axis_bits(ny, o.shift),
-                                                               axis_bits(nz, o.shift)));
-    o.inactive = 1u << (3 * bits);
-    o.end_bit = 3 * bits + 1;
+    o.x_bits = axis_bits(nx, kRunShift, kXBits);
+    const int bits = o.x_bits + 2 * std::max(axis_bits(ny, kBlockShift, kYZBits),
+                                             axis_bits(nz, kBlockShift, kYZBits));
+    o.inactive = 1u << bits;
+    o.end_bit = bits + 1;
     if (n == 0) return hipSuccess;
     auto padded = [](size_t bytes) { return (bytes + 255) / 256 * 256; };
     const size_t state = padded((size_t)n * sizeof(float4)), word = padded((size_t)n * 4);
@@ -299,7 +338,7 @@ hipError_t order3d_begin(ConeOrder3D& o, const ConeRules& r, ConeArrays cones,
                          hipStream_t stream) {
     if (o.n == 0) return hipSuccess;
     hipLaunchKernelGGL(k_pack3d, dim3(blocks_for(o.n)), dim3(kThreads), 0, stream, r, cones,
-                       o.tip[o.cur], o.dir[o.cur], o.key[0], o.slot[0], o.shift, o.inactive);
+                       o.tip[o.cur], o.dir[o.cur], o.key[0], o.slot[0], o.x_bits, o.inactive);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return sort_and_gather(o, stream);
@@ -308,7 +347,7 @@ hipError_t order3d_begin(ConeOrder3D& o, const ConeRules& r, ConeArrays cones,
 hipError_t order3d_refresh(ConeOrder3D& o, const ConeRules& r, hipStream_t stream) {
     if (o.n == 0) return hipSuccess;
     hipLaunchKernelGGL(k_keys3d, dim3(blocks_for(o.n)), dim3(kThreads), 0, stream, r,
-                       o.tip[o.cur], o.n, o.key[0], o.slot[0], o.shift, o.inactive);
+                       o.tip[o.cur], o.n, o.key[0], o.slot[0], o.x_bits, o.inactive);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return sort_and_gather(o, stream);
@@ -329,6 +368,22 @@ hipError_t launch_cones3d_ordered(const ConeRules& r, const float* f0, const flo
         hipLaunchKernelGGL(k_cones3d_ordered<1>, dim3(wgs_per_xcd * kXcds), dim3(kConeThreads), 0,
                            stream, r, f0, f1, o.tip[o.cur], o.dir[o.cur], o.n, per_xcd, cones,
                            step);
+    return hipGetLastError();
+}
+
+hipError_t launch_step3d(const ConeRules& r, ConeOrder3D& o, ConeArrays cones, uint32_t step,
+                         const Field3DArgs& next, hipStream_t stream) {
+    const int64_t bytes = (int64_t)next.n_species * next.nx * next.ny * next.nz * 4;
+    const bool dense = o.n > kSpreadCones && bytes <= kL2Bytes;
+    const int per_wg = dense ? kBoxThreads3D : 64;
+    const int cone_wgs = (o.n + per_wg * kXcds - 1) / (per_wg * kXcds);
+    const dim3 grid((next.per_xcd + cone_wgs) * kXcds);
+    if (r.n_species > 1)
+        hipLaunchKernelGGL(k_step3d<2>, grid, dim3(kBoxThreads3D), 0, stream, r, o.tip[o.cur],
+                           o.dir[o.cur], o.n, cone_wgs, per_wg, cones, step, next);
+    else
+        hipLaunchKernelGGL(k_step3d<1>, grid, dim3(kBoxThreads3D), 0, stream, r, o.tip[o.cur],
+                           o.dir[o.cur], o.n, cone_wgs, per_wg, cones, step, next);
     return hipGetLastError();
 }
 

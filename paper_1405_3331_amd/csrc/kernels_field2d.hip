@@ -21,6 +21,7 @@
 #include <algorithm>
 #include <vector>
 
+#include "field_step.hpp"
 #include "internal.hpp"
 #include "memory.hpp"
 
@@ -28,15 +29,12 @@ namespace cuesim {
 
 namespace {
 
-// 256 columns x 8 rows, all 8 rows' loads at once (measured best)
-constexpr int kRX = 256, kRY = 8, kRUnroll = 8;
 // two steps per launch: boxes of 256 x kPY cells held with a two-cell
 // ring (kPW x kPH) for the first step and a one-cell ring (kQW x kQH) for the second; 4 rows
 // measured best (2, 6 and 8 rows slower)
 constexpr int kPY = 4;
 constexpr int kPW = kRX + 4, kPH = kPY + 4;
 constexpr int kQW = kRX + 2, kQH = kPY + 2;
-constexpr int kXcds = 8;
 
 struct Tiles2D {
     int tx, ty;
@@ -44,12 +42,6 @@ struct Tiles2D {
 
 Tiles2D tiles_for(int nx, int ny, int rows = kRY) {
     return Tiles2D{(nx + kRX - 1) / kRX, (ny + rows - 1) / rows};
-}
-
-__device__ __forceinline__ float stencil2d(float c, float w, float e, float s, float n,
-                                           const StencilCoef& k) {
-    const float lap = fmaf(-4.0f, c, (w + e) + (s + n));
-    return fmaf(k.r, lap, fmaf(-k.kdt, c, c));
 }
 
 // Logical box of this workgroup (die-contiguous stretches of the box order).
@@ -60,51 +52,7 @@ __device__ __forceinline__ int box_of(int per_xcd) {
 __global__ __launch_bounds__(kRX) void k_field2d_rows(Field2DStepArgs a) {
     const int box = box_of(a.per_xcd);
     if (box >= a.n_species * a.tx * a.ty) return;
-    const int bx = box % a.tx, by = (box / a.tx) % a.ty, s = box / (a.tx * a.ty);
-    int e = a.src_start[box];
-    const int e_end = a.src_start[box + 1];
-    const int tid = threadIdx.x;
-    const int i = bx * kRX + tid;
-    if (i >= a.nx) return;   // no barriers below
-    const StencilCoef k = a.coef[s];
-    const int nx = a.nx, ny = a.ny;
-    const float* col = a.in[s] + i;
-    float* dst = a.out[s] + i;
-    const int dw = i > 0 ? -1 : 0, de = i < nx - 1 ? 1 : 0;
-    const int j0 = by * kRY, j1 = min(j0 + kRY, ny);
-    float c = col[(size_t)j0 * nx];
-    float below = col[(size_t)max(j0 - 1, 0) * nx];
-    int j = j0;
-    auto finish = [&](float v, int row) {
-        while (e < e_end && a.src_row[e] == row) {
-            if (a.src_col[e] == tid) v += a.src_q[e];
-            ++e;
-        }
-        dst[(size_t)row * nx] = v;
-    };
-    for (; j + kRUnroll <= j1; j += kRUnroll) {
-        float up[kRUnroll], w[kRUnroll], ea[kRUnroll];
-#pragma unroll
-        for (int u = 0; u < kRUnroll; ++u) {
-            const float* p = col + (size_t)(j + u) * nx;
-            up[u] = col[(size_t)min(j + u + 1, ny - 1) * nx];
-            w[u] = p[dw];
-            ea[u] = p[de];
-        }
-#pragma unroll
-        for (int u = 0; u < kRUnroll; ++u) {
-            finish(stencil2d(c, w[u], ea[u], below, up[u], k), j + u);
-            below = c;
-            c = up[u];
-        }
-    }
-    for (; j < j1; ++j) {
-        const float* p = col + (size_t)j * nx;
-        const float above = col[(size_t)min(j + 1, ny - 1) * nx];
-        finish(stencil2d(c, p[dw], p[de], below, above, k), j);
-        below = c;
-        c = above;
-    }
+    field2d_box(a, box, threadIdx.x);
 }
 
 // Two forward steps of one species per box; the stencil and the separate source add are
@@ -294,9 +242,8 @@ void field2d_release(Field2DStep& f) {
     f = Field2DStep{};
 }
 
-hipError_t launch_field2d_rows(const Field2DStep& f, const float* const* in, float* const* out,
-                               const StencilCoef* coef, hipStream_t stream, hipEvent_t start,
-                               hipEvent_t stop) {
+Field2DStepArgs field2d_args(const Field2DStep& f, const float* const* in, float* const* out,
+                             const StencilCoef* coef) {
     const Tiles2D t = tiles_for(f.nx, f.ny);
     Field2DStepArgs a = {};
     for (int s = 0; s < f.n_species; ++s) {
@@ -314,6 +261,13 @@ hipError_t launch_field2d_rows(const Field2DStep& f, const float* const* in, flo
     a.src_row = f.src_row;
     a.src_col = f.src_col;
     a.src_q = f.src_q;
+    return a;
+}
+
+hipError_t launch_field2d_rows(const Field2DStep& f, const float* const* in, float* const* out,
+                               const StencilCoef* coef, hipStream_t stream, hipEvent_t start,
+                               hipEvent_t stop) {
+    Field2DStepArgs a = field2d_args(f, in, out, coef);
     void* args[] = {&a};
     if (!start && !stop)   // a plain launch (also what a graph capture records)
         return hipLaunchKernel((const void*)k_field2d_rows, dim3(a.per_xcd * kXcds), dim3(kRX),

@@ -6,8 +6,8 @@
 // consecutive planes of one species and marches up the planes; each thread keeps the planes below, at and above its cell in registers and reads the four
 // in-plane neighbours from lines the workgroup has just brought into L1/L2, so a cell is
 // fetched from HBM about once per step: 8 algorithmic bytes per species-cell-update.
-// Planes are taken kUnroll at a time with every load of the group issued before the
-// arithmetic, which keeps kUnroll times more reads in flight than a plane-by-plane march.
+// Planes are taken kUnroll3D at a time with every load of the group issued before the
+// arithmetic, which keeps kUnroll3D times more reads in flight than a plane-by-plane march.
 // Walls are handled by clamping the neighbour index, which reads the cell itself exactly
 // where the ghost value is the cell's own.
 //
@@ -22,6 +22,7 @@
 #include <algorithm>
 #include <vector>
 
+#include "field_step.hpp"
 #include "internal.hpp"
 #include "memory.hpp"
 
@@ -29,10 +30,7 @@ namespace cuesim {
 
 namespace {
 
-constexpr int kTX = 64, kTY = 8, kUnroll = 4;
-constexpr int kThreads = kTX * kTY;
-constexpr int kXcds = 8;
-// Planes per box: kDeep, or kUnroll where that leaves CUs without a box.  More planes per box
+// Planes per box: kDeep, or kUnroll3D where that leaves CUs without a box.  More planes per box
 // read fewer planes twice, fewer put more boxes in flight and keep a die's boxes closer
 // together.  Per step, 4 / 8 / 16 planes: 97 x 64 x 51 4.0 / 4.3 / 5.6 us; 128^3 6.4 / 6.1 /
 // 6.3; 160^3 10.1 / 8.5 / 9.0; 200^3 17.3 / 13.5 / 15.6; 256^3 25.5 / 21.5 / 23.5, with two
@@ -48,86 +46,17 @@ struct Boxes {
 Boxes boxes_for(int nx, int ny, int nz, int n_species) {
     Boxes b{(nx + kTX - 1) / kTX, (ny + kTY - 1) / kTY, (nz + kDeep - 1) / kDeep, kDeep};
     if (n_species * b.per_species() < kDeepBoxes) {
-        b.planes = kUnroll;
-        b.tz = (nz + kUnroll - 1) / kUnroll;
+        b.planes = kUnroll3D;
+        b.tz = (nz + kUnroll3D - 1) / kUnroll3D;
     }
     return b;
 }
 
-__device__ __forceinline__ float stencil(float c, float w, float e, float s, float n,
-                                         float below, float above, const StencilCoef& k) {
-    const float lap = fmaf(-6.0f, c, ((w + e) + (s + n)) + (below + above));
-    return fmaf(k.r, lap, fmaf(-k.kdt, c, c));
-}
-
-__global__ __launch_bounds__(kThreads) void k_field3d(Field3DArgs a) {
+__global__ __launch_bounds__(kBoxThreads3D) void k_field3d(Field3DArgs a) {
     const int n_boxes = a.n_species * a.tx * a.ty * a.tz;
     const int box = (blockIdx.x % kXcds) * a.per_xcd + blockIdx.x / kXcds;
     if (box >= n_boxes) return;
-    int rest = box;
-    const int bx = rest % a.tx;
-    rest /= a.tx;
-    const int by = rest % a.ty;
-    rest /= a.ty;
-    const int bz = rest % a.tz;
-    const int s = rest / a.tz;
-    // this workgroup's slice of the source list
-    int e = a.src_start[box];
-    const int e_end = a.src_start[box + 1];
-
-    const int tid = threadIdx.x;
-    const int i = bx * kTX + tid % kTX;
-    const int j = by * kTY + tid / kTX;
-    if (i >= a.nx || j >= a.ny) {
-        return;   // no barriers below: idle threads may leave
-    }
-    const StencilCoef k = a.coef[s];
-    const size_t plane = (size_t)a.nx * a.ny;
-    const float* col = a.in[s] + (size_t)j * a.nx + i;
-    float* dst = a.out[s] + (size_t)j * a.nx + i;
-    const int dw = i > 0 ? -1 : 0, de = i < a.nx - 1 ? 1 : 0;
-    const int ds = j > 0 ? -a.nx : 0, dn = j < a.ny - 1 ? a.nx : 0;
-    const int nz = a.nz;
-    const int z0 = bz * a.planes, z1 = min(z0 + a.planes, nz);
-
-    float c = col[(size_t)z0 * plane];
-    float below = col[(size_t)max(z0 - 1, 0) * plane];
-    int l = z0;
-    for (; l + kUnroll <= z1; l += kUnroll) {
-        float up[kUnroll], w[kUnroll], ea[kUnroll], so[kUnroll], no[kUnroll];
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const float* p = col + (size_t)(l + u) * plane;
-            up[u] = col[(size_t)min(l + u + 1, nz - 1) * plane];
-            w[u] = p[dw];
-            ea[u] = p[de];
-            so[u] = p[ds];
-            no[u] = p[dn];
-        }
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            float v = stencil(c, w[u], ea[u], so[u], no[u], below, up[u], k);
-            while (e < e_end && a.src_plane[e] == l + u) {
-                if (a.src_thread[e] == tid) v += a.src_q[e];
-                ++e;
-            }
-            dst[(size_t)(l + u) * plane] = v;
-            below = c;
-            c = up[u];
-        }
-    }
-    for (; l < z1; ++l) {
-        const float* p = col + (size_t)l * plane;
-        const float above = col[(size_t)min(l + 1, nz - 1) * plane];
-        float v = stencil(c, p[dw], p[de], p[ds], p[dn], below, above, k);
-        while (e < e_end && a.src_plane[e] == l) {
-            if (a.src_thread[e] == tid) v += a.src_q[e];
-            ++e;
-        }
-        dst[(size_t)l * plane] = v;
-        below = c;
-        c = above;
-    }
+    field3d_box(a, box, threadIdx.x);
 }
 
 }  // namespace
@@ -146,7 +75,7 @@ hipError_t field3d_prepare(Field3D& f, int nx, int ny, int nz, int n_species,
                       l = (int)(cell / ((int64_t)nx * ny));
             const int box = ((s * b.tz + l / b.planes) * b.ty + j / kTY) * b.tx + i / kTX;
             const int tid = (j % kTY) * kTX + i % kTX;
-            per_box[box].push_back({(int64_t)l * kThreads + tid, q[s][m]});
+            per_box[box].push_back({(int64_t)l * kBoxThreads3D + tid, q[s][m]});
         }
     std::vector<int32_t> start(n_boxes + 1, 0), plane_of, thread_of;
     std::vector<float> amount;
@@ -157,8 +86,8 @@ hipError_t field3d_prepare(Field3D& f, int nx, int ny, int nz, int n_species,
                       return x.first < y.first;
                   });
         for (auto& en : v) {
-            plane_of.push_back((int32_t)(en.first / kThreads));
-            thread_of.push_back((int32_t)(en.first % kThreads));
+            plane_of.push_back((int32_t)(en.first / kBoxThreads3D));
+            thread_of.push_back((int32_t)(en.first % kBoxThreads3D));
             amount.push_back(en.second);
         }
         start[box + 1] = (int32_t)plane_of.size();
@@ -185,9 +114,8 @@ void field3d_release(Field3D& f) {
     f = Field3D{};
 }
 
-hipError_t launch_field3d(const Field3D& f, const float* const* in, float* const* out,
-                          const StencilCoef* coef, hipStream_t stream, hipEvent_t start,
-                          hipEvent_t stop) {
+Field3DArgs field3d_args(const Field3D& f, const float* const* in, float* const* out,
+                         const StencilCoef* coef) {
     const Boxes b = boxes_for(f.nx, f.ny, f.nz, f.n_species);
     Field3DArgs a = {};
     for (int s = 0; s < f.n_species; ++s) {
@@ -208,8 +136,15 @@ hipError_t launch_field3d(const Field3D& f, const float* const* in, float* const
     a.src_plane = f.src_plane;
     a.src_thread = f.src_thread;
     a.src_q = f.src_q;
+    return a;
+}
+
+hipError_t launch_field3d(const Field3D& f, const float* const* in, float* const* out,
+                          const StencilCoef* coef, hipStream_t stream, hipEvent_t start,
+                          hipEvent_t stop) {
+    Field3DArgs a = field3d_args(f, in, out, coef);
     void* args[] = {&a};
-    return hipExtLaunchKernel((const void*)k_field3d, dim3(a.per_xcd * kXcds), dim3(kThreads),
+    return hipExtLaunchKernel((const void*)k_field3d, dim3(a.per_xcd * kXcds), dim3(kBoxThreads3D),
                               args, 0, stream, start, stop, 0);
 }
 

@@ -1,10 +1,12 @@
 // kernels_plain.hip -- the parts of an un-blocked 2D step besides the field update: the
-// cones, one thread each in the caller's order, against the just-updated fields; and the
-// FP64 mass of a field.
+// cones, one thread each in the caller's order, against the just-updated fields, alone or with
+// the next field step in their launch; the near map of a target grid; and the FP64 mass of a
+// field.
 #include <hip/hip_ext.h>
 
 #include <algorithm>
 
+#include "field_step.hpp"
 #include "internal.hpp"
 
 namespace cuesim {
@@ -17,12 +19,11 @@ struct Global2D {
     __device__ float operator()(int i, int j) const { return f[j * nx + i]; }
 };
 
-// RECORD: what the reverse needs of the step goes to step t of the run's cone tape.
+// Step of cone i.  RECORD: what the reverse needs of it goes to step t of the run's cone tape.
 template <bool RECORD>
-__global__ __launch_bounds__(256) void k_cones2d(ConeRules r, const float* __restrict__ f0,
-                                                 const float* __restrict__ f1, ConeArrays c,
-                                                 uint32_t step, ConeTape tape, size_t t) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void step_cone(const ConeRules& r, const float* __restrict__ f0,
+                                          const float* __restrict__ f1, const ConeArrays& c,
+                                          uint32_t step, const ConeTape& tape, size_t t, int i) {
     if (i >= c.n || c.status[i] != kActive) return;
     float x = c.pos[2 * i], y = c.pos[2 * i + 1], th = c.dir[i];
     float gx, gy, conc = 0.0f;
@@ -58,6 +59,28 @@ __global__ __launch_bounds__(256) void k_cones2d(ConeRules r, const float* __res
         c.target[i] = ev.target;
         c.event_step[i] = (int32_t)(step + 1);
     }
+}
+
+template <bool RECORD>
+__global__ __launch_bounds__(256) void k_cones2d(ConeRules r, const float* __restrict__ f0,
+                                                 const float* __restrict__ f1, ConeArrays c,
+                                                 uint32_t step, ConeTape tape, size_t t) {
+    step_cone<RECORD>(r, f0, f1, c, step, tape, t, blockIdx.x * 256 + threadIdx.x);
+}
+
+// One step's cones (the first cone_wgs workgroups, a multiple of the dies) and the next field
+// step: both only read the fields as they are between them, so one launch and one round of
+// latency serve both (1203 x 901, one species, 10.3 -> 6.0 us per step).
+__global__ __launch_bounds__(256) void k_step2d(ConeRules r, ConeArrays c, uint32_t step,
+                                                int cone_wgs, Field2DStepArgs a) {
+    const int wg = blockIdx.x;
+    if (wg < cone_wgs) {
+        step_cone<false>(r, a.in[0], a.in[r.n_species > 1 ? 1 : 0], c, step, ConeTape{}, 0,
+                         wg * 256 + threadIdx.x);
+        return;
+    }
+    const int box = (wg % kXcds) * a.per_xcd + (wg - cone_wgs) / kXcds;
+    if (box < a.n_species * a.tx * a.ty) field2d_box(a, box, threadIdx.x);
 }
 
 // Marks in the near map every cell that a tip in range of target blockIdx.x * 256 + threadIdx.x
@@ -167,6 +190,14 @@ hipError_t launch_cones2d(const ConeRules& rules, const float* f0, const float* 
     else
         hipLaunchKernelGGL(k_cones2d<false>, grid, dim3(256), 0, stream, rules, f0, f1, cones,
                            step, ConeTape{}, (size_t)0);
+    return hipGetLastError();
+}
+
+hipError_t launch_step2d(const ConeRules& rules, ConeArrays cones, uint32_t step,
+                         const Field2DStepArgs& next, hipStream_t stream) {
+    const int cone_wgs = (cones.n + 256 * kXcds - 1) / (256 * kXcds) * kXcds;
+    hipLaunchKernelGGL(k_step2d, dim3(cone_wgs + next.per_xcd * kXcds), dim3(256), 0, stream,
+                       rules, cones, step, cone_wgs, next);
     return hipGetLastError();
 }
 

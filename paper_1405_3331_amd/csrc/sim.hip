@@ -474,9 +474,8 @@ sim_status collect_timing(sim_handle* h) {
     return SIM_OK;
 }
 
-// One un-blocked step: one launch for the stencil and sources of every species, then the
-// cones (2D: in caller order; 3D: in spatial order).
-sim_status plain_step(sim_handle* h) {
+// The field step of every species in one launch, sources included.
+sim_status plain_field(sim_handle* h) {
     hipEvent_t t0, t1;
     sim_status st = timing_events(h, &t0, &t1);
     if (st != SIM_OK) return st;
@@ -497,27 +496,59 @@ sim_status plain_step(sim_handle* h) {
                                                        h->n_species + s) * h->n_cells,
                                       h->field[s][h->cur[s]], (size_t)h->n_cells * 4,
                                       hipMemcpyDeviceToDevice, h->stream));
-    const float* f0 = h->field[0][h->cur[0]];
-    const float* f1 = h->n_species > 1 ? h->field[1][h->cur[1]] : f0;
-    if (h->dim == 2) {
-        HIP_TRY(h, launch_cones2d(h->rules, f0, f1, h->cones, (uint32_t)h->step, h->stream,
-                                  h->record ? &h->cone_record : nullptr,
-                                  (size_t)(h->step - h->record_n0)));
-    } else if (h->order3d.n > 0) {
-        if (!h->cones_ordered) {
-            HIP_TRY(h, order3d_begin(h->order3d, h->rules, h->cones, h->stream));
-            h->cones_ordered = true;
-            h->since_refresh = 0;
-        } else if (h->since_refresh >= kOrderRefresh) {
-            HIP_TRY(h, order3d_refresh(h->order3d, h->rules, h->stream));
-            h->since_refresh = 0;
+    return SIM_OK;
+}
+
+// n un-blocked steps: each is the field step, then the cones against the new fields (2D: in
+// caller order; 3D: in spatial order).  The cones change no field, so a step's cones and the
+// next step's field share a launch; with launches timed (each then times a field step alone) or
+// a run recorded, every part has its own.
+sim_status plain_steps(sim_handle* h, int64_t n) {
+    const bool shared = !h->timing && !h->record && h->cones.n > 0;
+    for (int64_t i = 0; i < n; ++i) {
+        if (i == 0 || !shared) {
+            const sim_status st = plain_field(h);
+            if (st != SIM_OK) return st;
         }
-        HIP_TRY(h, launch_cones3d_ordered(h->rules, f0, f1, h->order3d, h->cones,
-                                          (uint32_t)h->step, h->stream));
-        h->since_refresh += 1;
+        const float* f[SIM_MAX_SPECIES] = {};
+        float* out[SIM_MAX_SPECIES] = {};
+        for (int s = 0; s < h->n_species; ++s) {
+            f[s] = h->field[s][h->cur[s]];
+            out[s] = h->field[s][h->cur[s] ^ 1];
+        }
+        const float* f1 = h->n_species > 1 ? f[1] : f[0];
+        const bool with_field = shared && i + 1 < n;
+        const uint32_t step = (uint32_t)h->step;
+        if (h->dim == 2) {
+            if (with_field)
+                HIP_TRY(h, launch_step2d(h->rules, h->cones, step,
+                                         field2d_args(h->field2d, f, out, h->coef), h->stream));
+            else
+                HIP_TRY(h, launch_cones2d(h->rules, f[0], f1, h->cones, step, h->stream,
+                                          h->record ? &h->cone_record : nullptr,
+                                          (size_t)(h->step - h->record_n0)));
+        } else if (h->order3d.n > 0) {
+            if (!h->cones_ordered) {
+                HIP_TRY(h, order3d_begin(h->order3d, h->rules, h->cones, h->stream));
+                h->cones_ordered = true;
+                h->since_refresh = 0;
+            } else if (h->since_refresh >= kOrderRefresh) {
+                HIP_TRY(h, order3d_refresh(h->order3d, h->rules, h->stream));
+                h->since_refresh = 0;
+            }
+            if (with_field)
+                HIP_TRY(h, launch_step3d(h->rules, h->order3d, h->cones, step,
+                                         field3d_args(h->field3d, f, out, h->coef), h->stream));
+            else
+                HIP_TRY(h, launch_cones3d_ordered(h->rules, f[0], f1, h->order3d, h->cones, step,
+                                                  h->stream));
+            h->since_refresh += 1;
+        }
+        if (with_field)
+            for (int s = 0; s < h->n_species; ++s) h->cur[s] ^= 1;
+        h->step += 1;
+        h->cones_synced = h->dim == 2;   // a 2D step works on the caller-order arrays
     }
-    h->step += 1;
-    h->cones_synced = h->dim == 2;   // a 2D step works on the caller-order arrays
     return SIM_OK;
 }
 
@@ -847,7 +878,7 @@ sim_status sim_step(sim_handle* h, int64_t n_steps) {
         if (h->block_steps > 1) {
             st = tiled_steps(h, n);
         } else {
-            for (int64_t i = 0; i < n && st == SIM_OK; ++i) st = plain_step(h);
+            st = plain_steps(h, n);
         }
         if (st != SIM_OK) return st;
         n_steps -= n;
