@@ -37,13 +37,19 @@ constexpr int kConeWgsPerXcd = 32 * 8;
 // a larger volume is only less compact.
 constexpr int kRunShift = 5, kBlockShift = 3, kXBits = 6, kYZBits = 12;
 
-__device__ __forceinline__ uint32_t spread2(uint32_t v) {   // kYZBits bits -> every second bit
+__host__ __device__ __forceinline__ uint32_t spread2(uint32_t v) {   // kYZBits bits -> every second bit
     v &= (1u << kYZBits) - 1u;
     v = (v | (v << 8)) & 0x00ff00ffu;
     v = (v | (v << 4)) & 0x0f0f0f0fu;
     v = (v | (v << 2)) & 0x33333333u;
     v = (v | (v << 1)) & 0x55555555u;
     return v;
+}
+
+__host__ __device__ __forceinline__ uint32_t cell_key(uint32_t x, uint32_t y, uint32_t z,
+                                                      int x_bits) {
+    return (spread2(y >> kBlockShift) | spread2(z >> kBlockShift) << 1) << x_bits |
+           ((x >> kRunShift) & ((1u << x_bits) - 1u));
 }
 
 // Cell of a coordinate, clamped to the grid (as a float first: a NaN tip maps to cell 0).
@@ -53,10 +59,8 @@ __device__ __forceinline__ uint32_t cell_coord(float p, float inv_dx, int n) {
 
 __device__ __forceinline__ uint32_t order_key(const ConeRules& r, float x, float y, float z,
                                               int x_bits) {
-    const uint32_t run = cell_coord(x, r.inv_dx, r.nx) >> kRunShift;
-    return (spread2(cell_coord(y, r.inv_dx, r.ny) >> kBlockShift) |
-            spread2(cell_coord(z, r.inv_dx, r.nz) >> kBlockShift) << 1) << x_bits |
-           (run & ((1u << x_bits) - 1u));
+    return cell_key(cell_coord(x, r.inv_dx, r.nx), cell_coord(y, r.inv_dx, r.ny),
+                    cell_coord(z, r.inv_dx, r.nz), x_bits);
 }
 
 // Caller order -> (tip, heading) with keys; inactive cones get id -1 and the key past every
@@ -304,10 +308,14 @@ hipError_t order3d_allocate(ConeOrder3D& o, int n, int nx, int ny, int nz) {
     o = ConeOrder3D{};
     o.n = n;
     o.x_bits = axis_bits(nx, kRunShift, kXBits);
-    const int bits = o.x_bits + 2 * std::max(axis_bits(ny, kBlockShift, kYZBits),
-                                             axis_bits(nz, kBlockShift, kYZBits));
-    o.inactive = 1u << bits;
-    o.end_bit = bits + 1;
+    // past the far corner's key, the largest where no bits are dropped
+    const bool whole = axis_bits(ny, kBlockShift, kYZBits + 1) <= kYZBits &&
+                       axis_bits(nz, kBlockShift, kYZBits + 1) <= kYZBits &&
+                       axis_bits(nx, kRunShift, kXBits + 1) <= kXBits;
+    o.inactive = whole ? cell_key(nx - 1, ny - 1, nz - 1, o.x_bits) + 1
+                       : 1u << (2 * kYZBits + o.x_bits);
+    for (o.end_bit = 1; o.inactive >> o.end_bit != 0; ++o.end_bit) {
+    }
     if (n == 0) return hipSuccess;
     auto padded = [](size_t bytes) { return (bytes + 255) / 256 * 256; };
     const size_t state = padded((size_t)n * sizeof(float4)), word = padded((size_t)n * 4);

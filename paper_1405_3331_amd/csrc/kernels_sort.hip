@@ -10,9 +10,11 @@
 // One pass over a digit:
 //   histogram  one workgroup per tile of kTile consecutive items counts the tile's digits
 //              in LDS and writes them digit-major: hist[digit * n_tiles + tile];
-//   scan       one workgroup turns hist into exclusive prefix sums, so entry
-//              (digit, tile) is where the tile's first item with that digit goes;
-//   scatter    every tile re-reads its items in order, kSortThreads at a time; an item's
+//   scan       one workgroup per digit turns its row of hist into inclusive sums (with at most
+//              kRowTiles tiles the scatter adds up the row itself, which takes less than a
+//              launch);
+//   scatter    every tile scans the digits' totals, which gives where its first item of each
+//              digit goes, and re-reads its items in order, kSortThreads at a time; an item's
 //              place among equal digits of the same round comes from wavefront ballots
 //              (the lanes whose digit matches, below it), the waves before it and the
 //              items of earlier rounds, so equal digits keep their input order.
@@ -30,7 +32,7 @@ constexpr int kDigitBits = 8;
 constexpr int kBins = 1 << kDigitBits;   // == kSortThreads: one bin per thread
 constexpr int kRounds = 8;
 constexpr int kTile = kSortThreads * kRounds;
-constexpr int kScanThreads = 1024;
+constexpr int kRowTiles = 32;   // a line of hist per digit
 static_assert(kBins == kSortThreads, "one digit bin per thread");
 
 int sort_tiles(int n) { return (n + kTile - 1) / kTile; }
@@ -54,73 +56,51 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_hist(const uint32_t* __re
     hist[tid * n_tiles + tile] = count[tid];
 }
 
-// Exclusive scan of a[0..n) in place by one workgroup, kScanPer entries per thread at a
-// time: each thread loads its run of kScanPer consecutive entries into registers (16-byte
-// loads when the run lies inside the array, else loads at clamped indices; either way all
-// issued before any is used), the run totals are scanned across each wavefront by lane
-// shuffles and across the wavefronts in LDS, and each thread writes its run back; longer
-// arrays take several such rounds, carrying the total.
-constexpr int kScanPer = 32;
-constexpr int kScanWaves = kScanThreads / 64;
-
-__global__ __launch_bounds__(kScanThreads) void k_sort_scan(int32_t* __restrict__ a, int n) {
-    __shared__ int32_t wave_total[kScanWaves];
+// Inclusive sum of v over a workgroup's threads up to and including this one; *total: over all.
+__device__ __forceinline__ int32_t block_scan(int32_t v, int32_t* total) {
+    __shared__ int32_t wave_total[kSortWaves];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int32_t y = __shfl_up(v, off, 64);
+        if (lane >= off) v += y;
+    }
+    if (lane == 63) wave_total[wave] = v;
+    __syncthreads();
+    *total = 0;
+#pragma unroll
+    for (int w = 0; w < kSortWaves; ++w) {
+        const int32_t t = wave_total[w];
+        v += w < wave ? t : 0;
+        *total += t;
+    }
+    __syncthreads();   // every thread has read wave_total
+    return v;
+}
+
+// Inclusive sums along each digit's row of hist, in place.  A workgroup per digit (one for the
+// whole table, its threads taking 32 entries each, needed 8 us for 32 tiles and 22 for 128, on
+// one CU and with every lane in a line of its own; rows side by side take 3).
+__global__ __launch_bounds__(kSortThreads) void k_sort_scan(int32_t* __restrict__ hist,
+                                                            int n_tiles) {
+    int32_t* row = hist + (size_t)blockIdx.x * n_tiles;
     int32_t carry = 0;
-    for (int base = 0; base < n; base += kScanThreads * kScanPer) {
-        const int lo = base + (int)threadIdx.x * kScanPer;
-        int32_t v[kScanPer];
-        if (lo + kScanPer <= n && (lo & 3) == 0) {
-#pragma unroll
-            for (int u = 0; u < kScanPer; u += 4) {
-                const int4 q = *(const int4*)(a + lo + u);
-                v[u] = q.x;
-                v[u + 1] = q.y;
-                v[u + 2] = q.z;
-                v[u + 3] = q.w;
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < kScanPer; ++u) v[u] = a[min(lo + u, n - 1)];
-#pragma unroll
-            for (int u = 0; u < kScanPer; ++u) v[u] = lo + u < n ? v[u] : 0;
-        }
-        int32_t sum = 0;
-#pragma unroll
-        for (int u = 0; u < kScanPer; ++u) sum += v[u];
-        int32_t incl = sum;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int32_t y = __shfl_up(incl, off, 64);
-            if (lane >= off) incl += y;
-        }
-        if (lane == 63) wave_total[wave] = incl;
-        __syncthreads();
-        int32_t at = carry + incl - sum, round_total = 0;
-#pragma unroll
-        for (int w = 0; w < kScanWaves; ++w) {
-            const int32_t t = wave_total[w];
-            at += w < wave ? t : 0;
-            round_total += t;
-        }
-#pragma unroll
-        for (int u = 0; u < kScanPer; ++u) {
-            if (lo + u < n) a[lo + u] = at;
-            at += v[u];
-        }
-        carry += round_total;
-        __syncthreads();   // every thread has read wave_total
+    for (int base = 0; base < n_tiles; base += kSortThreads) {
+        const int t = base + (int)threadIdx.x;
+        int32_t total;
+        const int32_t sum = block_scan(t < n_tiles ? row[t] : 0, &total);
+        if (t < n_tiles) row[t] = carry + sum;
+        carry += total;
     }
 }
 
 __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(
     const uint32_t* __restrict__ kin, const int32_t* __restrict__ vin,
     uint32_t* __restrict__ kout, int32_t* __restrict__ vout, int n, int shift, int n_tiles,
-    const int32_t* __restrict__ start) {
+    const int32_t* __restrict__ hist) {
     __shared__ int32_t next[kBins];                 // next output position per digit
     __shared__ int32_t wave_count[kSortWaves][kBins];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, tile = blockIdx.x;
-    next[tid] = start[tid * n_tiles + tile];
     const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     // every round's item first (indices clamped, so nothing branches between the loads)
     uint32_t keys[kRounds];
@@ -131,6 +111,21 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(
         keys[r] = kin[i];
         vals[r] = vin[i];
     }
+    // this thread's digit: items in the tiles before this one, and in all
+    const int32_t* row = hist + (size_t)tid * n_tiles;
+    int32_t before = 0, all = 0, unused;
+    if (n_tiles > kRowTiles) {
+        before = tile > 0 ? row[tile - 1] : 0;
+        all = row[n_tiles - 1];
+    } else {
+#pragma unroll 8
+        for (int t = 0; t < n_tiles; ++t) {
+            const int32_t c = row[t];
+            before += t < tile ? c : 0;
+            all += c;
+        }
+    }
+    next[tid] = block_scan(all, &unused) - all + before;
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
         const int i = tile * kTile + r * kSortThreads + tid;
@@ -172,6 +167,8 @@ size_t sort_pairs_scratch_bytes(int n) {
     return (size_t)kBins * (size_t)std::max(sort_tiles(n), 1) * sizeof(int32_t);
 }
 
+bool sort_in_alt(int key_bits) { return (key_bits + kDigitBits - 1) / kDigitBits % 2 == 1; }
+
 hipError_t sort_pairs(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t* vals_alt,
                       int n, int key_bits, int32_t* scratch, hipStream_t stream, bool* in_alt) {
     *in_alt = false;
@@ -183,15 +180,16 @@ hipError_t sort_pairs(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t
     for (int shift = 0; shift < key_bits; shift += kDigitBits) {
         hipLaunchKernelGGL(k_sort_hist, dim3(tiles), dim3(kSortThreads), 0, stream, k[cur], n,
                            shift, tiles, scratch);
-        hipLaunchKernelGGL(k_sort_scan, dim3(1), dim3(kScanThreads), 0, stream, scratch,
-                           kBins * tiles);
+        if (tiles > kRowTiles)
+            hipLaunchKernelGGL(k_sort_scan, dim3(kBins), dim3(kSortThreads), 0, stream, scratch,
+                               tiles);
         hipLaunchKernelGGL(k_sort_scatter, dim3(tiles), dim3(kSortThreads), 0, stream, k[cur],
                            v[cur], k[cur ^ 1], v[cur ^ 1], n, shift, tiles, scratch);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         cur ^= 1;
     }
-    *in_alt = cur == 1;
+    *in_alt = cur == 1;   // == sort_in_alt(key_bits)
     return hipSuccess;
 }
 
