@@ -244,6 +244,7 @@ struct GraphBuffers {
     int32_t* grew = nullptr;           // [1]
     int32_t* scratch = nullptr;        // counting-sort histograms (sort_pairs)
     int n_neurons = 0;
+    int n_edges = 0;                   // of the adjacency list last read back
 };
 hipError_t launch_adjacency(const GraphBuffers& g, const int32_t* status, const int32_t* target,
                             int n_cones, int n_neurons, hipStream_t stream);
@@ -255,13 +256,18 @@ sim_status connectivity_validate(sim_handle* h, int32_t n_neurons, const int32_t
                                  const int32_t* target_owner, const int32_t* row_start,
                                  const int32_t* edges, int64_t edge_capacity,
                                  const int64_t* n_edges);
-sim_status connectivity_build(sim_handle* h, const GraphBuffers& g, const int32_t* cone_owner,
+sim_status connectivity_build(sim_handle* h, GraphBuffers& g, const int32_t* cone_owner,
                               const int32_t* target_owner, int32_t* row_start, int32_t* edges,
                               int64_t edge_capacity, int64_t* n_edges);
 sim_status handle_fail(sim_handle* h, sim_status st, const char* msg);
 int handle_cones(const sim_handle* h);
 int handle_targets(const sim_handle* h);
 int handle_device(const sim_handle* h);   // the device the handle was created on
+// The neuron that owns each edge of the list (the sorted keys).
+const int32_t* adjacency_from(const GraphBuffers& g);
+// Levels of every vertex in one launch, for graphs that bfs_in_one_launch admits.
+bool bfs_in_one_launch(int n, int64_t n_edges);
+hipError_t launch_bfs(const GraphBuffers& g, int n_edges, int root, hipStream_t stream);
 hipError_t launch_bfs_init(int32_t* level, int n, int root, hipStream_t stream);
 hipError_t launch_bfs_level(const int32_t* row_start, const int32_t* edges, int n, int depth,
                             int32_t* level, int32_t* grew, hipStream_t stream);
@@ -272,6 +278,7 @@ hipError_t launch_bfs_level(const int32_t* row_start, const int32_t* edges, int 
 // ping-pong; *in_alt tells which pair holds the result.  scratch holds
 // sort_pairs_scratch_bytes(n) bytes.
 size_t sort_pairs_scratch_bytes(int n);
+bool sort_in_alt(int key_bits);   // whether such a sort ends in the alternate arrays
 hipError_t sort_pairs(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t* vals_alt,
                       int n, int key_bits, int32_t* scratch, hipStream_t stream, bool* in_alt);
 

@@ -822,7 +822,7 @@ sim_status connectivity_validate(sim_handle* h, int32_t n_neurons, const int32_t
     return SIM_OK;
 }
 
-sim_status connectivity_build(sim_handle* h, const GraphBuffers& g, const int32_t* cone_owner,
+sim_status connectivity_build(sim_handle* h, GraphBuffers& g, const int32_t* cone_owner,
                               const int32_t* target_owner, int32_t* row_start, int32_t* edges,
                               int64_t edge_capacity, int64_t* n_edges) {
     const int M = h->n_cones, T = h->n_targets;
@@ -841,6 +841,7 @@ sim_status connectivity_build(sim_handle* h, const GraphBuffers& g, const int32_
     HIP_TRY(h, hipStreamSynchronize(h->stream));
     const int64_t E = row_start[g.n_neurons];
     *n_edges = E;
+    g.n_edges = (int)E;   // at most the cones
     if (E > edge_capacity)
         return fail(h, SIM_ERANGE, "edge buffer holds %lld edges, %lld needed",
                     (long long)edge_capacity, (long long)E);
@@ -1532,8 +1533,10 @@ sim_status sim_bfs_levels(sim_handle* h, int32_t root, int32_t* level) {
     if (!level) return fail(h, SIM_EINVAL, "level is NULL");
     const int N = g.n_neurons;
     if (root < 0 || root >= N) return fail(h, SIM_EINVAL, "root %d out of range", root);
-    HIP_TRY(h, launch_bfs_init(g.level, N, root, h->stream));
-    for (int depth = 0; depth < N; ++depth) {
+    const bool one_launch = bfs_in_one_launch(N, g.n_edges);
+    HIP_TRY(h, one_launch ? launch_bfs(g, g.n_edges, root, h->stream)
+                          : launch_bfs_init(g.level, N, root, h->stream));
+    for (int depth = 0; depth < N && !one_launch; ++depth) {
         int32_t grew = 0;
         HIP_TRY(h, hipMemsetAsync(g.grew, 0, sizeof(int32_t), h->stream));
         HIP_TRY(h, launch_bfs_level(g.row_start, g.edges, N, depth, g.level, g.grew, h->stream));
