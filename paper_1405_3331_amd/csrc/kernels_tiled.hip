@@ -930,11 +930,40 @@ const void* batch_kernel_for(int n_species, int cpl) {
 
 namespace {
 
+// Cells a tile is loaded with on each side of its core at depth B: B sub-steps of shrinkage,
+// cone travel before the last sub-step and the gradient footprint (two cells); the small epsilon
+// covers FP32 rounding of travel.  Rounded up to the lane segment, which keeps every segment of
+// the tile and its core aligned: whole-segment vector loads and stores.
+int halo_for(int B, double step_cells, int cpl) {
+    const int travel = (int)std::ceil((B - 1) * step_cells + 1e-3);
+    return (B + travel + 2 + cpl - 1) / cpl * cpl;
+}
+
+// Microseconds per step of a plan, for the choice of the depth: a launch takes 7 us besides its
+// sub-steps, a sub-step 1.1 us and 3.2 ns per row of each two-column species plane in its CU
+// (a quarter more with one tile there, which hides latency poorly), and tiles past two per CU
+// wait for the others.  Per step, measured at depths 4 / 8 / 12 / 16 / 20 / 24: 128 x 128 3.0 /
+// 2.1 / 1.84 / 1.73 / 1.68 / 1.72 us; 777 x 389, two species 4.1 / 3.1 / 2.93 / 2.89 / 3.1 /
+// 3.2; 1000 x 600 3.2 / 2.3 / 2.01 / 1.97 / 1.94 / 2.0; 1500 x 1100 4.0 / 3.0 / 2.69 / 2.65 /
+// 2.70 / 2.9.  Depths past 16 gain nothing, and calls of few steps pay for their halo.
+constexpr int kDeepest = 16;
+
+double step_time(const TiledPlan& p) {
+    const int per_cu = ceil_div(p.n_tiles, 256);
+    const int fit = std::max(1, std::min(2, (int)(160 * 1024 / (p.lds_bytes + kStaticLds))));
+    const double rows = (double)p.height * std::min(per_cu, fit) * p.n_species * p.cpl / 2;
+    const double sub = (1.1 + 0.0032 * rows) * (fit < 2 ? 1.25 : 1.0);
+    return ceil_div(per_cu, fit) * (7.0 / p.block_steps + sub);
+}
+
 // Best tile plan by the cost model, restricted to row width 64 * only_cpl and loaded height
-// only_height when those are non-zero.
+// only_height when those are non-zero.  Depth: the deepest that fits up to block_steps, or with
+// block_steps 0 the fastest up to kDeepest.
 TiledPlan plan_search(int dim, int nx, int ny, int nz, int n_species, double step_cells,
                       int block_steps, int n_cones, int only_cpl, int only_height) {
-    TiledPlan best;
+    TiledPlan best, fastest;
+    const bool any_depth = block_steps == 0;
+    if (any_depth) block_steps = kDeepest;
     best.dim = dim;
     best.nx = nx;
     best.ny = ny;
@@ -942,18 +971,13 @@ TiledPlan plan_search(int dim, int nx, int ny, int nz, int n_species, double ste
     best.n_species = n_species;
     best.block_steps = 1;
     if (dim != 2 || block_steps < 2) return best;
+    fastest = best;
     double best_cost = 1e300;
     for (int B = block_steps; B >= 2; --B) {
-        // halo: B sub-steps of shrinkage + cone travel before the last sub-step + the
-        // gradient footprint (two cells); the small epsilon covers FP32 rounding of travel
-        const int travel = (int)std::ceil((B - 1) * step_cells + 1e-3);
-        const int H_min = B + travel + 2;
         const int move = (int)std::ceil(B * step_cells + 1e-3);
         for (int cpl : {2, 4}) {
             if (only_cpl && cpl != only_cpl) continue;
-            // a halo (and so a core) that is a multiple of the lane segment keeps every
-            // segment aligned: whole-segment vector loads and stores
-            const int H = (H_min + cpl - 1) / cpl * cpl;
+            const int H = halo_for(B, step_cells, cpl);
             const int W = 64 * cpl;
             const int TX = W - 2 * H;
             if (TX < 16 || TX <= move) continue;
@@ -996,9 +1020,13 @@ TiledPlan plan_search(int dim, int nx, int ny, int nz, int n_species, double ste
                 }
             }
         }
-        if (best.block_steps > 1) break;   // prefer the deepest blocking that fits
+        if (best.block_steps <= 1) continue;
+        if (!any_depth) return best;
+        if (fastest.block_steps <= 1 || step_time(best) < step_time(fastest)) fastest = best;
+        best.block_steps = 1;
+        best_cost = 1e300;
     }
-    return best;
+    return any_depth ? fastest : best;
 }
 
 }  // namespace
@@ -1011,6 +1039,59 @@ TiledPlan tiled_plan(int dim, int nx, int ny, int nz, int n_species, double step
         if (forced.block_steps > 1) return forced;
     }
     return plan_search(dim, nx, ny, nz, n_species, step_cells, block_steps, n_cones, 0, 0);
+}
+
+// A launch of a batch takes its items' time over the workgroups that run at once.  An item of
+// height h takes T = 6 us + h (0.125 + 0.0118 B) us where two share a CU (fit over batches of
+// heights 56 .. 144 at depths 8 .. 16, two-column rows of one species), and 7 + B (1.1 + 0.0032 h)
+// where it has a CU to itself.  Planned as if it had the chip to itself, every simulation took
+// the smallest cores, 16 rows of 44 loaded: 128 simulations of side 64 .. 512 took 33.6 us per
+// step, with 144 rows at depth 8 13.9 and at depth 12 13.3.
+int tiled_batch_shape(const sim_params* const* params, int n, int cpl,
+                      std::vector<int>& height) {
+    const int n_species = params[0]->n_species, fixed = params[0]->block_steps;
+    const int row_bytes = n_species * 64 * cpl * (int)sizeof(float);
+    const int tallest = (int)(80 * 1024 - kStaticLds) / row_bytes - kGuardRows;   // two per CU
+    const double planes = n_species * cpl / 2.0;
+    double best = 1e300;
+    int depth = 0;
+    height.assign(n, 0);
+    for (const int B : {16, 12, 8}) {
+        if (fixed != 0 && B != 16) break;
+        const int b = fixed != 0 ? fixed : B;
+        for (int cap = 32; cap <= tallest; cap += 8) {
+            std::vector<int> h(n, 0);
+            double work = 0.0, longest = 0.0, alone = 0.0;
+            int64_t items = 0;
+            bool fits = true;
+            for (int i = 0; i < n && fits; ++i) {
+                const sim_params& p = *params[i];
+                const double step_cells = p.step_len / p.dx;
+                const int H = halo_for(b, step_cells, cpl), TX = 64 * cpl - 2 * H;
+                const int least = std::max(16, (int)std::ceil(b * step_cells + 1e-3) + 1);
+                fits = TX >= least && 2 * H + least <= cap;
+                if (!fits) break;
+                const int tiles_y = ceil_div(p.ny, cap - 2 * H);
+                h[i] = 2 * H + std::max(least, ceil_div(p.ny, tiles_y));
+                const int tiles = ceil_div(p.nx, TX) * ceil_div(p.ny, h[i] - 2 * H);
+                const double t = 6.0 + h[i] * planes * (0.125 + 0.0118 * b);
+                items += tiles;
+                work += tiles * t;
+                longest = std::max(longest, t);
+                alone = std::max(alone, 7.0 + b * (1.1 + 0.0032 * h[i] * planes));
+            }
+            if (!fits) continue;
+            const double t = (items <= 256   ? alone
+                              : items <= 512 ? longest
+                                             : work / 512 + 0.5 * longest) / b;
+            if (t < best) {
+                best = t;
+                depth = b;
+                height = h;
+            }
+        }
+    }
+    return depth;
 }
 
 hipError_t tiled_allocate(const TiledPlan& plan, TiledState& st, int n_cones,

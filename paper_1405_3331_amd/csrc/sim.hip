@@ -684,8 +684,8 @@ sim_status create_impl(const sim_params* p, void* hip_stream, int force_cpl, sim
     if (st != SIM_OK) return bail(st);
     h->target_host.assign(p->target_pos, p->target_pos + (size_t)p->n_targets * p->dim);
     // temporal blocking plan
-    h->block_steps = p->block_steps == 0 ? kDefaultBlockSteps : p->block_steps;
-    if (h->block_steps > 1) {
+    h->block_steps = p->block_steps;   // 0: the planner's choice
+    if (h->block_steps != 1) {
         h->plan = tiled_plan(h->dim, h->nx, h->ny, h->nz, h->n_species, p->step_len / p->dx,
                              h->block_steps, h->n_cones,
                              force_cpl ? force_cpl : p->tile_cols_per_lane, p->tile_height);
@@ -694,6 +694,7 @@ sim_status create_impl(const sim_params* p, void* hip_stream, int force_cpl, sim
         if (h->plan.block_steps <= 1) {
             h->block_steps = 1;   // no tile shape fits: fall back to one step per launch
         } else {
+            h->block_steps = h->plan.block_steps;
             e = tiled_allocate(h->plan, h->tiled, h->n_cones, h->rules, p, h->field, h->cones,
                                h->stream);
             if (e != hipSuccess) return bail(device_fail(h, e, "tiled state allocation"));
@@ -1590,9 +1591,17 @@ sim_status sim_batch_create(const sim_params* const* params, int32_t n, void* hi
     b->n_species = params[0]->n_species;
     b->cpl = params[0]->tile_cols_per_lane ? params[0]->tile_cols_per_lane : 2;
     int64_t total_cones = 0;
+    std::vector<int> height;
+    int depth = 0;
+    for (int i = 0; i < n; ++i) {   // the shape is planned from checked parameters
+        const sim_status st = validate(params[i]);
+        if (st != SIM_OK) return bail(st);
+    }
+    depth = tiled_batch_shape(params, n, b->cpl, height);
     for (int i = 0; i < n; ++i) {
         sim_params q = *params[i];
-        if (q.block_steps == 0) q.block_steps = kDefaultBlockSteps;
+        if (q.block_steps == 0) q.block_steps = depth ? depth : kDefaultBlockSteps;
+        if (q.tile_height == 0 && depth) q.tile_height = height[i];
         sim_handle* h = nullptr;
         sim_status st = create_impl(&q, b->stream, b->cpl, &h);
         if (st != SIM_OK) return bail(st);

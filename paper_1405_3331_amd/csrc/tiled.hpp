@@ -9,7 +9,7 @@
 
 namespace cuesim {
 
-constexpr int kDefaultBlockSteps = 8;
+constexpr int kDefaultBlockSteps = 8;   // of a batch that no planned shape fits
 
 // Tile geometry chosen once per simulation.
 struct TiledPlan {
@@ -65,11 +65,15 @@ struct TiledState {
     int room = 0;                              // workgroups resident beside one per tile
 };
 
-// Choose B and the tile shape; block_steps = 1 in the result means no tiling fits.
+// Choose B (up to block_steps; 0: the planner's choice) and the tile shape; block_steps = 1 in the
+// result means no tiling fits.
 // force_cpl != 0 restricts the row width to 64 * force_cpl columns, force_height != 0 the
 // loaded tile height; a forced shape that does not fit falls back to the planner's choice.
 TiledPlan tiled_plan(int dim, int nx, int ny, int nz, int n_species, double step_cells,
                      int block_steps, int n_cones, int force_cpl = 0, int force_height = 0);
+// Depth and tile heights for a batch of simulations with row width 64 * cpl: the depth (theirs
+// where they ask for one; 0 if no shape fits them all) and each simulation's loaded height.
+int tiled_batch_shape(const sim_params* const* params, int n, int cpl, std::vector<int>& height);
 // Allocate buckets and per-tile tables and upload the argument table; fields[s][b] are the
 // simulation's ping-pong field buffers, cones its caller-order arrays.
 hipError_t tiled_allocate(const TiledPlan& plan, TiledState& st, int n_cones,
