@@ -15,7 +15,7 @@
 // a multiple of the per-lane segment width so that segments stay aligned to the grid.
 //
 // Layout of a tile row in LDS: one wavefront spans the loaded width W = 64 * CPL, lane l
-// owning columns CPL*l .. CPL*l + CPL-1.  The eight wavefronts of a workgroup own
+// owning columns CPL*l .. CPL*l + CPL-1.  The wavefronts of a workgroup own
 // consecutive strips of rows and update them in place (see strip_update).
 //
 // HBM traffic per launch: the tile with its halo is read once and the core written once,
@@ -40,14 +40,22 @@ namespace cuesim {
 
 namespace {
 
-constexpr int kWaves = 8;
-constexpr int kThreads = 64 * kWaves;
+// Wavefronts of a workgroup: 8, two workgroups to a CU, or 16 where a tile of four-column
+// segments takes a CU's LDS by itself and is tall enough to feed them.  Twice as wide, a tile
+// spends less on its halo: 2048^2 with 65,536 cones, first 1200 steps: depth 14, 134 rows of 256
+// columns 3.64 us per step (8 wavefronts, depth 12: 4.8 and more), two tiles of 143 rows of 128
+// columns per CU, depth 12, 4.00.  Short tiles lose by it (777 x 389, two species, 56 rows: 5.0
+// against 4.2 us), and two-column tiles too (1000 x 600: 2.14 against 1.98).
+constexpr int kWideRows = 96;
+int waves_for(int n_species, int cpl, int height) {
+    return cpl == 4 && n_species == 1 && height >= kWideRows ? 16 : 8;
+}
 constexpr int kMaxTileTargets = 256;        // targets staged in LDS per tile
 constexpr size_t kLdsBudget = 154 * 1024;   // dynamic LDS; the rest is static (targets,
                                             // re-bucketing counters)
 constexpr int kLoadBatch = 10;              // tile rows a wavefront has in flight at load
 constexpr int kConeSlots = 1;               // cones per thread held in registers
-constexpr int kPartCones = kConeSlots * kThreads;   // cones one work item steps
+constexpr int kPartCones = kConeSlots * 512;   // cones one work item of 8 wavefronts steps
 constexpr size_t kStaticLds = kMaxTileTargets * 16 + 3 * 9 * 4 + 16;   // static LDS per tile
 constexpr int kSmallest = 192;              // and when a tile's cones are split furthest
 constexpr int kHeadItems = 64;              // sources and targets of a tile kept at a fixed
@@ -98,21 +106,21 @@ namespace {
 // read as zero; cells inside never use them (they take their own value for out-of-grid
 // neighbours).
 // issued() runs once the first batch's loads are on their way (before the wait for them).
-template <int CPL, bool ALIGNED, class Issued>
+template <int CPL, int WAVES, bool ALIGNED, class Issued>
 __device__ __forceinline__ void load_tile(float* dst, GlobalPtr<const float> f, int nx, int ny,
                                           int y0, int HL, int gx0, int cx, int wave,
                                           const bool (&col_in)[CPL], const Issued& issued) {
     using V = typename Row<CPL>::T;
     constexpr int W = 64 * CPL;
-    for (int ly0 = wave; ly0 < HL; ly0 += kLoadBatch * kWaves) {
+    for (int ly0 = wave; ly0 < HL; ly0 += kLoadBatch * WAVES) {
         RowVec<CPL> v[kLoadBatch];
 #pragma unroll
         for (int r = 0; r < kLoadBatch; ++r)
-            v[r] = load_row<CPL, ALIGNED>(f, nx, ny, y0 + min(ly0 + r * kWaves, HL - 1), gx0);
+            v[r] = load_row<CPL, ALIGNED>(f, nx, ny, y0 + min(ly0 + r * WAVES, HL - 1), gx0);
         if (ly0 == wave) issued();
 #pragma unroll
         for (int r = 0; r < kLoadBatch; ++r) {
-            const int ly = min(ly0 + r * kWaves, HL);
+            const int ly = min(ly0 + r * WAVES, HL);
             const bool row_in = (unsigned)(y0 + ly) < (unsigned)ny;
             V out;
 #pragma unroll
@@ -382,7 +390,7 @@ __device__ __forceinline__ int2 next_tile(const float4& st, int tx, int ty, int 
 // through global-address-space stores.  The tile's rows are strided over the wavefronts.
 // STREAM: non-temporal stores, for the run tape, which is read only by a later reverse sweep
 // (the recording forward run of a 1024^2 gradient: 8.1 against 8.4 ms).
-template <int NS, int CPL, bool STREAM = false>
+template <int NS, int CPL, int WAVES, bool STREAM = false>
 __device__ __forceinline__ void store_core(float* const dst[], const TiledArgs2D& a, int tx,
                                            int ty, int plane, int cx, int wave, bool aligned) {
     using V = typename Row<CPL>::T;
@@ -390,7 +398,7 @@ __device__ __forceinline__ void store_core(float* const dst[], const TiledArgs2D
     extern __shared__ __align__(16) float lds[];
     const int H = a.halo;
     const int cx0 = tx * a.tx_core, cy0 = ty * a.ty_core;
-    for (int ly = wave; ly < a.ty_core; ly += kWaves) {
+    for (int ly = wave; ly < a.ty_core; ly += WAVES) {
         const int gy = cy0 + ly;
         if (gy >= a.ny) break;
 #pragma unroll
@@ -425,12 +433,13 @@ __device__ __forceinline__ void store_core(float* const dst[], const TiledArgs2D
 }
 
 // Candidate part sizes of a crowded tile, largest first: the parts that a launch steps it in
-// take at most this many cones each.  A persistent launch, whose queue balances itself, uses
-// the first only.
+// take at most this many cones each, twice as many with 16 wavefronts (`wide`).  A persistent
+// launch, whose queue balances itself, uses the first only.
 static_assert(kPartCones == 512, "candidate part sizes assume 512-cone parts");
 __device__ __forceinline__ int tile_parts(int c, int p) { return max(1, (c + p - 1) / p); }
 // Parts of a tile of c cones under candidate j (constant divisors: no integer division).
-__device__ __forceinline__ int candidate_parts(int c, int j) {
+__device__ __forceinline__ int candidate_parts(int c, int j, bool wide) {
+    if (wide) c = (c + 1) / 2;   // ceil(ceil(c / 2) / p) == ceil(c / 2p)
     switch (j) {
         case 1: return tile_parts(c, 384);
         case 2: return tile_parts(c, 320);
@@ -450,6 +459,7 @@ struct PartLists {
     int phase;    // of the next launch
     int sizes;    // candidates in use
     int sim;
+    bool wide;    // 16 wavefronts step a part
 };
 
 // A tile's count has gone from `before` to `now` cones by one atomic addition: every part
@@ -460,7 +470,7 @@ struct PartLists {
 __device__ __forceinline__ void list_parts(const PartLists& to, int tile, int before, int now) {
     if (now <= kSmallest) return;
     for (int j = 0; j < to.sizes; ++j) {
-        const int a = candidate_parts(before, j), b = candidate_parts(now, j);
+        const int a = candidate_parts(before, j, to.wide), b = candidate_parts(now, j, to.wide);
         if (b <= a) continue;
         const int at = atomicAdd(&to.ls->extra_n[to.phase][j], b - a);
         for (int q = a; q < b; ++q)
@@ -497,7 +507,7 @@ __device__ __forceinline__ int arrive(LaunchState* ls) {
 
 // One work item: one part of one tile of one simulation for `steps` sub-steps.  Every part
 // of a tile computes the tile's field; each part steps its even share of the tile's cones
-// (at most kPartCones), and only part 0 writes the field back, so a tile crowded with cones
+// (at most one per thread), and only part 0 writes the field back, so a tile crowded with cones
 // is spread over several workgroups.  par selects the input half of every ping-pong pair
 // (fields and cone buckets; the other half is written), phase the input third of the counts.
 //
@@ -506,11 +516,12 @@ __device__ __forceinline__ int arrive(LaunchState* ls) {
 // first cone slots), so that it all travels together with the tile's rows; before, headers,
 // targets and sources were read one after the other's answer (about 3 us of a launch).
 // (with LISTED the item comes from a persistent launch's queue)
-template <int NS, int CPL, bool RECORD, bool LISTED>
+template <int NS, int CPL, int WAVES, bool RECORD, bool LISTED>
 __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& w,
                                           const PartLists& lists) {
     using V = typename Row<CPL>::T;
     constexpr int W = 64 * CPL;
+    constexpr int kThreads = 64 * WAVES;
     extern __shared__ __align__(16) float lds[];
     __shared__ int dest_count[9];
     __shared__ int dest_base[9];
@@ -541,8 +552,8 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& 
     // 0. the tile's count and header, its first sources (every wavefront keeps them, one per
     //    lane) and targets, and the first cone slots, requested together with the tile's
     //    rows.  Every cone of the part stays in registers for the whole launch: cone i sits
-    //    in thread i % kThreads, slot i / kThreads (a part holds at most kPartCones =
-    //    kConeSlots * kThreads cones).
+    //    in thread i % kThreads, slot i / kThreads (a part holds at most kConeSlots *
+    //    kThreads cones).
     const bool first_part = w.part == 0;
     const GlobalPtr<const float4> live = gbl((const float4*)a.bucket[par]) +
                                          (size_t)tile * a.capacity;
@@ -553,7 +564,7 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& 
     if (spec) mine[0] = gload(live + threadIdx.x);
     const int2 hs = gload(gbl(a.head_src) + (size_t)tile * kHeadItems + lane);
     float4 ht = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (wave == kWaves - 1) ht = gload(gbl(a.head_tgt) + (size_t)tile * kHeadItems + lane);
+    if (wave == WAVES - 1) ht = gload(gbl(a.head_tgt) + (size_t)tile * kHeadItems + lane);
     const int n_all = *gbl(count_in + tile);
     const i4v head = *(GlobalPtr<const i4v>)gbl(a.head + tile);
     const int t_lo = head.x, n_tt = head.y, src_lo = head.z, n_src = head.w;
@@ -562,7 +573,7 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& 
     // the part's share of the tile's cones (the first n_all % parts parts take one more), and
     // its remaining cones, once the count is there
     auto rest = [&]() {
-        const int parts = candidate_parts(n_all, w.chosen);
+        const int parts = candidate_parts(n_all, w.chosen, WAVES > 8);
         const int each = parts == 1 ? n_all : n_all / parts, more = n_all - each * parts;
         n_cones = each + (w.part < more ? 1 : 0);
         const int first = w.part * each + min(w.part, more);
@@ -590,14 +601,14 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& 
         const GlobalPtr<const float> f = gbl((const float*)in[s]);
         float* const dst = lds + s * plane + W;
         if (aligned)
-            load_tile<CPL, true>(dst, f, a.nx, a.ny, y0, HL, gx0, cx, wave, col_in,
+            load_tile<CPL, WAVES, true>(dst, f, a.nx, a.ny, y0, HL, gx0, cx, wave, col_in,
                                  [&] { if (s == 0) rest(); });
         else
-            load_tile<CPL, false>(dst, f, a.nx, a.ny, y0, HL, gx0, cx, wave, col_in,
+            load_tile<CPL, WAVES, false>(dst, f, a.nx, a.ny, y0, HL, gx0, cx, wave, col_in,
                                   [&] { if (s == 0) rest(); });
     }
     if (contact.staged) {
-        if (wave == kWaves - 1 && lane < n_tt) tile_targets[lane] = ht;
+        if (wave == WAVES - 1 && lane < n_tt) tile_targets[lane] = ht;
         for (int k = kHeadItems + threadIdx.x; k < n_tt; k += kThreads)
             tile_targets[k] = gload(gbl(a.tgt_pts) + t_lo + k);
     }
@@ -636,16 +647,16 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& 
         int slots = 0;
 #pragma unroll
         for (int k = 0; k < kConeSlots; ++k) {
-            cw[k] = min(kWaves, (max(n_cones - k * kThreads, 0) + 63) / 64);
+            cw[k] = min(WAVES, (max(n_cones - k * kThreads, 0) + 63) / 64);
             slots += cw[k];
         }
-        const float per = (float)(r1 - r0 + a.cone_rows * slots) / kWaves;
+        const float per = (float)(r1 - r0 + a.cone_rows * slots) / WAVES;
         int prev = r0;
-        for (int w = 1; w <= kWaves; ++w) {
+        for (int w = 1; w <= WAVES; ++w) {
             int used = 0;
 #pragma unroll
             for (int k = 0; k < kConeSlots; ++k) used += a.cone_rows * min(w, cw[k]);
-            const int b = w == kWaves ? r1 : min(max(r0 + (int)rintf(w * per) - used, prev), r1);
+            const int b = w == WAVES ? r1 : min(max(r0 + (int)rintf(w * per) - used, prev), r1);
             if (w == wave) ybeg = b;       // wavefront w's strip is [b(w), b(w + 1))
             if (w == wave + 1) yend = b;
             prev = b;
@@ -708,7 +719,7 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& 
             const size_t at = (size_t)(first_step + (uint32_t)b + 1u - a.record_n0) * NS;
             float* tape[SIM_MAX_SPECIES] = {a.record + at * cells,
                                             a.record + (at + (NS - 1)) * cells};
-            store_core<NS, CPL, true>(tape, a, tx, ty, plane, cx, wave, aligned);
+            store_core<NS, CPL, WAVES, true>(tape, a, tx, ty, plane, cx, wave, aligned);
             __syncthreads();
         }
         // 4. cones against the updated field.  Every read of the field (the gradients)
@@ -730,7 +741,7 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& 
     }
 
     // 5. write the core back (one part per tile does)
-    if (first_part) store_core<NS, CPL>(out, a, tx, ty, plane, cx, wave, aligned);
+    if (first_part) store_core<NS, CPL, WAVES>(out, a, tx, ty, plane, cx, wave, aligned);
 
     // 6. re-bucket surviving cones, straight from registers, into the tile that now holds
     //    their tip (one of the 3 x 3 tiles around this one)
@@ -784,15 +795,15 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& 
 // What the launch reads that other workgroups change while it runs is the launch state's
 // first group alone, which is written after all have read it; counts, lists and buckets are
 // read by the next launch, after the kernel boundary.
-template <int NS, int CPL, bool RECORD>
-__global__ __launch_bounds__(kThreads) void k_tiled2d(TiledArgs2D a, int tile_wgs, int steps,
+template <int NS, int CPL, bool RECORD, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_tiled2d(TiledArgs2D a, int tile_wgs, int steps,
                                                       LaunchState* ls, int4* extra,
                                                       int extra_cap, int room) {
     const int4 head = *(const int4*)ls;   // step, parity, phase
     const int par = head.y, phase = head.z;
     const int next_phase = phase == 2 ? 0 : phase + 1;
     const PartLists lists{ls, extra + (size_t)(par ^ 1) * kPartSizes * extra_cap, extra_cap,
-                          next_phase, kPartSizes, 0};
+                          next_phase, kPartSizes, 0, WAVES > 8};
     int chosen = 0, chosen_n = min(ls->extra_n[phase][0], extra_cap);
 #pragma unroll
     for (int j = 1; j < kPartSizes; ++j) {   // the counts grow with j: keep the last that fits
@@ -815,7 +826,7 @@ __global__ __launch_bounds__(kThreads) void k_tiled2d(TiledArgs2D a, int tile_wg
     // the third of the list lengths that last launch read is the next launch's output
     if (b == 0 && threadIdx.x < kPartSizes) ls->extra_n[3 - phase - next_phase][threadIdx.x] = 0;
     if (w.tile >= 0) {
-        tile_body<NS, CPL, RECORD, false>(a, w, lists);
+        tile_body<NS, CPL, WAVES, RECORD, false>(a, w, lists);
     } else {
         __syncthreads();   // every wavefront has read the launch state
         if (threadIdx.x == 0 && arrive(ls) == (int)gridDim.x - 1)
@@ -826,7 +837,7 @@ __global__ __launch_bounds__(kThreads) void k_tiled2d(TiledArgs2D a, int tile_wg
 // The persistent form for a batch: a fixed grid pulls items (a tile of a simulation, then
 // the further parts of crowded ones) from an atomic queue until it runs dry.
 template <int NS, int CPL>
-__global__ __launch_bounds__(kThreads) void k_tiled2d_batch(
+__global__ __launch_bounds__(512) void k_tiled2d_batch(
     const TiledArgs2D* __restrict__ table, const int2* __restrict__ base, int n_base, int steps,
     LaunchState* ls, int4* extra, int extra_cap) {
     __shared__ int item_idx;
@@ -856,9 +867,9 @@ __global__ __launch_bounds__(kThreads) void k_tiled2d_batch(
             part = it.z;
         }
         const PartLists lists{ls, extra + (size_t)(par ^ 1) * extra_cap, extra_cap, next_phase,
-                              kBatchPartLists, sim};
+                              kBatchPartLists, sim, false};
         const TileWork w{tile, part, 0, steps, (uint32_t)head.x, par, phase};
-        tile_body<NS, CPL, false, true>(table[sim], w, lists);
+        tile_body<NS, CPL, 8, false, true>(table[sim], w, lists);
         // every thread read item_idx before tile_body's first barrier
         if (threadIdx.x == 0) item_idx = next;
         __syncthreads();   // the item is done with LDS; item_idx holds the next index
@@ -907,17 +918,20 @@ __global__ void k_sync_cones2d(ConeArrays c, const float4* bucket, int32_t* coun
 
 int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
-// The kernel variant for a species count and row width; `record` selects the one that also
-// writes every sub-step's state to the run tape (only a recording run launches it).
-const void* kernel_for(int n_species, int cpl, bool record = false) {
-    if (record) {
-        if (n_species == 1)
-            return cpl == 4 ? (const void*)k_tiled2d<1, 4, true> : (const void*)k_tiled2d<1, 2, true>;
-        return cpl == 4 ? (const void*)k_tiled2d<2, 4, true> : (const void*)k_tiled2d<2, 2, true>;
-    }
-    if (n_species == 1)
-        return cpl == 4 ? (const void*)k_tiled2d<1, 4, false> : (const void*)k_tiled2d<1, 2, false>;
-    return cpl == 4 ? (const void*)k_tiled2d<2, 4, false> : (const void*)k_tiled2d<2, 2, false>;
+// The kernel variant for a species count, row width and wavefronts; `record` selects the one
+// that also writes every sub-step's state to the run tape (only a recording run launches it).
+template <bool RECORD>
+const void* kernel_of(const TiledPlan& p) {
+    if (p.n_species > 1)
+        return p.cpl == 4 ? (const void*)k_tiled2d<2, 4, RECORD, 8>
+                          : (const void*)k_tiled2d<2, 2, RECORD, 8>;
+    if (p.cpl != 4) return (const void*)k_tiled2d<1, 2, RECORD, 8>;
+    return p.waves > 8 ? (const void*)k_tiled2d<1, 4, RECORD, 16>
+                       : (const void*)k_tiled2d<1, 4, RECORD, 8>;
+}
+
+const void* kernel_for(const TiledPlan& p, bool record = false) {
+    return record ? kernel_of<true>(p) : kernel_of<false>(p);
 }
 
 const void* batch_kernel_for(int n_species, int cpl) {
@@ -941,7 +955,7 @@ int halo_for(int B, double step_cells, int cpl) {
 
 // Microseconds per step of a plan, for the choice of the depth: a launch takes 7 us besides its
 // sub-steps, a sub-step 1.1 us and 3.2 ns per row of each two-column species plane in its CU
-// (a quarter more with one tile there, which hides latency poorly), and tiles past two per CU
+// (a quarter more with one tile of 8 wavefronts there, which hides latency poorly), and tiles past two per CU
 // wait for the others.  Per step, measured at depths 4 / 8 / 12 / 16 / 20 / 24: 128 x 128 3.0 /
 // 2.1 / 1.84 / 1.73 / 1.68 / 1.72 us; 777 x 389, two species 4.1 / 3.1 / 2.93 / 2.89 / 3.1 /
 // 3.2; 1000 x 600 3.2 / 2.3 / 2.01 / 1.97 / 1.94 / 2.0; 1500 x 1100 4.0 / 3.0 / 2.69 / 2.65 /
@@ -952,7 +966,7 @@ double step_time(const TiledPlan& p) {
     const int per_cu = ceil_div(p.n_tiles, 256);
     const int fit = std::max(1, std::min(2, (int)(160 * 1024 / (p.lds_bytes + kStaticLds))));
     const double rows = (double)p.height * std::min(per_cu, fit) * p.n_species * p.cpl / 2;
-    const double sub = (1.1 + 0.0032 * rows) * (fit < 2 ? 1.25 : 1.0);
+    const double sub = (1.1 + 0.0032 * rows) * (fit < 2 && p.waves == 8 ? 1.25 : 1.0);
     return ceil_div(per_cu, fit) * (7.0 / p.block_steps + sub);
 }
 
@@ -992,21 +1006,23 @@ TiledPlan plan_search(int dim, int nx, int ny, int nz, int n_species, double ste
                 const int per_cu = ceil_div(tiles, 256);
                 const size_t per_cu_lds = 160 * 1024;
                 const int resident = std::max(1, std::min(2, (int)(per_cu_lds / (lds + kStaticLds))));
+                const int waves = waves_for(n_species, cpl, HL);
                 // per-step cost in cell-updates per compute unit: each tile's loaded area
                 // per sub-step plus its load/store per launch; one resident tile per CU
                 // hides latency poorly.  Cones gather (attracted to the sources), and a tile
                 // holding more than kPartCones of them takes extra workgroups: keep room
                 // for a quarter of the cones in full parts beside one workgroup per tile,
                 // or the launch runs in two generations.
-                const int spare = std::min(tiles, ceil_div(n_cones, 4 * kPartCones));
+                const int spare = std::min(tiles, ceil_div(n_cones, 4 * kPartCones * (waves / 8)));
                 double cost = (double)per_cu * W * HL * (1.0 + 2.0 / B) / B;
-                if (resident < 2 || ceil_div(tiles + spare, 256) > resident) cost *= 1.25;
+                if ((resident < 2 && waves == 8) || ceil_div(tiles + spare, 256) > resident) cost *= 1.25;
                 if (cost < best_cost * 0.999) {
                     best_cost = cost;
                     best.block_steps = B;
                     best.move = move;
                     best.halo = H;
                     best.cpl = cpl;
+                    best.waves = waves;
                     best.core_x = TX;
                     best.core_y = TY;
                     best.tiles_x = ceil_div(nx, TX);
@@ -1244,7 +1260,7 @@ hipError_t tiled_allocate(const TiledPlan& plan, TiledState& st, int n_cones,
     a.cones = cones;
     a.rules = rules;
     for (bool record : {false, true})
-        if ((e = hipFuncSetAttribute(kernel_for(plan.n_species, plan.cpl, record),
+        if ((e = hipFuncSetAttribute(kernel_for(plan, record),
                                      hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)plan.lds_bytes)) != hipSuccess)
             return e;
@@ -1283,7 +1299,7 @@ hipError_t tiled_bucket_batch(const TiledPlan& plan, TiledState& st, ConeArrays 
     if (cones.n == 0) return hipSuccess;
     const int sizes = launch == st.launch ? kPartSizes : kBatchPartLists;
     const PartLists lists{launch, extra + (size_t)st.cur * sizes * extra_cap, extra_cap,
-                          st.phase, sizes, sim};
+                          st.phase, sizes, sim, launch == st.launch && plan.waves > 8};
     hipLaunchKernelGGL(k_bucket2d, dim3(ceil_div(cones.n, 256)), dim3(256), 0, stream, cones,
                        plan.nx, plan.ny, plan.core_x, plan.core_y, plan.tiles_x, plan.inv_dx,
                        st.bucket[st.cur], st.count[st.phase], st.capacity, lists);
@@ -1308,8 +1324,8 @@ hipError_t tiled_launch(const TiledPlan& plan, TiledState& st, int steps, hipStr
     int tile_wgs = ceil_div(plan.n_tiles, kXcds) * kXcds;
     void* args[] = {st.args, &tile_wgs, &steps, &st.launch, &st.extra, &st.extra_cap, &st.room};
     const hipError_t e = hipExtLaunchKernel(
-        kernel_for(plan.n_species, plan.cpl, st.args->record != nullptr),
-        dim3(tile_wgs + st.extra_cap), dim3(kThreads), args, plan.lds_bytes, stream, start, stop,
+        kernel_for(plan, st.args->record != nullptr),
+        dim3(tile_wgs + st.extra_cap), dim3(64 * plan.waves), args, plan.lds_bytes, stream, start, stop,
         0);
     if (e == hipSuccess) tiled_advanced(st, 1);
     return e;
@@ -1334,7 +1350,7 @@ hipError_t tiled_launch_batch(const TiledArgs2D* table, int4* extra, const int2*
                               hipStream_t stream) {
     void* args[] = {&table, &base, &n_base, &steps, &launch, &extra, &extra_cap};
     return hipLaunchKernel(batch_kernel_for(n_species, cpl),
-                           dim3(tiled_persistent_grid(lds_bytes)), dim3(kThreads), args,
+                           dim3(tiled_persistent_grid(lds_bytes)), dim3(512), args,
                            lds_bytes, stream);
 }
 
