@@ -720,7 +720,7 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& 
             float* tape[SIM_MAX_SPECIES] = {a.record + at * cells,
                                             a.record + (at + (NS - 1)) * cells};
             store_core<NS, CPL, WAVES, true>(tape, a, tx, ty, plane, cx, wave, aligned);
-            __syncthreads();
+            if (n_cones == 0) __syncthreads();   // else that after the cones' reads
         }
         // 4. cones against the updated field.  Every read of the field (the gradients)
         //    happens before the barrier; the cones then finish their step after it,
