@@ -641,11 +641,11 @@ __device__ __forceinline__ float dot3(float ax, float ay, float az, float bx, fl
     return fmaf(az, bz, fmaf(ay, by, ax * bx));
 }
 
-// One step of an active 3D cone with unit heading (hx, hy, hz).
+// One step of an active 3D cone with unit heading (hx, hy, hz); zn are the step's three
+// deviates (normals<3>).
 template <class Contact>
 __device__ __forceinline__ ConeEvent cone_step_3d(const ConeRules& r, float gx, float gy,
-                                                  float gz, uint32_t id, uint32_t step,
-                                                  float& x, float& y, float& z, float& hx,
+                                                  float gz, const float* zn, float& x, float& y, float& z, float& hx,
                                                   float& hy, float& hz,
                                                   const Contact& contact) {
     // turn in the plane of h and g, toward h + gain*g, by at most max_turn
@@ -663,8 +663,6 @@ __device__ __forceinline__ ConeEvent cone_step_3d(const ConeRules& r, float gx, 
         hz = fmaf(c, hz, k * pz);
     }
     // tangent-plane Gaussian rotation
-    float zn[3];
-    normals<3>(r.key, id, step, zn);
     const float zh = dot3(zn[0], zn[1], zn[2], hx, hy, hz);
     const float wx = r.sigma * fmaf(-zh, hx, zn[0]);
     const float wy = r.sigma * fmaf(-zh, hy, zn[1]);

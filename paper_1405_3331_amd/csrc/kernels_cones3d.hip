@@ -171,11 +171,21 @@ __device__ __forceinline__ void step_ordered_cone(const ConeRules& r, const floa
     const float4 h = dir[t];
     float x = p.x, y = p.y, z = p.z, hx = h.x, hy = h.y, hz = h.z;
     const Corner3D k = corner_3d(r, x, y, z);
-    float gx, gy, gz;
-    if (r.nx >= 4)
-        gradient_from_3d(r, k, load_footprint_3d_rows(f0, r, k), gx, gy, gz);
-    else
+    // The deviates need the cone's id only: with one species they are worked out while the
+    // footprint travels (97 x 64 x 51: 11.0 -> 10.7 us per step).  With two, keeping them through
+    // both gradients costs registers and spills (256^3: 103.5 -> 105.2), so they come last.
+    float gx, gy, gz, zn[3];
+    if (r.nx >= 4) {
+        const Footprint3D fp = load_footprint_3d_rows(f0, r, k);
+        if (NS == 1) {
+            normals<3>(r.key, (uint32_t)id, step, zn);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        gradient_from_3d(r, k, fp, gx, gy, gz);
+    } else {
+        if (NS == 1) normals<3>(r.key, (uint32_t)id, step, zn);
         gradient_from_3d(r, k, load_footprint_3d(Global3D{f0, r.nx, r.ny}, k), gx, gy, gz);
+    }
     gx *= r.sign0;
     gy *= r.sign0;
     gz *= r.sign0;
@@ -190,7 +200,8 @@ __device__ __forceinline__ void step_ordered_cone(const ConeRules& r, const floa
         gy = fmaf(r.sign1, ay, gy);
         gz = fmaf(r.sign1, az, gz);
     }
-    const ConeEvent ev = cone_step_3d(r, gx, gy, gz, (uint32_t)id, step, x, y, z, hx, hy, hz,
+    if (NS > 1) normals<3>(r.key, (uint32_t)id, step, zn);
+    const ConeEvent ev = cone_step_3d(r, gx, gy, gz, zn, x, y, z, hx, hy, hz,
                                       GridContact{&r.targets});
     dir[t] = make_float4(hx, hy, hz, 0.0f);
     if (ev.status == kActive) {
