@@ -43,7 +43,8 @@ BYTES_PER_CELL_UPDATE = 8.0
 # WRITE_SIZE runs; used only while the kernel sources still hash to the recorded value.
 TRAFFIC_RECORD = os.path.join(ROOT, "profiles", "tiled_step_headline_2048_traffic.txt")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_1405_3331_amd", "csrc", f)
-                  for f in ("kernels_tiled.hip", "device.hpp", "tiled.hpp", "internal.hpp")]
+                  for f in ("kernels_tiled.hip", "rows.hpp", "device.hpp", "tiled.hpp",
+                            "internal.hpp")]
 
 
 def kernel_source_hash():

@@ -42,10 +42,11 @@ namespace {
 
 // Wavefronts of a workgroup: 8, two workgroups to a CU, or 16 where a tile of four-column
 // segments takes a CU's LDS by itself and is tall enough to feed them.  Twice as wide, a tile
-// spends less on its halo: 2048^2 with 65,536 cones, first 1200 steps: depth 14, 134 rows of 256
-// columns 3.64 us per step (8 wavefronts, depth 12: 4.8 and more), two tiles of 143 rows of 128
-// columns per CU, depth 12, 4.00.  Short tiles lose by it (777 x 389, two species, 56 rows: 5.0
-// against 4.2 us), and two-column tiles too (1000 x 600: 2.14 against 1.98).
+// spends less on its halo: 2048^2 with 65,536 cones, 10,000 steps after 200: depth 14, 138 rows
+// of 256 columns 3.98 us per step, two tiles of 143 rows of 128 columns per CU, depth 12, 4.46
+// (the first 1000: 3.82 and 3.87; 143 rows of 256 columns stepped by 8 wavefronts 4.8).  Short
+// tiles lose by it (777 x 389, two species, 56 rows: 5.0 against 4.2 us), and two-column tiles
+// too (1000 x 600: 2.14 against 1.98).
 constexpr int kWideRows = 96;
 int waves_for(int n_species, int cpl, int height) {
     return cpl == 4 && n_species == 1 && height >= kWideRows ? 16 : 8;
@@ -1193,7 +1194,11 @@ hipError_t tiled_allocate(const TiledPlan& plan, TiledState& st, int n_cones,
     }
     // further parts of crowded tiles: full parts always fit their list; smaller ones are used
     // only when they fit beside the tiles
-    st.room = std::max(0, tiled_persistent_grid(plan.lds_bytes) - plan.n_tiles);
+    // (workgroups are dealt to the dies round-robin, idle ones of the last round included: a
+    // part past this count would wait for a CU of its die; 220 tiles and 36 parts took 6.0 us per
+    // step instead of 4.0)
+    st.room = std::max(0, tiled_persistent_grid(plan.lds_bytes) -
+                              ceil_div(plan.n_tiles, kXcds) * kXcds);
     st.extra_cap = std::max(tiled_extra_capacity(n_cones),
                             std::min(st.room, ceil_div(n_cones, kSmallest)));
     st.room = std::min(st.room, st.extra_cap);
