@@ -16,7 +16,8 @@
 //
 // Layout of a tile row in LDS: one wavefront spans the loaded width W = 64 * CPL, lane l
 // owning columns CPL*l .. CPL*l + CPL-1.  The wavefronts of a workgroup own
-// consecutive strips of rows and update them in place (see strip_update).
+// consecutive strips of rows and update them in place or into a
+// second copy of the tile (see strip_update).
 //
 // HBM traffic per launch: the tile with its halo is read once and the core written once,
 // instead of B reads and B writes of every cell.
@@ -40,23 +41,33 @@ namespace cuesim {
 
 namespace {
 
-// Wavefronts of a workgroup: 8, two workgroups to a CU, or 16 where a tile of four-column
-// segments takes a CU's LDS by itself and is tall enough to feed them.  Twice as wide, a tile
-// spends less on its halo: 2048^2 with 65,536 cones, 10,000 steps after 200: depth 14, 138 rows
-// of 256 columns 3.98 us per step, two tiles of 143 rows of 128 columns per CU, depth 12, 4.46
-// (the first 1000: 3.82 and 3.87; 143 rows of 256 columns stepped by 8 wavefronts 4.8).  Short
-// tiles lose by it (777 x 389, two species, 56 rows: 5.0 against 4.2 us), and two-column tiles
-// too (1000 x 600: 2.14 against 1.98).
+// How a workgroup steps its tile (TileShape of a plan):
+//   kPair      8 wavefronts, one copy of the tile, two workgroups to a CU;
+//   kTwoPair   the same with two copies;
+//   kTwo       12 wavefronts, two copies, a CU's LDS to itself;
+//   kWide      16 wavefronts, one copy, a CU's LDS to itself.
+// With two copies of the tile a sub-step goes from one to the other, so that neither the strips'
+// edge rows nor the cones' reads of the field have to be kept apart from the next sub-step's
+// writes: one barrier per sub-step instead of three.  It is used where all tiles still start at
+// once.  Per step, over 6400 steps: 777 x 389, two species 3.05 -> 2.72 us, 1000 x 600 2.42 ->
+// 2.12, 1024^2 2.51 -> 2.10, 1500 x 1100 with 30,000 cones 3.31 -> 2.76; 128 x 128 1.66 -> 1.55.
+// Twelve wavefronts against eight in kTwo: 1024^2 2.04 -> 1.99, 1500 x 1100 2.57 -> 2.48 (sixteen:
+// 2.08, 2.55); where two workgroups share a CU eight are better (128 x 128 1.56 against 1.63).  A
+// second cone per thread in kTwo, so that crowded tiles need fewer parts, costs every tile:
+// 1024^2 2.17.
+// kWide: on the largest grids a tile twice as wide spends less on its halo: 2048^2 with 65,536
+// cones, 10,000 steps after 200: depth 14, 138 rows of 256 columns 3.98 us per step, two tiles of
+// 143 rows of 128 columns per CU, depth 12, 4.46 (the first 1000: 3.82 and 3.87; 143 rows of 256
+// columns stepped by 8 wavefronts 4.8).  Short tiles lose by it (777 x 389, two species, 56
+// rows: 5.0 against 4.2 us).
 constexpr int kWideRows = 96;
-int waves_for(int n_species, int cpl, int height) {
-    return cpl == 4 && n_species == 1 && height >= kWideRows ? 16 : 8;
-}
+constexpr size_t kCuLds = 160 * 1024;
 constexpr int kMaxTileTargets = 256;        // targets staged in LDS per tile
 constexpr size_t kLdsBudget = 154 * 1024;   // dynamic LDS; the rest is static (targets,
                                             // re-bucketing counters)
 constexpr int kLoadBatch = 10;              // tile rows a wavefront has in flight at load
 constexpr int kConeSlots = 1;               // cones per thread held in registers
-constexpr int kPartCones = kConeSlots * 512;   // cones one work item of 8 wavefronts steps
+constexpr int kPartCones = 512;             // cones that a part steps (kWide: twice as many)
 constexpr size_t kStaticLds = kMaxTileTargets * 16 + 3 * 9 * 4 + 16;   // static LDS per tile
 constexpr int kSmallest = 192;              // and when a tile's cones are split furthest
 constexpr int kHeadItems = 64;              // sources and targets of a tile kept at a fixed
@@ -65,6 +76,12 @@ constexpr int kSpecCones = 128;             // cone slots read before the tile's
 constexpr int kGuardRows = 4;               // one above and three below each species plane
 constexpr int kXcds = 8;                    // dies (XCDs); workgroup b of a launch runs on die
                                             // b % kXcds
+
+// Wavefronts and copies of the tile of each shape, and cones per part in units of kPartCones (in
+// kTwo the wavefronts past the eighth hold none and take more rows).
+constexpr int waves_of(int shape) { return shape == kWide ? 16 : shape == kTwo ? 12 : 8; }
+constexpr bool two_copies(int shape) { return shape == kTwoPair || shape == kTwo; }
+constexpr int part_units(int shape) { return shape == kWide ? 2 : 1; }
 
 }  // namespace
 
@@ -144,9 +161,9 @@ struct LdsField2D {
 };
 
 // One stencil + decay sub-step of one species over a wavefront's strip of rows
-// [ybeg, yend), in place.  L points at tile row 0; rows -1 and HL .. HL+2 are guard rows
+// [ybeg, yend), into `to`: L itself (in place) or the other copy.  L points at tile row 0; rows -1 and HL .. HL+2 are guard rows
 // (never meaningful) so reads, which reach at most two rows past the strip, need no
-// clamping.  Within a wavefront every LDS read of a row is issued before that row's write,
+// clamping.  (In place:) within a wavefront every LDS read of a row is issued before that row's write,
 // so interior rows are overwritten as soon as they are computed; the strip's first and
 // last rows are read by the neighbouring wavefronts and are returned for writing after a
 // barrier.  Four row registers cycle through their roles (above / at / below /
@@ -162,13 +179,13 @@ struct StripEdges {
 };
 
 template <int CPL, int COLS>
-__device__ __forceinline__ StripEdges<CPL> strip_update(float* L, int ybeg, int yend, int cx,
-                                                        int gx0, int nx, bool top, bool bottom,
-                                                        StencilCoef cf) {
+__device__ __forceinline__ StripEdges<CPL> strip_update(const float* L, float* to, int ybeg,
+                                                        int yend, int cx, int gx0, int nx,
+                                                        bool top, bool bottom, StencilCoef cf) {
     using V = typename Row<CPL>::T;
     constexpr int W = 64 * CPL;
     const float* rd = L + cx;
-    float* wr = L + cx;
+    float* wr = to + cx;
     auto load = [&](int yy) { return *(const V*)&rd[yy * W]; };
     auto store = [&](int yy, const V& v) { *(V*)&wr[yy * W] = v; };
     auto upd = [&](const V& s, const V& c, const V& n, int) {
@@ -392,11 +409,11 @@ __device__ __forceinline__ int2 next_tile(const float4& st, int tx, int ty, int 
 // STREAM: non-temporal stores, for the run tape, which is read only by a later reverse sweep
 // (the recording forward run of a 1024^2 gradient: 8.1 against 8.4 ms).
 template <int NS, int CPL, int WAVES, bool STREAM = false>
-__device__ __forceinline__ void store_core(float* const dst[], const TiledArgs2D& a, int tx,
-                                           int ty, int plane, int cx, int wave, bool aligned) {
+__device__ __forceinline__ void store_core(float* const dst[], const float* from,
+                                           const TiledArgs2D& a, int tx, int ty, int plane,
+                                           int cx, int wave, bool aligned) {
     using V = typename Row<CPL>::T;
     constexpr int W = 64 * CPL;
-    extern __shared__ __align__(16) float lds[];
     const int H = a.halo;
     const int cx0 = tx * a.tx_core, cy0 = ty * a.ty_core;
     for (int ly = wave; ly < a.ty_core; ly += WAVES) {
@@ -404,7 +421,7 @@ __device__ __forceinline__ void store_core(float* const dst[], const TiledArgs2D
         if (gy >= a.ny) break;
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            const V v = *(const V*)&lds[s * plane + (ly + H + 1) * W + cx];
+            const V v = *(const V*)&from[s * plane + (ly + H + 1) * W + cx];
             const GlobalPtr<float> row = gbl(dst[s]) + (size_t)gy * a.nx + cx0;
             if (aligned) {
                 const int lx = cx - H;   // the segment is wholly inside or outside the core
@@ -434,13 +451,13 @@ __device__ __forceinline__ void store_core(float* const dst[], const TiledArgs2D
 }
 
 // Candidate part sizes of a crowded tile, largest first: the parts that a launch steps it in
-// take at most this many cones each, twice as many with 16 wavefronts (`wide`).  A persistent
-// launch, whose queue balances itself, uses the first only.
+// take at most this many times `units` cones each.  A persistent launch, whose queue balances
+// itself, uses the first only.
 static_assert(kPartCones == 512, "candidate part sizes assume 512-cone parts");
 __device__ __forceinline__ int tile_parts(int c, int p) { return max(1, (c + p - 1) / p); }
 // Parts of a tile of c cones under candidate j (constant divisors: no integer division).
-__device__ __forceinline__ int candidate_parts(int c, int j, bool wide) {
-    if (wide) c = (c + 1) / 2;   // ceil(ceil(c / 2) / p) == ceil(c / 2p)
+__device__ __forceinline__ int candidate_parts(int c, int j, int units) {
+    if (units == 2) c = (c + 1) / 2;   // ceil(ceil(c / u) / p) == ceil(c / (u p))
     switch (j) {
         case 1: return tile_parts(c, 384);
         case 2: return tile_parts(c, 320);
@@ -460,7 +477,7 @@ struct PartLists {
     int phase;    // of the next launch
     int sizes;    // candidates in use
     int sim;
-    bool wide;    // 16 wavefronts step a part
+    int units;    // of a part's size
 };
 
 // A tile's count has gone from `before` to `now` cones by one atomic addition: every part
@@ -471,7 +488,8 @@ struct PartLists {
 __device__ __forceinline__ void list_parts(const PartLists& to, int tile, int before, int now) {
     if (now <= kSmallest) return;
     for (int j = 0; j < to.sizes; ++j) {
-        const int a = candidate_parts(before, j, to.wide), b = candidate_parts(now, j, to.wide);
+        const int a = candidate_parts(before, j, to.units);
+        const int b = candidate_parts(now, j, to.units);
         if (b <= a) continue;
         const int at = atomicAdd(&to.ls->extra_n[to.phase][j], b - a);
         for (int q = a; q < b; ++q)
@@ -517,12 +535,13 @@ __device__ __forceinline__ int arrive(LaunchState* ls) {
 // first cone slots), so that it all travels together with the tile's rows; before, headers,
 // targets and sources were read one after the other's answer (about 3 us of a launch).
 // (with LISTED the item comes from a persistent launch's queue)
-template <int NS, int CPL, int WAVES, bool RECORD, bool LISTED>
+template <int NS, int CPL, int SHAPE, bool RECORD, bool LISTED>
 __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& w,
                                           const PartLists& lists) {
     using V = typename Row<CPL>::T;
     constexpr int W = 64 * CPL;
-    constexpr int kThreads = 64 * WAVES;
+    constexpr int WAVES = waves_of(SHAPE), kThreads = 64 * WAVES;
+    constexpr bool TWO = two_copies(SHAPE);
     extern __shared__ __align__(16) float lds[];
     __shared__ int dest_count[9];
     __shared__ int dest_base[9];
@@ -574,7 +593,7 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& 
     // the part's share of the tile's cones (the first n_all % parts parts take one more), and
     // its remaining cones, once the count is there
     auto rest = [&]() {
-        const int parts = candidate_parts(n_all, w.chosen, WAVES > 8);
+        const int parts = candidate_parts(n_all, w.chosen, part_units(SHAPE));
         const int each = parts == 1 ? n_all : n_all / parts, more = n_all - each * parts;
         n_cones = each + (w.part < more ? 1 : 0);
         const int first = w.part * each + min(w.part, more);
@@ -669,47 +688,47 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& 
     const float src_q = __int_as_float(hs.y);
     const ConeRules& rules = a.rules;
     const int cols = x0 > 0 && x0 + W < a.nx ? kNoWall : aligned ? kWallAligned : kWallAny;
-    const LdsField2D f0{lds + W, x0, y0, W, HL};
-    const LdsField2D f1{lds + (NS > 1 ? plane : 0) + W, x0, y0, W, HL};
-
     for (int b = 0; b < steps; ++b) {
-        // 2. stencil + decay, in place, strip per wavefront.  After this sub-step only rows
+        // 2. stencil + decay, in place or into the other copy, strip per wavefront.  After this sub-step only rows
         //    [b + 1, HL - b - 1) are still valid (each sub-step loses one row at either
         //    edge of the tile), so rows outside that band are not computed.
         const int lo = max(ybeg, b + 1), hi = min(yend, HL - b - 1);
         const bool top = lo == -y0, bottom = hi == a.ny - y0;
+        float* const from = lds + (TWO && (b & 1) ? NS * plane : 0);
+        float* const to = lds + (TWO && !(b & 1) ? NS * plane : 0);
         StripEdges<CPL> edge[NS];
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             if (lo < hi) {
-                float* const L = lds + s * plane + W;
+                const float* const L = from + s * plane + W;
+                float* const T = to + s * plane + W;
                 if (cols == kNoWall)
-                    edge[s] = strip_update<CPL, kNoWall>(L, lo, hi, cx, gx0, a.nx, top, bottom,
-                                                         a.coef[s]);
+                    edge[s] = strip_update<CPL, kNoWall>(L, T, lo, hi, cx, gx0, a.nx, top,
+                                                         bottom, a.coef[s]);
                 else if (cols == kWallAligned)
-                    edge[s] = strip_update<CPL, kWallAligned>(L, lo, hi, cx, gx0, a.nx, top,
+                    edge[s] = strip_update<CPL, kWallAligned>(L, T, lo, hi, cx, gx0, a.nx, top,
                                                               bottom, a.coef[s]);
                 else
-                    edge[s] = strip_update<CPL, kWallAny>(L, lo, hi, cx, gx0, a.nx, top, bottom,
-                                                          a.coef[s]);
+                    edge[s] = strip_update<CPL, kWallAny>(L, T, lo, hi, cx, gx0, a.nx, top,
+                                                          bottom, a.coef[s]);
             }
         }
-        __syncthreads();
+        if (!TWO) __syncthreads();
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            if (lo < hi) *(V*)&lds[s * plane + (lo + 1) * W + cx] = edge[s].first;
-            if (hi - 1 > lo) *(V*)&lds[s * plane + hi * W + cx] = edge[s].last;
+            if (lo < hi) *(V*)&to[s * plane + (lo + 1) * W + cx] = edge[s].first;
+            if (hi - 1 > lo) *(V*)&to[s * plane + hi * W + cx] = edge[s].last;
         }
         // 3. sources in this wavefront's rows [lo, hi) (entries are unique cells per
         //    species; rows no wavefront computes are not valid after this sub-step), added
         //    after its own edge rows: a wavefront's LDS operations take effect in order, and
         //    the barrier below publishes them with the rest of the sub-step
         if (n_src > 0 && lo < hi) {
-            if (src_row >= lo && src_row < hi) lds[src_at] += src_q;
+            if (src_row >= lo && src_row < hi) to[src_at] += src_q;
             for (int e = src_lo + kHeadItems + lane; e < src_lo + n_src; e += 64) {
                 const int2 ent = gload(gbl(a.src_entry) + e);
                 const int row = ent.x / W;
-                if (row >= lo && row < hi) lds[ent.y * plane + W + ent.x] += gbl(a.src_amount)[e];
+                if (row >= lo && row < hi) to[ent.y * plane + W + ent.x] += gbl(a.src_amount)[e];
             }
         }
         __syncthreads();
@@ -720,20 +739,23 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& 
             const size_t at = (size_t)(first_step + (uint32_t)b + 1u - a.record_n0) * NS;
             float* tape[SIM_MAX_SPECIES] = {a.record + at * cells,
                                             a.record + (at + (NS - 1)) * cells};
-            store_core<NS, CPL, WAVES, true>(tape, a, tx, ty, plane, cx, wave, aligned);
-            if (n_cones == 0) __syncthreads();   // else that after the cones' reads
+            store_core<NS, CPL, WAVES, true>(tape, to, a, tx, ty, plane, cx, wave, aligned);
+            if (!TWO && n_cones == 0) __syncthreads();   // else that after the cones' reads
         }
-        // 4. cones against the updated field.  Every read of the field (the gradients)
-        //    happens before the barrier; the cones then finish their step after it,
-        //    overlapping the next sub-step's in-place stencil, which they no longer read.
+        // 4. cones against the updated field.  In place, every read of the field (the
+        //    gradients) happens before the barrier; the cones then finish their step after
+        //    it, overlapping the next sub-step's stencil.  With two copies the next sub-step
+        //    writes the other one, which was last read before this sub-step's barrier.
         const uint32_t step = first_step + (uint32_t)b;
         const size_t rec = RECORD ? step - a.record_n0 : 0;
         if (n_cones > 0) {
+            const LdsField2D f0{to + W, x0, y0, W, HL};
+            const LdsField2D f1{to + (NS > 1 ? plane : 0) + W, x0, y0, W, HL};
             float3 g[kConeSlots];
 #pragma unroll
-            for (int k = 0; k < kConeSlots; ++k) 
+            for (int k = 0; k < kConeSlots; ++k)
                 g[k] = tile_cone_gradient<NS, RECORD>(mine[k], f0, f1, rules, a.cone_record, rec);
-            __syncthreads();
+            if (!TWO) __syncthreads();
 #pragma unroll
             for (int k = 0; k < kConeSlots; ++k)
                 tile_cone_advance<RECORD>(mine[k], trig[k], spare[k], g[k], rules, step, b == 0,
@@ -742,7 +764,8 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& 
     }
 
     // 5. write the core back (one part per tile does)
-    if (first_part) store_core<NS, CPL, WAVES>(out, a, tx, ty, plane, cx, wave, aligned);
+    if (first_part)
+        store_core<NS, CPL, WAVES>(out, lds + (TWO && (steps & 1) ? NS * plane : 0), a, tx, ty, plane, cx, wave, aligned);
 
     // 6. re-bucket surviving cones, straight from registers, into the tile that now holds
     //    their tip (one of the 3 x 3 tiles around this one)
@@ -796,15 +819,15 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& 
 // What the launch reads that other workgroups change while it runs is the launch state's
 // first group alone, which is written after all have read it; counts, lists and buckets are
 // read by the next launch, after the kernel boundary.
-template <int NS, int CPL, bool RECORD, int WAVES>
-__global__ __launch_bounds__(64 * WAVES) void k_tiled2d(TiledArgs2D a, int tile_wgs, int steps,
+template <int NS, int CPL, bool RECORD, int SHAPE>
+__global__ __launch_bounds__(64 * waves_of(SHAPE)) void k_tiled2d(TiledArgs2D a, int tile_wgs, int steps,
                                                       LaunchState* ls, int4* extra,
                                                       int extra_cap, int room) {
     const int4 head = *(const int4*)ls;   // step, parity, phase
     const int par = head.y, phase = head.z;
     const int next_phase = phase == 2 ? 0 : phase + 1;
     const PartLists lists{ls, extra + (size_t)(par ^ 1) * kPartSizes * extra_cap, extra_cap,
-                          next_phase, kPartSizes, 0, WAVES > 8};
+                          next_phase, kPartSizes, 0, part_units(SHAPE)};
     int chosen = 0, chosen_n = min(ls->extra_n[phase][0], extra_cap);
 #pragma unroll
     for (int j = 1; j < kPartSizes; ++j) {   // the counts grow with j: keep the last that fits
@@ -827,7 +850,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_tiled2d(TiledArgs2D a, int tile_
     // the third of the list lengths that last launch read is the next launch's output
     if (b == 0 && threadIdx.x < kPartSizes) ls->extra_n[3 - phase - next_phase][threadIdx.x] = 0;
     if (w.tile >= 0) {
-        tile_body<NS, CPL, WAVES, RECORD, false>(a, w, lists);
+        tile_body<NS, CPL, SHAPE, RECORD, false>(a, w, lists);
     } else {
         __syncthreads();   // every wavefront has read the launch state
         if (threadIdx.x == 0 && arrive(ls) == (int)gridDim.x - 1)
@@ -868,9 +891,9 @@ __global__ __launch_bounds__(512) void k_tiled2d_batch(
             part = it.z;
         }
         const PartLists lists{ls, extra + (size_t)(par ^ 1) * extra_cap, extra_cap, next_phase,
-                              kBatchPartLists, sim, false};
+                              kBatchPartLists, sim, part_units(kPair)};
         const TileWork w{tile, part, 0, steps, (uint32_t)head.x, par, phase};
-        tile_body<NS, CPL, 8, false, true>(table[sim], w, lists);
+        tile_body<NS, CPL, kPair, false, true>(table[sim], w, lists);
         // every thread read item_idx before tile_body's first barrier
         if (threadIdx.x == 0) item_idx = next;
         __syncthreads();   // the item is done with LDS; item_idx holds the next index
@@ -919,16 +942,23 @@ __global__ void k_sync_cones2d(ConeArrays c, const float4* bucket, int32_t* coun
 
 int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
-// The kernel variant for a species count, row width and wavefronts; `record` selects the one
-// that also writes every sub-step's state to the run tape (only a recording run launches it).
+// The kernel variant for a species count, row width and shape; `record` selects the one that
+// also writes every sub-step's state to the run tape (only a recording run launches it).
 template <bool RECORD>
 const void* kernel_of(const TiledPlan& p) {
-    if (p.n_species > 1)
-        return p.cpl == 4 ? (const void*)k_tiled2d<2, 4, RECORD, 8>
-                          : (const void*)k_tiled2d<2, 2, RECORD, 8>;
-    if (p.cpl != 4) return (const void*)k_tiled2d<1, 2, RECORD, 8>;
-    return p.waves > 8 ? (const void*)k_tiled2d<1, 4, RECORD, 16>
-                       : (const void*)k_tiled2d<1, 4, RECORD, 8>;
+    if (p.cpl == 4) {
+        if (p.n_species > 1) return (const void*)k_tiled2d<2, 4, RECORD, kPair>;
+        return p.shape == kWide ? (const void*)k_tiled2d<1, 4, RECORD, kWide>
+                                : (const void*)k_tiled2d<1, 4, RECORD, kPair>;
+    }
+    if (p.shape == kTwo)
+        return p.n_species > 1 ? (const void*)k_tiled2d<2, 2, RECORD, kTwo>
+                               : (const void*)k_tiled2d<1, 2, RECORD, kTwo>;
+    if (p.shape == kTwoPair)
+        return p.n_species > 1 ? (const void*)k_tiled2d<2, 2, RECORD, kTwoPair>
+                               : (const void*)k_tiled2d<1, 2, RECORD, kTwoPair>;
+    return p.n_species > 1 ? (const void*)k_tiled2d<2, 2, RECORD, kPair>
+                           : (const void*)k_tiled2d<1, 2, RECORD, kPair>;
 }
 
 const void* kernel_for(const TiledPlan& p, bool record = false) {
@@ -954,20 +984,40 @@ int halo_for(int B, double step_cells, int cpl) {
     return (B + travel + 2 + cpl - 1) / cpl * cpl;
 }
 
+// Workgroups of `lds` bytes of dynamic LDS that share a CU (two at most).
+int sharing(size_t lds) {
+    return std::max(1, std::min(2, (int)(kCuLds / (lds + kStaticLds))));
+}
+
+// Shape for `tiles` tiles whose single copy takes `lds` bytes (alone: not in a batch, whose
+// queue steps more tiles than start at once).  kTwo leaves a CU to each tile and so fewer for the
+// further parts of crowded ones: not where evenly spread cones would already be split (900 x 700,
+// 228 tiles, 40,000 cones: 2.29 us per step against 2.73; 60,000: 3.64 against 2.89).
+TileShape shape_for(int n_species, int cpl, int height, int tiles, int n_cones, size_t lds,
+                    bool alone) {
+    if (!alone) return kPair;
+    if (cpl == 4) return n_species == 1 && height >= kWideRows ? kWide : kPair;
+    const int at_once = ceil_div(tiles, kXcds) * kXcds;
+    if (sharing(2 * lds) == 2 && at_once <= 512) return kTwoPair;
+    const bool sparse = n_cones <= (int64_t)kSmallest * tiles;
+    return 2 * lds <= kLdsBudget && at_once <= 256 && sparse ? kTwo : kPair;
+}
+
 // Microseconds per step of a plan, for the choice of the depth: a launch takes 7 us besides its
-// sub-steps, a sub-step 1.1 us and 3.2 ns per row of each two-column species plane in its CU
-// (a quarter more with one tile of 8 wavefronts there, which hides latency poorly), and tiles past two per CU
-// wait for the others.  Per step, measured at depths 4 / 8 / 12 / 16 / 20 / 24: 128 x 128 3.0 /
-// 2.1 / 1.84 / 1.73 / 1.68 / 1.72 us; 777 x 389, two species 4.1 / 3.1 / 2.93 / 2.89 / 3.1 /
-// 3.2; 1000 x 600 3.2 / 2.3 / 2.01 / 1.97 / 1.94 / 2.0; 1500 x 1100 4.0 / 3.0 / 2.69 / 2.65 /
-// 2.70 / 2.9.  Depths past 16 gain nothing, and calls of few steps pay for their halo.
+// sub-steps, a sub-step 1.1 us (1.0 with two copies of the tile) and 3.2 ns per row of each
+// two-column species plane in its CU (a quarter more for 8 wavefronts alone there, which hide
+// latency poorly), and tiles past those that start at once wait.  Per step, measured with one
+// copy at depths 4 / 8 / 12 / 16 / 20 / 24: 128 x 128 3.0 / 2.1 / 1.84 / 1.73 / 1.68 / 1.72 us;
+// 777 x 389, two species 4.1 / 3.1 / 2.93 / 2.89 / 3.1 / 3.2; 1000 x 600 3.2 / 2.3 / 2.01 /
+// 1.97 / 1.94 / 2.0; 1500 x 1100 4.0 / 3.0 / 2.69 / 2.65 / 2.70 / 2.9.  Depths past 16 gain
+// nothing, and calls of few steps pay for their halo.
 constexpr int kDeepest = 16;
 
 double step_time(const TiledPlan& p) {
-    const int per_cu = ceil_div(p.n_tiles, 256);
-    const int fit = std::max(1, std::min(2, (int)(160 * 1024 / (p.lds_bytes + kStaticLds))));
+    const int per_cu = ceil_div(p.n_tiles, 256), fit = sharing(p.lds_bytes);
     const double rows = (double)p.height * std::min(per_cu, fit) * p.n_species * p.cpl / 2;
-    const double sub = (1.1 + 0.0032 * rows) * (fit < 2 && p.waves == 8 ? 1.25 : 1.0);
+    const double sub = ((two_copies(p.shape) ? 1.0 : 1.1) + 0.0032 * rows) *
+                       (fit < 2 && p.shape == kPair ? 1.25 : 1.0);
     return ceil_div(per_cu, fit) * (7.0 / p.block_steps + sub);
 }
 
@@ -975,7 +1025,7 @@ double step_time(const TiledPlan& p) {
 // only_height when those are non-zero.  Depth: the deepest that fits up to block_steps, or with
 // block_steps 0 the fastest up to kDeepest.
 TiledPlan plan_search(int dim, int nx, int ny, int nz, int n_species, double step_cells,
-                      int block_steps, int n_cones, int only_cpl, int only_height) {
+                      int block_steps, int n_cones, int only_cpl, int only_height, bool alone) {
     TiledPlan best, fastest;
     const bool any_depth = block_steps == 0;
     if (any_depth) block_steps = kDeepest;
@@ -1005,31 +1055,33 @@ TiledPlan plan_search(int dim, int nx, int ny, int nz, int n_species, double ste
                 const size_t lds = (size_t)n_species * W * (HL + kGuardRows) * sizeof(float);
                 const int tiles = ceil_div(nx, TX) * ceil_div(ny, TY);
                 const int per_cu = ceil_div(tiles, 256);
-                const size_t per_cu_lds = 160 * 1024;
-                const int resident = std::max(1, std::min(2, (int)(per_cu_lds / (lds + kStaticLds))));
-                const int waves = waves_for(n_species, cpl, HL);
+                const TileShape shape = shape_for(n_species, cpl, HL, tiles, n_cones, lds,
+                                                  alone);
+                const size_t used = two_copies(shape) ? 2 * lds : lds;
+                const int resident = sharing(used);
                 // per-step cost in cell-updates per compute unit: each tile's loaded area
-                // per sub-step plus its load/store per launch; one resident tile per CU
-                // hides latency poorly.  Cones gather (attracted to the sources), and a tile
-                // holding more than kPartCones of them takes extra workgroups: keep room
+                // per sub-step plus its load/store per launch; one tile of 8 wavefronts per
+                // CU hides latency poorly.  Cones gather (attracted to the sources), and a tile
+                // holding more than a part's of them takes extra workgroups: keep room
                 // for a quarter of the cones in full parts beside one workgroup per tile,
                 // or the launch runs in two generations.
-                const int spare = std::min(tiles, ceil_div(n_cones, 4 * kPartCones * (waves / 8)));
+                const int spare = std::min(tiles, ceil_div(n_cones, 4 * kPartCones * part_units(shape)));
                 double cost = (double)per_cu * W * HL * (1.0 + 2.0 / B) / B;
-                if ((resident < 2 && waves == 8) || ceil_div(tiles + spare, 256) > resident) cost *= 1.25;
+                if ((resident < 2 && shape == kPair) || ceil_div(tiles + spare, 256) > resident)
+                    cost *= 1.25;
                 if (cost < best_cost * 0.999) {
                     best_cost = cost;
                     best.block_steps = B;
                     best.move = move;
                     best.halo = H;
                     best.cpl = cpl;
-                    best.waves = waves;
+                    best.shape = shape;
                     best.core_x = TX;
                     best.core_y = TY;
                     best.tiles_x = ceil_div(nx, TX);
                     best.tiles_y = ceil_div(ny, TY);
                     best.n_tiles = best.tiles_x * best.tiles_y;
-                    best.lds_bytes = lds;
+                    best.lds_bytes = used;
                     best.height = HL;
                     // one cone step costs about as much as a stencil row of ~30 cells per
                     // lane-slot pair: 15 rows of two-cell segments for one species
@@ -1049,13 +1101,16 @@ TiledPlan plan_search(int dim, int nx, int ny, int nz, int n_species, double ste
 }  // namespace
 
 TiledPlan tiled_plan(int dim, int nx, int ny, int nz, int n_species, double step_cells,
-                     int block_steps, int n_cones, int force_cpl, int force_height) {
+                     int block_steps, int n_cones, int force_cpl, int force_height,
+                     bool alone) {
     if (force_cpl != 0 || force_height != 0) {
         const TiledPlan forced = plan_search(dim, nx, ny, nz, n_species, step_cells,
-                                             block_steps, n_cones, force_cpl, force_height);
+                                             block_steps, n_cones, force_cpl, force_height,
+                                             alone);
         if (forced.block_steps > 1) return forced;
     }
-    return plan_search(dim, nx, ny, nz, n_species, step_cells, block_steps, n_cones, 0, 0);
+    return plan_search(dim, nx, ny, nz, n_species, step_cells, block_steps, n_cones, 0, 0,
+                       alone);
 }
 
 // A launch of a batch takes its items' time over the workgroups that run at once.  An item of
@@ -1304,7 +1359,7 @@ hipError_t tiled_bucket_batch(const TiledPlan& plan, TiledState& st, ConeArrays 
     if (cones.n == 0) return hipSuccess;
     const int sizes = launch == st.launch ? kPartSizes : kBatchPartLists;
     const PartLists lists{launch, extra + (size_t)st.cur * sizes * extra_cap, extra_cap,
-                          st.phase, sizes, sim, launch == st.launch && plan.waves > 8};
+                          st.phase, sizes, sim, part_units(plan.shape)};
     hipLaunchKernelGGL(k_bucket2d, dim3(ceil_div(cones.n, 256)), dim3(256), 0, stream, cones,
                        plan.nx, plan.ny, plan.core_x, plan.core_y, plan.tiles_x, plan.inv_dx,
                        st.bucket[st.cur], st.count[st.phase], st.capacity, lists);
@@ -1330,7 +1385,7 @@ hipError_t tiled_launch(const TiledPlan& plan, TiledState& st, int steps, hipStr
     void* args[] = {st.args, &tile_wgs, &steps, &st.launch, &st.extra, &st.extra_cap, &st.room};
     const hipError_t e = hipExtLaunchKernel(
         kernel_for(plan, st.args->record != nullptr),
-        dim3(tile_wgs + st.extra_cap), dim3(64 * plan.waves), args, plan.lds_bytes, stream, start, stop,
+        dim3(tile_wgs + st.extra_cap), dim3(64 * waves_of(plan.shape)), args, plan.lds_bytes, stream, start, stop,
         0);
     if (e == hipSuccess) tiled_advanced(st, 1);
     return e;
@@ -1344,9 +1399,7 @@ void tiled_advanced(TiledState& st, int launches) {
 size_t tiled_table_entry_bytes() { return sizeof(TiledArgs2D); }
 
 int tiled_persistent_grid(size_t lds_bytes) {
-    const size_t per_cu_lds = 160 * 1024;
-    const int resident = std::max(1, std::min(2, (int)(per_cu_lds / (lds_bytes + kStaticLds))));
-    return 256 * resident;
+    return 256 * sharing(lds_bytes);
 }
 
 hipError_t tiled_launch_batch(const TiledArgs2D* table, int4* extra, const int2* base,

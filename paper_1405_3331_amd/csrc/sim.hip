@@ -688,7 +688,8 @@ sim_status create_impl(const sim_params* p, void* hip_stream, int force_cpl, sim
     if (h->block_steps != 1) {
         h->plan = tiled_plan(h->dim, h->nx, h->ny, h->nz, h->n_species, p->step_len / p->dx,
                              h->block_steps, h->n_cones,
-                             force_cpl ? force_cpl : p->tile_cols_per_lane, p->tile_height);
+                             force_cpl ? force_cpl : p->tile_cols_per_lane, p->tile_height,
+                             force_cpl == 0);
         h->plan.inv_dx = h->rules.inv_dx;
         for (int s = 0; s < h->n_species; ++s) h->plan.coef[s] = h->coef[s];
         if (h->plan.block_steps <= 1) {

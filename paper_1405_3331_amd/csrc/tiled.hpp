@@ -11,6 +11,9 @@ namespace cuesim {
 
 constexpr int kDefaultBlockSteps = 8;   // of a batch that no planned shape fits
 
+// How a workgroup steps a tile (kernels_tiled.hip).
+enum TileShape { kPair, kTwoPair, kTwo, kWide };
+
 // Tile geometry chosen once per simulation.
 struct TiledPlan {
     int dim = 2;
@@ -22,7 +25,7 @@ struct TiledPlan {
     int height = 0;          // loaded tile height (rows), core_y + 2 * halo
     int move = 0;            // cells a tip can travel in one launch, ceil(B * s / dx)
     int cpl = 2;             // columns per lane: loaded tile width is 64 * cpl
-    int waves = 8;           // wavefronts per workgroup
+    TileShape shape = kPair;
     int cone_rows = 15;      // strip rows traded per occupied cone slot (load balance)
     int n_species = 1;
     int nx = 0, ny = 0, nz = 1;
@@ -70,8 +73,10 @@ struct TiledState {
 // result means no tiling fits.
 // force_cpl != 0 restricts the row width to 64 * force_cpl columns, force_height != 0 the
 // loaded tile height; a forced shape that does not fit falls back to the planner's choice.
+// alone: the simulation has launches of its own (a batch's members do not).
 TiledPlan tiled_plan(int dim, int nx, int ny, int nz, int n_species, double step_cells,
-                     int block_steps, int n_cones, int force_cpl = 0, int force_height = 0);
+                     int block_steps, int n_cones, int force_cpl = 0, int force_height = 0,
+                     bool alone = true);
 // Depth and tile heights for a batch of simulations with row width 64 * cpl: the depth (theirs
 // where they ask for one; 0 if no shape fits them all) and each simulation's loaded height.
 int tiled_batch_shape(const sim_params* const* params, int n, int cpl, std::vector<int>& height);

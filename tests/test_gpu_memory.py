@@ -83,7 +83,11 @@ def test_memory_between_objects_is_bounded():
 
     _run(_case(5))   # the runtime's own allocations
     before = free()
-    sims = [B.Simulation(S.headline(seed=k), block_steps=12) for k in range(3)]
+    sims = []
+    for k in range(3):
+        sc = S.headline(seed=k)
+        sc.tile = (2, 143)   # 480 tiles
+        sims.append(B.Simulation(sc, block_steps=12))
     assert before - free() > 3 << 29
     for sim in sims:
         sim.step(12)
