@@ -196,6 +196,21 @@ struct ReverseSegment {
     const int32_t* q_start;   // [species][tile + 1] into q_entry (reverse_sources)
     const int2* q_entry;
 };
+// The reverse of a segment's cone steps from step t_from of its len (t_from = len - 1 - a multiple
+// of kRevSteps) on, for every cone of `tape` (the segment's steps): sample adjoints and boxes as
+// in ReverseSegment, the cones' own adjoints in acone.  start_status: the cones' status at the
+// segment's first step, seg0; status and event_step: at the run's end.
+struct ConeChain {
+    ConeTape tape;
+    uint32_t seg0;
+    int len, t_from;
+    float2* ag;
+    float4* boxes;
+    const int32_t* start_status;
+    const int32_t* status;
+    const int32_t* event_step;
+    float* acone;   // [M][3]
+};
 int reverse_tiles(int nx, int ny);
 int reverse_launches(int len);
 // Entries that the list of one launch can need: M cones moving at most step_cells per step.
@@ -207,9 +222,11 @@ void reverse_sources(int nx, int ny, const std::vector<int32_t>& cells, int firs
 // reverse).
 hipError_t launch_reverse_lists(const ReverseSegment& g, double step_cells, hipStream_t stream);
 // Launch `launch` of reverse_launches(len): the field adjoint of every species from a_in to
-// a_out, kRevSteps steps back (fewer in the last launch).
+// a_out, kRevSteps steps back (fewer in the last launch); with `chain`, beside it kRevSteps steps
+// of that chain.
 hipError_t launch_field_reverse2d(const ReverseSegment& g, int launch, const float* const* a_in,
-                                  float* const* a_out, hipStream_t stream);
+                                  float* const* a_out, const ConeChain* chain,
+                                  hipStream_t stream);
 int adjoint_cone_blocks(int n);
 // Forward re-run of segments seg_first .. seg_first + n_seg - 1 of a run checkpointed every
 // `every` of its n_steps steps from step n0; run step t's fields are at
@@ -220,12 +237,10 @@ hipError_t launch_cones_segments2d(const ConeRules& rules, const float* fields, 
                                    int every, int n_steps, uint32_t n0, const float* ckpt_pos,
                                    const float* ckpt_dir, const int32_t* ckpt_int, int M,
                                    const ConeTape& tape, hipStream_t stream);
-// Reverse of a segment's cone steps (ag, boxes), then every step's largest contribution to a cell
-// (step_max).  start_status: the cones' status at the segment's first step.
-hipError_t launch_cone_adjoint_segment2d(const ReverseSegment& g, const int32_t* start_status,
-                                         const int32_t* status,
-                                         const int32_t* event_step, float* acone,
-                                         hipStream_t stream);
+// The rest of a segment's chain, down to its first step, in a launch of its own.
+hipError_t launch_cone_chain2d(const ConeRules& rules, const ConeChain& c, hipStream_t stream);
+// Every step's largest contribution to a cell (step_max), once the segment's chain is done.
+hipError_t launch_sample_max2d(const ReverseSegment& g, hipStream_t stream);
 hipError_t launch_adjoint_seed2d(const float* pos, const float* tip_target, const float* weight,
                                  float* acone, double* partial, int n, hipStream_t stream);
 

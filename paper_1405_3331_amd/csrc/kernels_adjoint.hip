@@ -10,14 +10,17 @@
 //   the forward run (or, where it did not record its states, k_cones_segments2d, which re-runs
 //                             the segment's cone steps against the re-run fields) records what
 //                             the reverse of each cone step needs of it (ConeTape);
-//   k_cone_adjoint_segment2d  walks the steps backwards carrying each cone's adjoint of
-//                             (p, theta) through advance, capped turn and interpolated
-//                             gradient, and records the adjoint of its sampled gradient
-//                             (two values per cone and step);
+//   cone_chain                (cone_adjoint.hpp) walks the steps backwards carrying each cone's
+//                             adjoint of (p, theta) through advance, capped turn and
+//                             interpolated gradient, and records the adjoint of its sampled
+//                             gradient (two values per cone and step); here in launches of
+//                             its own (k_cone_adjoint_segment2d);
 //   k_sample_max              takes each step's largest contribution to a cell, the scale of
 //                             its fixed-point sums;
 //   kernels_reverse2d.hip     reverses the segment's field steps, eight per launch, adding
-//                             the samples' adjoints where the cones were.
+//                             the samples' adjoints where the cones were, with the chain of
+//                             the segment before beside them where the run recorded it.
+#include "cone_adjoint.hpp"
 #include "internal.hpp"
 
 namespace cuesim {
@@ -41,73 +44,11 @@ __device__ double adj_block_sum(double v) {
     return t;
 }
 
-// Reverse of the interpolated central-difference gradient of one species at (x, y) with
-// respect to the tip, from the fractions and corner gradients of the forward sample:
-// (agx, agy) is the adjoint of the sampled gradient, already weighted by the species sign.
-// Adds into (apx, apy) -- the interpolation weights depend on the tip; along an axis where the
-// tip is clamped to the outermost centres they do not.  (The field's share is
-// sample_adjoint_2d.)
-__device__ __forceinline__ void sample_tip_adjoint_2d(float fx, float fy, const float4& gx,
-                                                      const float4& gy, const ConeRules& r,
-                                                      float x, float y, float agx, float agy,
-                                                      float& apx, float& apy) {
-    const float ux = fmaf(x, r.inv_dx, -0.5f), uy = fmaf(y, r.inv_dx, -0.5f);
-    const bool free_x = ux > 0.0f && ux < (float)(r.nx - 1);
-    const bool free_y = uy > 0.0f && uy < (float)(r.ny - 1);
-    // d w / d f along each axis, times d f / d p = 1 / dx where not clamped
-    const float aw00 = fmaf(agy, gy.x, agx * gx.x), aw10 = fmaf(agy, gy.y, agx * gx.y);
-    const float aw01 = fmaf(agy, gy.z, agx * gx.z), aw11 = fmaf(agy, gy.w, agx * gx.w);
-    if (free_x) apx = fmaf(r.inv_dx, fmaf(fy, aw11 - aw01, (1.0f - fy) * (aw10 - aw00)), apx);
-    if (free_y) apy = fmaf(r.inv_dx, fmaf(fx, aw11 - aw10, (1.0f - fx) * (aw01 - aw00)), apy);
-}
-
 struct Field2D {
     const float* f;
     int nx;
     __device__ float operator()(int i, int j) const { return f[j * nx + i]; }
 };
-
-// A cone step's record (ConeTape).
-template <int NS>
-struct ConeTerms {
-    float4 v[kConePlanes + 2 * NS];
-    __device__ __forceinline__ void load(const ConeTape& tape, int t, int i) {
-#pragma unroll
-        for (int j = 0; j < kConePlanes + 2 * NS; ++j)
-            v[j] = tape.base[j * tape.plane + (size_t)t * tape.M + i];
-    }
-};
-
-// Reverse of one cone step from its record.  (apx, apy, ath) holds the adjoint of the state
-// after the step on entry and of the state before it on exit; (agx, agy) receives the adjoint
-// of the weighted gradient.
-template <int NS>
-__device__ __forceinline__ void cone_adjoint_step(const ConeRules& r, const ConeTerms<NS>& m,
-                                                  float& apx, float& apy, float& ath,
-                                                  float& agx, float& agy) {
-    const float x = m.v[0].x, y = m.v[0].y, sn = m.v[0].z, cn = m.v[0].w;
-    const float cross = m.v[1].x, along = m.v[1].y, s = m.v[1].z, c = m.v[1].w;
-    const float gx = m.v[2].x, gy = m.v[2].y, fx = m.v[2].z, fy = m.v[2].w;
-    // reverse: p' = p + s (cos theta', sin theta')
-    const float athn = fmaf(r.step_len, fmaf(cn, apy, -(sn * apx)), ath);
-    // theta' = theta + turn(theta, g) + noise
-    ath = athn;
-    agx = agy = 0.0f;
-    if (!turn_capped(r, cross, along)) {
-        const float den = fmaf(along, along, cross * cross);
-        const float a_cross = athn * along / den, a_along = -athn * cross / den;
-        const float dot = fmaf(c, gx, s * gy);
-        ath = fmaf(a_cross, -r.gain * dot, fmaf(a_along, cross, ath));
-        agx = r.gain * fmaf(a_along, c, -(a_cross * s));
-        agy = r.gain * fmaf(a_cross, c, a_along * s);
-    }
-    sample_tip_adjoint_2d(fx, fy, m.v[3], m.v[4], r, x, y, r.sign0 * agx, r.sign0 * agy, apx,
-                          apy);
-    if (NS > 1)
-        sample_tip_adjoint_2d(fx, fy, m.v[kConePlanes + 2 * NS - 2],
-                              m.v[kConePlanes + 2 * NS - 1], r, x, y, r.sign1 * agx,
-                              r.sign1 * agy, apx, apy);
-}
 
 // Segments of a checkpointed run of n_steps steps from step n0, every `every` steps: run
 // step t's field state (after t steps) is fields + ((t - t_base) * n_species + s) * cells;
@@ -176,71 +117,11 @@ __global__ __launch_bounds__(kSegThreads) void k_cones_segments2d(ConeRules r, S
     }
 }
 
-// Last step of a segment (from step seg0, len steps) in which cone i takes part (-1: none):
-// none if it had stopped before the segment; status and event_step are the run's final ones,
-// and a cone stopped at step n takes part in steps < n only.
-__device__ __forceinline__ int last_step(uint32_t seg0, int len, const int32_t* start_status,
-                                         const int32_t* status, const int32_t* event_step,
-                                         int i) {
-    if (start_status[i] != kActive) return -1;
-    const int64_t last = status[i] == kActive ? INT64_MAX : (int64_t)event_step[i];
-    return (int)max<int64_t>(min<int64_t>(len - 1, last - 1 - (int64_t)seg0), -1);
-}
-
-// Reverse of one segment's cone steps, one thread per cone from the last step to the first;
-// the adjoint of step t's sampled gradient goes to ag[t * n + i] (zero at steps the cone takes
-// no part in).  The forward steps come from the cone tape, a streaming read kAhead steps
-// ahead, so that only what depends on the adjoint is left in the chain from step to step: 65
-// VALU instructions, two of them divisions.  (Before, each step gathered its 12 cells per
-// species from the run's fields, a 128-byte line for a few bytes, and computed the forward
-// step again: 115 us per 100 steps of 8192 cones.)
-// For every reverse launch (kRevSteps steps, from the segment's end) the box of the tips whose
-// samples have an adjoint goes to boxes[launch * n + i] (empty: x from above x to).
-constexpr int kAhead = 4;
-
 template <int NS>
-__global__ __launch_bounds__(kSegThreads) void k_cone_adjoint_segment2d(
-    ConeRules r, ConeTape tape, uint32_t seg0, int len, float2* __restrict__ ag,
-    float4* __restrict__ boxes, const int32_t* __restrict__ start_status,
-    const int32_t* __restrict__ status, const int32_t* __restrict__ event_step,
-    float* __restrict__ acone) {
-    const int n = tape.M;
+__global__ __launch_bounds__(kSegThreads) void k_cone_adjoint_segment2d(ConeRules r,
+                                                                        ConeChain c) {
     const int i = blockIdx.x * kSegThreads + threadIdx.x;
-    if (i >= n) return;
-    float apx = acone[3 * i], apy = acone[3 * i + 1], ath = acone[3 * i + 2];
-    const int t_hi = last_step(seg0, len, start_status, status, event_step, i);
-    const float4 none = make_float4(INFINITY, -INFINITY, INFINITY, -INFINITY);
-    float4 box = none;   // x from, x to, y from, y to
-    ConeTerms<NS> terms[kAhead];
-#pragma unroll
-    for (int a = 0; a < kAhead; ++a) terms[a].load(tape, max(len - 1 - a, 0), i);
-    // every cone walks all the steps (t is the same for the whole wavefront, so addresses are
-    // scalar work); a step it takes no part in leaves its adjoint alone
-    for (int t0 = len - 1; t0 >= 0; t0 -= kAhead) {
-#pragma unroll
-        for (int a = 0; a < kAhead; ++a) {
-            const int t = t0 - a;
-            if (t < 0) break;
-            const ConeTerms<NS> here = terms[a];
-            terms[a].load(tape, max(t - kAhead, 0), i);
-            float agx = 0.0f, agy = 0.0f;
-            if (t <= t_hi) {
-                cone_adjoint_step<NS>(r, here, apx, apy, ath, agx, agy);
-                if (agx != 0.0f || agy != 0.0f)
-                    box = make_float4(fminf(box.x, here.v[0].x), fmaxf(box.y, here.v[0].x),
-                                      fminf(box.z, here.v[0].y), fmaxf(box.w, here.v[0].y));
-            }
-            ag[(size_t)t * n + i] = make_float2(agx, agy);
-            const int k = len - 1 - t;
-            if (k % kRevSteps == kRevSteps - 1 || t == 0) {
-                boxes[(size_t)(k / kRevSteps) * n + i] = box;
-                box = none;
-            }
-        }
-    }
-    acone[3 * i] = apx;
-    acone[3 * i + 1] = apy;
-    acone[3 * i + 2] = ath;
+    if (i < c.tape.M) cone_chain<NS, 4>(r, c, i, c.len);
 }
 
 // Largest |adjoint| of the cells that one species' sample read.
@@ -330,21 +211,22 @@ hipError_t launch_cones_segments2d(const ConeRules& rules, const float* fields, 
     return hipGetLastError();
 }
 
-hipError_t launch_cone_adjoint_segment2d(const ReverseSegment& g, const int32_t* start_status,
-                                         const int32_t* status, const int32_t* event_step,
-                                         float* acone, hipStream_t stream) {
+hipError_t launch_cone_chain2d(const ConeRules& rules, const ConeChain& c, hipStream_t stream) {
+    if (c.t_from < 0 || c.tape.M == 0) return hipSuccess;
+    const dim3 grid((c.tape.M + kSegThreads - 1) / kSegThreads);
+    if (rules.n_species > 1)
+        hipLaunchKernelGGL(k_cone_adjoint_segment2d<2>, grid, dim3(kSegThreads), 0, stream, rules,
+                           c);
+    else
+        hipLaunchKernelGGL(k_cone_adjoint_segment2d<1>, grid, dim3(kSegThreads), 0, stream, rules,
+                           c);
+    return hipGetLastError();
+}
+
+hipError_t launch_sample_max2d(const ReverseSegment& g, hipStream_t stream) {
     const int n = g.M;
     if (g.len == 0 || n == 0) return hipSuccess;
-    const dim3 grid((n + kSegThreads - 1) / kSegThreads);
     const dim3 max_grid((n + kMaxCones - 1) / kMaxCones, g.len);
-    if (g.n_species > 1)
-        hipLaunchKernelGGL(k_cone_adjoint_segment2d<2>, grid, dim3(kSegThreads), 0, stream,
-                           g.rules, g.tape, g.seg0, g.len, g.ag, g.boxes, start_status,
-                           status, event_step, acone);
-    else
-        hipLaunchKernelGGL(k_cone_adjoint_segment2d<1>, grid, dim3(kSegThreads), 0, stream,
-                           g.rules, g.tape, g.seg0, g.len, g.ag, g.boxes, start_status,
-                           status, event_step, acone);
     hipLaunchKernelGGL(k_sample_max, max_grid, dim3(kMaxThreads), 0, stream, g.rules,
                        g.tape.base, g.ag, g.step_max, n);
     return hipGetLastError();

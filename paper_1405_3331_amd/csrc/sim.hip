@@ -52,7 +52,7 @@ struct AdjointRun {
         bool whole = false;             // the window is the whole run (else one segment)
         float* tape_own = nullptr;      // the window's field states when the run did not record
         float4* tape_cones = nullptr;   // the window's cone steps when the run did not record
-        float2* ag = nullptr;           // one segment's sample adjoints [K][M]
+        float2* ag = nullptr;           // two segments' sample adjoints [2][K][M]
         uint32_t* step_max = nullptr;   // [K]
         float4* boxes = nullptr;        // the cones' tips per launch, and the cones that touch
         int32_t* list_end = nullptr;    // each tile
@@ -1350,7 +1350,7 @@ sim_status sim_adjoint_backward(sim_handle* h, double* dL_dq, double* dL_dD, dou
         ((!recorded &&
           ((e = dalloc(&tape_own, (size_t)(window + 1) * ns * cells)) != hipSuccess ||
            (e = dalloc(&tape_cones, cone_tape_size(h, window))) != hipSuccess)) ||
-        (e = dalloc(&w.ag, (size_t)K * std::max<size_t>(Ms, 1))) != hipSuccess ||
+        (e = dalloc(&w.ag, (size_t)2 * K * std::max<size_t>(Ms, 1))) != hipSuccess ||
         (e = dalloc(&step_max, (size_t)K)) != hipSuccess ||
         (e = dalloc(&w.boxes, launches * std::max<size_t>(Ms, 1))) != hipSuccess ||
         (e = dalloc(&w.list_end, launches * fb)) != hipSuccess ||
@@ -1425,13 +1425,9 @@ sim_status sim_adjoint_backward(sim_handle* h, double* dL_dq, double* dL_dD, dou
         return r;
     };
     if (whole && !recorded) ADJ_TRY(rerun(0, 0, n_run, n_seg));
-    for (int j = n_seg - 1; j >= 0; --j) {
+    // segment j, and the chain of its cones from its last step
+    auto segment = [&](int j) {
         const int64_t t0 = (int64_t)j * a->every;
-        const int len = (int)std::min<int64_t>(a->every, n_run - t0);
-        if (!whole) {
-            t_base = t0;
-            ADJ_TRY(rerun(j, t0, len, 1));
-        }
         ReverseSegment g = {};
         g.rules = h->rules;
         for (int s = 0; s < ns; ++s) g.coef[s] = h->coef[s];
@@ -1439,12 +1435,12 @@ sim_status sim_adjoint_backward(sim_handle* h, double* dL_dq, double* dL_dD, dou
         g.ny = ny;
         g.n_species = ns;
         g.M = M;
-        g.len = len;
+        g.len = (int)std::min<int64_t>(a->every, n_run - t0);
         g.seg0 = (uint32_t)(a->n0 + t0);
         g.fields = field_at(t0, 0);
         g.tape = tape_of_cones;
         g.tape.base += (size_t)(t0 - t_base) * Ms;
-        g.ag = w.ag;
+        g.ag = w.ag + (size_t)(j & 1) * K * Ms;
         g.step_max = step_max;
         g.boxes = w.boxes;
         g.list_end = w.list_end;
@@ -1455,16 +1451,49 @@ sim_status sim_adjoint_backward(sim_handle* h, double* dL_dq, double* dL_dD, dou
         g.acc_q = acc_q;
         g.q_start = q_start;
         g.q_entry = q_entry;
+        return g;
+    };
+    auto chain_of = [&](int j, const ReverseSegment& g) {
+        ConeChain c = {};
+        c.tape = g.tape;
+        c.tape.M = M;
+        c.seg0 = g.seg0;
+        c.len = g.len;
+        c.t_from = g.len - 1;
+        c.ag = g.ag;
+        c.boxes = g.boxes;
+        c.start_status = a->ckpt_int + (size_t)j * 3 * Ms;
+        c.status = h->cones.status;
+        c.event_step = h->cones.event_step;
+        c.acone = a->acone;
+        return c;
+    };
+    // The cones' chain needs no field adjoint: with the whole run recorded, that of a segment
+    // runs beside the field steps of the segment after it, kRevSteps steps per launch (a few
+    // CUs for 55 us per 100 steps of 8192 cones otherwise).
+    ConeChain next = {};
+    next.t_from = -1;
+    for (int j = n_seg - 1; j >= 0; --j) {
+        if (!whole) {
+            const int64_t t0 = (int64_t)j * a->every;
+            t_base = t0;
+            ADJ_TRY(rerun(j, t0, std::min<int64_t>(a->every, n_run - t0), 1));
+        }
+        const ReverseSegment g = segment(j);
+        if (!whole || j == n_seg - 1) next = chain_of(j, g);
+        ADJ_TRY(launch_cone_chain2d(h->rules, next, h->stream));   // what is left of it
         ADJ_TRY(hipMemsetAsync(step_max, 0, (size_t)K * sizeof(uint32_t), h->stream));
-        // the segment's cone adjoints, the tiles they touch, then the field steps
-        ADJ_TRY(launch_cone_adjoint_segment2d(g, a->ckpt_int + (size_t)j * 3 * Ms,
-                                              h->cones.status, h->cones.event_step, a->acone,
-                                              h->stream));
+        ADJ_TRY(launch_sample_max2d(g, h->stream));
+        // the tiles the segment's cones touch, then the field steps
         ADJ_TRY(launch_reverse_lists(g, step_cells, h->stream));
-        for (int l = 0; l < reverse_launches(len); ++l) {
+        const bool beside = whole && j > 0 && M > 0;
+        if (beside) next = chain_of(j - 1, segment(j - 1));
+        for (int l = 0; l < reverse_launches(g.len); ++l) {
             const float* in[SIM_MAX_SPECIES] = {afield_at(0, cur), afield_at(ns - 1, cur)};
             float* out[SIM_MAX_SPECIES] = {afield_at(0, cur ^ 1), afield_at(ns - 1, cur ^ 1)};
-            ADJ_TRY(launch_field_reverse2d(g, l, in, out, h->stream));
+            const bool more = beside && next.t_from >= 0;
+            ADJ_TRY(launch_field_reverse2d(g, l, in, out, more ? &next : nullptr, h->stream));
+            if (more) next.t_from -= kRevSteps;
             cur ^= 1;
         }
     }
