@@ -148,13 +148,19 @@ __global__ __launch_bounds__(kMaxThreads) void k_sample_max(ConeRules r,
                                                             int n) {
     const int t = blockIdx.y;
     float m = 0.0f;
+    // every cone's loads first (an index past the end reads the last cone again)
+    constexpr int kEach = kMaxCones / kMaxThreads;
+    float2 gs[kEach], ps[kEach];
 #pragma unroll
-    for (int k = 0; k < kMaxCones / kMaxThreads; ++k) {
-        const int i = blockIdx.x * kMaxCones + k * kMaxThreads + threadIdx.x;
-        if (i >= n) break;
-        const float2 g = ag[(size_t)t * n + i];
+    for (int k = 0; k < kEach; ++k) {
+        const int i = min((int)(blockIdx.x * kMaxCones + k * kMaxThreads + threadIdx.x), n - 1);
+        gs[k] = ag[(size_t)t * n + i];
+        ps[k] = *(const float2*)(tips + (size_t)t * n + i);
+    }
+#pragma unroll
+    for (int k = 0; k < kEach; ++k) {
+        const float2 g = gs[k], p = ps[k];
         if (g.x == 0.0f && g.y == 0.0f) continue;
-        const float2 p = *(const float2*)(tips + (size_t)t * n + i);
         m = fmaxf(m, sample_max(r, p, r.sign0 * g.x, r.sign0 * g.y));
         if (r.n_species > 1) m = fmaxf(m, sample_max(r, p, r.sign1 * g.x, r.sign1 * g.y));
     }

@@ -445,20 +445,11 @@ __device__ __forceinline__ TileBox tiles_of(const ListArgs& a, float xa, float x
     return b;
 }
 
-// Calls each(tile) once for every tile that cone i is listed for in launch g: the tiles of its
-// box, or, where cones move so far that a box would cover many tiles that no sample touches,
-// those of each sample.
+// Calls each(tile) once for every tile that a sample of cone i touches in launch g (where cones
+// move so far that a box would cover many tiles that no sample touches).
 template <class Each>
 __device__ __forceinline__ void for_touched_tiles(const ListArgs& a, int i, int g,
                                                   const Each& each) {
-    if (a.boxed) {
-        const float4 p = a.boxes[(size_t)g * a.M + i];
-        if (!(p.x <= p.y)) return;
-        const TileBox b = tiles_of(a, p.x, p.y, p.z, p.w);
-        for (int ty = b.y1; ty <= b.y2; ++ty)
-            for (int tx = b.x1; tx <= b.x2; ++tx) each(ty * a.tiles_x + tx);
-        return;
-    }
     const int t_hi = a.len - 1 - g * kRevSteps;
     TileBox seen[kRevSteps];
 #pragma unroll
@@ -483,8 +474,10 @@ __device__ __forceinline__ void for_touched_tiles(const ListArgs& a, int i, int 
 
 // The lists of launch blockIdx.x, by one workgroup: cones counted per tile (in LDS where the
 // tiles fit: device-wide atomics and a scan of their own took 37 us per 100-step segment at
-// 8192 cones, this 22), the counts scanned to where each tile's cones start, and the cones put
-// there; a tile's start becomes its end (the next tile's start).  The order of a tile's cones
+// 8192 cones, this 16), the counts scanned to where each tile's cones start, and the cones put
+// there; a tile's start becomes its end (the next tile's start).  A thread requests the boxes of
+// kKeep cones together and keeps their tiles for the second pass (one cone after the other, read
+// twice: 22 us).  The order of a tile's cones
 // does not matter: their contributions are added as integers.
 template <bool LDS>
 __global__ __launch_bounds__(kListThreads) void k_tile_lists(ListArgs a) {
@@ -506,8 +499,37 @@ __global__ __launch_bounds__(kListThreads) void k_tile_lists(ListArgs a) {
     };
     for (int k = tid; k < n; k += kListThreads) set(k, 0);
     __syncthreads();
-    for (int i = tid; i < a.M; i += kListThreads)
-        for_touched_tiles(a, i, g, [&](int tile) { atomicAdd(&count[tile], 1); });
+    // the tiles of the boxes of cones base + u * kListThreads + tid
+    constexpr int kKeep = 8, kChunk = kKeep * kListThreads;
+    TileBox kept[kKeep];
+    auto keep = [&](int base) {
+        float4 p[kKeep];
+#pragma unroll
+        for (int u = 0; u < kKeep; ++u)
+            p[u] = a.boxes[(size_t)g * a.M + min(base + u * kListThreads + tid, a.M - 1)];
+#pragma unroll
+        for (int u = 0; u < kKeep; ++u) {
+            const bool any = base + u * kListThreads + tid < a.M && p[u].x <= p[u].y;
+            kept[u] = any ? tiles_of(a, p[u].x, p[u].y, p[u].z, p[u].w) : TileBox{1, 0, 1, 0};
+        }
+    };
+    auto for_kept = [&](int base, auto each) {   // each(cone, tile)
+#pragma unroll
+        for (int u = 0; u < kKeep; ++u)
+            for (int ty = kept[u].y1; ty <= kept[u].y2; ++ty)
+                for (int tx = kept[u].x1; tx <= kept[u].x2; ++tx)
+                    each(base + u * kListThreads + tid, ty * a.tiles_x + tx);
+    };
+    const int last = a.M > 0 ? (a.M - 1) / kChunk * kChunk : -1;   // the last chunk's first cone
+    if (a.boxed) {
+        for (int base = 0; base <= last; base += kChunk) {
+            keep(base);
+            for_kept(base, [&](int, int tile) { atomicAdd(&count[tile], 1); });
+        }
+    } else {
+        for (int i = tid; i < a.M; i += kListThreads)
+            for_touched_tiles(a, i, g, [&](int tile) { atomicAdd(&count[tile], 1); });
+    }
     __syncthreads();
     const int lane = tid & 63, wave = tid >> 6;
     int32_t carry = 0;
@@ -530,11 +552,19 @@ __global__ __launch_bounds__(kListThreads) void k_tile_lists(ListArgs a) {
         carry += total;
         __syncthreads();   // every thread has read wave_total
     }
-    for (int i = tid; i < a.M; i += kListThreads)
-        for_touched_tiles(a, i, g, [&](int tile) {
-            const int at = atomicAdd(&count[tile], 1);
-            if (at < a.cap) list[at] = i;   // (the capacity holds every cone's most tiles)
-        });
+    auto put = [&](int i, int tile) {
+        const int at = atomicAdd(&count[tile], 1);
+        if (at < a.cap) list[at] = i;   // (the capacity holds every cone's most tiles)
+    };
+    if (a.boxed) {
+        for (int base = last; base >= 0; base -= kChunk) {
+            if (base != last) keep(base);
+            for_kept(base, put);
+        }
+    } else {
+        for (int i = tid; i < a.M; i += kListThreads)
+            for_touched_tiles(a, i, g, [&](int tile) { put(i, tile); });
+    }
     if (LDS) {
         __syncthreads();
         for (int k = tid; k < n; k += kListThreads) out[k] = count[k];
