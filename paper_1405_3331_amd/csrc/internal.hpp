@@ -211,6 +211,13 @@ struct ConeChain {
     const int32_t* event_step;
     float* acone;   // [M][3]
 };
+// Column and row of a tile, tiles_x to a row.  A division, once per workgroup: the high word of
+// tile * ceil(2^32 / tiles_x) is one too large from tile * (ceil(2^32 / tiles_x) * tiles_x - 2^32)
+// = 2^32 on, which grids a few hundred thousand columns wide reach.
+__host__ __device__ __forceinline__ int2 tile_place(int tile, int tiles_x) {
+    const int row = tile / tiles_x;
+    return make_int2(tile - row * tiles_x, row);
+}
 int reverse_tiles(int nx, int ny);
 int reverse_launches(int len);
 // Entries that the list of one launch can need: M cones moving at most step_cells per step.

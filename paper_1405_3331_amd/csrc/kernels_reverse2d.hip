@@ -69,7 +69,6 @@ struct ReverseArgs {
     const float* fields;       // c^t of species s: fields + (t * n_species + s) * cells
     size_t cells;
     int n_species, nx, ny, tiles_x, n_tiles, per_xcd;
-    uint32_t tiles_x_inv;      // ceil(2^32 / tiles_x)
     int t_hi, steps;           // segment steps t_hi, t_hi - 1, .. are reversed
     int M;
     const float4* tips;        // [t][M]: tip (x, y, ..) at the start of step t
@@ -228,8 +227,8 @@ __global__ __launch_bounds__(kThreads, 4) void k_field_reverse2d(ReverseArgs a) 
     }
     const int tile = (blockIdx.x % kXcds) * a.per_xcd + blockIdx.x / kXcds, s = blockIdx.y;
     if (tile >= a.n_tiles) return;   // whole workgroup: the barriers stay uniform
-    const int ty = a.tiles_x > 1 ? (int)__umulhi((uint32_t)tile, a.tiles_x_inv) : tile;
-    const int tx = tile - ty * a.tiles_x;
+    const int2 place = tile_place(tile, a.tiles_x);
+    const int tx = place.x, ty = place.y;
     const int x0 = tx * kTX - kH, y0 = ty * kTY - kH;
     const int nx = a.nx, ny = a.ny, tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -668,7 +667,6 @@ hipError_t launch_field_reverse2d(const ReverseSegment& g, int launch, const flo
     a.nx = g.nx;
     a.ny = g.ny;
     a.per_xcd = (a.n_tiles + kXcds - 1) / kXcds;
-    a.tiles_x_inv = (uint32_t)(((1ull << 32) + a.tiles_x - 1) / a.tiles_x);
     a.t_hi = g.len - 1 - launch * kRevSteps;
     a.steps = std::min(kRevSteps, a.t_hi + 1);
     a.M = g.M;
