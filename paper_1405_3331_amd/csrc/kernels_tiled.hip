@@ -1113,12 +1113,25 @@ TiledPlan tiled_plan(int dim, int nx, int ny, int nz, int n_species, double step
                        alone);
 }
 
+// Whether a loaded height leaves a core that holds every cone for a launch of depth B, the tile in
+// LDS (the conditions of plan_search).
+static bool height_fits(const sim_params& p, int B, int cpl, int height) {
+    const double step_cells = p.step_len / p.dx;
+    const int H = halo_for(B, step_cells, cpl), W = 64 * cpl;
+    const int move = (int)std::ceil(B * step_cells + 1e-3);
+    const size_t row = (size_t)p.n_species * W * sizeof(float);
+    return W - 2 * H >= std::max(16, move + 1) && height - 2 * H >= std::max(16, move + 1) &&
+           height <= (int)(kLdsBudget / row) - kGuardRows;
+}
+
 // A launch of a batch takes its items' time over the workgroups that run at once.  An item of
 // height h takes T = 6 us + h (0.125 + 0.0118 B) us where two share a CU (fit over batches of
 // heights 56 .. 144 at depths 8 .. 16, two-column rows of one species), and 7 + B (1.1 + 0.0032 h)
 // where it has a CU to itself.  Planned as if it had the chip to itself, every simulation took
 // the smallest cores, 16 rows of 44 loaded: 128 simulations of side 64 .. 512 took 33.6 us per
 // step, with 144 rows at depth 8 13.9 and at depth 12 13.3.
+// A member's tile_height is its height, at depths where it fits; one that fits at no depth is
+// ignored.
 int tiled_batch_shape(const sim_params* const* params, int n, int cpl,
                       std::vector<int>& height) {
     const int n_species = params[0]->n_species, fixed = params[0]->block_steps;
@@ -1128,6 +1141,11 @@ int tiled_batch_shape(const sim_params* const* params, int n, int cpl,
     double best = 1e300;
     int depth = 0;
     height.assign(n, 0);
+    std::vector<int> hint(n, 0);
+    for (int i = 0; i < n; ++i)
+        for (int B = fixed != 0 ? fixed : kDeepest; B >= 2 && hint[i] == 0; --B)
+            if (height_fits(*params[i], B, cpl, params[i]->tile_height))
+                hint[i] = params[i]->tile_height;
     for (const int B : {16, 12, 8}) {
         if (fixed != 0 && B != 16) break;
         const int b = fixed != 0 ? fixed : B;
@@ -1141,10 +1159,15 @@ int tiled_batch_shape(const sim_params* const* params, int n, int cpl,
                 const double step_cells = p.step_len / p.dx;
                 const int H = halo_for(b, step_cells, cpl), TX = 64 * cpl - 2 * H;
                 const int least = std::max(16, (int)std::ceil(b * step_cells + 1e-3) + 1);
-                fits = TX >= least && 2 * H + least <= cap;
+                fits = hint[i] ? height_fits(p, b, cpl, hint[i])
+                               : TX >= least && 2 * H + least <= cap;
                 if (!fits) break;
-                const int tiles_y = ceil_div(p.ny, cap - 2 * H);
-                h[i] = 2 * H + std::max(least, ceil_div(p.ny, tiles_y));
+                if (hint[i]) {
+                    h[i] = hint[i];
+                } else {
+                    const int tiles_y = ceil_div(p.ny, cap - 2 * H);
+                    h[i] = 2 * H + std::max(least, ceil_div(p.ny, tiles_y));
+                }
                 const int tiles = ceil_div(p.nx, TX) * ceil_div(p.ny, h[i] - 2 * H);
                 const double t = 6.0 + h[i] * planes * (0.125 + 0.0118 * b);
                 items += tiles;

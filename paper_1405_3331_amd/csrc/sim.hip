@@ -1631,7 +1631,7 @@ sim_status sim_batch_create(const sim_params* const* params, int32_t n, void* hi
     for (int i = 0; i < n; ++i) {
         sim_params q = *params[i];
         if (q.block_steps == 0) q.block_steps = depth ? depth : kDefaultBlockSteps;
-        if (q.tile_height == 0 && depth) q.tile_height = height[i];
+        if (depth) q.tile_height = height[i];
         sim_handle* h = nullptr;
         sim_status st = create_impl(&q, b->stream, b->cpl, &h);
         if (st != SIM_OK) return bail(st);

@@ -78,7 +78,8 @@ TiledPlan tiled_plan(int dim, int nx, int ny, int nz, int n_species, double step
                      int block_steps, int n_cones, int force_cpl = 0, int force_height = 0,
                      bool alone = true);
 // Depth and tile heights for a batch of simulations with row width 64 * cpl: the depth (theirs
-// where they ask for one; 0 if no shape fits them all) and each simulation's loaded height.
+// where they ask for one; 0 if no shape fits them all) and each simulation's loaded height (its
+// tile_height where it gives one that fits at any depth).
 int tiled_batch_shape(const sim_params* const* params, int n, int cpl, std::vector<int>& height);
 // Allocate buckets and per-tile tables and upload the argument table; fields[s][b] are the
 // simulation's ping-pong field buffers, cones its caller-order arrays.
