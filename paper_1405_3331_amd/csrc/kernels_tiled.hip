@@ -1109,8 +1109,8 @@ TiledPlan tiled_plan(int dim, int nx, int ny, int nz, int n_species, double step
                                              alone);
         if (forced.block_steps > 1) return forced;
     }
-    return plan_search(dim, nx, ny, nz, n_species, step_cells, block_steps, n_cones, 0, 0,
-                       alone);
+    return plan_search(dim, nx, ny, nz, n_species, step_cells, block_steps, n_cones,
+                       alone ? 0 : force_cpl, 0, alone);
 }
 
 // Whether a loaded height leaves a core that holds every cone for a launch of depth B, the tile in
@@ -1187,6 +1187,33 @@ int tiled_batch_shape(const sim_params* const* params, int n, int cpl,
         }
     }
     return depth;
+}
+
+// (the other row width where the one asked for, or two columns per lane, leaves no common shape:
+// steps of 31 cells fit 256 columns at depth 2 and 128 at none)
+int tiled_batch_plan(const sim_params* const* params, int n, BatchPlan& plan) {
+    const int asked = params[0]->tile_cols_per_lane ? params[0]->tile_cols_per_lane : 2;
+    int misfit = -1;
+    for (const int cpl : {asked, 6 - asked}) {
+        std::vector<int> height;
+        const int depth = tiled_batch_shape(params, n, cpl, height);
+        int common = 0, i = 0;
+        for (; i < n; ++i) {
+            const sim_params& p = *params[i];
+            const int b = p.block_steps ? p.block_steps : depth ? depth : kDefaultBlockSteps;
+            if (depth == 0) height[i] = p.tile_height;
+            const TiledPlan t = tiled_plan(p.dim, p.nx, p.ny, 1, p.n_species, p.step_len / p.dx, b,
+                                           p.n_cones, cpl, height[i], false);
+            if (i == 0) common = t.block_steps;
+            if (t.block_steps <= 1 || t.block_steps != common) break;
+        }
+        if (i == n) {
+            plan = BatchPlan{cpl, common, height};
+            return -1;
+        }
+        if (cpl == asked) misfit = i;
+    }
+    return misfit;
 }
 
 hipError_t tiled_allocate(const TiledPlan& plan, TiledState& st, int n_cones,

@@ -1619,34 +1619,34 @@ sim_status sim_batch_create(const sim_params* const* params, int32_t n, void* hi
         b->own_stream = true;
     }
     b->n_species = params[0]->n_species;
-    b->cpl = params[0]->tile_cols_per_lane ? params[0]->tile_cols_per_lane : 2;
     int64_t total_cones = 0;
-    std::vector<int> height;
-    int depth = 0;
     for (int i = 0; i < n; ++i) {   // the shape is planned from checked parameters
         const sim_status st = validate(params[i]);
         if (st != SIM_OK) return bail(st);
     }
-    depth = tiled_batch_shape(params, n, b->cpl, height);
-    for (int i = 0; i < n; ++i) {
+    BatchPlan shape;
+    int misfit = tiled_batch_plan(params, n, shape);
+    b->cpl = shape.cpl;
+    for (int i = 0; i < n && misfit < 0; ++i) {
         sim_params q = *params[i];
-        if (q.block_steps == 0) q.block_steps = depth ? depth : kDefaultBlockSteps;
-        if (depth) q.tile_height = height[i];
+        q.block_steps = shape.block_steps;
+        q.tile_height = shape.height[i];
         sim_handle* h = nullptr;
         sim_status st = create_impl(&q, b->stream, b->cpl, &h);
         if (st != SIM_OK) return bail(st);
         b->sims.push_back(h);
-        if (h->block_steps <= 1 || h->plan.block_steps != b->sims[0]->plan.block_steps) {
-            char m[160];
-            snprintf(m, sizeof m, "simulation %d: no tiling with %d steps per launch fits", i,
-                     q.block_steps);
-            return bail(batch_fail(b, SIM_EINVAL, m));
-        }
+        // (the launch's kernel is that of one depth and row width)
+        if (h->block_steps != shape.block_steps || h->plan.cpl != b->cpl) misfit = i;
         b->lds_bytes = std::max(b->lds_bytes, h->plan.lds_bytes);
         b->n_base += h->plan.n_tiles;
         total_cones += h->n_cones;
     }
-    b->block_steps = b->sims[0]->plan.block_steps;
+    if (misfit >= 0) {
+        char m[160];
+        snprintf(m, sizeof m, "simulation %d: no tiling that fits all members fits it", misfit);
+        return bail(batch_fail(b, SIM_EINVAL, m));
+    }
+    b->block_steps = shape.block_steps;
     if (total_cones > INT32_MAX / 2)
         return bail(batch_fail(b, SIM_EINVAL, "too many cones in the batch"));
     b->extra_cap = tiled_extra_capacity(total_cones);

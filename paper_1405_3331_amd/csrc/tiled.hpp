@@ -73,7 +73,8 @@ struct TiledState {
 // result means no tiling fits.
 // force_cpl != 0 restricts the row width to 64 * force_cpl columns, force_height != 0 the
 // loaded tile height; a forced shape that does not fit falls back to the planner's choice.
-// alone: the simulation has launches of its own (a batch's members do not).
+// alone: the simulation has launches of its own; a batch's members do not, and the launch that
+// they share has one row width, so that only the height falls back.
 TiledPlan tiled_plan(int dim, int nx, int ny, int nz, int n_species, double step_cells,
                      int block_steps, int n_cones, int force_cpl = 0, int force_height = 0,
                      bool alone = true);
@@ -81,6 +82,13 @@ TiledPlan tiled_plan(int dim, int nx, int ny, int nz, int n_species, double step
 // where they ask for one; 0 if no shape fits them all) and each simulation's loaded height (its
 // tile_height where it gives one that fits at any depth).
 int tiled_batch_shape(const sim_params* const* params, int n, int cpl, std::vector<int>& height);
+// The row width, depth and heights with which every member of a batch can be planned.  Returns -1,
+// or a member that no common shape fits.
+struct BatchPlan {
+    int cpl = 2, block_steps = 0;
+    std::vector<int> height;
+};
+int tiled_batch_plan(const sim_params* const* params, int n, BatchPlan& plan);
 // Allocate buckets and per-tile tables and upload the argument table; fields[s][b] are the
 // simulation's ping-pong field buffers, cones its caller-order arrays.
 hipError_t tiled_allocate(const TiledPlan& plan, TiledState& st, int n_cones,

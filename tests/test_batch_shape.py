@@ -27,13 +27,15 @@ def shape(tmp_path_factory):
                     B.LIBRARY, f"-Wl,-rpath,{os.path.dirname(B.LIBRARY)}", "-o", exe],
                    check=True, capture_output=True, timeout=300)
 
-    def run(members, depth=0):
+    def run(members, depth=0, cols=0, whole=False):
         """(planned depth, [(depth, height) of every member]); members: (nx, ny, species, step,
-        cones, tile height)."""
+        cones, tile height).  whole: (misfit, width, depth, [(width, depth) of every member])."""
         args = [str(v) for m in members for v in m]
-        out = subprocess.run([exe, str(depth), *args], check=True, capture_output=True, text=True,
-                             timeout=60).stdout.split()
-        v = [int(x) for x in out]
+        out = subprocess.run([exe, str(depth), str(cols), *args], check=True, capture_output=True,
+                             text=True, timeout=60).stdout.splitlines()
+        v = [int(x) for x in out[1 if whole else 0].split()]
+        if whole:
+            return v[0], v[1], v[2], list(zip(v[3::2], v[4::2]))
         return v[0], list(zip(v[1::2], v[2::2]))
     return run
 
@@ -71,3 +73,24 @@ def test_with_a_depth_asked_for(shape):
     depth, plans = shape(_members((80, 0)), depth=12)
     assert depth == 12
     assert plans[0] == (12, 80) and plans[1][0] == 12
+
+
+@pytest.mark.parametrize("members,depth,cols,want", [
+    ([(600, 600, 1, 31.0, 500, 0)] * 3, 0, 0, (4, 2)),      # no core at 128 columns
+    ([(600, 600, 1, 31.0, 500, 0)] * 3, 0, 2, (4, 2)),
+    ([(300, 300, 1, 4.5, 500, 30)] * 2, 16, 0, (2, 8)),     # a height that fits nowhere
+    ([(300, 300, 1, 4.5, 500, 30)] * 2, 16, 4, (4, 9)),
+    ([(300, 300, 1, 0.5, 500, 0), (80, 90, 1, 3.0, 5, 0)], 0, 0, (2, 8)),
+    ([(300, 300, 2, 0.5, 500, 0)] * 2, 8, 4, (4, 8)),
+])
+def test_one_row_width(shape, members, depth, cols, want):
+    misfit, width, steps, plans = shape(members, depth, cols, whole=True)
+    assert misfit == -1 and (width, steps) == want
+    assert all(p == want for p in plans)
+
+
+def test_no_common_depth(shape):
+    """A member that no launch as deep as the others' fits, at either row width."""
+    members = [(600, 600, 1, 0.5, 500, 0), (600, 600, 1, 31.0, 500, 0)]
+    assert shape(members, whole=True)[0] == 1
+    assert shape([(600, 600, 1, 0.5, 500, 0), (600, 600, 1, 120.0, 500, 0)], whole=True)[0] == 1

@@ -30,3 +30,27 @@ def test_hinted_members(hints):
                 want, got = one.cones(), bt.cones(i)
                 for k in want:
                     np.testing.assert_array_equal(got[k], want[k])
+
+
+@pytest.mark.parametrize("n,step_len,depth,tile", [
+    ((600, 420), 31.0, 0, (0, 0)), ((300, 300), 4.5, 16, (0, 30)), ((300, 300), 4.5, 16, (4, 30)),
+    ((200, 150), 12.0, 0, (2, 0)),
+])
+def test_one_row_width(n, step_len, depth, tile):
+    """Shapes that leave no core at the width asked for (or at two columns per lane): the batch
+    takes the other width as a whole."""
+    print(f"[gpu] {n} step {step_len} depth {depth} tile {tile}", flush=True)
+    scs = [S.make_scenario("width", 2, n, 1.0, 0.2, ((1.0, 0.01, 1.0),), 5, (0.5, 2.0), 400, 12,
+                           step_len=step_len, seed=30 + i, sim_index=i) for i in range(2)]
+    for sc in scs:
+        sc.tile = tile
+    with B.Batch([copy.copy(sc) for sc in scs], block_steps=depth) as bt:
+        assert bt.tiling(0)["cols_per_lane"] == bt.tiling(1)["cols_per_lane"]
+        bt.step(29)
+        for i, sc in enumerate(scs):
+            with B.Simulation(sc, block_steps=1) as one:
+                one.step(29)
+                np.testing.assert_array_equal(bt.field(i), one.field())
+                want, got = one.cones(), bt.cones(i)
+                for k in want:
+                    np.testing.assert_array_equal(got[k], want[k])
