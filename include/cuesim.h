@@ -224,8 +224,9 @@ const char* sim_last_error(const sim_handle* h);
 /* Advance n_steps >= 0 steps (as sim_step does), checkpointing every checkpoint_every >= 1
  * steps, and return the loss in *loss (synchronises the stream).  assign[M] (target index
  * per cone, 0 <= assign[i] < n_targets) and weight[M] are host arrays copied during the
- * call.  Replaces any earlier record on the handle.  SIM_EINVAL for a 3D handle, bad
- * counts or indices, non-finite weights; SIM_ENOMEM if the checkpoints do not fit. */
+ * call.  Replaces any earlier record on the handle (a call that fails after its arguments were
+ * accepted leaves none).  SIM_EINVAL for a 3D handle, bad counts or indices, non-finite
+ * weights; SIM_ENOMEM if the checkpoints do not fit. */
 sim_status sim_adjoint_run(sim_handle* h, int64_t n_steps, int32_t checkpoint_every,
                            const int32_t* assign, const float* weight, double* loss);
 

@@ -1167,6 +1167,15 @@ static size_t adjoint_tape_limit(const sim_handle* h) {
     return (free_bytes + device_idle_bytes(h->device)) / 2;
 }
 
+// Drops the handle's record when it goes out of scope: that of a run that failed on the way holds
+// less than its length says.
+struct RecordUndo {
+    sim_handle* h;
+    ~RecordUndo() {
+        if (h) adjoint_release(h);
+    }
+};
+
 // Ends the recording of a run's field states (both paths) when it goes out of scope.
 struct RecordGuard {
     sim_handle* h = nullptr;
@@ -1206,6 +1215,7 @@ sim_status sim_adjoint_run(sim_handle* h, int64_t n_steps, int32_t checkpoint_ev
     AdjointRun* a = new (std::nothrow) AdjointRun();
     if (!a) return fail(h, SIM_ENOMEM, "adjoint record");
     h->adj = a;
+    RecordUndo undo{h};
     a->n0 = h->step;
     a->n_steps = n_steps;
     a->every = checkpoint_every;
@@ -1221,7 +1231,6 @@ sim_status sim_adjoint_run(sim_handle* h, int64_t n_steps, int32_t checkpoint_ev
         (e = dalloc(&a->weight, Ms)) != hipSuccess ||
         (e = dalloc(&a->acone, Ms * 3)) != hipSuccess ||
         (e = dalloc(&a->loss_partial, (size_t)cone_blocks(h))) != hipSuccess) {
-        adjoint_release(h);
         if (e == hipErrorOutOfMemory)
             return fail(h, SIM_ENOMEM, "adjoint checkpoints: out of device memory");
         return device_fail(h, e, "adjoint allocation");
@@ -1289,6 +1298,7 @@ sim_status sim_adjoint_run(sim_handle* h, int64_t n_steps, int32_t checkpoint_ev
     double L = 0.0;
     for (double v : part) L += v;
     *loss = M > 0 ? L : 0.0;
+    undo.h = nullptr;
     return SIM_OK;
 }
 
