@@ -70,14 +70,14 @@ __device__ __forceinline__ void cone_adjoint_step(const ConeRules& r, const Cone
 }
 
 // Last step of a segment (from step seg0, len steps) in which cone i takes part (-1: none):
-// none if it had stopped before the segment; status and event_step are the run's final ones,
-// and a cone stopped at step n takes part in steps < n only.
-__device__ __forceinline__ int last_step(uint32_t seg0, int len, const int32_t* start_status,
-                                         const int32_t* status, const int32_t* event_step,
-                                         int i) {
-    if (start_status[i] != kActive) return -1;
-    const int64_t last = status[i] == kActive ? INT64_MAX : (int64_t)event_step[i];
-    return (int)max<int64_t>(min<int64_t>(len - 1, last - 1 - (int64_t)seg0), -1);
+// none if it had stopped before the segment; a cone stopped at step n takes part in steps < n only,
+// by the run's end and by the handle's state.
+__device__ __forceinline__ int last_step(const ConeChain& c, int i) {
+    if (c.start_status[i] != kActive) return -1;
+    const int64_t now = c.status[i] == kActive ? INT64_MAX : (int64_t)c.event_step[i];
+    const int64_t run = c.run_status[i] == kActive ? INT64_MAX : (int64_t)c.run_event[i];
+    return (int)max<int64_t>(
+        min<int64_t>(c.len - 1, min<int64_t>(now, run) - 1 - (int64_t)c.seg0), -1);
 }
 
 // Reverse of cone i's steps c.t_from, c.t_from - 1, .., at most `most` of them; the adjoint of step
@@ -94,7 +94,7 @@ __device__ __forceinline__ void cone_chain(const ConeRules& r, const ConeChain& 
                                            int most) {
     const int n = c.tape.M, t_from = c.t_from, t_to = max(t_from - most + 1, 0);
     float apx = c.acone[3 * i], apy = c.acone[3 * i + 1], ath = c.acone[3 * i + 2];
-    const int t_hi = last_step(c.seg0, c.len, c.start_status, c.status, c.event_step, i);
+    const int t_hi = last_step(c, i);
     const float4 none = make_float4(INFINITY, -INFINITY, INFINITY, -INFINITY);
     float4 box = none;   // x from, x to, y from, y to
     ConeTerms<NS> terms[AHEAD];

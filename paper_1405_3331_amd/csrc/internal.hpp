@@ -199,7 +199,8 @@ struct ReverseSegment {
 // The reverse of a segment's cone steps from step t_from of its len (t_from = len - 1 - a multiple
 // of kRevSteps) on, for every cone of `tape` (the segment's steps): sample adjoints and boxes as
 // in ReverseSegment, the cones' own adjoints in acone.  start_status: the cones' status at the
-// segment's first step, seg0; status and event_step: at the run's end.
+// segment's first step, seg0; status and event_step: the handle's, run_status and run_event: at the
+// run's end (the tape holds no steps past a cone's stop, whatever was written since).
 struct ConeChain {
     ConeTape tape;
     uint32_t seg0;
@@ -209,6 +210,8 @@ struct ConeChain {
     const int32_t* start_status;
     const int32_t* status;
     const int32_t* event_step;
+    const int32_t* run_status;
+    const int32_t* run_event;
     float* acone;   // [M][3]
 };
 // Column and row of a tile, tiles_x to a row.  A division, once per workgroup: the high word of
@@ -248,8 +251,11 @@ hipError_t launch_cones_segments2d(const ConeRules& rules, const float* fields, 
 hipError_t launch_cone_chain2d(const ConeRules& rules, const ConeChain& c, hipStream_t stream);
 // Every step's largest contribution to a cell (step_max), once the segment's chain is done.
 hipError_t launch_sample_max2d(const ReverseSegment& g, hipStream_t stream);
-hipError_t launch_adjoint_seed2d(const float* pos, const float* tip_target, const float* weight,
-                                 float* acone, double* partial, int n, hipStream_t stream);
+// Loss partials and the seed of the cones' adjoints; with stop (2 n words) the cones' status and
+// event step go there.
+hipError_t launch_adjoint_seed2d(const ConeArrays& cones, const float* tip_target,
+                                 const float* weight, float* acone, double* partial,
+                                 int32_t* stop, hipStream_t stream);
 
 // Adjacency list of the connections and its breadth-first levels (kernels_graph.hip).
 struct GraphBuffers {

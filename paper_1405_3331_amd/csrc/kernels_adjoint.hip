@@ -174,11 +174,13 @@ __global__ __launch_bounds__(kMaxThreads) void k_sample_max(ConeRules r,
     }
 }
 
-// Loss at the final tips and the seed of the cone adjoints: a_p = 2 w (p - t), a_theta = 0.
+// Loss at the final tips and the seed of the cone adjoints: a_p = 2 w (p - t), a_theta = 0.  With
+// `stop`, status and event step of the n cones go there.
 __global__ __launch_bounds__(kAdjThreads) void k_adjoint_seed2d(
-    const float* __restrict__ pos, const float* __restrict__ tip_target,
+    const float* __restrict__ pos, const int32_t* __restrict__ status,
+    const int32_t* __restrict__ event_step, const float* __restrict__ tip_target,
     const float* __restrict__ weight, float* __restrict__ acone, double* __restrict__ partial,
-    int n) {
+    int32_t* __restrict__ stop, int n) {
     const int i = blockIdx.x * kAdjThreads + threadIdx.x;
     double l = 0.0;
     if (i < n) {
@@ -189,6 +191,10 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint_seed2d(
         acone[3 * i + 1] = 2.0f * w * dy;
         acone[3 * i + 2] = 0.0f;
         l = (double)w * ((double)dx * dx + (double)dy * dy);
+        if (stop) {
+            stop[i] = status[i];
+            stop[n + i] = event_step[i];
+        }
     }
     const double t = adj_block_sum(l);
     if (threadIdx.x == 0) partial[blockIdx.x] = t;
@@ -238,13 +244,15 @@ hipError_t launch_sample_max2d(const ReverseSegment& g, hipStream_t stream) {
     return hipGetLastError();
 }
 
-hipError_t launch_adjoint_seed2d(const float* pos, const float* tip_target, const float* weight,
-                                 float* acone, double* partial, int n, hipStream_t stream) {
+hipError_t launch_adjoint_seed2d(const ConeArrays& cones, const float* tip_target,
+                                 const float* weight, float* acone, double* partial,
+                                 int32_t* stop, hipStream_t stream) {
+    const int n = cones.n;
     if (n == 0) return hipSuccess;
     hipLaunchKernelGGL(k_adjoint_seed2d, dim3(adjoint_cone_blocks(n)), dim3(kAdjThreads), 0,
-                       stream, pos, tip_target, weight, acone, partial, n);
+                       stream, cones.pos, cones.status, cones.event_step, tip_target, weight,
+                       acone, partial, stop, n);
     return hipGetLastError();
 }
-
 
 }  // namespace cuesim

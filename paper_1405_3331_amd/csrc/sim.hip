@@ -38,6 +38,7 @@ struct AdjointRun {
     float* ckpt_pos = nullptr;          // [n_ckpt][M][2]
     float* ckpt_dir = nullptr;          // [n_ckpt][M]
     int32_t* ckpt_int = nullptr;        // [n_ckpt][3][M]: status, target, event_step
+    int32_t* stop = nullptr;            // [2][M]: status and event step at the run's end
     float* tip_target = nullptr;        // [M][2]: t_a(i)
     float* weight = nullptr;            // [M]
     float* acone = nullptr;             // [M][3]
@@ -216,6 +217,7 @@ void adjoint_release(sim_handle* h) {
     dfree(a->ckpt_pos);
     dfree(a->ckpt_dir);
     dfree(a->ckpt_int);
+    dfree(a->stop);
     dfree(a->tip_target);
     dfree(a->weight);
     dfree(a->acone);
@@ -1134,13 +1136,14 @@ namespace {
 static int64_t cone_blocks(const sim_handle* h) { return adjoint_cone_blocks(std::max(h->n_cones, 1)); }
 
 // Loss seed from the current (final) cone state: a_p = 2 w (p - t), a_theta = 0; the
-// per-workgroup loss partials are left in adj->loss_partial.
-static sim_status adjoint_seed(sim_handle* h) {
+// per-workgroup loss partials are left in adj->loss_partial.  At the run's end (`stop` given) also
+// where the cones stopped.
+static sim_status adjoint_seed(sim_handle* h, int32_t* stop = nullptr) {
     sim_status st = sync_cones(h);
     if (st != SIM_OK) return st;
     AdjointRun* a = h->adj;
-    HIP_TRY(h, launch_adjoint_seed2d(h->cones.pos, a->tip_target, a->weight, a->acone,
-                                     a->loss_partial, h->n_cones, h->stream));
+    HIP_TRY(h, launch_adjoint_seed2d(h->cones, a->tip_target, a->weight, a->acone,
+                                     a->loss_partial, stop, h->stream));
     return SIM_OK;
 }
 
@@ -1227,6 +1230,7 @@ sim_status sim_adjoint_run(sim_handle* h, int64_t n_steps, int32_t checkpoint_ev
         (e = dalloc(&a->ckpt_pos, nck * Ms * 2)) != hipSuccess ||
         (e = dalloc(&a->ckpt_dir, nck * Ms)) != hipSuccess ||
         (e = dalloc(&a->ckpt_int, nck * 3 * Ms)) != hipSuccess ||
+        (e = dalloc(&a->stop, 2 * Ms)) != hipSuccess ||
         (e = dalloc(&a->tip_target, Ms * 2)) != hipSuccess ||
         (e = dalloc(&a->weight, Ms)) != hipSuccess ||
         (e = dalloc(&a->acone, Ms * 3)) != hipSuccess ||
@@ -1288,7 +1292,7 @@ sim_status sim_adjoint_run(sim_handle* h, int64_t n_steps, int32_t checkpoint_ev
         st = sim_step(h, len);
         if (st != SIM_OK) return st;
     }
-    sim_status st = adjoint_seed(h);
+    sim_status st = adjoint_seed(h, a->stop);
     if (st != SIM_OK) return st;
     std::vector<double> part((size_t)cone_blocks(h), 0.0);
     if (M > 0)
@@ -1475,6 +1479,8 @@ sim_status sim_adjoint_backward(sim_handle* h, double* dL_dq, double* dL_dD, dou
         c.start_status = a->ckpt_int + (size_t)j * 3 * Ms;
         c.status = h->cones.status;
         c.event_step = h->cones.event_step;
+        c.run_status = a->stop;
+        c.run_event = a->stop + Ms;
         c.acone = a->acone;
         return c;
     };
