@@ -289,7 +289,7 @@ struct ConeRules {
 
 // Tip coordinate -> lower corner cell and fraction along one axis (cell centres at
 // (i + 1/2) dx; clamped so the tip is interpolated between in-grid centres).
-__device__ __forceinline__ void corner(float p, float inv_dx, int n, int& i0, float& f) {
+__host__ __device__ __forceinline__ void corner(float p, float inv_dx, int n, int& i0, float& f) {
     float u = fmaf(p, inv_dx, -0.5f);
     u = fminf(fmaxf(u, 0.0f), (float)(n - 1));
     i0 = min((int)floorf(u), n - 2);

@@ -564,10 +564,9 @@ __global__ __launch_bounds__(kListThreads) void k_tile_lists(ListArgs a) {
         for (int i = tid; i < a.M; i += kListThreads)
             for_touched_tiles(a, i, g, [&](int tile) { put(i, tile); });
     }
-    if (LDS) {
-        __syncthreads();
-        for (int k = tid; k < n; k += kListThreads) out[k] = count[k];
-    }
+    // (within the list's memory, whatever the tips: no entry past it was written)
+    __syncthreads();
+    for (int k = tid; k < n; k += kListThreads) out[k] = min(get(k), a.cap);
 }
 
 int tiles_along(int n, int core) { return (n + core - 1) / core; }
@@ -586,12 +585,16 @@ int reverse_launches(int len) { return (len + kRevSteps - 1) / kRevSteps; }
 
 // Most tiles a cone is listed for in one launch: the tiles that kRevSteps footprints of 4 x 4
 // cells touch, each on its own (apart), or their box, which covers at most span + 6 cells
-// along an axis (one for rounding) when the cone moves `span` cells.
+// along an axis (one for rounding) when the cone moves `span` cells.  The FP32 rounding of the
+// kRevSteps - 1 moves and of both ends' cells, half a unit in the last place each, is up to
+// (kRevSteps + 1) n 2^-24 cells on an axis of n: a tile more from some millions of cells on.
 static void tiles_per_cone(int nx, int ny, double step_cells, size_t& apart, size_t& boxed) {
     const int tx = tiles_along(nx, kTX), ty = tiles_along(ny, kTY);
     const double cells = (kRevSteps - 1) * step_cells + 6;
+    const double rounding = (kRevSteps + 1) * 0x1p-24;
     apart = (size_t)kRevSteps * tiles_touched(4, kTX, tx) * tiles_touched(4, kTY, ty);
-    boxed = (size_t)tiles_touched(cells, kTX, tx) * tiles_touched(cells, kTY, ty);
+    boxed = (size_t)tiles_touched(cells + nx * rounding, kTX, tx) *
+            tiles_touched(cells + ny * rounding, kTY, ty);
 }
 
 size_t reverse_list_capacity(int nx, int ny, int M, double step_cells) {
