@@ -221,6 +221,17 @@ __host__ __device__ __forceinline__ int2 tile_place(int tile, int tiles_x) {
     const int row = tile / tiles_x;
     return make_int2(tile - row * tiles_x, row);
 }
+// A launch over n_tiles tiles: per_slice workgroups (a multiple of the dies, which take contiguous
+// stretches) for each of `slices` slices of the grid's z axis, so that no axis has more than 2^32
+// threads (a row of cells 2^30 wide has 9.6 million tiles of 512 threads).
+struct ReverseGrid {
+    int slices, per_slice;
+    // tile of workgroup x of slice z (none from n_tiles on)
+    __host__ __device__ __forceinline__ int tile(int x, int z) const {
+        return z * per_slice + (x % 8) * (per_slice / 8) + x / 8;
+    }
+};
+ReverseGrid reverse_grid(int n_tiles);
 int reverse_tiles(int nx, int ny);
 int reverse_launches(int len);
 // Entries that the list of one launch can need: M cones moving at most step_cells per step.

@@ -393,7 +393,8 @@ hipError_t launch_cones3d_ordered(const ConeRules& r, const float* f0, const flo
 hipError_t launch_step3d(const ConeRules& r, ConeOrder3D& o, ConeArrays cones, uint32_t step,
                          const Field3DArgs& next, hipStream_t stream) {
     const int64_t bytes = (int64_t)next.n_species * next.nx * next.ny * next.nz * 4;
-    const bool dense = o.n > kSpreadCones && bytes <= kL2Bytes;
+    // (one wavefront in eight of a launch of fewer than 2^32 threads holds 2^28 cones)
+    const bool dense = (o.n > kSpreadCones && bytes <= kL2Bytes) || o.n > 1 << 28;
     const int per_wg = dense ? kBoxThreads3D : 64;
     const int cone_wgs = (o.n + per_wg * kXcds - 1) / (per_wg * kXcds);
     const dim3 grid((next.per_xcd + cone_wgs) * kXcds);

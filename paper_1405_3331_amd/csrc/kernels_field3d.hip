@@ -37,6 +37,7 @@ namespace {
 // species 50.4 / 41.4 / 43.4.
 constexpr int kDeep = 8;
 constexpr int kDeepBoxes = 256;   // CUs
+constexpr int64_t kMostBoxes = 1 << 22;
 
 struct Boxes {
     int tx, ty, tz, planes;   // boxes per axis, planes per box
@@ -48,6 +49,11 @@ Boxes boxes_for(int nx, int ny, int nz, int n_species) {
     if (n_species * b.per_species() < kDeepBoxes) {
         b.planes = kUnroll3D;
         b.tz = (nz + kUnroll3D - 1) / kUnroll3D;
+    }
+    // (a launch holds fewer than 2^32 threads: thin volumes of tens of millions of planes)
+    while (b.tz > 1 && (int64_t)n_species * b.tx * b.ty * b.tz > kMostBoxes) {
+        b.planes *= 2;
+        b.tz = (nz + b.planes - 1) / b.planes;
     }
     return b;
 }

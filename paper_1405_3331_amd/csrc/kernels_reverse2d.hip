@@ -52,7 +52,7 @@ constexpr int kH = kRevSteps;             // halo
 constexpr int kEdgeCore = 2, kMidCore = 3;
 constexpr int kTX = kW - 2 * kH, kTY = 2 * kEdgeCore + (kWaves - 2) * kMidCore;
 constexpr int kHL = kTY + 2 * kH;         // loaded height
-constexpr int kXcds = 8;
+constexpr int kXcds = 8;                  // (ReverseGrid)
 constexpr int kTileCones = kThreads / 4;  // cones of a tile whose steps are held in LDS: one
                                           // cone per four threads
 constexpr int kListThreads = 1024;
@@ -68,7 +68,8 @@ struct ReverseArgs {
     ConeRules rules;
     const float* fields;       // c^t of species s: fields + (t * n_species + s) * cells
     size_t cells;
-    int n_species, nx, ny, tiles_x, n_tiles, per_xcd;
+    int n_species, nx, ny, tiles_x, n_tiles;
+    ReverseGrid grid;
     int t_hi, steps;           // segment steps t_hi, t_hi - 1, .. are reversed
     int M;
     const float4* tips;        // [t][M]: tip (x, y, ..) at the start of step t
@@ -81,8 +82,7 @@ struct ReverseArgs {
     const int32_t* q_start;    // [species][tile + 1] into q_entry
     const int2* q_entry;       // (LDS cell in its tile, source number)
     double* acc_q;
-    ConeChain chain;           // kRevSteps steps of it, by the workgroups past tile_wgs
-    int tile_wgs;
+    ConeChain chain;           // kRevSteps steps of it, by the workgroups past the tiles'
 };
 
 // Sum of v over the wavefront, valid in lane 63: shifts within rows of 16 lanes, then the row
@@ -216,16 +216,16 @@ __global__ __launch_bounds__(kThreads, 4) void k_field_reverse2d(ReverseArgs a) 
     __shared__ __align__(16) unsigned long long sums[kHL * kW];
     __shared__ float4 cones[kRevSteps][kTileCones];   // (x, y, agx, agy), step t_hi - k in row k
     __shared__ double part[2][kWaves];
-    if ((int)blockIdx.x >= a.tile_wgs) {   // whole workgroup
-        const int i = (blockIdx.x - a.tile_wgs) * kThreads + threadIdx.x;
-        if (i >= a.chain.tape.M || blockIdx.y > 0) return;
+    if ((int)blockIdx.x >= a.grid.per_slice) {   // whole workgroup
+        const int i = (blockIdx.x - a.grid.per_slice) * kThreads + threadIdx.x;
+        if (i >= a.chain.tape.M || blockIdx.y > 0 || blockIdx.z > 0) return;
         if (a.n_species > 1)
             cone_chain<2, 2>(a.rules, a.chain, i, kRevSteps);
         else
             cone_chain<1, 2>(a.rules, a.chain, i, kRevSteps);
         return;
     }
-    const int tile = (blockIdx.x % kXcds) * a.per_xcd + blockIdx.x / kXcds, s = blockIdx.y;
+    const int tile = a.grid.tile(blockIdx.x, blockIdx.z), s = blockIdx.y;
     if (tile >= a.n_tiles) return;   // whole workgroup: the barriers stay uniform
     const int2 place = tile_place(tile, a.tiles_x);
     const int tx = place.x, ty = place.y;
@@ -581,6 +581,12 @@ int tiles_touched(double cells, int core, int tiles) {
 
 int reverse_tiles(int nx, int ny) { return tiles_along(nx, kTX) * tiles_along(ny, kTY); }
 
+ReverseGrid reverse_grid(int n_tiles) {
+    constexpr int kSlice = 1 << 20;
+    if (n_tiles <= kSlice) return ReverseGrid{1, (n_tiles + kXcds - 1) / kXcds * kXcds};
+    return ReverseGrid{(n_tiles + kSlice - 1) / kSlice, kSlice};
+}
+
 int reverse_launches(int len) { return (len + kRevSteps - 1) / kRevSteps; }
 
 // Most tiles a cone is listed for in one launch: the tiles that kRevSteps footprints of 4 x 4
@@ -669,7 +675,7 @@ hipError_t launch_field_reverse2d(const ReverseSegment& g, int launch, const flo
     a.n_species = g.n_species;
     a.nx = g.nx;
     a.ny = g.ny;
-    a.per_xcd = (a.n_tiles + kXcds - 1) / kXcds;
+    a.grid = reverse_grid(a.n_tiles);
     a.t_hi = g.len - 1 - launch * kRevSteps;
     a.steps = std::min(kRevSteps, a.t_hi + 1);
     a.M = g.M;
@@ -683,13 +689,12 @@ hipError_t launch_field_reverse2d(const ReverseSegment& g, int launch, const flo
     a.q_start = g.q_start;
     a.q_entry = g.q_entry;
     a.acc_q = g.acc_q;
-    a.tile_wgs = a.per_xcd * kXcds;
     int chain_wgs = 0;
     if (chain) {
         a.chain = *chain;
         chain_wgs = (chain->tape.M + kThreads - 1) / kThreads;
     }
-    const dim3 grid(a.tile_wgs + chain_wgs, g.n_species);
+    const dim3 grid(a.grid.per_slice + chain_wgs, g.n_species, a.grid.slices);
     if (g.nx % 2 == 0)
         hipLaunchKernelGGL(k_field_reverse2d<true>, grid, dim3(kThreads), 0, stream, a);
     else

@@ -1003,6 +1003,13 @@ TileShape shape_for(int n_species, int cpl, int height, int tiles, int n_cones, 
     return 2 * lds <= kLdsBudget && at_once <= 256 && sparse ? kTwo : kPair;
 }
 
+// Threads of a launch (at most: the parts' list is as long as every cone can make it), of which the
+// runtime takes fewer than 2^32: grids of some hundred million columns and few rows need wide tiles.
+int64_t launch_threads(int tiles, int n_cones, TileShape shape) {
+    const int64_t parts = std::max(tiled_extra_capacity(n_cones), 512);
+    return ((int64_t)ceil_div(tiles, kXcds) * kXcds + parts) * 64 * waves_of(shape);
+}
+
 // Microseconds per step of a plan, for the choice of the depth: a launch takes 7 us besides its
 // sub-steps, a sub-step 1.1 us (1.0 with two copies of the tile) and 3.2 ns per row of each
 // two-column species plane in its CU (a quarter more for 8 wavefronts alone there, which hide
@@ -1057,6 +1064,7 @@ TiledPlan plan_search(int dim, int nx, int ny, int nz, int n_species, double ste
                 const int per_cu = ceil_div(tiles, 256);
                 const TileShape shape = shape_for(n_species, cpl, HL, tiles, n_cones, lds,
                                                   alone);
+                if (launch_threads(tiles, n_cones, shape) > UINT32_MAX) continue;
                 const size_t used = two_copies(shape) ? 2 * lds : lds;
                 const int resident = sharing(used);
                 // per-step cost in cell-updates per compute unit: each tile's loaded area
