@@ -45,14 +45,15 @@ struct AdjointRun {
     double* loss_partial = nullptr;     // [cone workgroups]
     float* tape = nullptr;              // [n_steps + 1][n_species][n_cells]: every field state
                                         // of the run, recorded as it ran (null: not recorded)
-    float4* cone_tape = nullptr;        // and every cone step (ConeTape)
+    float4* cone_tape = nullptr;        // and every cone step (ConeTape; null: the fields alone)
     // The reverse sweep's workspace, allocated by its first call and kept for further calls
     // on the same record (freed with the record).
     struct Work {
         bool ready = false;
-        bool whole = false;             // the window is the whole run (else one segment)
-        float* tape_own = nullptr;      // the window's field states when the run did not record
-        float4* tape_cones = nullptr;   // the window's cone steps when the run did not record
+        bool whole = false;             // the field window is the whole run (else one segment)
+        int cone_segs = 1;              // segments of the cone window
+        float* tape_own = nullptr;      // the windows' field states and cone steps, where the run
+        float4* tape_cones = nullptr;   // did not record them
         float2* ag = nullptr;           // two segments' sample adjoints [2][K][M]
         uint32_t* step_max = nullptr;   // [K]
         float4* boxes = nullptr;        // the cones' tips per launch, and the cones that touch
@@ -527,7 +528,8 @@ sim_status plain_steps(sim_handle* h, int64_t n) {
                                          field2d_args(h->field2d, f, out, h->coef), h->stream));
             else
                 HIP_TRY(h, launch_cones2d(h->rules, f[0], f1, h->cones, step, h->stream,
-                                          h->record ? &h->cone_record : nullptr,
+                                          h->record && h->cone_record.base ? &h->cone_record
+                                                                           : nullptr,
                                           (size_t)(h->step - h->record_n0)));
         } else if (h->order3d.n > 0) {
             if (!h->cones_ordered) {
@@ -1156,10 +1158,16 @@ static ConeTape cone_tape_view(const sim_handle* h, float4* base, int64_t n_step
     return ConeTape{base, (size_t)n_steps * (size_t)h->n_cones, h->n_cones};
 }
 
-// Bytes of every field state of a run of n_steps and of its cone steps.
+// Bytes of every field state of a run of n_steps and of its cone steps; or of the field states and
+// a float4 per cone step, which go towards a window of several segments' cone steps.
+static size_t adjoint_field_bytes(const sim_handle* h, int64_t n_steps) {
+    return (size_t)(n_steps + 1) * (size_t)h->n_species * (size_t)h->n_cells * 4;
+}
 static size_t adjoint_whole_bytes(const sim_handle* h, int64_t n_steps) {
-    const size_t ns = (size_t)h->n_species, cells = (size_t)h->n_cells;
-    return (size_t)(n_steps + 1) * ns * cells * 4 + cone_tape_size(h, n_steps) * sizeof(float4);
+    return adjoint_field_bytes(h, n_steps) + cone_tape_size(h, n_steps) * sizeof(float4);
+}
+static size_t adjoint_fields_alone_bytes(const sim_handle* h, int64_t n_steps) {
+    return adjoint_field_bytes(h, n_steps) + (size_t)n_steps * (size_t)h->n_cones * sizeof(float4);
 }
 
 // The handle's tape limit (sim_adjoint_set_tape_limit), or half the free device memory.
@@ -1245,15 +1253,17 @@ sim_status sim_adjoint_run(sim_handle* h, int64_t n_steps, int32_t checkpoint_ev
         HIP_TRY(h, hipMemcpyAsync(a->weight, weight, Ms * 4, hipMemcpyHostToDevice, h->stream));
     }
     // When the whole run's states fit the tape limit, record every field state and cone step
-    // as the run goes; if the tape cannot be had, the sweep re-runs them from the checkpoints
-    // instead.
+    // as the run goes, or the field states alone where the cone steps do not fit beside them;
+    // what was not recorded, or whose tape cannot be had, the sweep re-runs from the checkpoints.
     RecordGuard recording;
-    if (a->n_ckpt > 1 && adjoint_whole_bytes(h, n_steps) < adjoint_tape_limit(h)) {
-        if (dalloc(&a->tape, (size_t)(n_steps + 1) * ns * cells) != hipSuccess ||
-            dalloc(&a->cone_tape, cone_tape_size(h, n_steps)) != hipSuccess) {
+    const size_t limit = a->n_ckpt > 1 ? adjoint_tape_limit(h) : 0;
+    if (adjoint_fields_alone_bytes(h, n_steps) < limit) {
+        if (dalloc(&a->tape, (size_t)(n_steps + 1) * ns * cells) != hipSuccess) {
             (void)hipGetLastError();
-            dfree(a->tape);
         } else {
+            if (adjoint_whole_bytes(h, n_steps) < limit &&
+                dalloc(&a->cone_tape, cone_tape_size(h, n_steps)) != hipSuccess)
+                (void)hipGetLastError();
             for (size_t s = 0; s < ns; ++s)
                 HIP_TRY(h, hipMemcpyAsync(a->tape + s * cells, h->field[s][h->cur[s]], cells * 4,
                                           hipMemcpyDeviceToDevice, h->stream));
@@ -1324,21 +1334,29 @@ sim_status sim_adjoint_backward(sim_handle* h, double* dL_dq, double* dL_dD, dou
     const int nq_all = n_q[0] + (ns > 1 ? n_q[1] : 0);
 
     // Workspace.  One segment's per-step sample adjoints and the lists of the cones that touch
-    // each tile, the field adjoint (ping-pong per species), FP64 accumulators and, when the run
-    // did not record them, the field states and cone steps of a window of steps: the whole run
-    // if it fits the limit after all (the fields are re-run once and the cone steps of every
-    // segment at once, one thread per segment and cone), else a segment after the other.
+    // each tile, the field adjoint (ping-pong per species), FP64 accumulators and what the run did
+    // not record of its field states and cone steps, for a window of segments: the whole run if
+    // both fit the limit after all (re-run once, one thread per segment and cone for the cones),
+    // else a segment after the other; with the field states recorded, as many segments' cone steps
+    // as a float4 per cone step of the run holds, and one more.
     const int n_seg = a->n_ckpt;
     const int64_t n_run = a->n_steps;
-    // the run recorded its field states and cone steps (sim_adjoint_run)
-    const bool recorded = a->tape != nullptr;
+    const bool fields_recorded = a->tape != nullptr, cones_recorded = a->cone_tape != nullptr;
     AdjointRun::Work& w = a->work;
     const bool fresh = !w.ready;   // first sweep of this record: allocate the workspace
-    if (fresh)
-        w.whole = recorded || (n_seg > 1 &&
-                               adjoint_whole_bytes(h, n_run) < adjoint_tape_limit(h));
+    if (fresh) {
+        constexpr int kMostSegs = 32768;   // of one re-run launch
+        const bool fits = n_seg > 1 && adjoint_whole_bytes(h, n_run) < adjoint_tape_limit(h);
+        w.whole = fields_recorded || fits;
+        w.cone_segs = cones_recorded ? n_seg
+                      : !w.whole     ? 1
+                      : fits         ? std::min(n_seg, kMostSegs)
+                                     : std::min(1 + n_seg / (kConePlanes + 2 * ns), kMostSegs);
+    }
     const bool whole = w.whole;
-    const int64_t window = whole ? n_run : K;
+    const int64_t window = whole ? n_run : K;   // steps: of the fields, and of the cones
+    const int64_t cone_window =
+        std::min<int64_t>(n_run, (int64_t)std::max(w.cone_segs, 1) * a->every);
     float*& tape_own = w.tape_own;
     float4*& tape_cones = w.tape_cones;
     uint32_t*& step_max = w.step_max;
@@ -1361,9 +1379,10 @@ sim_status sim_adjoint_backward(sim_handle* h, double* dL_dq, double* dL_dD, dou
     hipError_t e = hipSuccess;
     const size_t acc_n = (size_t)2 * ns * fb + (size_t)std::max(nq_all, 1);
     if (fresh &&
-        ((!recorded &&
-          ((e = dalloc(&tape_own, (size_t)(window + 1) * ns * cells)) != hipSuccess ||
-           (e = dalloc(&tape_cones, cone_tape_size(h, window))) != hipSuccess)) ||
+        ((!fields_recorded &&
+          (e = dalloc(&tape_own, (size_t)(window + 1) * ns * cells)) != hipSuccess) ||
+         (!cones_recorded &&
+          (e = dalloc(&tape_cones, cone_tape_size(h, cone_window))) != hipSuccess) ||
         (e = dalloc(&w.ag, (size_t)2 * K * std::max<size_t>(Ms, 1))) != hipSuccess ||
         (e = dalloc(&step_max, (size_t)K)) != hipSuccess ||
         (e = dalloc(&w.boxes, launches * std::max<size_t>(Ms, 1))) != hipSuccess ||
@@ -1404,18 +1423,17 @@ sim_status sim_adjoint_backward(sim_handle* h, double* dL_dq, double* dL_dD, dou
         free_all();
         return st;
     }
-    int64_t t_base = 0;   // run step whose field state is at the start of the window
-    float* const tape = recorded ? a->tape : tape_own;
+    int64_t t_base = 0;   // run step whose field state is at the start of the field window
+    float* const tape = fields_recorded ? a->tape : tape_own;
     auto field_at = [&](int64_t t, int s) {
         return tape + ((size_t)(t - t_base) * ns + s) * cells;
     };
     int cur = 0;
     auto afield_at = [&](int s, int half) { return afield + ((size_t)s * 2 + half) * cells; };
-    const ConeTape tape_of_cones =
-        recorded ? cone_tape_view(h, a->cone_tape, n_run) : cone_tape_view(h, tape_cones, window);
-    // re-run the fields of run steps [t0, t0 + len) from the checkpoint of segment j, and
-    // the cone steps of segments j .. j + n - 1 (a run that recorded them needs neither)
-    auto rerun = [&](int j, int64_t t0, int64_t len, int n) -> hipError_t {
+    const ConeTape tape_of_cones = cones_recorded ? cone_tape_view(h, a->cone_tape, n_run)
+                                                  : cone_tape_view(h, tape_cones, cone_window);
+    // re-run the fields of run steps [t0, t0 + len) from the checkpoint of segment j
+    auto rerun_fields = [&](int j, int64_t t0, int64_t len) -> hipError_t {
         hipError_t r = hipMemcpyAsync(field_at(t0, 0), a->ckpt_field + (size_t)j * ns * cells,
                                       (size_t)ns * cells * 4, hipMemcpyDeviceToDevice,
                                       h->stream);
@@ -1432,13 +1450,19 @@ sim_status sim_adjoint_backward(sim_handle* h, double* dL_dq, double* dL_dD, dou
             float* out[SIM_MAX_SPECIES] = {field_at(t + 1, 0), field_at(t + 1, ns - 1)};
             r = launch_field2d_rows(h->field2d, in, out, h->coef, h->stream);
         }
-        if (r == hipSuccess)
-            r = launch_cones_segments2d(h->rules, tape, cells, ns, (int)t_base, j, n, a->every,
-                                        (int)n_run, (uint32_t)a->n0, a->ckpt_pos, a->ckpt_dir,
-                                        a->ckpt_int, M, tape_of_cones, h->stream);
         return r;
     };
-    if (whole && !recorded) ADJ_TRY(rerun(0, 0, n_run, n_seg));
+    // and the cone steps of segments c_lo .. j, which the cone window then holds
+    int c_lo = cones_recorded ? 0 : n_seg;   // first segment in the window
+    auto rerun_cones = [&](int j) -> hipError_t {
+        c_lo = std::max(0, j - w.cone_segs + 1);
+        const int64_t c0 = (int64_t)c_lo * a->every;
+        return launch_cones_segments2d(h->rules, field_at(c0, 0), cells, ns, (int)c0, c_lo,
+                                       j - c_lo + 1, a->every, (int)n_run, (uint32_t)a->n0,
+                                       a->ckpt_pos, a->ckpt_dir, a->ckpt_int, M, tape_of_cones,
+                                       h->stream);
+    };
+    if (whole && !fields_recorded) ADJ_TRY(rerun_fields(0, 0, n_run));
     // segment j, and the chain of its cones from its last step
     auto segment = [&](int j) {
         const int64_t t0 = (int64_t)j * a->every;
@@ -1453,7 +1477,7 @@ sim_status sim_adjoint_backward(sim_handle* h, double* dL_dq, double* dL_dD, dou
         g.seg0 = (uint32_t)(a->n0 + t0);
         g.fields = field_at(t0, 0);
         g.tape = tape_of_cones;
-        g.tape.base += (size_t)(t0 - t_base) * Ms;
+        g.tape.base += (size_t)(t0 - (int64_t)c_lo * a->every) * Ms;
         g.ag = w.ag + (size_t)(j & 1) * K * Ms;
         g.step_max = step_max;
         g.boxes = w.boxes;
@@ -1484,25 +1508,26 @@ sim_status sim_adjoint_backward(sim_handle* h, double* dL_dq, double* dL_dD, dou
         c.acone = a->acone;
         return c;
     };
-    // The cones' chain needs no field adjoint: with the whole run recorded, that of a segment
-    // runs beside the field steps of the segment after it, kRevSteps steps per launch (a few
-    // CUs for 55 us per 100 steps of 8192 cones otherwise).
+    // The cones' chain needs no field adjoint: that of a segment whose cone steps are there already
+    // runs beside the field steps of the segment after it, kRevSteps steps per launch (a few CUs
+    // for 55 us per 100 steps of 8192 cones otherwise).
     ConeChain next = {};
     next.t_from = -1;
+    bool beside = false;   // the chain of segment j has begun
     for (int j = n_seg - 1; j >= 0; --j) {
         if (!whole) {
-            const int64_t t0 = (int64_t)j * a->every;
-            t_base = t0;
-            ADJ_TRY(rerun(j, t0, std::min<int64_t>(a->every, n_run - t0), 1));
+            t_base = (int64_t)j * a->every;
+            ADJ_TRY(rerun_fields(j, t_base, std::min<int64_t>(a->every, n_run - t_base)));
         }
+        if (j < c_lo) ADJ_TRY(rerun_cones(j));
         const ReverseSegment g = segment(j);
-        if (!whole || j == n_seg - 1) next = chain_of(j, g);
+        if (!beside) next = chain_of(j, g);
         ADJ_TRY(launch_cone_chain2d(h->rules, next, h->stream));   // what is left of it
         ADJ_TRY(hipMemsetAsync(step_max, 0, (size_t)K * sizeof(uint32_t), h->stream));
         ADJ_TRY(launch_sample_max2d(g, h->stream));
         // the tiles the segment's cones touch, then the field steps
         ADJ_TRY(launch_reverse_lists(g, step_cells, h->stream));
-        const bool beside = whole && j > 0 && M > 0;
+        beside = j > c_lo && M > 0;
         if (beside) next = chain_of(j - 1, segment(j - 1));
         for (int l = 0; l < reverse_launches(g.len); ++l) {
             const float* in[SIM_MAX_SPECIES] = {afield_at(0, cur), afield_at(ns - 1, cur)};

@@ -77,3 +77,40 @@ def test_states_written_after_the_run(species, limit):
         sim.write(B.CONE_EVENT_STEP, c["event_step"])
         for got, v in zip(sim.adjoint_backward(), want):
             np.testing.assert_array_equal(got, v)
+
+
+def _limits(sc, steps):
+    """Tape limits that hold everything, the field states and 16 bytes per cone step, nothing."""
+    fields = 4 * (steps + 1) * len(sc.species) * sc.n_cells
+    alone = fields + 16 * steps * sc.n_cones
+    whole = fields + (80 if len(sc.species) == 1 else 112) * steps * sc.n_cones
+    return {"all": whole + 1, "all but a byte": whole, "fields": alone + 1, "fields but a byte": alone,
+            "none": 1}
+
+
+@pytest.mark.parametrize("species", [1, 2])
+@pytest.mark.parametrize("steps,every,cones,block_steps", [
+    (10, 100, 70, 0), (70, 7, 513, 0), (90, 4, 64, 1), (41, 20, 700, 0), (33, 1, 40, 0),
+    (66, 33, 1200, 5), (130, 11, 3, 0),
+])
+def test_every_way_to_record(steps, every, cones, species, block_steps):
+    """Everything recorded, the field states alone (the cones re-run, windows of several segments
+    that do not divide the run), nothing, or nothing and then room for the whole run: the same loss
+    and gradient, bit for bit."""
+    print(f"[gpu] {steps} steps, every {every}, {cones} cones, {species} species", flush=True)
+    sc = _case(species, cones, seed=17)
+    assign, weight = np.arange(cones) % 20, np.linspace(0.5, 1.5, cones)
+    want = None
+    limits = _limits(sc, steps)
+    for name, after in [(k, None) for k in limits] + [("none", "all"), ("fields", "all"),
+                                                      ("all", "none"), ("none", "fields")]:
+        with B.Simulation(sc, block_steps=block_steps) as sim:
+            sim.set_tape_limit(limits[name])
+            out = [np.array(sim.adjoint(steps, assign, weight, every))]
+            if after:
+                sim.set_tape_limit(limits[after])
+            for _ in range(2):
+                got = out + [np.array(v) for v in sim.adjoint_backward()]
+                want = want or got
+                for g, v in zip(got, want):
+                    np.testing.assert_array_equal(g, v, err_msg=f"{name}, {after}")
