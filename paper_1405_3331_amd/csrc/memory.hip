@@ -38,6 +38,7 @@ struct Pool {
     std::multimap<std::pair<int, size_t>, std::list<Block>::iterator> by_size;
     size_t idle_bytes = 0;
     int users = 0;
+    std::vector<int32_t*> words;   // free pinned words
 
     void forget(std::list<Block>::iterator b) {
         auto r = by_size.equal_range({b->device, b->bytes});
@@ -133,6 +134,30 @@ void device_free(void* p) {
         out = q.trim(q.users > 0 ? kIdleBusy : kIdleRest);
     }
     give_back(out);
+}
+
+hipError_t pinned_word(int32_t** p) {
+    constexpr size_t kLine = 64, kPage = 4096;
+    *p = nullptr;
+    Pool& q = pool();
+    std::lock_guard<std::mutex> hold(q.lock);
+    if (q.words.empty()) {
+        char* page = nullptr;
+        const hipError_t e = hipHostMalloc((void**)&page, kPage, hipHostMallocPortable);
+        if (e != hipSuccess) return e;
+        for (size_t at = 0; at < kPage; at += kLine) q.words.push_back((int32_t*)(page + at));
+    }
+    *p = q.words.back();
+    q.words.pop_back();
+    **p = 0;
+    return hipSuccess;
+}
+
+void pinned_word_free(int32_t* p) {
+    if (!p) return;
+    Pool& q = pool();
+    std::lock_guard<std::mutex> hold(q.lock);
+    q.words.push_back(p);
 }
 
 size_t device_idle_bytes(int device) {

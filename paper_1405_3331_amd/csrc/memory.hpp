@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stdint.h>
 
 #include <cstring>
 #include <vector>
@@ -19,6 +20,12 @@ void device_free(void* p);
 size_t device_idle_bytes(int device);
 // An object that owns device memory begins or ends; between objects fewer idle blocks are kept.
 void device_memory_user(int change);
+
+// A zeroed word of pinned host memory, a line of its own, from pages that the library keeps (64
+// words each; allocating one takes longer than the rest of sim_create on a small grid).  Whatever
+// writes it must have finished when it is given back; nullptr is a no-op.
+hipError_t pinned_word(int32_t** p);
+void pinned_word_free(int32_t* p);
 
 // Several host arrays placed in one device block and uploaded by one copy: add() returns an
 // array's offset in the block.

@@ -86,7 +86,7 @@ struct sim_handle {
     int cur[SIM_MAX_SPECIES] = {0, 0};
     Field2DStep field2d = {};   // 2D un-blocked field step with its per-box source lists
     ConeArrays cones = {};
-    char* cone_memory = nullptr;     // the arrays of `cones`
+    char* cone_memory = nullptr;     // the arrays of `cones`, and the mass check's
     char* target_memory = nullptr;   // the target grid
     uint32_t* near_map = nullptr;    // and its near map
     double* mass_partial = nullptr;
@@ -264,10 +264,7 @@ void release(sim_handle* h) {
     dfree(h->cone_memory);
     dfree(h->target_memory);
     dfree(h->near_map);
-    dfree(h->mass_partial);
-    dfree(h->mass_out);
-    dfree(h->mass_flag);
-    if (h->mass_flag_host) (void)hipHostFree(h->mass_flag_host);
+    pinned_word_free(h->mass_flag_host);
     h->mass_flag_host = nullptr;
     if (h->mass_event) (void)hipEventDestroy(h->mass_event);
     h->mass_event = nullptr;
@@ -286,24 +283,6 @@ void poll_mass_check(sim_handle* h) {
     if (!h->mass_pending || hipEventQuery(h->mass_event) != hipSuccess) return;
     h->mass_pending = false;
     if (*(volatile int32_t*)h->mass_flag_host) h->nonfinite = true;
-}
-
-// The mass check's buffers, made by its first use.
-sim_status mass_prepare(sim_handle* h) {
-    if (h->mass_event) return SIM_OK;
-    dfree(h->mass_partial);   // (left by an earlier attempt)
-    dfree(h->mass_out);
-    dfree(h->mass_flag);
-    if (h->mass_flag_host) (void)hipHostFree(h->mass_flag_host);
-    h->mass_flag_host = nullptr;
-    HIP_TRY(h, dalloc(&h->mass_partial, kMassPartials));
-    HIP_TRY(h, dalloc(&h->mass_out, SIM_MAX_SPECIES));
-    HIP_TRY(h, dalloc(&h->mass_flag, 1));
-    HIP_TRY(h, hipMemsetAsync(h->mass_flag, 0, sizeof(int32_t), h->stream));
-    HIP_TRY(h, hipHostMalloc((void**)&h->mass_flag_host, sizeof(int32_t)));
-    *h->mass_flag_host = 0;
-    HIP_TRY(h, hipEventCreateWithFlags(&h->mass_event, hipEventDisableTiming));
-    return SIM_OK;
 }
 
 sim_status nonfinite_fail(sim_handle* h) {
@@ -664,7 +643,8 @@ sim_status create_impl(const sim_params* p, void* hip_stream, int force_cpl, sim
         const size_t at_pos = up.add(p->cone_pos, M * p->dim),
                      at_dir = up.add(p->cone_dir, M * dir_width(p->dim)),
                      at_status = up.add(active), at_target = up.add(minus1),
-                     at_event = up.add(minus1);
+                     at_event = up.add(minus1),
+                     at_mass = up.add(std::vector<double>(kMassPartials + SIM_MAX_SPECIES + 1));
         e = up.upload(&h->cone_memory);
         if (e != hipSuccess) return bail(device_fail(h, e, "cone upload"));
         h->cones.pos = (float*)(h->cone_memory + at_pos);
@@ -672,7 +652,14 @@ sim_status create_impl(const sim_params* p, void* hip_stream, int force_cpl, sim
         h->cones.status = (int32_t*)(h->cone_memory + at_status);
         h->cones.target = (int32_t*)(h->cone_memory + at_target);
         h->cones.event_step = (int32_t*)(h->cone_memory + at_event);
+        h->mass_partial = (double*)(h->cone_memory + at_mass);
+        h->mass_out = h->mass_partial + kMassPartials;
+        h->mass_flag = (int32_t*)(h->mass_out + SIM_MAX_SPECIES);
     }
+    // (made here, so that no later call of a mass check needs memory)
+    if ((e = pinned_word(&h->mass_flag_host)) != hipSuccess ||
+        (e = hipEventCreateWithFlags(&h->mass_event, hipEventDisableTiming)) != hipSuccess)
+        return bail(device_fail(h, e, "mass check set-up"));
     if (p->dim == 3)
         e = field3d_prepare(h->field3d, h->nx, h->ny, h->nz, h->n_species, h->src_merged_cell,
                             h->src_merged_q);
@@ -907,10 +894,6 @@ sim_status sim_set_mass_check(sim_handle* h, int64_t every) {
     if (!h) return fail(nullptr, SIM_EINVAL, "handle is NULL");
     if (h->poisoned) return fail(h, SIM_ESTATE, "handle poisoned by an earlier device error");
     if (every < 0) return fail(h, SIM_EINVAL, "every < 0");
-    if (every > 0) {
-        const sim_status st = mass_prepare(h);
-        if (st != SIM_OK) return st;
-    }
     h->mass_every = every;
     return SIM_OK;
 }
@@ -987,8 +970,6 @@ sim_status sim_read_state(sim_handle* h, sim_item what, int32_t index, void* dst
             return SIM_OK;
         }
         case SIM_MASS: {
-            st = mass_prepare(h);
-            if (st != SIM_OK) return st;
             for (int s = 0; s < h->n_species; ++s)
                 HIP_TRY(h, launch_mass(h->field[s][h->cur[s]], h->n_cells, h->mass_partial,
                                        kMassPartials, h->mass_out + s, h->stream));
