@@ -201,6 +201,13 @@ sim_status sim_synchronize(sim_handle* h);
  * (resources are released regardless). */
 sim_status sim_destroy(sim_handle* h);
 
+/* Give the device memory that released objects left for the next ones back to the driver (other
+ * allocators of the process can have it then).  The library keeps at most a sixteenth of a
+ * device's memory so while a simulation exists and 1 GiB otherwise, and gives it all back by
+ * itself when an allocation of its own fails.  May be called at any time, from any thread.
+ * SIM_EDEVICE if a HIP call failed. */
+sim_status sim_release_memory(void);
+
 /* Message for the last failed call on h, or for the calling thread's last failed
  * sim_create when h is NULL.  Library-owned, valid until the next call on h. */
 const char* sim_last_error(const sim_handle* h);

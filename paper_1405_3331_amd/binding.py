@@ -29,7 +29,8 @@ FIELD, CONE_POS, CONE_DIR, CONE_STATUS, CONE_TARGET, CONE_EVENT_STEP, EVENTS, MA
     COUNTS, KERNEL_TIME, TILING = range(12)
 
 EXPORTED = ["sim_create", "sim_step", "sim_set_mass_check", "sim_read_state",
-            "sim_write_state", "sim_device_ptr", "sim_set_timing", "sim_synchronize", "sim_destroy", "sim_last_error",
+            "sim_write_state", "sim_device_ptr", "sim_set_timing", "sim_synchronize", "sim_destroy",
+            "sim_release_memory", "sim_last_error",
             "sim_batch_create", "sim_batch_step", "sim_batch_read_state",
             "sim_batch_synchronize", "sim_batch_destroy", "sim_batch_last_error",
             "sim_adjoint_run", "sim_adjoint_backward", "sim_adjoint_set_tape_limit",
@@ -90,6 +91,7 @@ def load(path: str = LIBRARY):
     lib.sim_set_timing.argtypes = [H, C.c_int32]
     lib.sim_synchronize.argtypes = [H]
     lib.sim_destroy.argtypes = [H]
+    lib.sim_release_memory.argtypes = []
     lib.sim_last_error.argtypes = [H]
     lib.sim_last_error.restype = C.c_char_p
     lib.sim_batch_create.argtypes = [C.POINTER(C.POINTER(SimParams)), C.c_int32, C.c_void_p,
@@ -248,6 +250,11 @@ def sim_synchronize(h):
 
 def sim_destroy(h):
     _check(load().sim_destroy(h))
+
+
+def sim_release_memory():
+    """Device memory kept for the library's next objects, back to the driver."""
+    _check(load().sim_release_memory())
 
 
 def sim_last_error(h=None) -> str:

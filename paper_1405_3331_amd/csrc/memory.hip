@@ -3,17 +3,17 @@
 // A parameter fit creates and destroys a simulation per iteration and a gradient replaces its
 // record per run: the same sizes again and again.  From the runtime that costs about 40
 // allocations and as many frees per iteration (600 us, each free waiting for the device), and
-// memory given back to the driver is cleared before it can be had again (34 GB/s): a loop of
-// 2000-step gradients at 1024^2, with 10 GB of recorded states each, ran at 17 ms per pass
-// until the cleared memory was used up and at 250 ms from then on.
+// memory given back to the driver is cleared before it can be had again (34 GB/s, 250 ms for the
+// 8.4 GB of field states of 2000 steps at 1024^2).
 //
-// Idle blocks are bounded: kIdleBusy bytes while any object is alive, kIdleRest between
-// objects, the longest idle given back first; and all of a device's are given back when an
-// allocation fails.
+// Idle blocks are bounded: a sixteenth of a device's memory while any object is alive, kIdleRest
+// between objects, the longest idle given back first; all of a device's are given back when an
+// allocation fails, and all of them by release_device_memory.
 #include <algorithm>
 #include <list>
 #include <map>
 #include <mutex>
+#include <new>
 #include <unordered_map>
 
 #include "memory.hpp"
@@ -22,7 +22,7 @@ namespace cuesim {
 
 namespace {
 
-constexpr size_t kIdleBusy = (size_t)12 << 30;   // of 288 GB; the record of that gradient is 10
+constexpr size_t kBusyShare = 16;
 constexpr size_t kIdleRest = (size_t)1 << 30;
 
 struct Block {
@@ -31,12 +31,17 @@ struct Block {
     int device;
 };
 
+struct Device {
+    size_t idle = 0;   // bytes
+    size_t busy = 0;   // idle bytes to keep while an object lives (0: not asked for yet)
+};
+
 struct Pool {
     std::mutex lock;
     std::unordered_map<void*, Block> live;
     std::list<Block> idle;   // longest idle first
     std::multimap<std::pair<int, size_t>, std::list<Block>::iterator> by_size;
-    size_t idle_bytes = 0;
+    std::map<int, Device> devices;
     int users = 0;
     std::vector<int32_t*> words;   // free pinned words
 
@@ -47,15 +52,30 @@ struct Pool {
                 by_size.erase(k);
                 break;
             }
-        idle_bytes -= b->bytes;
+        devices[b->device].idle -= b->bytes;
         idle.erase(b);
     }
-    // Blocks to give back so that at most `limit` bytes stay (of `device` only, if >= 0).
-    std::vector<Block> trim(size_t limit, int device = -1) {
+    // Idle bytes to keep on a device as things are.
+    size_t limit(int device) {
+        Device& d = devices[device];
+        if (d.busy == 0) {
+            size_t total = 0;
+            if (hipDeviceTotalMem(&total, device) != hipSuccess) {
+                (void)hipGetLastError();
+                total = 0;
+            }
+            d.busy = std::max<size_t>(total / kBusyShare, 1);
+        }
+        return users > 0 ? d.busy : std::min(d.busy, kIdleRest);
+    }
+    // Blocks to give back so that no device (`device` only, if >= 0) keeps more than its limit,
+    // or any idle block at all.
+    std::vector<Block> trim(bool all, int device = -1) {
         std::vector<Block> out;
-        for (auto b = idle.begin(); b != idle.end() && idle_bytes > limit;) {
+        for (auto b = idle.begin(); b != idle.end();) {
             const auto next = std::next(b);
-            if (device < 0 || b->device == device) {
+            if ((device < 0 || b->device == device) &&
+                (all || devices[b->device].idle > limit(b->device))) {
                 out.push_back(*b);
                 forget(b);
             }
@@ -71,8 +91,13 @@ Pool& pool() {
     return *p;
 }
 
-void give_back(const std::vector<Block>& blocks) {
-    for (const Block& b : blocks) (void)hipFree(b.p);
+hipError_t give_back(const std::vector<Block>& blocks) {
+    hipError_t e = hipSuccess;
+    for (const Block& b : blocks) {
+        const hipError_t f = hipFree(b.p);
+        if (f != hipSuccess) e = f;
+    }
+    return e;
 }
 
 size_t rounded(size_t bytes) {
@@ -106,10 +131,10 @@ hipError_t device_malloc(void** p, size_t bytes) {
         std::vector<Block> out;
         {
             std::lock_guard<std::mutex> hold(q.lock);
-            out = q.trim(0, device);
+            out = q.trim(true, device);
         }
         if (out.empty()) return e;
-        give_back(out);
+        (void)give_back(out);
         e = hipMalloc(p, need);
         if (e != hipSuccess) return e;
     }
@@ -130,10 +155,20 @@ void device_free(void* p) {
         q.live.erase(k);
         const auto b = std::prev(q.idle.end());
         q.by_size.emplace(std::make_pair(b->device, b->bytes), b);
-        q.idle_bytes += b->bytes;
-        out = q.trim(q.users > 0 ? kIdleBusy : kIdleRest);
+        q.devices[b->device].idle += b->bytes;
+        if (q.devices[b->device].idle > q.limit(b->device)) out = q.trim(false, b->device);
     }
-    give_back(out);
+    (void)give_back(out);
+}
+
+hipError_t release_device_memory() {
+    Pool& q = pool();
+    std::vector<Block> out;
+    {
+        std::lock_guard<std::mutex> hold(q.lock);
+        out = q.trim(true);
+    }
+    return give_back(out);
 }
 
 hipError_t pinned_word(int32_t** p) {
@@ -163,9 +198,7 @@ void pinned_word_free(int32_t* p) {
 size_t device_idle_bytes(int device) {
     Pool& q = pool();
     std::lock_guard<std::mutex> hold(q.lock);
-    size_t n = 0;
-    for (const Block& b : q.idle) n += b.device == device ? b.bytes : 0;
-    return n;
+    return q.devices[device].idle;
 }
 
 void device_memory_user(int change) {
@@ -174,9 +207,9 @@ void device_memory_user(int change) {
     {
         std::lock_guard<std::mutex> hold(q.lock);
         q.users += change;
-        if (q.users == 0) out = q.trim(kIdleRest);
+        if (q.users == 0) out = q.trim(false);
     }
-    give_back(out);
+    (void)give_back(out);
 }
 
 }  // namespace cuesim

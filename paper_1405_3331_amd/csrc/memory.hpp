@@ -16,6 +16,8 @@ hipError_t device_malloc(void** p, size_t bytes);
 // Give a block back.  All device work that uses it must have finished: the next owner may
 // write it at once, on any stream.  nullptr is a no-op.
 void device_free(void* p);
+// Every idle block back to the runtime.
+hipError_t release_device_memory();
 // Bytes that idle blocks hold on a device (free memory that the runtime does not count).
 size_t device_idle_bytes(int device);
 // An object that owns device memory begins or ends; between objects fewer idle blocks are kept.

@@ -1107,6 +1107,12 @@ sim_status sim_destroy(sim_handle* h) {
     return SIM_OK;
 }
 
+sim_status sim_release_memory(void) {
+    const hipError_t e = release_device_memory();
+    if (e != hipSuccess) return device_fail(nullptr, e, "sim_release_memory");
+    return SIM_OK;
+}
+
 const char* sim_last_error(const sim_handle* h) {
     return h ? h->err.c_str() : g_create_error.c_str();
 }
