@@ -386,9 +386,8 @@ struct ConeTape {
     float4* base;
     size_t plane;
     int M;
-    // (a run that records its fields alone has no memory for the cones': the same for all threads)
     __device__ __forceinline__ void put(int j, size_t t, int i, float4 v) const {
-        if (base) base[j * plane + t * M + i] = v;
+        base[j * plane + t * M + i] = v;
     }
     __device__ __forceinline__ void sample(int s, size_t t, int i,
                                            const CornerGradients2D& g) const {

@@ -46,6 +46,7 @@ struct AdjointRun {
     float* tape = nullptr;              // [n_steps + 1][n_species][n_cells]: every field state
                                         // of the run, recorded as it ran (null: not recorded)
     float4* cone_tape = nullptr;        // and every cone step (ConeTape; null: the fields alone)
+    float4* cone_unkept = nullptr;      // [M]: where the run puts cone steps that are not kept
     // The reverse sweep's workspace, allocated by its first call and kept for further calls
     // on the same record (freed with the record).
     struct Work {
@@ -225,6 +226,7 @@ void adjoint_release(sim_handle* h) {
     dfree(a->loss_partial);
     dfree(a->tape);
     dfree(a->cone_tape);
+    dfree(a->cone_unkept);
     adjoint_work_release(a->work);
     delete a;
     h->adj = nullptr;
@@ -507,8 +509,7 @@ sim_status plain_steps(sim_handle* h, int64_t n) {
                                          field2d_args(h->field2d, f, out, h->coef), h->stream));
             else
                 HIP_TRY(h, launch_cones2d(h->rules, f[0], f1, h->cones, step, h->stream,
-                                          h->record && h->cone_record.base ? &h->cone_record
-                                                                           : nullptr,
+                                          h->record ? &h->cone_record : nullptr,
                                           (size_t)(h->step - h->record_n0)));
         } else if (h->order3d.n > 0) {
             if (!h->cones_ordered) {
@@ -1245,19 +1246,24 @@ sim_status sim_adjoint_run(sim_handle* h, int64_t n_steps, int32_t checkpoint_ev
     RecordGuard recording;
     const size_t limit = a->n_ckpt > 1 ? adjoint_tape_limit(h) : 0;
     if (adjoint_fields_alone_bytes(h, n_steps) < limit) {
-        if (dalloc(&a->tape, (size_t)(n_steps + 1) * ns * cells) != hipSuccess) {
+        if (adjoint_whole_bytes(h, n_steps) < limit &&
+            dalloc(&a->cone_tape, cone_tape_size(h, n_steps)) != hipSuccess)
             (void)hipGetLastError();
+        if ((!a->cone_tape && dalloc(&a->cone_unkept, std::max<size_t>(Ms, 1)) != hipSuccess) ||
+            dalloc(&a->tape, (size_t)(n_steps + 1) * ns * cells) != hipSuccess) {
+            (void)hipGetLastError();
+            dfree(a->cone_tape);
         } else {
-            if (adjoint_whole_bytes(h, n_steps) < limit &&
-                dalloc(&a->cone_tape, cone_tape_size(h, n_steps)) != hipSuccess)
-                (void)hipGetLastError();
             for (size_t s = 0; s < ns; ++s)
                 HIP_TRY(h, hipMemcpyAsync(a->tape + s * cells, h->field[s][h->cur[s]], cells * 4,
                                           hipMemcpyDeviceToDevice, h->stream));
             recording.h = h;
             h->record = a->tape;
             h->record_n0 = h->step;
-            h->cone_record = cone_tape_view(h, a->cone_tape, n_steps);
+            // (the recording kernels write every cone step's record: all of them into one, where
+            // they are not kept, since a branch there costs 6% of such a launch)
+            h->cone_record = a->cone_tape ? cone_tape_view(h, a->cone_tape, n_steps)
+                                          : ConeTape{a->cone_unkept, 0, 0};
             if (h->block_steps > 1)
                 tiled_set_record(h->tiled, a->tape, h->cone_record, (uint32_t)h->step);
         }

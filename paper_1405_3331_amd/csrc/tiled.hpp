@@ -98,7 +98,7 @@ hipError_t tiled_allocate(const TiledPlan& plan, TiledState& st, int n_cones,
 hipError_t tiled_set_launch_state(TiledState& st, uint32_t step, int parity, hipStream_t stream);
 // Record mode: while tape is non-null every launch also writes the state after each of its
 // sub-steps to tape + ((step - n0) * n_species + s) * cells and every cone step's record to
-// `cones` (step - n0), if that has memory (null: off).
+// `cones` (step - n0) (null: off).
 void tiled_set_record(TiledState& st, float* tape, const ConeTape& cones, uint32_t n0);
 void tiled_release(TiledState& st);
 // Move active cones from the caller-order arrays into the tile buckets (which hold none:
