@@ -209,8 +209,8 @@ struct Strip {
 };
 
 // ALIGNED: nx is even, so that a lane's two cells lie inside the grid's columns together and
-// are loaded and stored as one 8-byte value.
-template <bool ALIGNED>
+// are loaded and stored as one 8-byte value.  CROWDED: many cones for the grid (crowded_grid).
+template <bool ALIGNED, bool CROWDED>
 __global__ __launch_bounds__(kThreads, 4) void k_field_reverse2d(ReverseArgs a) {
     __shared__ __align__(16) float tile_a[(kHL + 2) * kW];     // row ly at (ly + 1) * kW
     __shared__ __align__(16) unsigned long long sums[kHL * kW];
@@ -278,7 +278,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_field_reverse2d(ReverseArgs a) 
 
     // the cones' contributions of sub-step k's step into the sums, and from there into the
     // tile: of all contributions to a cell the first to take its sum adds it, the others find
-    // zero (a crowded tile takes its further cones in turn)
+    // zero
     auto exponent = [&](int k) {
         return fixed_exponent((uint32_t)__builtin_amdgcn_readlane(max_bits, k));
     };
@@ -297,6 +297,17 @@ __global__ __launch_bounds__(kThreads, 4) void k_field_reverse2d(ReverseArgs a) 
             if (at[k] >= 0) atomicAdd(&sums[at[k]], (unsigned long long)n);
         }
     };
+    auto add_cone = [&](const float4& p, double scale) __attribute__((always_inline)) {
+        const Scatter2D c = sample_adjoint_2d(a.rules, p.x, p.y, sign * p.z, sign * p.w);
+#pragma unroll
+        for (int k = 0; k < 12; ++k) {
+            const int lx = c.i[k] - x0, ly = c.j[k] - y0;
+            const double x = (double)c.v[k] * scale;
+            const long long n = isfinite(x) ? (long long)rint(x) : 0;
+            if (n != 0 && (unsigned)lx < (unsigned)kW && (unsigned)ly < (unsigned)kHL)
+                atomicAdd(&sums[ly * kW + lx], (unsigned long long)n);
+        }
+    };
     auto take = [&](const int (&at)[3], double inv) {
         long long n[3];
         float v[3];
@@ -309,25 +320,48 @@ __global__ __launch_bounds__(kThreads, 4) void k_field_reverse2d(ReverseArgs a) 
             if (n[k] != 0) tile_a[kW + at[k]] = v[k] + (float)((double)n[k] * inv);
     };
     auto moving = [](const float4& p) { return p.z != 0.0f || p.w != 0.0f; };
-    auto add_step = [&](int k) {
+    auto add_step = [&](int k) __attribute__((always_inline)) {
         const double scale = ldexp(1.0, kFixedBits - exponent(k));
         mine[0] = mine[1] = mine[2] = -1;
         if (my_cone < n_list) {
             const float4 p = cones[k][my_cone];
             if (moving(p)) add(p, my_share, scale, mine);
         }
-        for (int m = kTileCones * kShares + tid; m < n_list * kShares; m += kThreads) {
-            const float4 p = load_cone(a.list[list_lo + m / kShares], a.t_hi - k);
-            int at[3];
-            if (moving(p)) add(p, m % kShares, scale, at);
+        if (!CROWDED) {   // the tile's further cones, four threads each as well
+            for (int m = kTileCones * kShares + tid; m < n_list * kShares; m += kThreads) {
+                const float4 p = load_cone(a.list[list_lo + m / kShares], a.t_hi - k);
+                int at[3];
+                if (moving(p)) add(p, m % kShares, scale, at);
+            }
+        } else if (n_list > kTileCones + (tid & ~63)) {   // a thread each (whole wavefronts)
+            // the next one's record and the number of the one after it travel meanwhile
+            auto number = [&](int m) { return a.list[list_lo + min(m, n_list - 1)]; };
+            int m = kTileCones + tid;
+            float4 p = load_cone(number(m), a.t_hi - k);
+            int i = number(m + kThreads);
+            for (; m < n_list; m += kThreads) {
+                const float4 q = load_cone(i, a.t_hi - k);
+                i = number(m + 2 * kThreads);
+                if (moving(p)) add_cone(p, scale);
+                p = q;
+            }
         }
     };
-    auto take_step = [&](int k) {
+    auto take_step = [&](int k) __attribute__((always_inline)) {
         const double inv = ldexp(1.0, exponent(k) - kFixedBits);
-        take(mine, inv);
-        for (int m = kTileCones * kShares + tid; m < n_list * kShares; m += kThreads) {
-            const float4 p = load_cone(a.list[list_lo + m / kShares], a.t_hi - k);
-            if (moving(p)) take(share_of(a.rules, sign, p, m % kShares, x0, y0).at, inv);
+        if (n_list <= kTileCones) {
+            take(mine, inv);
+            return;
+        }
+        // more cones than that: every cell of the tile is looked at
+        for (int c = tid; c < kHL * kW / 2; c += kThreads) {
+            const longlong2 n = *(longlong2*)&sums[2 * c];
+            if (n.x == 0 && n.y == 0) continue;
+            *(ulonglong2*)&sums[2 * c] = make_ulonglong2(0, 0);
+            V v = *(V*)&tile_a[kW + 2 * c];
+            if (n.x != 0) v.x += (float)((double)n.x * inv);
+            if (n.y != 0) v.y += (float)((double)n.y * inv);
+            *(V*)&tile_a[kW + 2 * c] = v;
         }
     };
     const bool core_col = cx >= kH && cx < kH + kTX;   // both cells (kH and kTX are even)
@@ -337,18 +371,21 @@ __global__ __launch_bounds__(kThreads, 4) void k_field_reverse2d(ReverseArgs a) 
     };
     // the sub-steps on this wavefront's strip, `ly0` its first row; every wavefront passes the
     // same barriers
-    auto sweep = [&](auto strip, int ly0) {
+    auto sweep = [&](auto strip, int ly0) __attribute__((always_inline)) {
         const int gy0 = y0 + ly0;
         strip.load_c(fields_at(a.t_hi), nx, ny, gy0, gx0);
         __syncthreads();
-        if (n_list > 0) {
-            add_step(0);
-            __syncthreads();
-            take_step(0);
-            __syncthreads();
-        }
         for (int k = 0; k < a.steps; ++k) {
             const int t = a.t_hi - k;
+            // the cones' adjoints of the step; the barrier also ends the strips' sub-step before
+            if (n_list > 0) {
+                add_step(k);
+                __syncthreads();
+                take_step(k);
+                __syncthreads();
+            } else if (k > 0) {
+                __syncthreads();
+            }
             // b^t is complete in the tile: its source cells, and this strip's rows
             if (src.x >= 0) q_sum += (double)tile_a[kW + src.x];
             for (int m = tid + kThreads; m < n_q; m += kThreads) {
@@ -358,14 +395,8 @@ __global__ __launch_bounds__(kThreads, 4) void k_field_reverse2d(ReverseArgs a) 
             strip.read(L, ly0);
             __syncthreads();
             strip.step(L, ly0, k, gy0, gx0, nx, ny, coef, core_col, pD, pk);
-            if (k + 1 == a.steps) break;
-            strip.load_c(fields_at(t - 1), nx, ny, gy0, gx0);   // one sub-step ahead of its use
-            if (n_list > 0) add_step(k + 1);
-            __syncthreads();
-            if (n_list > 0) {
-                take_step(k + 1);
-                __syncthreads();
-            }
+            // one sub-step ahead of its use
+            if (k + 1 < a.steps) strip.load_c(fields_at(t - 1), nx, ny, gy0, gx0);
         }
         strip.store(L, gbl(a.a_out[s]), ly0, gy0, gx0, nx, ny, core_col);
     };
@@ -581,6 +612,18 @@ int tiles_touched(double cells, int core, int tiles) {
 
 int reverse_tiles(int nx, int ny) { return tiles_along(nx, kTX) * tiles_along(ny, kTY); }
 
+// Whether a tile's loaded region holds so many cones on average that one thread should do all of a
+// cone past the first kTileCones: four threads work out its share of the weights four times, but
+// are done sooner where only the tiles at the sources hold that many.  Launch of eight steps, four
+// threads / one: 1024^2 with 8192 cones 22.3 / 23.6 us, 27,000 (128 to a tile) 39.0 / 40.2, 55,000
+// (255) 50.1 / 45.7, 110,000 79 / 59; 256^2 with 3500 23.9 / 24.3, 7000 (520) 35.5 / 31.2, 65,536
+// 131 / 54.  (One kernel with both takes 24.3 us for the first of these.)  While such cones were
+// added four threads each and taken from the sums by the same threads again: 23.0, 40.4, 60.6, 108,
+// 25.6, 42.1 and 195; the sums in HBM before that needed 130 for the last.
+static bool crowded_grid(int nx, int ny, int M) {
+    return (double)M * kHL * kW > 1.5 * kTileCones * nx * ny;
+}
+
 ReverseGrid reverse_grid(int n_tiles) {
     constexpr int kSlice = 1 << 20;
     if (n_tiles <= kSlice) return ReverseGrid{1, (n_tiles + kXcds - 1) / kXcds * kXcds};
@@ -695,10 +738,12 @@ hipError_t launch_field_reverse2d(const ReverseSegment& g, int launch, const flo
         chain_wgs = (chain->tape.M + kThreads - 1) / kThreads;
     }
     const dim3 grid(a.grid.per_slice + chain_wgs, g.n_species, a.grid.slices);
-    if (g.nx % 2 == 0)
-        hipLaunchKernelGGL(k_field_reverse2d<true>, grid, dim3(kThreads), 0, stream, a);
-    else
-        hipLaunchKernelGGL(k_field_reverse2d<false>, grid, dim3(kThreads), 0, stream, a);
+    const bool crowded = crowded_grid(g.nx, g.ny, g.M);
+    auto* const kernel = g.nx % 2 == 0 ? crowded ? k_field_reverse2d<true, true>
+                                                 : k_field_reverse2d<true, false>
+                         : crowded     ? k_field_reverse2d<false, true>
+                                       : k_field_reverse2d<false, false>;
+    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, stream, a);
     return hipGetLastError();
 }
 
