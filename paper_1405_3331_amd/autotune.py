@@ -2,10 +2,11 @@
 
 The library's planner picks the blocking depth B and the tile shape from a cost model.  This
 module measures instead: for a scenario it times whole runs (the scenario's step count, so
-that the late phase, when cones crowd around sources and targets, weighs in) of candidate
-(B, row width, tile height) settings on the GPU through the C ABI -- on fresh copies of the
-scenario, so nothing the caller holds is advanced -- and caches the fastest setting per size
-class in ``tile_cache.json`` next to this file.  For a batch (one shared B and row width,
+that the late phase, when cones crowd around sources and targets, weighs in) and their first
+tenth, which counts as much (calls of fewer steps are as common), of candidate (B, row width,
+tile height) settings on the GPU through the C ABI -- on fresh copies of the scenario, so nothing
+the caller holds is advanced -- and caches the fastest setting per size class in
+``tile_cache.json`` next to this file.  For a batch (one shared B and row width,
 and a tile height hint for every simulation) it times batch launches per candidate and
 records the fastest per batch class.
 
@@ -37,10 +38,13 @@ def size_class(sc) -> str:
 
 def default_candidates():
     """(block_steps, cols_per_lane, height) triples; height 0 = the planner's choice.  The
-    explicit heights keep two tiles resident per compute unit (LDS) at either row width;
-    144 rows is the tallest 64 x 2-column tile that does."""
-    return ([(b, 2, h) for b in (6, 8, 10, 12, 14, 16) for h in (0, 110, 130, 138, 144)] +
-            [(b, 4, h) for b in (6, 8, 12, 16) for h in (0, 70)])
+    explicit heights of two-column rows are those of two tiles to a compute unit's LDS (144 rows
+    is the tallest that does) or of two copies of one; of four-column rows, 70 for two tiles and
+    from 96 the tall ones that have an LDS to themselves (146 is the tallest)."""
+    return ([(b, 2, h) for b in (6, 8, 10, 12, 14, 16)
+             for h in (0, 64, 76, 90, 110, 130, 138, 144)] +
+            [(b, 4, h) for b in (6, 8, 10, 12, 14, 16)
+             for h in (0, 70, 96, 106, 116, 126, 132, 138, 142, 146)])
 
 
 def _time_single(sc, block, cpl, height, steps):
@@ -53,31 +57,38 @@ def _time_single(sc, block, cpl, height, steps):
         return None, tiling
     sim.step(block)                      # warm-up launch
     sim.synchronize()
+    first = max(steps // 10, 1)
     t0 = time.perf_counter()
-    sim.step(steps)
+    sim.step(first)
+    sim.synchronize()
+    early = (time.perf_counter() - t0) / first
+    sim.step(steps - first)
     sim.synchronize()
     dt = (time.perf_counter() - t0) / steps
     sim.close()
-    return dt, tiling
+    return (dt, early), tiling
 
 
 def tune(sc, candidates=None, steps=None, verbose=False) -> dict:
     """Time every candidate (block_steps, cols_per_lane, height; 0 = planner's height) over
-    `steps` steps (default: the scenario's run length) and return
-    {"best": (block, cpl, height), "seconds_per_step": ..., "trials": [...]}."""
+    `steps` steps (default: the scenario's run length) and their first tenth, and return
+    {"best": (block, cpl, height), "seconds_per_step": ..., "trials": [...]}: the candidate with the
+    smallest sum of the two times per step, and its time over all of them."""
     steps = int(steps or getattr(sc, "n_steps", 0) or 2000)
     trials = []
     for block, cpl, height in candidates or default_candidates():
-        dt, tiling = _time_single(sc, block, cpl, height, steps)
+        times, tiling = _time_single(sc, block, cpl, height, steps)
+        dt, early = times or (None, None)
         trials.append({"block_steps": block, "cols_per_lane": cpl, "height": tiling["height"],
-                       "seconds_per_step": dt})
+                       "seconds_per_step": dt, "early_seconds_per_step": early})
         if verbose:
-            print(f"[autotune] B={block} cpl={cpl} height={tiling['height']}: "
-                  f"{'n/a' if dt is None else f'{dt * 1e6:.2f} us/step'}", flush=True)
+            print(f"[autotune] B={block} cpl={cpl} height={tiling['height']}: " +
+                  ("n/a" if dt is None else f"{dt * 1e6:.2f} us/step, {early * 1e6:.2f} at first"),
+                  flush=True)
     ok = [t for t in trials if t["seconds_per_step"] is not None]
     if not ok:
         raise RuntimeError("no candidate tiling fits this scenario")
-    best = min(ok, key=lambda t: t["seconds_per_step"])
+    best = min(ok, key=lambda t: t["seconds_per_step"] + t["early_seconds_per_step"])
     return {"best": (best["block_steps"], best["cols_per_lane"], best["height"]),
             "seconds_per_step": best["seconds_per_step"], "trials": trials}
 
@@ -148,6 +159,7 @@ def record_batch(scenarios, result, path=CACHE):
         "height": result["best"][2], "seconds_per_step": result["seconds_per_step"]}
     with open(path, "w") as f:
         json.dump(cache, f, indent=1, sort_keys=True)
+        f.write("\n")
 
 
 def apply_batch(scenarios, path=CACHE) -> int:
@@ -176,6 +188,7 @@ def record(sc, result, path=CACHE):
                              "seconds_per_step": result["seconds_per_step"]}
     with open(path, "w") as f:
         json.dump(cache, f, indent=1, sort_keys=True)
+        f.write("\n")
 
 
 def lookup(sc, path=CACHE):
