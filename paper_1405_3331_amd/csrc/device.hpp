@@ -367,14 +367,6 @@ __device__ __forceinline__ void gradient_from_2d(const Footprint2D& p,
     if (value) *value = fmaf(w11, p.b2, fmaf(w01, p.b1, fmaf(w10, p.a2, w00 * p.a1)));
 }
 
-// Interpolated central-difference gradient of one species at (x, y).
-template <class F>
-__device__ __forceinline__ void gradient_2d(const F& f, const ConeRules& r, float x, float y,
-                                            float& gx, float& gy, float* value = nullptr) {
-    const Footprint2D p = footprint_2d(f, r, x, y);
-    gradient_from_2d(p, corner_gradients_2d(p, r), gx, gy, value);
-}
-
 // What the reverse of a cone step needs of the forward step, recorded as it runs: planes of one
 // float4 per step and cone, plane j of step t at base + j * plane + t * M (M cones).
 //   0  tip before the step, sine and cosine of the heading after it
@@ -494,13 +486,6 @@ __device__ __forceinline__ void gradient_from_3d(const ConeRules& r, const Corne
     gx *= r.half_inv_dx;
     gy *= r.half_inv_dx;
     gz *= r.half_inv_dx;
-}
-
-template <class F>
-__device__ __forceinline__ void gradient_3d(const F& f, const ConeRules& r, float x, float y,
-                                            float z, float& gx, float& gy, float& gz) {
-    const Corner3D k = corner_3d(r, x, y, z);
-    gradient_from_3d(r, k, load_footprint_3d(f, k), gx, gy, gz);
 }
 
 struct ConeEvent {

@@ -20,8 +20,6 @@ struct StencilCoef {
     float r, kdt;
 };
 
-// Per-species source entries (unique cells, amounts already divided by dx^dim).
-
 // Cone state in the caller's order (structure of arrays).
 struct ConeArrays {
     float* pos;          // [M][dim]
@@ -321,8 +319,6 @@ bool sort_in_alt(int key_bits);   // whether such a sort ends in the alternate a
 hipError_t sort_pairs(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t* vals_alt,
                       int n, int key_bits, int32_t* scratch, hipStream_t stream, bool* in_alt);
 
-// Sum of a field in FP64 (deterministic two-pass reduction) into *out (device); when
-// nonfinite is given, a non-finite sum sets *nonfinite = 1 (device).
 // Up to kMaxSpans device-to-device copies of whole 4-byte words in one launch: span k copies
 // word_end[k] - word_end[k - 1] words from src[k] to dst[k] (word_end is cumulative).
 constexpr int kMaxSpans = 8;
@@ -334,6 +330,8 @@ struct CopySpans {
 };
 hipError_t launch_copy_spans(const CopySpans& c, hipStream_t stream);
 
+// Sum of a field in FP64 (deterministic two-pass reduction) into *out (device); when
+// nonfinite is given, a non-finite sum sets *nonfinite = 1 (device).
 hipError_t launch_mass(const float* field, int64_t n, double* partial, int n_partial,
                        double* out, hipStream_t stream, int32_t* nonfinite = nullptr);
 constexpr int kMassPartials = 1024;

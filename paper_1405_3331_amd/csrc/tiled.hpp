@@ -19,8 +19,8 @@ struct TiledPlan {
     int dim = 2;
     int block_steps = 1;     // B: steps advanced per launch (1 = tiling unavailable)
     int halo = 0;            // H: cells loaded around each tile core
-    int core_x = 0, core_y = 0, core_z = 1;
-    int tiles_x = 0, tiles_y = 0, tiles_z = 1;
+    int core_x = 0, core_y = 0;
+    int tiles_x = 0, tiles_y = 0;
     int n_tiles = 0;
     int height = 0;          // loaded tile height (rows), core_y + 2 * halo
     int move = 0;            // cells a tip can travel in one launch, ceil(B * s / dx)
