@@ -1163,19 +1163,21 @@ int tiled_batch_plan(const sim_params* const* params, int n, BatchPlan& plan) {
     int misfit = -1;
     for (const int cpl : {asked, 6 - asked}) {
         std::vector<int> height;
+        std::vector<TiledPlan> members;
         const int depth = tiled_batch_shape(params, n, cpl, height);
         int common = 0, i = 0;
         for (; i < n; ++i) {
             const sim_params& p = *params[i];
             const int b = p.block_steps ? p.block_steps : depth ? depth : kDefaultBlockSteps;
-            if (depth == 0) height[i] = p.tile_height;
             const TiledPlan t = tiled_plan(p.dim, p.nx, p.ny, 1, p.n_species, p.step_len / p.dx, b,
-                                           p.n_cones, cpl, height[i], false);
+                                           p.n_cones, cpl, depth ? height[i] : p.tile_height,
+                                           false);
             if (i == 0) common = t.block_steps;
             if (t.block_steps <= 1 || t.block_steps != common) break;
+            members.push_back(t);
         }
         if (i == n) {
-            plan = BatchPlan{cpl, common, height};
+            plan = BatchPlan{cpl, common, members};
             return -1;
         }
         if (cpl == asked) misfit = i;

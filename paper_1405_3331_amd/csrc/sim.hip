@@ -555,8 +555,9 @@ sim_status tiled_steps(sim_handle* h, int64_t n) {
     return SIM_OK;
 }
 
-// sim_create with an optional forced tile row width (batches need one kernel variant).
-sim_status create_impl(const sim_params* p, void* hip_stream, int force_cpl, sim_handle** out) {
+// sim_create, with `member` as the tiling of a batch's member.
+sim_status create_impl(const sim_params* p, void* hip_stream, const TiledPlan* member,
+                       sim_handle** out) {
     if (!out) return fail(nullptr, SIM_EINVAL, "out is NULL");
     *out = nullptr;
     sim_status st = validate(p);
@@ -678,10 +679,10 @@ sim_status create_impl(const sim_params* p, void* hip_stream, int force_cpl, sim
     // temporal blocking plan
     h->block_steps = p->block_steps;   // 0: the planner's choice
     if (h->block_steps != 1) {
-        h->plan = tiled_plan(h->dim, h->nx, h->ny, h->nz, h->n_species, p->step_len / p->dx,
-                             h->block_steps, h->n_cones,
-                             force_cpl ? force_cpl : p->tile_cols_per_lane, p->tile_height,
-                             force_cpl == 0);
+        h->plan = member ? *member
+                         : tiled_plan(h->dim, h->nx, h->ny, h->nz, h->n_species,
+                                      p->step_len / p->dx, h->block_steps, h->n_cones,
+                                      p->tile_cols_per_lane, p->tile_height);
         h->plan.inv_dx = h->rules.inv_dx;
         for (int s = 0; s < h->n_species; ++s) h->plan.coef[s] = h->coef[s];
         if (h->plan.block_steps <= 1) {
@@ -853,7 +854,7 @@ extern "C" {
 
 
 sim_status sim_create(const sim_params* p, void* hip_stream, sim_handle** out) {
-    return create_impl(p, hip_stream, 0, out);
+    return create_impl(p, hip_stream, nullptr, out);
 }
 
 sim_status sim_step(sim_handle* h, int64_t n_steps) {
@@ -1659,28 +1660,25 @@ sim_status sim_batch_create(const sim_params* const* params, int32_t n, void* hi
         if (st != SIM_OK) return bail(st);
     }
     BatchPlan shape;
-    int misfit = tiled_batch_plan(params, n, shape);
-    b->cpl = shape.cpl;
-    for (int i = 0; i < n && misfit < 0; ++i) {
-        sim_params q = *params[i];
-        q.block_steps = shape.block_steps;
-        q.tile_height = shape.height[i];
-        sim_handle* h = nullptr;
-        sim_status st = create_impl(&q, b->stream, b->cpl, &h);
-        if (st != SIM_OK) return bail(st);
-        b->sims.push_back(h);
-        // (the launch's kernel is that of one depth and row width)
-        if (h->block_steps != shape.block_steps || h->plan.cpl != b->cpl) misfit = i;
-        b->lds_bytes = std::max(b->lds_bytes, h->plan.lds_bytes);
-        b->n_base += h->plan.n_tiles;
-        total_cones += h->n_cones;
-    }
+    const int misfit = tiled_batch_plan(params, n, shape);
     if (misfit >= 0) {
         char m[160];
         snprintf(m, sizeof m, "simulation %d: no tiling that fits all members fits it", misfit);
         return bail(batch_fail(b, SIM_EINVAL, m));
     }
+    b->cpl = shape.cpl;
     b->block_steps = shape.block_steps;
+    for (int i = 0; i < n; ++i) {
+        sim_params q = *params[i];
+        q.block_steps = shape.block_steps;
+        sim_handle* h = nullptr;
+        sim_status st = create_impl(&q, b->stream, &shape.members[i], &h);
+        if (st != SIM_OK) return bail(st);
+        b->sims.push_back(h);
+        b->lds_bytes = std::max(b->lds_bytes, h->plan.lds_bytes);
+        b->n_base += h->plan.n_tiles;
+        total_cones += h->n_cones;
+    }
     if (total_cones > INT32_MAX / 2)
         return bail(batch_fail(b, SIM_EINVAL, "too many cones in the batch"));
     b->extra_cap = tiled_extra_capacity(total_cones);

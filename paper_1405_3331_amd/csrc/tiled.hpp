@@ -82,11 +82,11 @@ TiledPlan tiled_plan(int dim, int nx, int ny, int nz, int n_species, double step
 // where they ask for one; 0 if no shape fits them all) and each simulation's loaded height (its
 // tile_height where it gives one that fits at any depth).
 int tiled_batch_shape(const sim_params* const* params, int n, int cpl, std::vector<int>& height);
-// The row width, depth and heights with which every member of a batch can be planned.  Returns -1,
-// or a member that no common shape fits.
+// The row width and depth with which every member of a batch can be planned, and their plans.
+// Returns -1, or a member that no common shape fits.
 struct BatchPlan {
     int cpl = 2, block_steps = 0;
-    std::vector<int> height;
+    std::vector<TiledPlan> members;
 };
 int tiled_batch_plan(const sim_params* const* params, int n, BatchPlan& plan);
 // Allocate buckets and per-tile tables and upload the argument table; fields[s][b] are the

@@ -45,9 +45,7 @@ int main(int argc, char** argv) {
     const int misfit = tiled_batch_plan(at.data(), n, plan);
     std::printf("%d %d %d", misfit, plan.cpl, plan.block_steps);
     for (int i = 0; i < n && misfit < 0; ++i) {
-        const TiledPlan t = tiled_plan(2, p[i].nx, p[i].ny, 1, p[i].n_species, p[i].step_len,
-                                       plan.block_steps, p[i].n_cones, plan.cpl, plan.height[i],
-                                       false);
+        const TiledPlan& t = plan.members[i];
         std::printf(" %d %d", t.cpl, t.block_steps);
     }
     std::printf("\n");
