@@ -87,7 +87,7 @@ struct sim_handle {
     int cur[SIM_MAX_SPECIES] = {0, 0};
     Field2DStep field2d = {};   // 2D un-blocked field step with its per-box source lists
     ConeArrays cones = {};
-    char* cone_memory = nullptr;     // the arrays of `cones`, and the mass check's
+    char* cone_memory = nullptr;     // the arrays of `cones`
     char* target_memory = nullptr;   // the target grid
     uint32_t* near_map = nullptr;    // and its near map
     double* mass_partial = nullptr;
@@ -266,6 +266,7 @@ void release(sim_handle* h) {
     dfree(h->cone_memory);
     dfree(h->target_memory);
     dfree(h->near_map);
+    dfree(h->mass_partial);   // and mass_out, mass_flag
     pinned_word_free(h->mass_flag_host);
     h->mass_flag_host = nullptr;
     if (h->mass_event) (void)hipEventDestroy(h->mass_event);
@@ -645,8 +646,7 @@ sim_status create_impl(const sim_params* p, void* hip_stream, const TiledPlan* m
         const size_t at_pos = up.add(p->cone_pos, M * p->dim),
                      at_dir = up.add(p->cone_dir, M * dir_width(p->dim)),
                      at_status = up.add(active), at_target = up.add(minus1),
-                     at_event = up.add(minus1),
-                     at_mass = up.add(std::vector<double>(kMassPartials + SIM_MAX_SPECIES + 1));
+                     at_event = up.add(minus1);
         e = up.upload(&h->cone_memory);
         if (e != hipSuccess) return bail(device_fail(h, e, "cone upload"));
         h->cones.pos = (float*)(h->cone_memory + at_pos);
@@ -654,12 +654,16 @@ sim_status create_impl(const sim_params* p, void* hip_stream, const TiledPlan* m
         h->cones.status = (int32_t*)(h->cone_memory + at_status);
         h->cones.target = (int32_t*)(h->cone_memory + at_target);
         h->cones.event_step = (int32_t*)(h->cone_memory + at_event);
-        h->mass_partial = (double*)(h->cone_memory + at_mass);
-        h->mass_out = h->mass_partial + kMassPartials;
-        h->mass_flag = (int32_t*)(h->mass_out + SIM_MAX_SPECIES);
     }
-    // (made here, so that no later call of a mass check needs memory)
-    if ((e = pinned_word(&h->mass_flag_host)) != hipSuccess ||
+    // The mass check's memory is made here, so that none of its calls needs any; a block of its own:
+    // behind the cones' it moves what follows in memory, and 100 simulations of 200 x 200 cells with
+    // 5000 cones each then step 15% slower in a batch.
+    e = dalloc(&h->mass_partial, kMassPartials + SIM_MAX_SPECIES + 1);
+    if (e != hipSuccess) return bail(device_fail(h, e, "mass check memory"));
+    h->mass_out = h->mass_partial + kMassPartials;
+    h->mass_flag = (int32_t*)(h->mass_out + SIM_MAX_SPECIES);
+    if ((e = hipMemsetAsync(h->mass_flag, 0, sizeof(int32_t), h->stream)) != hipSuccess ||
+        (e = pinned_word(&h->mass_flag_host)) != hipSuccess ||
         (e = hipEventCreateWithFlags(&h->mass_event, hipEventDisableTiming)) != hipSuccess)
         return bail(device_fail(h, e, "mass check set-up"));
     if (p->dim == 3)
