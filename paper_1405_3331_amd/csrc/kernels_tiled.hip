@@ -66,6 +66,9 @@ constexpr int kMaxTileTargets = 256;        // targets staged in LDS per tile
 constexpr size_t kLdsBudget = 154 * 1024;   // dynamic LDS; the rest is static (targets,
                                             // re-bucketing counters)
 constexpr int kLoadBatch = 10;              // tile rows a wavefront has in flight at load
+constexpr int kConeSlots = 1;               // cones per thread held in registers (as plain
+                                            // variables they are allotted other registers:
+                                            // 1000 x 600 1.81 us per step against 1.78)
 constexpr int kPartCones = 512;             // cones that a part steps (kWide: twice as many)
 constexpr size_t kStaticLds = kMaxTileTargets * 16 + 3 * 9 * 4 + 16;   // static LDS per tile
 constexpr int kSmallest = 192;              // and when a tile's cones are split furthest
@@ -563,14 +566,17 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& 
 
     // 0. the tile's count and header, its first sources (every wavefront keeps them, one per
     //    lane) and targets, and the first cone slots, requested together with the tile's
-    //    rows.  Every cone of the part stays in registers for the whole launch, cone i in
-    //    thread i.
+    //    rows.  Every cone of the part stays in registers for the whole launch: cone i sits
+    //    in thread i % kThreads, slot i / kThreads (a part holds at most kConeSlots *
+    //    kThreads cones).
     const bool first_part = w.part == 0;
     const GlobalPtr<const float4> live = gbl((const float4*)a.bucket[par]) +
                                          (size_t)tile * a.capacity;
     const bool spec = first_part && (int)threadIdx.x < min(kSpecCones, a.capacity);
-    float4 mine = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (spec) mine = gload(live + threadIdx.x);
+    float4 mine[kConeSlots];
+#pragma unroll
+    for (int k = 0; k < kConeSlots; ++k) mine[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (spec) mine[0] = gload(live + threadIdx.x);
     const int2 hs = gload(gbl(a.head_src) + (size_t)tile * kHeadItems + lane);
     float4 ht = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     if (wave == WAVES - 1) ht = gload(gbl(a.head_tgt) + (size_t)tile * kHeadItems + lane);
@@ -586,10 +592,14 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& 
         const int each = parts == 1 ? n_all : n_all / parts, more = n_all - each * parts;
         n_cones = each + (w.part < more ? 1 : 0);
         const int first = w.part * each + min(w.part, more);
-        if ((int)threadIdx.x < n_cones) {
-            if (!spec) mine = gload(live + first + (int)threadIdx.x);
-        } else {
-            mine.w = __int_as_float(-1);
+#pragma unroll
+        for (int k = 0; k < kConeSlots; ++k) {
+            const int i = threadIdx.x + k * kThreads;
+            if (i < n_cones) {
+                if (k > 0 || !spec) mine[k] = gload(live + first + i);
+            } else {
+                mine[k].w = __int_as_float(-1);
+            }
         }
     };
 
@@ -617,11 +627,16 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& 
         for (int k = kHeadItems + threadIdx.x; k < n_tt; k += kThreads)
             tile_targets[k] = gload(gbl(a.tgt_pts) + t_lo + k);
     }
-    // sin and cos of the heading, carried alongside the cone from sub-step to sub-step, and
+    // sin and cos of every heading, carried alongside the cone from sub-step to sub-step, and
     // the second half of the current Philox block
-    float2 trig = make_float2(0.0f, 1.0f);
-    uint2 spare = make_uint2(0u, 0u);
-    if ((int)threadIdx.x < n_cones) sincos_angle(mine.z, trig.x, trig.y);
+    float2 trig[kConeSlots];
+    uint2 spare[kConeSlots];
+#pragma unroll
+    for (int k = 0; k < kConeSlots; ++k) {
+        trig[k] = make_float2(0.0f, 1.0f);
+        spare[k] = make_uint2(0u, 0u);
+        if (threadIdx.x + k * kThreads < n_cones) sincos_angle(mine[k].z, trig[k].x, trig[k].y);
+    }
     if (threadIdx.x < 9) {
         dest_count[threadIdx.x] = 0;
         dest_fill[threadIdx.x] = 0;
@@ -642,6 +657,7 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& 
     const int r0 = max(0, -y0), r1 = min(HL, a.ny - y0);
     int ybeg = 0, yend = 0;
     {
+        static_assert(kConeSlots == 1, "one slot's cones are counted");
         const int cw = min(WAVES, (n_cones + 63) / 64);   // wavefronts holding a cone
         const float per = (float)(r1 - r0 + a.cone_rows * cw) / WAVES;
         int prev = r0;
@@ -722,10 +738,15 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& 
         if (n_cones > 0) {
             const LdsField2D f0{to + W, x0, y0, W, HL};
             const LdsField2D f1{to + (NS > 1 ? plane : 0) + W, x0, y0, W, HL};
-            const float3 g = tile_cone_gradient<NS, RECORD>(mine, f0, f1, rules, a.cone_record, rec);
+            float3 g[kConeSlots];
+#pragma unroll
+            for (int k = 0; k < kConeSlots; ++k)
+                g[k] = tile_cone_gradient<NS, RECORD>(mine[k], f0, f1, rules, a.cone_record, rec);
             if (!TWO) __syncthreads();
-            tile_cone_advance<RECORD>(mine, trig, spare, g, rules, step, b == 0, contact, a.cones,
-                                      a.cone_record, rec);
+#pragma unroll
+            for (int k = 0; k < kConeSlots; ++k)
+                tile_cone_advance<RECORD>(mine[k], trig[k], spare[k], g[k], rules, step, b == 0,
+                                          contact, a.cones, a.cone_record, rec);
         }
     }
 
@@ -735,12 +756,16 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& 
 
     // 6. re-bucket surviving cones, straight from registers, into the tile that now holds
     //    their tip (one of the 3 x 3 tiles around this one)
-    int dest = -1;
-    if ((int)threadIdx.x < n_cones && __float_as_int(mine.w) >= 0) {
-        const int2 nt = next_tile(mine, tx, ty, a.tiles_x, tiles_y, rules.inv_dx, a.nx, a.ny,
-                                  a.tx_core, a.ty_core);
-        dest = (nt.y - ty + 1) * 3 + (nt.x - tx + 1);
-        atomicAdd(&dest_count[dest], 1);
+    int dest[kConeSlots];
+#pragma unroll
+    for (int k = 0; k < kConeSlots; ++k) {
+        dest[k] = -1;
+        if (threadIdx.x + k * kThreads < n_cones && __float_as_int(mine[k].w) >= 0) {
+            const int2 nt = next_tile(mine[k], tx, ty, a.tiles_x, tiles_y, rules.inv_dx, a.nx,
+                                      a.ny, a.tx_core, a.ty_core);
+            dest[k] = (nt.y - ty + 1) * 3 + (nt.x - tx + 1);
+            atomicAdd(&dest_count[dest[k]], 1);
+        }
     }
     __syncthreads();
     if (threadIdx.x < 9 && dest_count[threadIdx.x] > 0) {
@@ -751,10 +776,13 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& 
         list_parts(lists, to, before, before + n);
     }
     __syncthreads();
-    if (dest >= 0) {
-        const int ntx = tx + dest % 3 - 1, nty = ty + dest / 3 - 1;
-        const int slot = dest_base[dest] + atomicAdd(&dest_fill[dest], 1);
-        gstore(gbl(bucket_out) + (size_t)(nty * a.tiles_x + ntx) * a.capacity + slot, mine);
+#pragma unroll
+    for (int k = 0; k < kConeSlots; ++k) {
+        const int d = dest[k];
+        if (d < 0) continue;
+        const int ntx = tx + d % 3 - 1, nty = ty + d / 3 - 1;
+        const int slot = dest_base[d] + atomicAdd(&dest_fill[d], 1);
+        gstore(gbl(bucket_out) + (size_t)(nty * a.tiles_x + ntx) * a.capacity + slot, mine[k]);
     }
     if (!LISTED && order == (int)gridDim.x - 1)
         advance_launch(lists.ls, first_step + (uint32_t)steps, par, w.phase);
