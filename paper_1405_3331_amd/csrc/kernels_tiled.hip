@@ -66,9 +66,11 @@ constexpr int kMaxTileTargets = 256;        // targets staged in LDS per tile
 constexpr size_t kLdsBudget = 154 * 1024;   // dynamic LDS; the rest is static (targets,
                                             // re-bucketing counters)
 constexpr int kLoadBatch = 10;              // tile rows a wavefront has in flight at load
-constexpr int kConeSlots = 1;               // cones per thread held in registers (as plain
-                                            // variables they are allotted other registers:
-                                            // 1000 x 600 1.81 us per step against 1.78)
+constexpr int kConeSlots = 1;               // cones per thread held in registers: a second
+                                            // one costs every tile (above).  Without the loops
+                                            // over them the kernels are allotted other registers:
+                                            // 128 x 128 2.6% faster, 777 x 389 with two species 1
+                                            // to 2% slower
 constexpr int kPartCones = 512;             // cones that a part steps (kWide: twice as many)
 constexpr size_t kStaticLds = kMaxTileTargets * 16 + 3 * 9 * 4 + 16;   // static LDS per tile
 constexpr int kSmallest = 192;              // and when a tile's cones are split furthest
@@ -650,19 +652,27 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& 
     if (first_part && threadIdx.x == 0) count_next[tile] = 0;
 
     // Strips of the tile's rows inside the grid, [r0, r1), per wavefront, balanced against
-    // the cone work: a wavefront stepping cones gives up cone_rows rows to the others, so that
-    // every wavefront does about the same work between two barriers.  Boundaries are computed for every wavefront in scalar registers
+    // the cone work: a wavefront stepping cones in k register slots gives up
+    // k * cone_rows rows to the others, so that every wavefront does about the same work
+    // between two barriers.  Boundaries are computed for every wavefront in scalar registers
     // and kept monotone.  Rows outside the grid are never computed: no cell inside the grid
     // reads them (at the grid's first and last row the missing neighbour is the row itself).
     const int r0 = max(0, -y0), r1 = min(HL, a.ny - y0);
     int ybeg = 0, yend = 0;
     {
-        static_assert(kConeSlots == 1, "one slot's cones are counted");
-        const int cw = min(WAVES, (n_cones + 63) / 64);   // wavefronts holding a cone
-        const float per = (float)(r1 - r0 + a.cone_rows * cw) / WAVES;
+        int cw[kConeSlots];   // wavefronts holding a cone in slot k
+        int slots = 0;
+#pragma unroll
+        for (int k = 0; k < kConeSlots; ++k) {
+            cw[k] = min(WAVES, (max(n_cones - k * kThreads, 0) + 63) / 64);
+            slots += cw[k];
+        }
+        const float per = (float)(r1 - r0 + a.cone_rows * slots) / WAVES;
         int prev = r0;
         for (int w = 1; w <= WAVES; ++w) {
-            const int used = a.cone_rows * min(w, cw);
+            int used = 0;
+#pragma unroll
+            for (int k = 0; k < kConeSlots; ++k) used += a.cone_rows * min(w, cw[k]);
             const int b = w == WAVES ? r1 : min(max(r0 + (int)rintf(w * per) - used, prev), r1);
             if (w == wave) ybeg = b;       // wavefront w's strip is [b(w), b(w + 1))
             if (w == wave + 1) yend = b;
