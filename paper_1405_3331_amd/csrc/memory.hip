@@ -34,6 +34,7 @@ struct Block {
 struct Device {
     size_t idle = 0;   // bytes
     size_t busy = 0;   // idle bytes to keep while an object lives (0: not asked for yet)
+    std::vector<HostFlag> flags;   // idle ones
 };
 
 struct Pool {
@@ -43,7 +44,7 @@ struct Pool {
     std::multimap<std::pair<int, size_t>, std::list<Block>::iterator> by_size;
     std::map<int, Device> devices;
     int users = 0;
-    std::vector<int32_t*> words;   // free pinned words
+    std::vector<int32_t*> words;   // pinned ones of no flag yet
 
     void forget(std::list<Block>::iterator b) {
         auto r = by_size.equal_range({b->device, b->bytes});
@@ -171,28 +172,41 @@ hipError_t release_device_memory() {
     return give_back(out);
 }
 
-hipError_t pinned_word(int32_t** p) {
+hipError_t host_flag(HostFlag* f) {
     constexpr size_t kLine = 64, kPage = 4096;
-    *p = nullptr;
+    *f = HostFlag{};
+    int device = 0;
+    hipError_t e = hipGetDevice(&device);
+    if (e != hipSuccess) return e;
     Pool& q = pool();
     std::lock_guard<std::mutex> hold(q.lock);
-    if (q.words.empty()) {
-        char* page = nullptr;
-        const hipError_t e = hipHostMalloc((void**)&page, kPage, hipHostMallocPortable);
+    std::vector<HostFlag>& idle = q.devices[device].flags;
+    if (idle.empty()) {
+        if (q.words.empty()) {
+            char* page = nullptr;
+            e = hipHostMalloc((void**)&page, kPage, hipHostMallocPortable);
+            if (e != hipSuccess) return e;
+            for (size_t at = 0; at < kPage; at += kLine) q.words.push_back((int32_t*)(page + at));
+        }
+        HostFlag n;
+        e = hipEventCreateWithFlags(&n.event, hipEventDisableTiming);
         if (e != hipSuccess) return e;
-        for (size_t at = 0; at < kPage; at += kLine) q.words.push_back((int32_t*)(page + at));
+        n.word = q.words.back();
+        n.device = device;
+        q.words.pop_back();
+        idle.push_back(n);
     }
-    *p = q.words.back();
-    q.words.pop_back();
-    **p = 0;
+    *f = idle.back();
+    idle.pop_back();
+    *f->word = 0;
     return hipSuccess;
 }
 
-void pinned_word_free(int32_t* p) {
-    if (!p) return;
+void host_flag_free(const HostFlag& f) {
+    if (!f.word) return;
     Pool& q = pool();
     std::lock_guard<std::mutex> hold(q.lock);
-    q.words.push_back(p);
+    q.devices[f.device].flags.push_back(f);
 }
 
 size_t device_idle_bytes(int device) {

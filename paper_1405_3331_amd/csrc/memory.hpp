@@ -23,11 +23,17 @@ size_t device_idle_bytes(int device);
 // An object that owns device memory begins or ends; between objects fewer idle blocks are kept.
 void device_memory_user(int change);
 
-// A zeroed word of pinned host memory, a line of its own, from pages that the library keeps (64
-// words each; allocating one takes longer than the rest of sim_create on a small grid).  Whatever
-// writes it must have finished when it is given back; nullptr is a no-op.
-hipError_t pinned_word(int32_t** p);
-void pinned_word_free(int32_t* p);
+// A zeroed word of pinned host memory, a line of its own, and an event of the current device (without
+// timing), which the library keeps for the next object when one gives them back: as many as objects
+// lived at once.  (From the runtime a word takes longer than the rest of sim_create on a small
+// grid.)  Whatever writes the word must have finished then; none (no word) is a no-op.
+struct HostFlag {
+    int32_t* word = nullptr;
+    hipEvent_t event = nullptr;
+    int device = 0;
+};
+hipError_t host_flag(HostFlag* f);
+void host_flag_free(const HostFlag& f);
 
 // Several host arrays placed in one device block and uploaded by one copy: add() returns an
 // array's offset in the block.

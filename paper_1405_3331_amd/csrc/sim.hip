@@ -89,18 +89,17 @@ struct sim_handle {
     ConeArrays cones = {};
     char* cone_memory = nullptr;     // the arrays of `cones`
     char* target_memory = nullptr;   // the target grid
-    uint32_t* near_map = nullptr;    // and its near map
+    uint32_t* near_map = nullptr;    // and its near map, with the mass check's flag behind it
     double* mass_partial = nullptr;
     double* mass_out = nullptr;
     // periodic mass check: every mass_every steps (0: off) sim_step enqueues the FP64 mass of
     // every species; a non-finite total raises the device flag mass_flag, copied to the
-    // pinned host word mass_flag_host behind the event mass_event.  `nonfinite` is sticky:
+    // pinned host word behind the event of mass_host.  `nonfinite` is sticky:
     // set by a check that saw a non-finite total, cleared by a SIM_MASS read whose totals
     // are all finite.
     int64_t mass_every = 0;
     int32_t* mass_flag = nullptr;
-    int32_t* mass_flag_host = nullptr;
-    hipEvent_t mass_event = nullptr;
+    HostFlag mass_host;   // mass_flag's copy
     bool mass_pending = false;
     bool nonfinite = false;
 
@@ -266,11 +265,9 @@ void release(sim_handle* h) {
     dfree(h->cone_memory);
     dfree(h->target_memory);
     dfree(h->near_map);
-    dfree(h->mass_partial);   // and mass_out, mass_flag
-    pinned_word_free(h->mass_flag_host);
-    h->mass_flag_host = nullptr;
-    if (h->mass_event) (void)hipEventDestroy(h->mass_event);
-    h->mass_event = nullptr;
+    dfree(h->mass_partial);   // and mass_out
+    host_flag_free(h->mass_host);
+    h->mass_host = HostFlag{};
     tiled_release(h->tiled);
     order3d_release(h->order3d);
     field3d_release(h->field3d);
@@ -283,9 +280,9 @@ void release(sim_handle* h) {
 
 // Fold a finished periodic mass check into the sticky flag (never waits).
 void poll_mass_check(sim_handle* h) {
-    if (!h->mass_pending || hipEventQuery(h->mass_event) != hipSuccess) return;
+    if (!h->mass_pending || hipEventQuery(h->mass_host.event) != hipSuccess) return;
     h->mass_pending = false;
-    if (*(volatile int32_t*)h->mass_flag_host) h->nonfinite = true;
+    if (*(volatile int32_t*)h->mass_host.word) h->nonfinite = true;
 }
 
 sim_status nonfinite_fail(sim_handle* h) {
@@ -364,9 +361,10 @@ sim_status build_targets(sim_handle* h, const sim_params* p) {
     tg.near_wx = (n[0] + (dim == 2 ? 7 : 3)) / (dim == 2 ? 8 : 4);
     tg.near_wy = (n[1] + 3) / 4;
     const size_t words = (size_t)tg.near_wx * tg.near_wy * (size_t)((n[2] + 1) / 2);
-    HIP_TRY(h, dalloc(&h->near_map, words));
+    HIP_TRY(h, dalloc(&h->near_map, words + 1));
     tg.near = h->near_map;
-    HIP_TRY(h, launch_near_map(dim, tg, h->near_map, words, p->n_targets, h->stream));
+    h->mass_flag = (int32_t*)(h->near_map + words);   // zeroed with the map
+    HIP_TRY(h, launch_near_map(dim, tg, h->near_map, words + 1, p->n_targets, h->stream));
     return SIM_OK;
 }
 
@@ -655,17 +653,12 @@ sim_status create_impl(const sim_params* p, void* hip_stream, const TiledPlan* m
         h->cones.target = (int32_t*)(h->cone_memory + at_target);
         h->cones.event_step = (int32_t*)(h->cone_memory + at_event);
     }
-    // The mass check's memory is made here, so that none of its calls needs any; a block of its own:
-    // behind the cones' it moves what follows in memory, and 100 simulations of 200 x 200 cells with
-    // 5000 cones each then step 15% slower in a batch.
-    e = dalloc(&h->mass_partial, kMassPartials + SIM_MAX_SPECIES + 1);
-    if (e != hipSuccess) return bail(device_fail(h, e, "mass check memory"));
-    h->mass_out = h->mass_partial + kMassPartials;
-    h->mass_flag = (int32_t*)(h->mass_out + SIM_MAX_SPECIES);
-    if ((e = hipMemsetAsync(h->mass_flag, 0, sizeof(int32_t), h->stream)) != hipSuccess ||
-        (e = pinned_word(&h->mass_flag_host)) != hipSuccess ||
-        (e = hipEventCreateWithFlags(&h->mass_event, hipEventDisableTiming)) != hipSuccess)
+    // The mass check's memory is made here (its flag with the near map), so that none of its calls
+    // needs any.
+    if ((e = dalloc(&h->mass_partial, kMassPartials + SIM_MAX_SPECIES)) != hipSuccess ||
+        (e = host_flag(&h->mass_host)) != hipSuccess)
         return bail(device_fail(h, e, "mass check set-up"));
+    h->mass_out = h->mass_partial + kMassPartials;
     if (p->dim == 3)
         e = field3d_prepare(h->field3d, h->nx, h->ny, h->nz, h->n_species, h->src_merged_cell,
                             h->src_merged_q);
@@ -887,9 +880,9 @@ sim_status sim_step(sim_handle* h, int64_t n_steps) {
                 HIP_TRY(h, launch_mass(h->field[s][h->cur[s]], h->n_cells, h->mass_partial,
                                        kMassPartials, h->mass_out + s, h->stream,
                                        h->mass_flag));
-            HIP_TRY(h, hipMemcpyAsync(h->mass_flag_host, h->mass_flag, sizeof(int32_t),
+            HIP_TRY(h, hipMemcpyAsync(h->mass_host.word, h->mass_flag, sizeof(int32_t),
                                       hipMemcpyDeviceToHost, h->stream));
-            HIP_TRY(h, hipEventRecord(h->mass_event, h->stream));
+            HIP_TRY(h, hipEventRecord(h->mass_host.event, h->stream));
             h->mass_pending = true;
         }
     }
@@ -993,7 +986,7 @@ sim_status sim_read_state(sim_handle* h, sim_item what, int32_t index, void* dst
             // this check supersedes any earlier one: the flag follows what it found
             HIP_TRY(h, hipMemsetAsync(h->mass_flag, 0, sizeof(int32_t), h->stream));
             HIP_TRY(h, hipStreamSynchronize(h->stream));
-            *h->mass_flag_host = 0;
+            *h->mass_host.word = 0;
             h->mass_pending = false;
             h->nonfinite = !finite;
             if (!finite) return nonfinite_fail(h);

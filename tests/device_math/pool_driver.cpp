@@ -51,6 +51,10 @@ hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
     *p = std::malloc(n);
     return hipSuccess;
 }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
+    *e = (hipEvent_t)std::malloc(1);
+    return hipSuccess;
+}
 hipError_t hipMemcpy(void*, const void*, size_t, hipMemcpyKind) { return hipSuccess; }
 }
 
@@ -121,12 +125,22 @@ int main() {
         });
     for (auto& x : t) x.join();
     CHECK(held(0) == device_idle_bytes(0) && held(0) <= g_total / 16);
-    int32_t* w[130];
-    for (int k = 0; k < 130; ++k) CHECK(pinned_word(&w[k]) == hipSuccess && *w[k] == 0);
-    for (int k = 1; k < 130; ++k) CHECK(w[k] != w[k - 1]);
-    *w[5] = 7;
-    pinned_word_free(w[5]);
-    CHECK(pinned_word(&w[5]) == hipSuccess && *w[5] == 0);
+    // host flags: words and events of their own, zeroed again, of the device asked for
+    HostFlag f[130];
+    for (int k = 0; k < 130; ++k) {
+        CHECK(host_flag(&f[k]) == hipSuccess && *f[k].word == 0 && f[k].device == 0);
+        for (int i = 0; i < k; ++i) CHECK(f[k].word != f[i].word && f[k].event != f[i].event);
+    }
+    *f[5].word = 7;
+    host_flag_free(f[5]);
+    host_flag_free(HostFlag{});
+    g_device = 1;
+    HostFlag other;
+    CHECK(host_flag(&other) == hipSuccess && other.device == 1 && other.event != f[5].event);
+    g_device = 0;
+    const HostFlag before = f[5];
+    CHECK(host_flag(&f[5]) == hipSuccess && f[5].word == before.word && *f[5].word == 0 &&
+          f[5].event == before.event);
     std::printf("ok\n");
     return 0;
 }
