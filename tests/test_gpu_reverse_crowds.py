@@ -28,10 +28,14 @@ def _gradient(sc, weight, steps, every):
 def test_crowds(n, cones, species, gathered):
     print(f"[gpu] {n} {cones} cones {species} species {gathered}", flush=True)
     sc = S.make_scenario("crowd", 2, n, 1.0, 0.15, COEF[:species], 5, (0.5, 2.0), cones, 30, seed=6)
+    sc.turn_gain = 0.2   # so that turns are seldom capped, and most samples have an adjoint
     if gathered:   # around one place
         rng = np.random.default_rng(4)
         sc.cone_pos = (np.array(n) * 0.5 + rng.uniform(-6.0, 6.0, (cones, 2))).astype(
             np.float32).astype(np.float64)
+        for spc in sc.species:   # where the cue reaches them
+            at = rng.integers(-4, 5, (len(spc.source_q), 2)) + np.array(n) // 2
+            spc.source_cell = (at[:, 1] * n[0] + at[:, 0]).astype(np.int32)
     weight = np.linspace(0.5, 1.5, cones).astype(np.float32)
     whole = _gradient(sc, weight, 21, 13)
     assert np.all(whole == _gradient(sc, weight, 21, 13))
@@ -46,6 +50,7 @@ def test_crowds(n, cones, species, gathered):
     # samples' sum, the stencil), the sums over cells are FP64; both sides, 21 steps of growth.
     tol = 2 * 21 * 5 * 2.0 ** -24
     err = np.abs(np.sum(parts, axis=0) - whole)
+    assert np.all(size > 0)
     scale = np.maximum(size, 1e-3 * size.max())
     print(f"[gpu] largest error {np.max(err / scale):.2e} of its terms, bound {tol:.2e}", flush=True)
     assert np.all(err <= tol * scale)
