@@ -125,8 +125,11 @@ typedef struct sim_params {
     uint64_t seed;
     uint32_t sim_index;                /* fourth Philox counter word */
     int32_t block_steps;               /* steps fused into one launch of the tiled kernel;
-                                          0 = library default, 1 = one kernel sequence per
-                                          step (no temporal blocking), max 32 */
+                                          0 = library default (2D: up to 16, chosen for
+                                          calls of many steps; one of 4 to 8 steps on a
+                                          large grid can be faster with its own number
+                                          here), 1 = one kernel sequence per step (no
+                                          temporal blocking), max 32 */
     int32_t tile_cols_per_lane;        /* tiled kernel row width 64 * this (2 or 4);
                                           0 = chosen by the library's planner */
     int32_t tile_height;               /* loaded tile height in rows; 0 = planner's choice.
@@ -282,10 +285,10 @@ sim_status sim_connectivity_noalloc(sim_handle* h, int32_t n_neurons,
                                     int32_t* row_start, int32_t* edges, int64_t edge_capacity,
                                     int64_t* n_edges);
 
-/* Level-synchronous breadth-first traversal of the last sim_connectivity graph from root
- * (one device launch per level, one thread per vertex): level[n_neurons] (host) receives
- * the number of edges on a shortest path from root, -1 where unreachable.  SIM_ESTATE if no
- * graph was built. */
+/* Level-synchronous breadth-first traversal of the last sim_connectivity graph from root (one
+ * device launch up to 32,768 neurons and 262,144 edges, else one per level): level[n_neurons]
+ * (host) receives the number of edges on a shortest path from root, -1 where unreachable.
+ * SIM_ESTATE if no graph was built. */
 sim_status sim_bfs_levels(sim_handle* h, int32_t root, int32_t* level);
 
 /* ----------------------------------------------------------------------------------------
@@ -298,8 +301,10 @@ sim_status sim_bfs_levels(sim_handle* h, int32_t root, int32_t* level);
 typedef struct sim_batch sim_batch;
 
 /* Create n simulations from params[0..n-1] (each validated as by sim_create; arrays
- * copied).  All share block_steps and tile_cols_per_lane (0 = 2 for a batch); each keeps
- * its own tile_height hint.  graph_launches > 0 captures that many full-depth launches in a hipGraph that
+ * copied).  All share block_steps and tile_cols_per_lane (0 = 2 for a batch; the other width
+ * is taken where that one fits no depth that all members share); each keeps its own
+ * tile_height hint, which the planned depth (block_steps = 0) takes into account.
+ * graph_launches > 0 captures that many full-depth launches in a hipGraph that
  * sim_batch_step replays; 0 launches directly.  Errors as sim_create; *out = NULL on error
  * and sim_batch_last_error(NULL) describes it. */
 sim_status sim_batch_create(const sim_params* const* params, int32_t n, void* hip_stream,

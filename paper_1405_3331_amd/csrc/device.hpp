@@ -630,8 +630,8 @@ __device__ __forceinline__ float dot3(float ax, float ay, float az, float bx, fl
 // deviates (normals<3>).
 template <class Contact>
 __device__ __forceinline__ ConeEvent cone_step_3d(const ConeRules& r, float gx, float gy,
-                                                  float gz, const float* zn, float& x, float& y, float& z, float& hx,
-                                                  float& hy, float& hz,
+                                                  float gz, const float* zn, float& x, float& y,
+                                                  float& z, float& hx, float& hy, float& hz,
                                                   const Contact& contact) {
     // turn in the plane of h and g, toward h + gain*g, by at most max_turn
     const float gh = dot3(gx, gy, gz, hx, hy, hz);

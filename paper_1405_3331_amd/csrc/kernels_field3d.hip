@@ -2,10 +2,11 @@
 //
 // 7-point stencil with first-order decay, zero-flux walls (a missing neighbour is the cell
 // itself), then the point sources of the step (c' += q / dx^3).  One launch covers every
-// species.  A workgroup owns a box of kTX x kTY columns and 8 or 4
-// consecutive planes of one species and marches up the planes; each thread keeps the planes below, at and above its cell in registers and reads the four
-// in-plane neighbours from lines the workgroup has just brought into L1/L2, so a cell is
-// fetched from HBM about once per step: 8 algorithmic bytes per species-cell-update.
+// species.  A workgroup owns a box of kTX x kTY columns and 8 or 4 consecutive planes of one
+// species and marches up the planes; each thread keeps the planes below, at and above its cell in
+// registers and reads the four in-plane neighbours from lines the workgroup has just brought into
+// L1/L2, so a cell is fetched from HBM about once per step: 8 algorithmic bytes per
+// species-cell-update.
 // Planes are taken kUnroll3D at a time with every load of the group issued before the
 // arithmetic, which keeps kUnroll3D times more reads in flight than a plane-by-plane march.
 // Walls are handled by clamping the neighbour index, which reads the cell itself exactly

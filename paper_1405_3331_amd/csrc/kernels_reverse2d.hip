@@ -15,9 +15,9 @@
 // the tile as one float: integer additions, so the sum in a cell does not depend on the order
 // in which the contributions arrive and the gradient is bitwise reproducible.  Which cones can
 // touch a tile's loaded region during a launch is listed beforehand, per launch of a segment
-// (k_tile_lists); a contribution is rebuilt where it is needed from
-// the cone's tip and the adjoint of its sampled gradient (20 bytes per cone and step, against
-// a 96-byte record of the 12 cells and values).
+// (k_tile_lists); a contribution is rebuilt where it is needed from the cone's tip and the
+// adjoint of its sampled gradient (20 bytes per cone and step, against a 96-byte record of the
+// 12 cells and values).
 //
 // Before, each step's contributions went into a buffer of sums over the whole grid in HBM by
 // global 64-bit atomics (3.9 us per step at 1024^2 and 8192 cones), which the reverse step
@@ -28,8 +28,8 @@
 //
 // The cones' chain of the segment before (cone_adjoint.hpp) needs no field adjoint: eight of its
 // steps per launch run in workgroups past the tiles', on CUs that the tiles leave free.  1024^2,
-// 8192 cones: 24.2 us per launch instead of 23.5, against 55 us per 100 steps for the chain alone
-// (gradient of 2000 steps 14.27 -> 13.6 ms).
+// 8192 cones: 0.7 us more per launch (22.3 with it), against 55 us per 100 steps for the chain alone
+// (gradient of 2000 steps 14.27 -> 13.6 ms; now 13.1).
 #include <algorithm>
 #include <type_traits>
 

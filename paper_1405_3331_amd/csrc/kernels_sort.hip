@@ -1,9 +1,9 @@
 // kernels_sort.hip -- stable sort of (key, value) pairs by counting: per-tile histograms,
-// one exclusive scan, stable scatter; least significant 8-bit digit first.
+// sums along each digit's row of them, stable scatter; least significant 8-bit digit first.
 //
 // This is the hash -> sort -> cell-start step of the paper's uniform-grid broadphase
 // (Sec. 3.5, Table 1): items keyed by their cell end up grouped by cell, in their original
-// order within a cell, and the scanned histogram gives every cell's start.  The library
+// order within a cell, and the summed histogram gives every cell's start.  The library
 // uses it to order 3D cones by the cell of their tip and to group contact edges by the
 // neuron that owns them (Sec. 3.4).
 //

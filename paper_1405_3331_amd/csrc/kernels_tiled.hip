@@ -59,7 +59,9 @@ namespace {
 // cones, 10,000 steps after 200: depth 14, 138 rows of 256 columns 3.98 us per step, two tiles of
 // 143 rows of 128 columns per CU, depth 12, 4.46 (the first 1000: 3.82 and 3.87; 143 rows of 256
 // columns stepped by 8 wavefronts 4.8).  Short tiles lose by it (777 x 389, two species, 56
-// rows: 5.0 against 4.2 us).
+// rows: 5.0 against 4.2 us).  Past one round of tiles it still gains (over steps 48 to 624; the
+// best of 128 columns, of heights up to 296 and of 143 at depth 12): 3000^2 6.3 us against 7.1,
+// 4096^2 10.0 against 11.0, 6000 x 5000 18.4 against 18.5; at 8192^2 it no longer does (40.8, 37.8).
 constexpr int kWideRows = 96;
 constexpr size_t kCuLds = 160 * 1024;
 constexpr int kMaxTileTargets = 256;        // targets staged in LDS per tile
@@ -159,12 +161,12 @@ struct LdsField2D {
 };
 
 // One stencil + decay sub-step of one species over a wavefront's strip of rows
-// [ybeg, yend), into `to`: L itself (in place) or the other copy.  L points at tile row 0; rows -1 and HL .. HL+2 are guard rows
-// (never meaningful) so reads, which reach at most two rows past the strip, need no
-// clamping.  (In place:) within a wavefront every LDS read of a row is issued before that row's write,
-// so interior rows are overwritten as soon as they are computed; the strip's first and
-// last rows are read by the neighbouring wavefronts and are returned for writing after a
-// barrier.  Four row registers cycle through their roles (above / at / below /
+// [ybeg, yend), into `to`: L itself (in place) or the other copy.  L points at tile row 0; rows
+// -1 and HL .. HL+2 are guard rows (never meaningful) so reads, which reach at most two rows
+// past the strip, need no clamping.  In place, every LDS read of a row is issued within a
+// wavefront before that row's write, so interior rows are overwritten as soon as they are
+// computed; the strip's first and last rows are read by the neighbouring wavefronts and are
+// returned for writing after a barrier.  Four row registers cycle through their roles (above / at / below /
 // prefetched), so rows are prefetched two ahead with no register moves: a prefetched row
 // is either this strip's, still unmodified, or a neighbour's first row, written only after
 // the barrier (or is never used).  The first and last rows are peeled off, so the loop body
@@ -686,9 +688,9 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& 
     const ConeRules& rules = a.rules;
     const int cols = x0 > 0 && x0 + W < a.nx ? kNoWall : aligned ? kWallAligned : kWallAny;
     for (int b = 0; b < steps; ++b) {
-        // 2. stencil + decay, in place or into the other copy, strip per wavefront.  After this sub-step only rows
-        //    [b + 1, HL - b - 1) are still valid (each sub-step loses one row at either
-        //    edge of the tile), so rows outside that band are not computed.
+        // 2. stencil + decay, in place or into the other copy, strip per wavefront.  After this
+        //    sub-step only rows [b + 1, HL - b - 1) are still valid (each sub-step loses one row
+        //    at either edge of the tile), so rows outside that band are not computed.
         const int lo = max(ybeg, b + 1), hi = min(yend, HL - b - 1);
         const bool top = lo == -y0, bottom = hi == a.ny - y0;
         float* const from = lds + (TWO && (b & 1) ? NS * plane : 0);
@@ -762,7 +764,8 @@ __device__ __forceinline__ void tile_body(const TiledArgs2D& a, const TileWork& 
 
     // 5. write the core back (one part per tile does)
     if (first_part)
-        store_core<NS, CPL, WAVES>(out, lds + (TWO && (steps & 1) ? NS * plane : 0), a, tx, ty, plane, cx, wave, aligned);
+        store_core<NS, CPL, WAVES>(out, lds + (TWO && (steps & 1) ? NS * plane : 0), a, tx, ty,
+                                   plane, cx, wave, aligned);
 
     // 6. re-bucket surviving cones, straight from registers, into the tile that now holds
     //    their tip (one of the 3 x 3 tiles around this one)
@@ -1070,7 +1073,8 @@ TiledPlan plan_search(int dim, int nx, int ny, int nz, int n_species, double ste
                 // holding more than a part's of them takes extra workgroups: keep room
                 // for a quarter of the cones in full parts beside one workgroup per tile,
                 // or the launch runs in two generations.
-                const int spare = std::min(tiles, ceil_div(n_cones, 4 * kPartCones * part_units(shape)));
+                const int spare =
+                    std::min(tiles, ceil_div(n_cones, 4 * kPartCones * part_units(shape)));
                 double cost = (double)per_cu * W * HL * (1.0 + 2.0 / B) / B;
                 if ((resident < 2 && shape == kPair) || ceil_div(tiles + spare, 256) > resident)
                     cost *= 1.25;
@@ -1442,8 +1446,8 @@ hipError_t tiled_launch(const TiledPlan& plan, TiledState& st, int steps, hipStr
     void* args[] = {st.args, &tile_wgs, &steps, &st.launch, &st.extra, &st.extra_cap, &st.room};
     const hipError_t e = hipExtLaunchKernel(
         kernel_for(plan, st.args->record != nullptr),
-        dim3(tile_wgs + st.extra_cap), dim3(64 * waves_of(plan.shape)), args, plan.lds_bytes, stream, start, stop,
-        0);
+        dim3(tile_wgs + st.extra_cap), dim3(64 * waves_of(plan.shape)), args, plan.lds_bytes,
+        stream, start, stop, 0);
     if (e == hipSuccess) tiled_advanced(st, 1);
     return e;
 }
