@@ -161,7 +161,9 @@ typedef struct sim_handle sim_handle;
 sim_status sim_create(const sim_params* p, void* hip_stream, sim_handle** out);
 
 /* Enqueue n_steps >= 0 time steps on the handle's stream and return without waiting.
- * SIM_ENONFINITE (nothing enqueued) once a mass check has found a non-finite total. */
+ * SIM_ENONFINITE (nothing enqueued) once a mass check has found a non-finite total.  Captured in
+ * a HIP graph after an earlier step, temporally blocked steps are those that follow whenever the
+ * graph is replayed (SIM_STEP counts the calls only); un-blocked ones are the same steps again. */
 sim_status sim_step(sim_handle* h, int64_t n_steps);
 
 /* Mass check every `every` steps (0 = off, the default): whenever the step count reaches a

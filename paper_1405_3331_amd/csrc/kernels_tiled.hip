@@ -1402,6 +1402,15 @@ hipError_t tiled_set_launch_state(TiledState& st, uint32_t step, int parity, hip
     return hipStreamSynchronize(stream);
 }
 
+hipError_t tiled_get_launch_state(TiledState& st) {
+    int32_t head[3];   // step, parity, phase
+    const hipError_t e = hipMemcpy(head, st.launch, sizeof head, hipMemcpyDeviceToHost);
+    if (e != hipSuccess) return e;
+    st.cur = head[1];
+    st.phase = head[2];
+    return hipSuccess;
+}
+
 int tiled_extra_capacity(int64_t n_cones) {
     // a tile of c cones has ceil(c / kPartCones) - 1 < c / kPartCones further full parts
     return (int)(n_cones / kPartCones) + 1;

@@ -109,6 +109,7 @@ struct sim_handle {
     TiledState tiled = {};
     bool cones_bucketed = false;   // active cones live in the tile buckets
     bool cones_synced = true;      // the caller-order arrays hold the active cones' state
+    bool captured = false;         // launches were captured: a caller's graph may replay them
 
     // 3D: field step with its per-box source lists; active cones in spatial order,
     // refreshed every kOrderRefresh steps
@@ -408,9 +409,22 @@ sim_status item_size(sim_handle* h, sim_item what, int32_t index, size_t* bytes)
     return SIM_OK;
 }
 
+// Where a caller's graph may have replayed launches, the host's copies of the launch state (which
+// half of the fields and buckets is current, which third of the counts) are taken from the device's.
+sim_status follow_replays(sim_handle* h) {
+    if (!h->captured) return SIM_OK;
+    HIP_TRY(h, hipStreamSynchronize(h->stream));
+    HIP_TRY(h, tiled_get_launch_state(h->tiled));
+    for (int s = 0; s < h->n_species; ++s) h->cur[s] = h->tiled.cur;
+    h->cones_synced = !h->cones_bucketed;
+    return SIM_OK;
+}
+
 // Bring the caller-order arrays up to date with the active cones' working copies (the tile
 // buckets, or the 3D spatial order), which stay valid: stepping goes on from them.
 sim_status sync_cones(sim_handle* h) {
+    const sim_status st = follow_replays(h);
+    if (st != SIM_OK) return st;
     if (h->cones_synced) return SIM_OK;
     if (h->cones_ordered) HIP_TRY(h, order3d_end(h->order3d, h->cones, h->stream));
     if (h->cones_bucketed)
@@ -421,11 +435,13 @@ sim_status sync_cones(sim_handle* h) {
 
 // The same, and the working copies are given up: the caller-order arrays are about to change.
 sim_status unbucket(sim_handle* h) {
+    sim_status st = follow_replays(h);
+    if (st != SIM_OK) return st;
     if (h->cones_bucketed) {
         HIP_TRY(h, tiled_sync_cones(h->plan, h->tiled, h->cones, h->stream, true));
         h->cones_bucketed = false;
     } else {
-        sim_status st = sync_cones(h);
+        st = sync_cones(h);
         if (st != SIM_OK) return st;
     }
     h->cones_ordered = false;
@@ -536,6 +552,14 @@ sim_status plain_steps(sim_handle* h, int64_t n) {
 }
 
 sim_status tiled_steps(sim_handle* h, int64_t n) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(h->stream, &capture) != hipSuccess) (void)hipGetLastError();
+    if (capture != hipStreamCaptureStatusNone) {
+        h->captured = true;
+    } else if (!h->cones_bucketed || h->mass_every > 0) {   // what uses the host's copies
+        const sim_status st = follow_replays(h);
+        if (st != SIM_OK) return st;
+    }
     if (!h->cones_bucketed) {
         HIP_TRY(h, tiled_bucket(h->plan, h->tiled, h->cones, h->stream));
         h->cones_bucketed = true;
@@ -949,6 +973,8 @@ sim_status sim_read_state(sim_handle* h, sim_item what, int32_t index, void* dst
     if (need && !dst) return fail(h, SIM_EINVAL, "dst is NULL");
     switch (what) {
         case SIM_FIELD:
+            st = follow_replays(h);
+            if (st != SIM_OK) return st;
             HIP_TRY(h, hipStreamSynchronize(h->stream));
             HIP_TRY(h, hipMemcpy(dst, h->field[index][h->cur[index]], need, hipMemcpyDeviceToHost));
             return SIM_OK;
@@ -969,6 +995,8 @@ sim_status sim_read_state(sim_handle* h, sim_item what, int32_t index, void* dst
             return SIM_OK;
         }
         case SIM_MASS: {
+            st = follow_replays(h);
+            if (st != SIM_OK) return st;
             for (int s = 0; s < h->n_species; ++s)
                 HIP_TRY(h, launch_mass(h->field[s][h->cur[s]], h->n_cells, h->mass_partial,
                                        kMassPartials, h->mass_out + s, h->stream));
@@ -1028,6 +1056,8 @@ sim_status sim_write_state(sim_handle* h, sim_item what, int32_t index, const vo
     if (need && !src) return fail(h, SIM_EINVAL, "src is NULL");
     switch (what) {
         case SIM_FIELD:
+            st = follow_replays(h);
+            if (st != SIM_OK) return st;
             HIP_TRY(h, hipStreamSynchronize(h->stream));
             HIP_TRY(h, hipMemcpy(h->field[index][h->cur[index]], src, need, hipMemcpyHostToDevice));
             return SIM_OK;
@@ -1051,6 +1081,8 @@ sim_status sim_write_state(sim_handle* h, sim_item what, int32_t index, const vo
             int64_t v;
             std::memcpy(&v, src, sizeof v);
             if (v < 0 || v > 2147483647LL) return fail(h, SIM_EINVAL, "step out of range");
+            st = follow_replays(h);
+            if (st != SIM_OK) return st;
             HIP_TRY(h, hipStreamSynchronize(h->stream));
             h->step = v;
             if (h->block_steps > 1)
@@ -1069,6 +1101,7 @@ sim_status sim_device_ptr(sim_handle* h, sim_item what, int32_t index, void** de
     if (what != SIM_FIELD) return fail(h, SIM_EINVAL, "only SIM_FIELD has a device view");
     size_t need = 0;
     sim_status st = item_size(h, what, index, &need);
+    if (st == SIM_OK) st = follow_replays(h);
     if (st != SIM_OK) return st;
     *dev_ptr = h->field[index][h->cur[index]];
     if (bytes) *bytes = need;
@@ -1208,6 +1241,8 @@ sim_status sim_adjoint_run(sim_handle* h, int64_t n_steps, int32_t checkpoint_ev
         tips[2 * i] = h->target_host[(size_t)assign[i] * 2];
         tips[2 * i + 1] = h->target_host[(size_t)assign[i] * 2 + 1];
     }
+    sim_status st = follow_replays(h);
+    if (st != SIM_OK) return st;
     adjoint_release(h);
     AdjointRun* a = new (std::nothrow) AdjointRun();
     if (!a) return fail(h, SIM_ENOMEM, "adjoint record");
@@ -1267,7 +1302,7 @@ sim_status sim_adjoint_run(sim_handle* h, int64_t n_steps, int32_t checkpoint_ev
         }
     }
     for (int j = 0; j < a->n_ckpt; ++j) {
-        sim_status st = sync_cones(h);
+        st = sync_cones(h);
         if (st != SIM_OK) return st;
         // the checkpoint: fields and cone arrays in one copy launch
         CopySpans cp = {};
@@ -1293,7 +1328,7 @@ sim_status sim_adjoint_run(sim_handle* h, int64_t n_steps, int32_t checkpoint_ev
         st = sim_step(h, len);
         if (st != SIM_OK) return st;
     }
-    sim_status st = adjoint_seed(h, a->stop);
+    st = adjoint_seed(h, a->stop);
     if (st != SIM_OK) return st;
     std::vector<double> part((size_t)cone_blocks(h), 0.0);
     if (M > 0)

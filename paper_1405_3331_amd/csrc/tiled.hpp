@@ -96,6 +96,8 @@ hipError_t tiled_allocate(const TiledPlan& plan, TiledState& st, int n_cones,
                           ConeArrays cones, hipStream_t stream);
 // Set the device launch state (step counter; parity = input half of the ping-pong pairs).
 hipError_t tiled_set_launch_state(TiledState& st, uint32_t step, int parity, hipStream_t stream);
+// The host's copies (st.cur, st.phase) from the device launch state.
+hipError_t tiled_get_launch_state(TiledState& st);
 // Record mode: while tape is non-null every launch also writes the state after each of its
 // sub-steps to tape + ((step - n0) * n_species + s) * cells and every cone step's record to
 // `cones` (step - n0) (null: off).
