@@ -221,7 +221,10 @@ void device_memory_user(int change) {
     {
         std::lock_guard<std::mutex> hold(q.lock);
         q.users += change;
-        if (q.users == 0) out = q.trim(false);
+        if (q.users == 0)
+            for (const auto& d : q.devices)
+                if (d.second.idle > q.limit(d.first))
+                    for (const Block& b : q.trim(false, d.first)) out.push_back(b);
     }
     (void)give_back(out);
 }
